@@ -254,7 +254,8 @@ int ff_sim_batch(ff_sim_t* sim, const ff_opcfg_t* d_strategies, uint32_t B, uint
 
 /* Which kernel instantiation ff_sim_batch launches for B candidates on this handle (measurement
  * aid: a profile of the kernel can be matched to the launch it belongs to): writes
- * "k_sim_batch<WIDE, LDSW, STATS, Q, CACHE, EXT, GPN>" with the template arguments as they appear
+ * "k_loop_batch<STATS, LDSW, Q, ROWL, EXT, GPN>", or for tensors or links that need 64-bit arithmetic
+ * "k_sim_batch<WIDE, LDSW, STATS, Q, CACHE, EXT, GPN>", with the template arguments as they appear
  * in a kernel trace into buf (HOST memory, len bytes; FF_ERANGE if it does not fit). */
 int ff_sim_batch_kernel_name(const ff_sim_t* sim, uint32_t B, char* buf, size_t len);
 

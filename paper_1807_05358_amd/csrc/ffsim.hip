@@ -57,6 +57,21 @@ struct ff_sim {
     size_t batch_slot_bytes = 0;  // slot_bytes, plus the kept set-up where it lives in HBM
     size_t lds_cached = 0;        // dynamic LDS of the caching variant (= lds if the set-up lives in HBM)
     uint32_t max_slots_cached = 0;
+    // the batch kernels on kept set-up (ffsim_loop.h); s->loop says whether they serve this graph and machine
+    OpLite* d_op_lite = nullptr;
+    EdgeLite* d_edge_lite = nullptr;
+    std::vector<OpLite> h_op_lite;
+    bool loop = false;
+    bool loop_extents = false;    // all extents fit 16 bits
+    bool loop_retry = false;      // a link row might be booked beyond 32 bits: look for candidates to simulate again
+    LoopChoice loop_choice{};
+    size_t loop_slot_bytes = 0;   // HBM per resident wavefront
+    size_t loop_lds = 0;
+    uint32_t max_slots_loop = 0;
+    uint32_t max_parts = 0;       // most parts any op can have
+    uint64_t max_elems = 0;       // of the largest tensor
+    uint64_t sum_edge_bytes = 0;  // over all edges, of the producer's tensor (saturating)
+    uint64_t sum_cost = 0;        // over all ops, of the longest task (saturating)
     size_t lds = 0;               // dynamic LDS per wavefront, batch kernel
     size_t lds_common = 0;        // device rows + queue levels 1 and 2
     size_t lds_chain = 0;         // dynamic LDS per wavefront, chain kernel (adds the strategy; words in HBM)
@@ -134,6 +149,12 @@ static chain_kernel_t chain_kernel(const ff_sim* s) {
     if (s->dev.gpus_per_node == 4) return ext == 2 ? chain_kernels<2, 4>(k) : (ext == 1 ? chain_kernels<1, 4>(k) : chain_kernels<0, 4>(k));
     return ext == 2 ? chain_kernels<2, 0>(k) : (ext == 1 ? chain_kernels<1, 0>(k) : chain_kernels<0, 0>(k));
 }
+static loop_kernel_t loop_kernel(const ff_sim* s, int ext) {
+    LoopChoice k = s->loop_choice;
+    k.stats = s->d_stats != nullptr;
+    if (s->dev.gpus_per_node == 4) return ext == 2 ? loop_kernels<2, 4>(k) : (ext == 1 ? loop_kernels<1, 4>(k) : loop_kernels<0, 4>(k));
+    return ext == 2 ? loop_kernels<2, 0>(k) : (ext == 1 ? loop_kernels<1, 0>(k) : loop_kernels<0, 0>(k));
+}
 static try_kernel_t try_kernel(const ff_sim* s) {
     const KernelChoice k = choice(s, s->chain_cache);
     const int ext = ext_level(s);
@@ -151,6 +172,7 @@ static bool allow_lds(const void* kernel, size_t bytes) {
 static void release(ff_sim* s) {
     if (!s) return;
     hipFree(s->d_ops); hipFree(s->d_edges); hipFree(s->d_in_edges); hipFree(s->d_cost); hipFree(s->d_magic);
+    hipFree(s->d_op_lite); hipFree(s->d_edge_lite);
     delete s;
 }
 
@@ -179,10 +201,16 @@ const char* ff_sim_strerror(int code) {
 // op whose configuration it takes, or empty.  Layout: ffsim_device.h.
 static std::vector<uint32_t> constants_image(const ff_machine_t& m, const std::vector<uint32_t>& intra_bw, const std::vector<uint32_t>& intra_lat,
                                              const std::vector<uint32_t>& node_bw, const std::vector<uint32_t>& node_lat,
-                                             const std::vector<uint32_t>& ties) {
+                                             const std::vector<uint32_t>& ties, const std::vector<LinkTime>& loop_links, uint32_t n_ops) {
     const size_t G2 = (size_t)m.gpus_per_node * m.gpus_per_node, N2 = (size_t)m.n_nodes * m.n_nodes;
     const size_t tie_at = tie_table_at(m.gpus_per_node, m.n_nodes);
-    std::vector<uint32_t> c(tie_at + std::max<size_t>(ties.size(), 1), 0);
+    const size_t loop_at = loop_links_at(m.gpus_per_node, m.n_nodes, n_ops);
+    std::vector<uint32_t> c(loop_at + 4 * std::max<size_t>(loop_links.size(), 1), 0);
+    for (size_t p = 0; p < loop_links.size(); p++) {
+        c[loop_at + 4 * p + 0] = loop_links[p].m;
+        c[loop_at + 4 * p + 1] = loop_links[p].k;
+        c[loop_at + 4 * p + 2] = loop_links[p].lat1;
+    }
     for (uint32_t d = 2; d <= 64; d++) c[d] = magic_plus1(d);
     for (size_t p = 0; p < G2; p++) {
         const uint32_t bw = intra_bw.empty() ? m.intra_Bpns : intra_bw[p];
@@ -201,12 +229,92 @@ static std::vector<uint32_t> constants_image(const ff_machine_t& m, const std::v
 }
 
 // The narrow kernels count elements, bytes and a link row's running sum of transfer times in
-// 32 bits: every tensor must stay below 2^32 bytes, and gpus_per_node of the longest possible
-// transfers (the most one producer part can queue on one row) below 2^32 ns.  Everything else
-// runs in the 64-bit (WIDE) kernels.
-static bool needs_wide(bool big_tensors, uint32_t bw_min, uint32_t lat_max, uint32_t gpus_per_node) {
-    const uint64_t ns_max = (0xffffffffull + bw_min - 1) / bw_min + lat_max;
+// 32 bits: every tensor must stay below 2^32 bytes, and gpus_per_node transfers of the largest tensor
+// (the most one producer part can queue on one row) below 2^32 ns.  Everything else runs in the
+// 64-bit (WIDE) kernels.
+static bool needs_wide(bool big_tensors, uint64_t max_bytes, uint32_t bw_min, uint32_t lat_max, uint32_t gpus_per_node) {
+    const uint64_t ns_max = (max_bytes + bw_min - 1) / bw_min + lat_max;
     return big_tensors || ns_max * gpus_per_node >= (1ull << 32);
+}
+
+// What the event loop on kept set-up needs to know about link times: elem_sh and per link (inside a node, between nodes, then
+// every pair of the tables in force) m, k, lat1 with
+//     (umulhi((elems << elem_sh) - 1, m) >> k) + lat1 == ceil(elems * elem_bytes / bandwidth) + latency
+// for 1 <= elems <= max_elems.  With g a common divisor of elem_bytes and all bandwidths, q = bandwidth / g and x =
+// elems * elem_bytes / g - 1, the right side is floor(x / q) + 1 + latency; floor(x / q) = umulhi(x, m) >> k for
+// m = floor(2^(32+k) / q) + 1 as long as x * (m * q - 2^(32+k)) < 2^(32+k).  False: no such constants.
+static bool link_time(uint64_t q, uint64_t x_max, uint32_t lat, LinkTime* out) {
+    if (lat == 0xffffffffu) return false;
+    for (uint32_t k = 0; k < 32; k++) {
+        const uint64_t P = 1ull << (32 + k), mm = P / q + 1;
+        if (mm >> 32) return false;
+        const uint64_t e = mm * q - P;                      // 1..q
+        if ((unsigned __int128)x_max * e < P) { *out = LinkTime{(uint32_t)mm, k, lat + 1}; return true; }
+    }
+    return false;
+}
+static bool link_times(const ff_machine_t& m, uint64_t max_elems, const std::vector<uint32_t>& bw, const std::vector<uint32_t>& lat,
+                       uint32_t* elem_sh, std::vector<LinkTime>* out) {
+    uint64_t g = m.elem_bytes;
+    for (uint32_t b : bw) g = std::__gcd<uint64_t>(g, b);
+    uint64_t mul = m.elem_bytes / g, scale = 1;
+    if (mul & (mul - 1)) return false;
+    for (uint32_t b : bw) if (b / g < 2) scale = 2;         // (m of q = 1 would not fit 32 bits)
+    mul *= scale;
+    const unsigned __int128 x_max = (unsigned __int128)max_elems * mul - 1;
+    if (x_max >> 32) return false;
+    *elem_sh = (uint32_t)__builtin_ctzll(mul);
+    out->resize(bw.size());
+    for (size_t p = 0; p < bw.size(); p++)
+        if (!link_time(bw[p] / g * scale, (uint64_t)x_max, lat[p], &(*out)[p])) return false;
+    return true;
+}
+
+static uint64_t sat_add(uint64_t a, uint64_t b) { return a + b < a ? ~0ull : a + b; }
+static uint64_t sat_mul(uint64_t a, uint64_t b) { return b && a > ~0ull / b ? ~0ull : a * b; }
+
+// Everything that depends on the links, ties and parameters in force: 64-bit kernels or not, the constants of the event loop,
+// whether it can serve, and the constants buffer's contents.
+static std::vector<uint32_t> derive(ff_sim* s) {
+    const ff_machine_t& m = s->mach;
+    const uint32_t G = m.gpus_per_node, N = m.n_nodes;
+    // inside a node, between nodes, then the pairs (entries that stand for no link repeat one that does)
+    std::vector<uint32_t> bw{m.intra_Bpns, m.inter_Bpns}, lat{m.intra_lat_ns, m.inter_lat_ns};
+    if (!s->intra_bw.empty()) { bw[0] = bw[1]; lat[0] = lat[1]; }
+    if (!s->node_bw.empty()) { bw[1] = bw[0]; lat[1] = lat[0]; }
+    if (!s->intra_bw.empty() && !s->node_bw.empty()) {
+        bw[0] = bw[1] = G > 1 ? s->intra_bw[1] : (N > 1 ? s->node_bw[1] : m.intra_Bpns);
+        lat[0] = lat[1] = G > 1 ? s->intra_lat[1] : (N > 1 ? s->node_lat[1] : m.intra_lat_ns);
+    }
+    for (uint32_t a = 0; a < G; a++)
+        for (uint32_t b = 0; b < G; b++) {
+            const bool given = !s->intra_bw.empty() && a != b;
+            bw.push_back(given ? s->intra_bw[a * G + b] : bw[0]);
+            lat.push_back(given ? s->intra_lat[a * G + b] : lat[0]);
+        }
+    for (uint32_t a = 0; a < N; a++)
+        for (uint32_t b = 0; b < N; b++) {
+            const bool given = !s->node_bw.empty() && a != b;
+            bw.push_back(given ? s->node_bw[a * N + b] : bw[1]);
+            lat.push_back(given ? s->node_lat[a * N + b] : lat[1]);
+        }
+    const uint32_t bw_min = *std::min_element(bw.begin(), bw.end()), lat_max = *std::max_element(lat.begin(), lat.end());
+    s->wide = needs_wide(s->big_tensors, s->max_elems * m.elem_bytes, bw_min, lat_max, G);
+    std::vector<LinkTime> lt;
+    SimDev& S = s->dev;
+    uint32_t sh = 0;
+    s->loop = !s->wide && s->loop_extents && link_times(m, s->max_elems, bw, lat, &sh, &lt);
+    if (s->loop_extents && !s->loop) s->wide = true;       // (no such constants: odd element sizes, extreme bandwidths)
+    if (s->loop) { S.near_link = lt[0]; S.far_link = lt[1]; S.elem_sh = sh; lt.erase(lt.begin(), lt.begin() + 2); }
+    // No simulated time can pass the sum of all tasks and transfers: every consumer part reads at most the whole tensor of
+    // every edge, in at most parts^2 transfers, and (parameters in step) sends at most the op's parameters once.
+    const uint64_t P = s->max_parts;
+    uint64_t bound = sat_mul(P, sat_add(s->sum_edge_bytes / bw_min + 1, s->sum_cost));
+    bound = sat_add(bound, sat_mul(sat_mul(P * P, S.n_edges + 1), (uint64_t)lat_max + 2));
+    for (const OpLite& o : s->h_op_lite)
+        if (o.param_bytes) bound = sat_add(bound, sat_mul(P, (uint64_t)o.param_bytes / bw_min + 2 + lat_max));
+    s->loop_retry = bound >= 0xfffffff0ull;
+    return constants_image(m, s->intra_bw, s->intra_lat, s->node_bw, s->node_lat, s->ties, lt, S.n_ops);
 }
 
 static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector<uint32_t>& cost, uint32_t n_cols, ff_sim_t** out) {
@@ -295,15 +403,32 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         }
         for (uint32_t k = 0; k < g->n_edges; k++) in_edges[ops[edges[k].dst].in_end++] = edges[k];
     }
-    std::vector<uint32_t> magic = constants_image(*m, {}, {}, {}, {}, {});
+    // the short records of the event loop on kept set-up: kept rows are numbered in edge order
+    std::vector<EdgeLite> edge_lite(g->n_edges);
+    std::vector<OpLite> op_lite(g->n_ops);
+    uint32_t n_kept = 0;
+    {
+        std::vector<uint32_t> seen(g->n_ops, 0);
+        for (uint32_t k = 0; k < g->n_edges; k++) {
+            const bool four = edges[k].src_ndim > 2;
+            edge_lite[k] = EdgeLite{edges[k].dst | (four ? EL_FOUR : 0u) | (edges[k].kind ? EL_CONTRIB : 0u), seen[edges[k].dst]++, n_kept, 0};
+            n_kept += four ? KEPT_ROWS : KEPT_ROWS_2;
+        }
+        for (uint32_t i = 0; i < g->n_ops; i++) {
+            op_lite[i] = OpLite{ops[i].out_begin, ops[i].out_end, 0, 0, EdgeLite{0, 0, 0, 0}};
+            if (ops[i].out_end > ops[i].out_begin) op_lite[i].first = edge_lite[ops[i].out_begin];
+        }
+    }
 
     ff_sim* s = new (std::nothrow) ff_sim;
     if (!s) return FF_ENOMEM;
     int rc;
     if ((rc = upload(ops, &s->d_ops)) || (rc = upload(edges, &s->d_edges)) || (rc = upload(in_edges, &s->d_in_edges)) ||
-        (rc = upload(cost, &s->d_cost)) || (rc = upload(magic, &s->d_magic))) { release(s); return rc; }
+        (rc = upload(op_lite, &s->d_op_lite)) || (rc = upload(edge_lite, &s->d_edge_lite)) ||
+        (rc = upload(cost, &s->d_cost))) { release(s); return rc; }
 
     s->h_ops = ops;
+    s->h_op_lite = op_lite;
     s->has_contributing = has_contributing;
     SimDev& S = s->dev;
     S.n_ops = g->n_ops; S.n_edges = g->n_edges; S.n_cols = n_cols;
@@ -318,8 +443,24 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
     S.n_groups = S.n_ops_pad / 64;
     s->mach = *m;
     s->big_tensors = max_bytes >= ((unsigned __int128)1 << 32);
-    s->wide = needs_wide(s->big_tensors, std::min(m->intra_Bpns, m->inter_Bpns), std::max(m->intra_lat_ns, m->inter_lat_ns),
-                         m->gpus_per_node);
+    S.n_kept = n_kept;
+    s->max_parts = S.max_parts;
+    for (uint32_t i = 0; i < g->n_ops; i++) {
+        uint64_t elems = 1, longest = 0;
+        for (int d = 0; d < 4; d++) elems *= ops[i].extent[d];
+        s->max_elems = std::max(s->max_elems, elems);
+        // (an edge hands over elements of its producer's tensor; a contributing one, of its consumer's)
+        for (uint32_t k = ops[i].out_begin; k < ops[i].out_end; k++) {
+            uint64_t shared = 1;
+            for (int d = 0; d < 4; d++) shared *= edges[k].src_extent[d];
+            s->sum_edge_bytes = sat_add(s->sum_edge_bytes, sat_mul(shared, m->elem_bytes));
+        }
+        if (n_cols) for (uint32_t c = 0; c < n_cols; c++) longest = std::max<uint64_t>(longest, cost[(size_t)i * n_cols + c]);
+        else for (uint32_t t = cost[i]; t < cost[i + 1]; t++) longest = std::max<uint64_t>(longest, cost[(size_t)g->n_ops + 1 + cost[g->n_ops] + t]);
+        s->sum_cost = sat_add(s->sum_cost, longest);
+    }
+    s->loop_extents = max_extent <= ECACHE_MAX_EXTENT;
+    if ((rc = upload(derive(s), &s->d_magic))) { release(s); return rc; }
     s->slot_bytes = (slot_bytes(S.n_ops, S.n_ops_pad) + 255) & ~(size_t)255;
     s->lds_common = lds_common_bytes(S.n_rows, S.n_ops_pad);
     s->lds_chain = s->lds_common + (size_t)S.n_ops_pad * 8;
@@ -361,6 +502,23 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel(s, true), WAVE, s->lds_cached);
         if (e != hipSuccess || per_cu < 1) per_cu = 1;
         s->max_slots_cached = (uint32_t)cus * (uint32_t)per_cu;
+    }
+    if (s->loop_extents) {
+        // Rows of 16 lanes where no op can have more parts.  Graphs of up to 64 ops whose state fits a quarter of a compute unit's
+        // LDS (four wavefronts, one per SIMD) keep it there.
+        LoopChoice& k = s->loop_choice;
+        k.rowl = S.max_parts <= 16 ? 16 : 64;
+        const size_t rows_lds = loop_lds_bytes(S.n_rows, S.n_dev);
+        const size_t lds_all = slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, k.rowl, true).bytes + rows_lds;
+        k.lds = S.n_ops <= 64 && lds_all <= 40 * 1024;
+        k.queue = k.lds ? (S.n_ops <= 16 && k.rowl == 16 ? Q_OP16 : Q_OP) : Q_SLOT;
+        s->loop_lds = k.lds ? lds_all : rows_lds;
+        s->loop_slot_bytes = k.lds ? 0 : slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, k.rowl, false).bytes;
+        if (!allow_lds((const void*)loop_kernel(s, 0), s->loop_lds)) { release(s); return FF_EHIP; }
+        per_cu = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, loop_kernel(s, 0), WAVE, s->loop_lds);
+        if (e != hipSuccess || per_cu < 1) per_cu = 1;
+        s->max_slots_loop = (uint32_t)cus * (uint32_t)per_cu;
     }
     per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, try_kernel(s), WAVE, s->lds_common);
@@ -415,36 +573,28 @@ int ff_sim_set_params(ff_sim_t* s, const uint32_t* param_bytes, const uint8_t* p
     if (!s || (param_bytes && !param_dims)) return FF_EINVAL;
     bool any = false;
     std::vector<DOp> ops = s->h_ops;
+    std::vector<OpLite> lite = s->h_op_lite;
     for (uint32_t i = 0; i < s->dev.n_ops; i++) {
         DOp& o = ops[i];
         o.param_bytes = param_bytes ? param_bytes[i] : 0;
         o.param_dims = param_bytes ? (param_dims[i] & ((1u << o.ndim) - 1)) : 0;
+        lite[i].param_bytes = o.param_bytes;
         any = any || o.param_bytes;
     }
     if (hipDeviceSynchronize() != hipSuccess) return FF_EHIP;       // no launch may still read the old records
-    if (hipMemcpy(s->d_ops, ops.data(), ops.size() * sizeof(DOp), hipMemcpyHostToDevice) != hipSuccess) return FF_EHIP;
+    if (hipMemcpy(s->d_ops, ops.data(), ops.size() * sizeof(DOp), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(s->d_op_lite, lite.data(), lite.size() * sizeof(OpLite), hipMemcpyHostToDevice) != hipSuccess) return FF_EHIP;
     s->h_ops.swap(ops);
+    s->h_op_lite.swap(lite);
     s->dev.sync = any ? 1u : 0u;
+    derive(s);
     s->links_gen++;
     return FF_OK;
 }
 
 // uploads the constants for the link tables and ties in force and re-derives what depends on them
 static int apply_link_tables(ff_sim_t* s) {
-    const ff_machine_t& m = s->mach;
-    const uint32_t G = m.gpus_per_node, N = m.n_nodes;
-    uint32_t bw_min = 0xffffffffu, lat_max = 0;
-    if (s->intra_bw.empty()) { bw_min = std::min(bw_min, m.intra_Bpns); lat_max = std::max(lat_max, m.intra_lat_ns); }
-    else
-        for (uint32_t a = 0; a < G; a++)
-            for (uint32_t b = 0; b < G; b++)
-                if (a != b) { bw_min = std::min(bw_min, s->intra_bw[a * G + b]); lat_max = std::max(lat_max, s->intra_lat[a * G + b]); }
-    if (s->node_bw.empty()) { bw_min = std::min(bw_min, m.inter_Bpns); lat_max = std::max(lat_max, m.inter_lat_ns); }
-    else
-        for (uint32_t a = 0; a < N; a++)
-            for (uint32_t b = 0; b < N; b++)
-                if (a != b) { bw_min = std::min(bw_min, s->node_bw[a * N + b]); lat_max = std::max(lat_max, s->node_lat[a * N + b]); }
-    std::vector<uint32_t> image = constants_image(m, s->intra_bw, s->intra_lat, s->node_bw, s->node_lat, s->ties);
+    std::vector<uint32_t> image = derive(s);
     uint32_t* d_new = nullptr;
     int rc = upload(image, &d_new);
     if (rc) return rc;
@@ -455,7 +605,6 @@ static int apply_link_tables(ff_sim_t* s) {
     s->dev.node_table = s->node_bw.empty() ? 0u : 1u;
     s->dev.ties = s->ties.empty() ? 0u : 1u;
     s->links_gen++;
-    s->wide = needs_wide(s->big_tensors, bw_min, lat_max, G);
     return FF_OK;
 }
 
@@ -477,7 +626,7 @@ int ff_sim_set_links(ff_sim_t* s, const ff_linktable_t* links) {
     s->intra_bw.swap(bw);
     s->intra_lat.swap(lat);
     const int rc = apply_link_tables(s);
-    if (rc) { s->intra_bw.swap(bw); s->intra_lat.swap(lat); }     // nothing changed on the device: keep the old table
+    if (rc) { s->intra_bw.swap(bw); s->intra_lat.swap(lat); derive(s); }     // nothing changed on the device: keep the old table
     return rc;
 }
 
@@ -492,7 +641,7 @@ int ff_sim_set_ties(ff_sim_t* s, const uint32_t* leader) {
     }
     s->ties.swap(t);
     const int rc = apply_link_tables(s);
-    if (rc) s->ties.swap(t);
+    if (rc) { s->ties.swap(t); derive(s); }
     return rc;
 }
 
@@ -514,14 +663,16 @@ int ff_sim_set_node_links(ff_sim_t* s, const ff_nodelinks_t* links) {
     s->node_bw.swap(bw);
     s->node_lat.swap(lat);
     const int rc = apply_link_tables(s);
-    if (rc) { s->node_bw.swap(bw); s->node_lat.swap(lat); }
+    if (rc) { s->node_bw.swap(bw); s->node_lat.swap(lat); derive(s); }
     return rc;
 }
 
+// Enough for whichever kernels the links, ties and parameters in force at the time of a call select.
 size_t ff_sim_workspace_bytes(const ff_sim_t* s, uint32_t B) {
     if (!s) return 0;
-    if (s->lds_words) return 0;   // the whole per-candidate state lives in LDS
-    return (size_t)std::max<uint32_t>(1, batch_slots(s, B)) * s->batch_slot_bytes;
+    size_t need = s->lds_words ? 0 : (size_t)std::max<uint32_t>(1, batch_slots(s, B)) * s->batch_slot_bytes;
+    if (s->loop_extents && !s->loop_choice.lds) need = std::max(need, (size_t)std::max<uint32_t>(1, std::min(B, s->max_slots_loop)) * s->loop_slot_bytes);
+    return need;                  // 0: the whole per-candidate state lives in LDS
 }
 
 int ff_sim_set_workspace(ff_sim_t* s, void* d_ws, size_t bytes) {
@@ -540,11 +691,20 @@ int ff_sim_set_stats(ff_sim_t* s, ff_stats_t* d_stats) {
 // Keeping the per-edge set-up costs LDS for graphs whose words live there; it is used unless it
 // would leave part of the batch waiting for a free compute unit that the plain variant has room for.
 static bool batch_cached(const ff_sim* s, uint32_t B) {
-    return s->cache_ok && (B <= s->max_slots_cached || s->max_slots_cached >= s->max_slots);
+    return s->wide && s->cache_ok && (B <= s->max_slots_cached || s->max_slots_cached >= s->max_slots);
 }
 // wavefronts (= workspace slots) a launch of B candidates uses
 static uint32_t batch_slots(const ff_sim* s, uint32_t B) {
     return std::min(B, batch_cached(s, B) ? s->max_slots_cached : s->max_slots);
+}
+
+static int launch_batch(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_t* d_devmaps, uint32_t B, uint64_t* d_out_ns,
+                        hipStream_t st, int ext, bool cached, uint32_t slots, size_t slot_stride, uint32_t only_marked) {
+    if (!allow_lds((const void*)batch_kernel(s, cached, ext), cached ? s->lds_cached : s->lds)) return FF_EHIP;
+    hipLaunchKernelGGL(batch_kernel(s, cached, ext), dim3(slots), dim3(WAVE), cached ? s->lds_cached : s->lds, st, s->dev, s->d_ops,
+                       s->d_edges, s->d_in_edges, s->d_cost, s->d_magic, (const uint2*)d_strategies, B, (u64*)d_out_ns,
+                       (Counters*)s->d_stats, (unsigned char*)s->ws, slot_stride, d_devmaps, only_marked);
+    return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
 
 static int batch_impl(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_t* d_devmaps, uint32_t B, uint64_t* d_out_ns,
@@ -552,21 +712,39 @@ static int batch_impl(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_
     if (!s || (B && (!d_strategies || !d_out_ns))) return FF_EINVAL;
     if (B == 0) return FF_OK;
     const int ext = ext_level(s, d_devmaps != nullptr);
+    hipStream_t st = (hipStream_t)hip_stream;
+    static_assert(sizeof(Counters) == sizeof(ff_stats_t), "stats layout");
+    if (s->loop) {
+        const uint32_t slots = std::min(B, s->max_slots_loop);
+        const size_t need = s->loop_choice.lds ? 0 : (size_t)slots * s->loop_slot_bytes;
+        if (need && (!s->ws || s->ws_bytes < need)) return FF_EWORKSPACE;
+        if (!allow_lds((const void*)loop_kernel(s, ext), s->loop_lds)) return FF_EHIP;
+        hipLaunchKernelGGL(loop_kernel(s, ext), dim3(slots), dim3(WAVE), s->loop_lds, st, s->dev, s->d_ops, s->d_in_edges, s->d_op_lite,
+                           s->d_edge_lite, s->d_cost, s->d_magic, (const uint2*)d_strategies, B, (u64*)d_out_ns, (Counters*)s->d_stats,
+                           (unsigned char*)s->ws, s->loop_slot_bytes, s->d_edges, d_devmaps);
+        if (hipGetLastError() != hipSuccess) return FF_EHIP;
+        if (!s->loop_retry) return FF_OK;
+        // candidates that book a link more than four seconds ahead (hardly ever one) are left to the kernel with 64-bit rows
+        uint32_t again = std::min(B, s->max_slots);
+        if (!s->lds_words) again = (uint32_t)std::min<size_t>(again, s->ws_bytes / s->slot_bytes);
+        if (again < 1) return FF_EWORKSPACE;
+        return launch_batch(s, d_strategies, d_devmaps, B, d_out_ns, st, ext, false, again, s->slot_bytes, 1);
+    }
     const bool cached = batch_cached(s, B);
     const uint32_t slots = batch_slots(s, B);
     if (!s->lds_words && (!s->ws || s->ws_bytes < (size_t)slots * s->batch_slot_bytes)) return FF_EWORKSPACE;
-    hipStream_t st = (hipStream_t)hip_stream;
-    static_assert(sizeof(Counters) == sizeof(ff_stats_t), "stats layout");
-    if (!allow_lds((const void*)batch_kernel(s, cached, ext), cached ? s->lds_cached : s->lds)) return FF_EHIP;
-    hipLaunchKernelGGL(batch_kernel(s, cached, ext), dim3(slots), dim3(WAVE), cached ? s->lds_cached : s->lds, st, s->dev, s->d_ops,
-                       s->d_edges, s->d_in_edges, s->d_cost, s->d_magic, (const uint2*)d_strategies, B, (u64*)d_out_ns,
-                       (Counters*)s->d_stats, (unsigned char*)s->ws, s->batch_slot_bytes, d_devmaps);
-    return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
+    return launch_batch(s, d_strategies, d_devmaps, B, d_out_ns, st, ext, cached, slots, s->batch_slot_bytes, 0);
 }
 
 int ff_sim_batch_kernel_name(const ff_sim_t* s, uint32_t B, char* buf, size_t len) {
     if (!s || !buf || len < 1) return FF_EINVAL;
     const int ext = ext_level(s);
+    if (s->loop) {
+        const LoopChoice& l = s->loop_choice;
+        const int n = snprintf(buf, len, "k_loop_batch<%s, %s, %d, %u, %d, %d>", s->d_stats ? "true" : "false", l.lds ? "true" : "false", l.queue,
+                               l.rowl, ext, s->dev.gpus_per_node == 4 ? 4 : 0);
+        return (n < 0 || (size_t)n >= len) ? FF_ERANGE : FF_OK;
+    }
     const KernelChoice k = choice(s, batch_cached(s, B));
     const int n = snprintf(buf, len, "k_sim_batch<%s, %s, %s, %d, %s, %d, %d>", k.wide ? "true" : "false", k.lds_words ? "true" : "false",
                            k.stats ? "true" : "false", batch_queue_shape(k), k.cache ? "true" : "false", ext,

@@ -29,6 +29,7 @@ constexpr u32 PENDING_LIMIT = 0x7fff;       // a task may wait for fewer than th
 constexpr u64 RESULT_INVALID = ~0ull;        // invalid strategy
 constexpr u64 RESULT_INTERNAL = ~0ull - 1;   // internal consistency check failed (a bug)
 constexpr u64 RESULT_OVERFLOW = ~0ull - 2;   // a simulated time reached TIME_LIMIT
+constexpr u64 RESULT_MARK_RETRY = ~0ull - 3; // inside a call only: this candidate is left to the kernel with 64-bit link rows
 
 // cext = extent of the consumer's dim src_dim (1 if src_dim < 0)
 struct DMap { int32_t src_dim; uint32_t stride; int32_t a, b; uint32_t cext; };
@@ -57,6 +58,11 @@ struct DOp {
                                  // scalar burst brings the op and its first out-edge
 };
 
+// Link times of the event loop on kept set-up: elems elements take (umulhi((elems << SimDev::elem_sh) - 1, m) >> k) + lat1
+// ns, which equals ceil(elems * elem_bytes / bandwidth) + latency for every tensor of the graph (the host picks m, k and
+// elem_sh, and uses other kernels if there are none).
+struct LinkTime { uint32_t m, k, lat1; };
+
 // scalars describing (G, D, cost table); passed by value
 struct SimDev {
     uint32_t n_ops, n_edges, n_cols, max_parts;
@@ -71,6 +77,9 @@ struct SimDev {
     uint32_t sync;                     // 1: parameter synchronisation transfers are simulated (DOp::param_bytes)
     uint32_t node_table;               // 1: links between nodes differ per ordered node pair (table behind the one above)
     uint32_t ties;                     // 1: op i takes the configuration of op tie[i] (table behind the link tables)
+    LinkTime near_link, far_link;      // links inside a node, between nodes
+    uint32_t elem_sh;
+    uint32_t n_kept;                   // kept rows of all edges together (ffsim_kept.h)
 };
 // The constants buffer every kernel receives: words 0..64 are division constants
 // (floor(2^32/d)+1 for d = 2..64); if SimDev::link_table is set, four words per ordered pair of
@@ -81,6 +90,11 @@ struct SimDev {
 constexpr uint32_t LINK_TABLE_AT = 128;
 __host__ __device__ inline uint32_t tie_table_at(uint32_t gpus_per_node, uint32_t n_nodes) {
     return LINK_TABLE_AT + 4u * (gpus_per_node * gpus_per_node + n_nodes * n_nodes);
+}
+
+// behind that: {m, k, lat1, 0} (see LinkTime) per ordered pair of local GPUs, then per ordered pair of nodes
+__host__ __device__ inline uint32_t loop_links_at(uint32_t gpus_per_node, uint32_t n_nodes, uint32_t n_ops) {
+    return (tie_table_at(gpus_per_node, n_nodes) + n_ops + 3u) & ~3u;
 }
 
 // the per-lane condition "my bit of this lane mask is set" (the mask is used as it is)

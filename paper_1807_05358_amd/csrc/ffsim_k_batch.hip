@@ -22,10 +22,8 @@ static batch_kernel_t batch_kernel_of(const KernelChoice& k) {
 
 template <>
 batch_kernel_t batch_kernels<FFSIM_EXT, FFSIM_GPN>(const KernelChoice& k) {
-    if (k.cache) {
-        if (k.wide) return k.stats ? batch_kernel_of<true, true, true>(k) : batch_kernel_of<true, false, true>(k);
-        return k.stats ? batch_kernel_of<false, true, true>(k) : batch_kernel_of<false, false, true>(k);
-    }
+    // (graphs of small extents and tensors are served by k_loop_batch)
+    if (k.cache) return k.stats ? batch_kernel_of<true, true, true>(k) : batch_kernel_of<true, false, true>(k);
     if (k.wide) return k.stats ? batch_kernel_of<true, true, false>(k) : batch_kernel_of<true, false, false>(k);
     return k.stats ? batch_kernel_of<false, true, false>(k) : batch_kernel_of<false, false, false>(k);
 }

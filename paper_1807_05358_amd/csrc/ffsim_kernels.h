@@ -1,4 +1,6 @@
-// Kernels of the batched execution simulator: one candidate strategy per wavefront.
+// Kernels of the batched execution simulator: one candidate strategy per wavefront.  This file holds the batch kernel for
+// graphs whose tensors or links need 64-bit arithmetic or whose extents exceed 16 bits; all others are served by
+// k_loop_batch (ffsim_loop_kernels.h), which shares the design below but keeps more set-up and less queue.
 //
 // Task-graph construction (Section 5.1) and Algorithm 1 are fused: the task graph is never
 // written out.  A compute task is (op, part); its id is op*64 + part, which is
@@ -19,7 +21,7 @@
 //
 // Files: ffsim_device.h (word encoding, wavefront primitives), ffsim_strategy.h (configurations,
 // geometry, kept per-edge set-up, validity), ffsim_events.h (FIFO, recording, initial state, event
-// loop), this file (the batch kernel), ffsim_chain.h (delta simulation, search), ffsim_sweep.h
+// loop), this file (the batch kernel), ffsim_kept.h, ffsim_loop.h, ffsim_loop_kernels.h (the form on kept set-up), ffsim_chain.h (delta simulation, search), ffsim_sweep.h
 // (neighbour list and reduction), ffsim_select.h + ffsim_k_*.hip (the instantiations, compiled
 // side by side), ffsim.hip (host side of the C boundary).
 #pragma once
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(WAVE) void k_sim_batch(SimDev S, const DOp* __restr
                                                     const uint32_t* __restrict__ magic, const uint2* __restrict__ strategies,
                                                     uint32_t B, u64* __restrict__ out_ns, Counters* __restrict__ stats,
                                                     unsigned char* __restrict__ ws, size_t slot_stride,
-                                                    const uint16_t* __restrict__ devmaps) {
+                                                    const uint16_t* __restrict__ devmaps, uint32_t only_marked) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     u64* words;
@@ -91,6 +93,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_batch(SimDev S, const DOp* __restr
     const uint32_t magic_v = load_magic(magic);
     Recorder none = {};
     for (uint32_t b = blockIdx.x; b < B; b += gridDim.x) {
+        // (after a launch of the kernel with 32-bit link rows: only what that one could not simulate)
+        if (only_marked && first_u64(out_ns[b]) != RESULT_MARK_RETRY) continue;
         Counters cnt = {};
         SimT<false, EXT, GPN> m{S, T, strategies + (size_t)b * S.n_ops, words, exe_of, L, magic_v, 0, false, NO_OVERRIDE, make_uint2(0, 0), ecache, true};
         if (EXT) {

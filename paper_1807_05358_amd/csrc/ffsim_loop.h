@@ -1,0 +1,858 @@
+// The event loop (Algorithm 1) on kept set-up (ffsim_kept.h).
+#pragma once
+#include "ffsim_events.h"
+#include "ffsim_kept.h"
+#include <type_traits>
+
+namespace ffsim {
+
+// ---- queue of pending events -------------------------------------------------------------
+//
+// Only ops with a pending event matter to the queue, and there are few of them at any time: 2 to 10 on the
+// convolutional graphs, about 100 in the first moments of the unrolled recurrent graph and 7 after that.  So the queue is one
+// register, a lane per op with an event:
+//   Q_OP16 / Q_OP   graphs of at most 16 / 64 ops: lane = op;
+//   Q_SLOT          any graph: lane = slot, a second register holds the slot's op; when all 64 slots are taken, the op
+//                   with the latest event moves to a spill list in memory and comes back when its turn does.
+// A key is the event's word (2 * time + kind) relative to 2 * E, in 32 bits.  E, the epoch, follows the simulated time
+// in steps of about a second (advance_epoch); KEY_FAR stands for an event at a distance that does not fit (its word in
+// memory has it in full), KEY_NONE for no event.
+enum LoopQueue : int { Q_OP16 = 0, Q_OP = 1, Q_SLOT = 2 };
+constexpr uint32_t KEY_NONE = 0xffffffffu, KEY_FAR = 0xfffffffeu;
+constexpr uint32_t KEY_REFRESH = 0x80000000u;    // a smallest key from here on: no event left, or time to move the epoch
+constexpr uint32_t NO_OP = 0xffffffffu;
+constexpr u64 RESULT_RETRY = 2;                  // a link row is booked beyond 32 bits: simulate again with 64-bit rows
+constexpr uint32_t RUN_SPAN = 0x40000000u;       // events of one step lie at most this far apart
+
+struct Queue {
+    uint32_t key, op;           // per lane
+    uint32_t n_spill;           // uniform
+    u64 spill_min;              // smallest word on the spill list (absolute; W_NONE if it is empty)
+};
+
+// per-candidate state of the loop that outlives a call of run_loop
+struct LoopState {
+    Queue q;
+    u64 E;                      // epoch (ns)
+};
+
+// memory of one candidate (see slot_layout)
+struct LoopMem {
+    u64* words;                 // [n_ops][ROWL]
+    uint4* hdr;                 // [n_ops_pad]
+    uint32_t* rows;             // [n_edges][KEPT_ROWS][ROWL]
+    uint32_t* priv;             // trial mutations: the rows of the mutated op's in-edges, then of its out-edges
+    u64* spill_key;             // [n_ops_pad]
+    uint32_t* spill_op;         // [n_ops_pad]
+    u64* crow;                  // LDS [n_dev]: endTime of the last task of every compute device
+    uint32_t* lrow;             // LDS [n_links]: endTime of the last transfer of every link row, relative to E
+    uint8_t* tag;               // LDS [n_rows]: see fifo_commit
+    const uint4* links;         // {m, k, lat1, 0} per ordered pair of local GPUs, then per ordered pair of nodes; or null
+    const OpLite* op_lite;      // static records (ffsim_kept.h)
+    const EdgeLite* edge_lite;
+};
+
+// minimum over the parts of a row of ROWL lanes (lanes beyond them hold the identity)
+template <int ROWL>
+__device__ __forceinline__ uint32_t part_min_u32(uint32_t v) { return ROWL == 16 ? row0_min_u32(v) : wave_min_u32(v); }
+
+// the minimum of v over the lanes of a mask that is often a single lane
+template <int ROWL>
+__device__ __forceinline__ uint32_t part_min_of(uint32_t v, u64 mask) {
+    if ((mask & (mask - 1)) == 0) return readlane_u32(v, __builtin_ctzll(mask));
+    return part_min_u32<ROWL>(lanes_of(mask) ? v : KEY_NONE);
+}
+
+template <int ROWL>
+__device__ __forceinline__ u64 load_word(const u64* words, uint32_t op) {
+    const uint32_t lane = lane_id();
+    if (ROWL == WAVE) return words[(size_t)op * WAVE + lane];
+    u64 w = W_NONE;
+    if (lane < (uint32_t)ROWL) w = words[(size_t)op * ROWL + lane];
+    return w;
+}
+// smallest pending event of an op, from its words in memory (W_NONE: none)
+template <int ROWL>
+__device__ __forceinline__ u64 op_min_word(const u64* words, uint32_t op) {
+    const u64 w = load_word<ROWL>(words, op);
+    const u64 m = wave_min_u64(w);
+    return m >> 63 ? W_NONE : m;
+}
+__device__ __forceinline__ uint32_t rel_key(u64 word, u64 E) {
+    const u64 d = word - 2 * E;
+    return d >= KEY_FAR ? KEY_FAR : (uint32_t)d;
+}
+
+__device__ __forceinline__ void queue_clear(Queue& q) { q.key = KEY_NONE; q.op = NO_OP; q.n_spill = 0; q.spill_min = W_NONE; }
+
+__device__ __forceinline__ void spill_push(const LoopMem& mem, Queue& q, uint32_t op, u64 word) {
+    if (lane_id() == 0) { mem.spill_key[q.n_spill] = word; mem.spill_op[q.n_spill] = op; }
+    q.n_spill++;
+    q.spill_min = word < q.spill_min ? word : q.spill_min;
+    wave_sync();
+}
+// recomputes the minimum of the spill list
+__device__ __forceinline__ void spill_scan(const LoopMem& mem, Queue& q) {
+    u64 v = W_NONE;
+    for (uint32_t t = lane_id(); t < q.n_spill; t += WAVE) { const u64 w = mem.spill_key[t]; v = w < v ? w : v; }
+    q.spill_min = wave_min_u64(v);
+}
+// takes entry t off the spill list
+__device__ __forceinline__ void spill_remove(const LoopMem& mem, Queue& q, uint32_t t) {
+    q.n_spill--;
+    if (lane_id() == 0) { mem.spill_key[t] = mem.spill_key[q.n_spill]; mem.spill_op[t] = mem.spill_op[q.n_spill]; }
+    wave_sync();
+    spill_scan(mem, q);
+}
+
+// All slots are taken and op j, which has none, gets an event: the latest of the 65 events goes to the spill list.
+template <int ROWL>
+__device__ __forceinline__ void queue_spill(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
+    Queue& q = st.q;
+    const uint32_t kmax = ~wave_min_u32(~q.key);
+    // (a far event has its true word in memory; so has any other: the word is read back rather than rebuilt)
+    if (key >= kmax) {
+        spill_push(mem, q, j, key >= KEY_FAR ? op_min_word<ROWL>(mem.words, j) : 2 * st.E + key);
+        return;
+    }
+    const uint32_t slot = __builtin_ctzll(ballot(q.key == kmax));
+    const uint32_t old = readlane_u32(q.op, slot);
+    spill_push(mem, q, old, kmax >= KEY_FAR ? op_min_word<ROWL>(mem.words, old) : 2 * st.E + kmax);
+    if ((uint32_t)lane_id() == slot) { q.key = key; q.op = j; }
+}
+
+// gives op j the event `key` if it is earlier than what it has
+template <int Q, int ROWL>
+__device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
+    Queue& q = st.q;
+    if (Q != Q_SLOT) {
+        const uint32_t k = (uint32_t)lane_id() == j ? key : KEY_NONE;
+        q.key = k < q.key ? k : q.key;
+        return;
+    }
+    u64 at = ballot(q.op == j);
+    if (!at) {
+        if (q.n_spill) {
+            // on the spill list already?
+            for (uint32_t b = 0; b < q.n_spill; b += WAVE) {
+                const uint32_t t = b + lane_id();
+                const u64 hit = ballot(t < q.n_spill && mem.spill_op[t < q.n_spill ? t : 0] == j);
+                if (hit) {
+                    const uint32_t at_t = b + __builtin_ctzll(hit);
+                    const u64 word = key >= KEY_FAR ? W_NONE : 2 * st.E + key;
+                    if (lane_id() == 0 && word < mem.spill_key[at_t]) mem.spill_key[at_t] = word;
+                    wave_sync();
+                    spill_scan(mem, q);
+                    return;
+                }
+            }
+        }
+        at = ballot(q.op == NO_OP);
+        if (!at) { queue_spill<ROWL>(mem, st, j, key); return; }
+        at &= 0 - at;
+    }
+    const bool me = lanes_of(at);
+    const uint32_t k = me ? key : KEY_NONE;
+    q.key = k < q.key ? k : q.key;
+    q.op = me ? j : q.op;
+}
+
+// The smallest event on the spill list is not later than the smallest one in the slots: it changes places with the
+// latest event there (or takes a free slot).
+template <int ROWL>
+__device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st) {
+    Queue& q = st.q;
+    // the entry with the smallest word, the lowest op among equal ones
+    u64 best = W_NONE;
+    uint32_t bop = NO_OP, bt = 0;
+    for (uint32_t t = lane_id(); t < q.n_spill; t += WAVE) {
+        const u64 w = mem.spill_key[t];
+        const uint32_t o = mem.spill_op[t];
+        if (w < best || (w == best && o < bop)) { best = w; bop = o; bt = t; }
+    }
+    const u64 m = wave_min_u64(best);
+    const uint32_t mop = wave_min_u32(best == m ? bop : NO_OP);
+    const uint32_t t = readlane_u32(bt, __builtin_ctzll(ballot(best == m && bop == mop)));
+    spill_remove(mem, q, t);
+    const uint32_t key = rel_key(m, st.E);
+    u64 at = ballot(q.op == NO_OP);
+    uint32_t slot;
+    if (at) {
+        slot = __builtin_ctzll(at);
+    } else {
+        // the latest slot makes room (never a loop: the entry just taken off is not later than any slot that would
+        // bring it back; among equal keys the highest op leaves)
+        const uint32_t kmax = ~wave_min_u32(~q.key);
+        const uint32_t omax = ~wave_min_u32(q.key == kmax ? ~q.op : NO_OP);
+        slot = __builtin_ctzll(ballot(q.key == kmax && q.op == omax));
+        spill_push(mem, q, omax, kmax >= KEY_FAR ? op_min_word<ROWL>(mem.words, omax) : 2 * st.E + kmax);
+    }
+    if ((uint32_t)lane_id() == slot) { q.key = key; q.op = mop; }
+}
+
+// Moves the epoch to the next pending event.  Returns false if there is none.
+// (What a link row holds below the epoch no longer matters: nothing becomes ready before it.)
+template <int Q, int ROWL>
+__device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st, uint32_t n_links) {
+    Queue& q = st.q;
+    u64 word = q.key >= KEY_FAR ? W_NONE : 2 * st.E + q.key;      // this lane's event in full
+    u64 far = ballot(q.key == KEY_FAR);
+    while (far) {
+        const int l = __builtin_ctzll(far);
+        far &= far - 1;
+        const uint32_t op = Q == Q_SLOT ? readlane_u32(q.op, l) : (uint32_t)l;
+        const u64 w = op_min_word<ROWL>(mem.words, op);
+        if (lane_id() == l) word = w;
+    }
+    u64 next = wave_min_u64(word);
+    if (Q == Q_SLOT) next = q.spill_min < next ? q.spill_min : next;
+    if (next >> 63) return false;
+    const u64 E = next >> 1;
+    const u64 delta = E - st.E;
+    st.E = E;
+    q.key = word >> 63 ? KEY_NONE : rel_key(word, E);
+    const uint32_t d32 = delta >> 32 ? 0xffffffffu : (uint32_t)delta;
+    for (uint32_t r = lane_id(); r < n_links; r += WAVE) mem.lrow[r] = __builtin_elementwise_sub_sat(mem.lrow[r], d32);
+    wave_sync();
+    return true;
+}
+
+// ---- state: start, snapshots, result -------------------------------------------------------
+
+// Writes the next snapshot: the task words, and endTimes of all device and link rows (absolute).  Result: see save_snapshot
+// (ffsim_events.h).  The queue is not stored: it follows from the words.
+template <int ROWL, class SimX>
+__device__ __forceinline__ bool save_loop_snapshot(const SimX& m, const LoopMem& mem, const LoopState& st, Recorder& rec) {
+    const uint32_t lane = lane_id();
+    const uint32_t idx = rec.next, n_rows = m.S.n_rows, n_dev = m.S.n_dev;
+    const size_t k = (size_t)((((rec.loc >> idx) & 1u) ^ 1u) * rec.n_snaps + idx);   // the place the accepted timeline does not use
+    const bool check = idx < rec.check_below;
+    bool differs = false;
+    const size_t nw = (size_t)m.S.n_ops * ROWL;
+    u64* fr = rec.snap_free + k * (size_t)n_rows;
+    if (check) {
+        const size_t old = (size_t)(((rec.loc >> idx) & 1u) * rec.n_snaps + idx);
+        differs = copy_words_compare(rec.snap_words + k * nw, mem.words, rec.snap_words + old * nw, (uint32_t)nw);
+        const u64 t_snap = ((u64)idx * rec.step) >> 1;
+        const u64* ofr = rec.snap_free + old * (size_t)n_rows;
+        for (uint32_t t = lane; t < n_rows; t += WAVE) {
+            const u64 a = t < n_dev ? mem.crow[t] : st.E + mem.lrow[t - n_dev], b = ofr[t];
+            differs = differs || (a > t_snap ? a : t_snap) != (b > t_snap ? b : t_snap);
+        }
+        // a task of the changed op still pending would make equal words mean different things
+        differs = differs || load_word<ROWL>(mem.words, rec.check_op) != W_NONE;
+    } else {
+        copy_words(rec.snap_words + k * nw, mem.words, (uint32_t)nw);
+    }
+    for (uint32_t t = lane; t < n_rows; t += WAVE) fr[t] = t < n_dev ? mem.crow[t] : st.E + mem.lrow[t - n_dev];
+    rec.next++;
+    return check && !ballot(differs);
+}
+
+// The state of snapshot k of the accepted timeline: words copied, rows and queue rebuilt.  False if a link row is booked
+// beyond 32 bits after the snapshot's time.
+template <int Q, int ROWL, class SimX>
+__device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem& mem, LoopState& st, const Recorder& rec, uint32_t k) {
+    const uint32_t lane = lane_id();
+    const uint32_t n_rows = m.S.n_rows, n_dev = m.S.n_dev, n_ops = m.S.n_ops;
+    const size_t at = (size_t)(((rec.loc >> k) & 1u) * rec.n_snaps + k);
+    const u64 E = ((u64)k * rec.step) >> 1;        // no event before it
+    st.E = E;
+    bool beyond = false;
+    const u64* fr = rec.snap_free + at * (size_t)n_rows;
+    for (uint32_t t = lane; t < n_rows; t += WAVE) {
+        const u64 a = fr[t];
+        if (t < n_dev) { mem.crow[t] = a; continue; }
+        const u64 r = a > E ? a - E : 0;
+        beyond = beyond || r >= 0xffffffffull;
+        mem.lrow[t - n_dev] = (uint32_t)r;
+    }
+    queue_clear(st.q);
+    const u64* src = rec.snap_words + at * (size_t)n_ops * ROWL;
+    // eight rows of 64 words in flight; a row of ROWL = 16 holds the words of four ops
+    constexpr uint32_t PER = WAVE / ROWL;
+    const uint32_t n_words = n_ops * ROWL;
+    for (uint32_t b = 0; b < n_words; b += 8 * WAVE) {
+        u64 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) { const uint32_t t = b + u * WAVE + lane; v[u] = t < n_words ? src[t] : W_NONE; }
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const uint32_t t = b + u * WAVE + lane;
+            if (t < n_words) mem.words[t] = v[u];
+            if (ballot(!(v[u] >> 63))) {
+                for (uint32_t g = 0; g < PER; g++) {
+                    const u64 mine = lane / ROWL == g ? v[u] : W_NONE;
+                    const u64 mn = wave_min_u64(mine);
+                    if (!(mn >> 63)) queue_insert<Q, ROWL>(mem, st, (b + u * WAVE) / ROWL + g, rel_key(mn, E));
+                }
+            }
+        }
+    }
+    wave_sync();
+    return !ballot(beyond);
+}
+
+// Section 5.1 step 1 and the start of Algorithm 1: the tasks, how many inputs each waits for, the initial READY set,
+// idle devices.  FILL: computes and keeps the set-up of every edge; otherwise the kept rows are valid and only read.
+// Configurations are loaded 64 at a time and read from registers, so that no op waits for its own loads.
+template <int Q, int ROWL, class SimX>
+__device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, bool fill) {
+    const uint32_t lane = lane_id();
+    const uint32_t n_ops = m.S.n_ops, n_edges = m.S.n_edges;
+    for (uint32_t r = lane; r < m.S.n_dev; r += WAVE) mem.crow[r] = 0;
+    for (uint32_t r = lane; r < m.S.n_rows - m.S.n_dev; r += WAVE) mem.lrow[r] = 0;
+    queue_clear(st.q);
+    st.E = 0;
+    uint2 sc = make_uint2(0, 0);                    // configurations of the producers of the next 64 in-edges
+    uint32_t seid = 0, ssrc = 0;                    // their edge ids and producers
+    for (uint32_t base = 0; base < n_ops; base += WAVE) {
+        const uint32_t jl = base + lane < n_ops ? base + lane : n_ops - 1;
+        const uint2 cv = m.cfg_raw(jl);
+        const uint32_t ibv = m.T.ops[jl].in_begin, iev = m.T.ops[jl].in_end;
+        const uint32_t n = n_ops - base < (uint32_t)WAVE ? n_ops - base : (uint32_t)WAVE;
+        for (uint32_t jj = 0; jj < n; jj++) {
+            const uint32_t j = base + jj;
+            const OpCfg cj = unpack_cfg(make_uint2(readlane_u32(cv.x, jj), readlane_u32(cv.y, jj)));
+            const uint32_t ib = readlane_u32(ibv, jj), ie = readlane_u32(iev, jj);
+            uint32_t pending = 0;
+            for (uint32_t e_at = ib; e_at < ie; e_at++) {
+                const uint32_t el = e_at & (WAVE - 1);
+                if (el == 0) {
+                    const uint32_t t = e_at + lane < n_edges ? e_at + lane : n_edges - 1;
+                    ssrc = m.T.in_edges[t].src;
+                    seid = m.T.in_edges[t].eid;
+                    sc = m.cfg_raw(ssrc);
+                }
+                const uint32_t eid = readlane_u32(seid, el);
+                uint32_t* row = mem.rows + (size_t)mem.edge_lite[eid].row * ROWL;
+                if (fill) {
+                    const DEdge e = m.T.in_edges[e_at];
+                    const OpCfg cp = unpack_cfg(make_uint2(readlane_u32(sc.x, el), readlane_u32(sc.y, el)));
+                    pending += kept_edge<ROWL>(m, row, e, cp, cj);
+                } else {
+                    if (SimX::kOvr && mem.priv) {
+                        const uint32_t src = readlane_u32(ssrc, el);
+                        if (src == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (eid - m.T.ops[src].out_begin)) * (KEPT_ROWS * ROWL);
+                        else if (j == m.ov_op) row = mem.priv + (size_t)(e_at - ib) * (KEPT_ROWS * ROWL);
+                    }
+                    pending += (row[KR_SORT * ROWL + (lane & (ROWL - 1))] >> 24) & 0x7fu;
+                }
+            }
+            // pending < PENDING_LIMIT is guaranteed by ff_sim_create (at most 511 in-edges per op)
+            const u64 w = lane >= cj.parts ? W_NONE : (pending == 0 ? 1ull : (W_WAIT | ((u64)pending << 48)));
+            if (ROWL == WAVE || lane < (uint32_t)ROWL) mem.words[(size_t)j * ROWL + lane] = w;
+            if (ballot(w == 1ull)) queue_insert<Q, ROWL>(mem, st, j, 1u);
+            cnt.n_compute += cj.parts;
+        }
+    }
+    wave_sync();
+}
+
+// Section 4: every configuration valid?  Fills the kept op records.
+template <int Q, class SimX>
+__device__ __forceinline__ StrategyClass validate_loop(const SimX& m, const LoopMem& mem) {
+    const StrategyClass cls = validate_with(m, [&](uint32_t i, const OpCfg& c, uint32_t exe) __attribute__((always_inline)) { mem.hdr[i] = kept_header(c, exe); });
+    if (Q == Q_SLOT && cls != STRATEGY_INVALID) {
+        wave_sync();
+        for (uint32_t i = lane_id(); i < m.S.n_ops; i += WAVE) {
+            const OpLite o = mem.op_lite[i];
+            if (o.out_end > o.out_begin) mem.hdr[i].z = mem.hdr[o.first.word & EL_DST].x;
+        }
+    }
+    wave_sync();
+    return cls;
+}
+
+// Algorithm 1, result: see makespan (ffsim_events.h)
+template <class SimX>
+__device__ __forceinline__ u64 loop_makespan(const SimX& m, const LoopMem& mem, const LoopState& st) {
+    u64 mk = 0;
+    for (uint32_t d = lane_id(); d < m.S.n_dev; d += WAVE) mk = mem.crow[d] > mk ? mem.crow[d] : mk;
+    if (SimX::kExt && m.S.sync) {
+        for (uint32_t r = lane_id(); r < m.S.n_rows - m.S.n_dev; r += WAVE) {
+            const u64 t = mem.lrow[r] ? st.E + mem.lrow[r] : 0;
+            mk = t > mk ? t : mk;
+        }
+    }
+    return wave_max_u64(mk);
+}
+
+// ---- link rows in general order ----------------------------------------------------------
+
+// fifo_commit (ffsim_events.h) on link rows: the same serialisation in 32-bit times relative to the epoch; sums that do
+// not fit stick at 2^32 - 1 (the caller simulates again)
+__device__ __forceinline__ uint32_t fifo_links(bool act, uint32_t row, uint32_t exe, uint32_t r, bool may_share, const LoopMem& mem) {
+    const int lane = lane_id();
+    uint32_t f = 0;
+    bool lost = false;
+    if (may_share) {
+        if (act) mem.tag[row] = (uint8_t)lane;
+        wave_sync();
+        if (act) { lost = mem.tag[row] != (uint8_t)lane; f = mem.lrow[row]; }
+    } else if (act) {
+        f = mem.lrow[row];
+    }
+    const uint32_t base = f > r ? f : r;
+    uint32_t end = __builtin_elementwise_add_sat(base, exe);
+    u64 todo = ballot(lost);
+    while (todo) {
+        const int l = __builtin_ctzll(todo);
+        const uint32_t lrow = readlane_u32(row, l);
+        const bool peer = act && row == lrow;
+        const u64 peers = ballot(peer);
+        todo &= ~peers;
+        uint32_t t = 0;
+        u64 pm = peers;
+        while (pm) {
+            const int p = __builtin_ctzll(pm);
+            pm &= pm - 1;
+            t = __builtin_elementwise_add_sat(t, readlane_u32(exe, p));
+            if (lane == p) end = __builtin_elementwise_add_sat(base, t);
+        }
+    }
+    if (act) __hip_atomic_fetch_max(&mem.lrow[row], end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    wave_sync();
+    return end;
+}
+
+// ---- the loop ----------------------------------------------------------------------------
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t v) { return __builtin_bit_cast(u16x2, v); }
+// (one instruction that reads both halves; the compiler would rather multiply the halves by other factors one by one)
+__device__ __forceinline__ uint32_t pair_product(u16x2 v) {
+    uint32_t r;
+    asm("v_mul_u32_u24_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(r) : "v"(v));
+    return r;
+}
+// n + 1 on the lanes of a mask
+__device__ __forceinline__ uint32_t count_lanes(uint32_t n, u64 mask) {
+    asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(n) : "s"(mask) : "vcc");
+    return n;
+}
+// a uniform value the compiler is not to recompute (or to move into a branch of its own)
+__device__ __forceinline__ uint32_t opaque(uint32_t uniform) { asm("" : "+s"(uniform)); return uniform; }
+// lrow[row] = max(lrow[row], v) on the lanes of a mask, without a branch around it.  Call with all 64 lanes active; row must
+// be in range on every lane of the mask.
+__device__ __forceinline__ void row_max(uint32_t* lrow, uint32_t row, uint32_t v, u64 mask) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)(lrow + row);
+    asm volatile("s_mov_b64 exec, %2\n\tds_max_u32 %0, %1\n\ts_mov_b64 exec, -1" : : "v"(at), "v"(v), "s"(mask) : "memory");
+}
+// lengths of the intersection of two pairs of ranges [lo, hi), 0 where they do not meet
+__device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_b, uint32_t hi_b) {
+    const u16x2 lo = __builtin_elementwise_max(as_u16x2(lo_a), as_u16x2(lo_b));
+    const u16x2 hi = __builtin_elementwise_min(as_u16x2(hi_a), as_u16x2(hi_b));
+    return __builtin_elementwise_sub_sat(hi, lo);
+}
+
+// Algorithm 1 from the current state to the end.  RECORD, REG, STATS as for run_events; Q: LoopQueue; ROWL: lanes per row.
+// Returns 0, RUN_CONVERGED, RESULT_RETRY or a RESULT_* code.
+//
+// What bounds it: one wavefront is one dependent chain of instructions; a dependent vector instruction takes 8 cycles,
+// an independent one 5, a branch 20 to 35, an LDS round trip 52, a load that misses the scalar cache or hits L2 150 to 200
+// (measured on one wavefront of an otherwise idle compute unit).  With one wavefront per SIMD the chain is the time; with
+// four the vector unit is two thirds busy.  Both ask for the same thing, fewer instructions per event: boxes of parts as pairs of
+// 16-bit values (a pass over the consumer parts took 95 instructions in run_events, it takes 60 here), times in 32 bits,
+// the queue in a register.  Per launch, against run_events: 4096 x Inception-v3-shaped 9.34 -> 7.20 ms, 4096 x
+// ResNet-101-shaped 20.1 -> 13.9, 1024 x NMT-shaped 98.9 -> 74.2, 1024 x AlexNet-shaped 0.232 -> 0.219; general
+// strategies (777 x ResNet-101-shaped on 5 x 3 devices) 31.2 -> 22.4; training iterations (1024 x Inception-v3-shaped)
+// 24.6 -> 18.5.
+template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, class SimX>
+__device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec) {
+    constexpr bool RUNS = Q == Q_SLOT;       // runs of events (see run_events): on graphs of more than 64 ops
+    const uint32_t lane = lane_id();
+    PROF_DECL
+    const SimDev& S = m.S;
+    u64* words = mem.words;
+    u64 overflow_m = 0;                      // lanes that reached TIME_LIMIT
+    u64 retry_m = 0;                         // lanes whose link row is booked beyond 32 bits
+    const uint32_t G = m.gpn();
+    const uint32_t n_links = S.n_rows - S.n_dev;
+    // chosen per lane between the two of a pair: in vector registers, so that a select needs one scalar operand only
+    const uint32_t m_near = vector_copy(S.near_link.m), m_far = vector_copy(S.far_link.m);
+    const uint32_t k_near = vector_copy(S.near_link.k), k_far = vector_copy(S.far_link.k);
+    const uint32_t l_near = vector_copy(S.near_link.lat1), l_far = vector_copy(S.far_link.lat1);
+    const uint32_t elem_sh = vector_copy(S.elem_sh);
+    Queue& q = st.q;
+    const u64 max_events = 2ull * S.n_ops * WAVE + 8;
+    uint32_t snap_key = KEY_NONE;            // RECORD: key of the next snapshot boundary
+    auto set_snap_key = [&]() {
+        if (RECORD) {
+            const u64 at = (u64)rec.next * rec.step;
+            snap_key = rec.next < rec.n_snaps ? (at <= 2 * st.E ? 0u : rel_key(at, st.E)) : KEY_NONE;
+        }
+    };
+    set_snap_key();
+    for (u64 ev = 0; ev < max_events; ev++) {
+        // ---- pop
+        uint32_t kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
+        if (kmin >= KEY_REFRESH) {
+            if (!advance_epoch<Q, ROWL>(mem, st, n_links)) break;
+            set_snap_key();
+            kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
+        }
+        if (Q == Q_SLOT && q.n_spill) {
+            for (uint32_t guard = 0; q.n_spill && guard < S.n_ops + WAVE; guard++) {
+                const u64 top = 2 * st.E + kmin;
+                if (q.spill_min > top) break;
+                if (q.spill_min == top) {
+                    // equal keys: only needed if a spilled op comes first; bring in all of them
+                    const uint32_t lo_op = wave_min_u32(q.key == kmin ? q.op : NO_OP);
+                    uint32_t sop = NO_OP;
+                    for (uint32_t t = lane; t < q.n_spill; t += WAVE)
+                        if (mem.spill_key[t] == top && mem.spill_op[t] < sop) sop = mem.spill_op[t];
+                    if (wave_min_u32(sop) > lo_op) break;
+                }
+                queue_unspill<ROWL>(mem, st);
+                kmin = wave_min_u32(q.key);
+            }
+        }
+        if (RECORD) {
+            // the state before the first event at or after a multiple of `step` is a snapshot
+            while (kmin >= snap_key) {
+                if (save_loop_snapshot<ROWL>(m, mem, st, rec)) return RUN_CONVERGED;
+                set_snap_key();
+            }
+        }
+        u64 at = ballot(q.key == kmin);
+        uint32_t i;
+        if (Q != Q_SLOT) {
+            i = __builtin_ctzll(at);         // lowest op among equal keys
+            at &= 0 - at;
+        } else {
+            if (at & (at - 1)) {
+                i = wave_min_u32(lanes_of(at) ? q.op : NO_OP);
+                at &= ballot(q.op == i);
+            } else {
+                i = readlane_u32(q.op, __builtin_ctzll(at));
+            }
+        }
+        const u64 K = 2 * st.E + kmin;       // the popped word
+        PROF_MARK(1)
+        const OpLite lite = mem.op_lite[i];
+        u64 k0 = load_word<ROWL>(words, i);
+        uint4 h = mem.hdr[i];
+        const uint32_t exe = first_u32(h.x), offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
+        OpCfg ci;
+        ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
+        const uint32_t out_begin = lite.out_begin, out_end = lite.out_end;
+        const uint32_t dev_p = m.template device_of<REG>(i, ci);
+        PROF_MARK(1)
+        PROF_VMWAIT(2)
+        // distance of every event of the op from the popped one (words that are no events: all ones, an odd value)
+        uint32_t d;
+        {
+            const u64 dd = k0 - K;
+            d = (uint32_t)(dd >> 32) ? KEY_NONE : (uint32_t)dd;
+        }
+        const u64 mask_same = ballot(d == 0);
+        if (!mask_same) { cnt.exit_code = 2; return RESULT_INTERNAL; }
+        cnt.n_events++;
+        u64 mask = mask_same;
+        bool mixed = false;
+        if (RUNS && ((kmin & 1) ? REG : (out_end - out_begin == 1 && !(SimX::kExt && S.sync)))) {
+            const u64 kind_m = ballot((d & 1u) == 0u);
+            if (kind_m != mask_same) {
+                const uint32_t other_key = wave_min_u32(lanes_of(at) ? KEY_NONE : q.key);
+                uint32_t bound = other_key >= KEY_FAR ? KEY_NONE : other_key - kmin;
+                if (Q == Q_SLOT && q.n_spill) {
+                    const u64 s = q.spill_min - K;
+                    if (s < bound) bound = (uint32_t)s;
+                }
+                const uint32_t odd = part_min_u32<ROWL>((d & 1u) ? d : KEY_NONE);
+                bound = odd < bound ? odd : bound;
+                const uint32_t e = (kmin & 1) ? exe : next_exe;
+                const uint32_t first_new = e >= RUN_SPAN / 2 ? RUN_SPAN : 2 * e;
+                bound = first_new < bound ? first_new : bound;
+                if (RECORD && snap_key < KEY_FAR) { const uint32_t s = snap_key - kmin; bound = s < bound ? s : bound; }
+                mask = mask_same | ballot((d & 1u) == 0u && d < bound);
+                mixed = mask != mask_same;
+            }
+        }
+        const bool in_mask = lanes_of(mask);
+        uint32_t d_new = d;
+
+        if (kmin & 1) {
+            // dequeue READY tasks: start = max(readyTime, device free), end = start + exeTime
+            u64 end;
+            if (REG) {
+                const u64 f = mem.crow[dev_p];               // (in range for every lane)
+                const u64 r = k0 >> 1;
+                end = (f > r ? f : r) + exe;
+                if (in_mask) mem.crow[dev_p] = end;
+                wave_sync();
+            } else {
+                const bool may_share = (SimX::kExt && m.devmap != nullptr) || !(ci.stride == 1 && ci.parts <= S.n_dev);
+                end = fifo_commit(in_mask, dev_p, exe, K >> 1, may_share, m.L);
+            }
+            overflow_m |= mask & ballot(end >= TIME_LIMIT);
+            const bool releases = out_end > out_begin || (SimX::kExt && S.sync && lite.param_bytes != 0);
+            const u64 w = end << 1;
+            if (releases) {
+                const u64 dd = w - K;
+                const uint32_t dn = (uint32_t)(dd >> 32) ? KEY_NONE : (uint32_t)dd;
+                d_new = in_mask ? dn : d;
+            } else {
+                d_new = in_mask ? KEY_NONE : d;
+            }
+            if (in_mask) k0 = releases ? w : W_NONE;
+            if (RECORD) { if (in_mask && rec.end_try) rec.end_try[(size_t)i * ROWL + lane] = rec.tag | end; }
+            PROF_MARK(3)
+        } else {
+            const uint32_t node_p = m.node_of(dev_p);
+            const uint32_t now = kmin >> 1;                  // relative to the epoch
+            // The parts go in order: by part, or in a run by (time, part).  For a run what the passes read of the parts is
+            // first brought into that order (lane t then stands for the t-th part).
+            uint32_t order = lane;
+            u64 parts_m = mask;
+            if (mixed) {
+                uint32_t rank = 0;
+                u64 t = mask;
+                while (t) {
+                    const int p = __builtin_ctzll(t);
+                    t &= t - 1;
+                    const uint32_t dp = readlane_u32(d, p);
+                    rank = count_lanes(rank, ballot(dp < d) | (ballot(dp == d) & ~((2ull << p) - 1)));
+                }
+                const u64 rest = ~mask;
+                const uint32_t behind = __builtin_amdgcn_mbcnt_hi((uint32_t)(rest >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rest, (uint32_t)__popcll(mask)));
+                order = scatter_u32(lane, in_mask ? rank : behind);
+                parts_m = __popcll(mask) == 64 ? ~0ull : (1ull << __popcll(mask)) - 1;
+            }
+            uint32_t now_v = (kmin + d) >> 1, dev_v = dev_p;
+            if (mixed) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
+            for (uint32_t ei = out_begin; ei < out_end; ei++) {
+                EdgeLite lit = lite.first;
+                if (ei != out_begin) lit = mem.edge_lite[ei];
+                const uint32_t el = lit.word;
+                const uint32_t j = el & EL_DST;
+                const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
+                if (SimX::kOvr && mem.priv) {
+                    // a trial mutation's own edges have rows of their own
+                    if (i == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (ei - out_begin)) * (KEPT_ROWS * ROWL);
+                    else if (j == m.ov_op) row = mem.priv + (size_t)lit.in_pos * (KEPT_ROWS * ROWL);
+                }
+                const uint32_t* p = row + (ROWL < WAVE ? (lane & (ROWL - 1)) : lane);
+                uint32_t f = 0, clo = 0, chi = 0, plo = 0, phi = 0, clo2 = 0, chi2 = 0, plo2 = 0, phi2 = 0, sortw = 0;
+                u64 w = load_word<ROWL>(words, j);
+                f = p[KR_F * ROWL]; clo = p[KR_CLO * ROWL]; chi = p[KR_CHI * ROWL]; plo = p[KR_PLO * ROWL]; phi = p[KR_PHI * ROWL];
+                if (el & EL_FOUR) { clo2 = p[KR_CLO2 * ROWL]; chi2 = p[KR_CHI2 * ROWL]; plo2 = p[KR_PLO2 * ROWL]; phi2 = p[KR_PHI2 * ROWL]; }
+                if (!REG) sortw = p[KR_SORT * ROWL];
+                if (ROWL < WAVE) {
+                    // (no part there: an empty range)
+                    chi = lane < (uint32_t)ROWL ? chi : 0u;
+                    chi2 = lane < (uint32_t)ROWL ? chi2 : 0u;
+                }
+                const uint32_t dev_c = f & 1023u;
+                const uint32_t node_c = SimX::kGpn == 4 ? dev_c >> 2 : (f >> 10) & 1023u;
+                const uint32_t local_c = m.local_of(dev_c, node_c);
+                const uint32_t far_base = S.n_nodes * G * G + node_c;
+                u64 ready64 = w & (TIME_LIMIT - 1);
+                uint32_t ready;                             // relative to the epoch; what lies before it no longer matters
+                {
+                    const u64 rr = ready64 - st.E;
+                    ready = (int32_t)(uint32_t)(rr >> 32) < 0 ? 0u : (uint32_t)rr;
+                }
+                const uint32_t pending = (uint32_t)(w >> 48) & PENDING_LIMIT;
+                uint32_t c1 = 0, c2 = 0, c3 = 0, last_run = 0, first_len = 0;
+                bool wrapped = false;
+                if (REG) {
+                    c1 = (uint32_t)((int32_t)(f << 11) >> 31);
+                    c2 = (uint32_t)((int32_t)(f << 10) >> 31);
+                    c3 = (uint32_t)((int32_t)(f << 9) >> 31);
+                    last_run = (uint32_t)((int32_t)(f << 4) >> 31);
+                    const uint32_t u = first_u32(f);         // the last two fields are the same in every lane
+                    wrapped = (u >> 28) & 1u;
+                    first_len = u >> 29;
+                }
+                const u64 dup_m = REG ? 0 : ballot((sortw >> 23) & 1u);
+                PROF_MARK(4)
+                PROF_VMWAIT(5)
+
+                if (mixed) {
+                    plo = gather_u32(plo, order); phi = gather_u32(phi, order);
+                    if (el & EL_FOUR) { plo2 = gather_u32(plo2, order); phi2 = gather_u32(phi2, order); }
+                }
+                uint32_t hits = 0;
+                // One pass per producer part.  FORM 0: the parts' boxes meet in one pair of dims; 1: in one pair of dims, the
+                // other contributes the same factor for every producer part (which does not split it); 2: in both.
+                uint32_t factor = 1;
+                auto passes = [&](auto form_) __attribute__((always_inline)) {
+                    constexpr int FORM = decltype(form_)::value;
+                    u64 todo = parts_m;
+                    do {
+                        const int kp = __builtin_ctzll(todo);
+                        todo &= ~(1ull << kp);
+                        uint32_t elems = pair_product(meet(clo, chi, readlane_u32(plo, kp), readlane_u32(phi, kp)));
+                        if (FORM == 2) elems *= pair_product(meet(clo2, chi2, readlane_u32(plo2, kp), readlane_u32(phi2, kp)));
+                        if (FORM == 1) elems *= factor;
+                        const u64 hit_m = ballot(elems != 0);
+                        if (!hit_m) continue;
+                        const uint32_t dev_a = readlane_u32(dev_v, kp), now_kp = readlane_u32(now_v, kp);
+                        const uint32_t node_a = SimX::kGpn == 4 ? dev_a >> 2 : m.node_of(dev_a);
+                        const u64 comm_m = hit_m & ballot(dev_c != dev_a);
+                        uint32_t arrive = now_kp;
+                        if (comm_m) {
+                            // Section 5.1: the link device between the two devices; assumption A2: transfer time
+                            const u64 near_m = ballot(node_c == node_a);
+                            const bool near = lanes_of(near_m), comm = lanes_of(comm_m);
+                            const uint32_t row_near = opaque(dev_a * G) + local_c, row_far = opaque(node_a * S.n_nodes) + far_base;
+                            const uint32_t row = near ? row_near : row_far;
+                            uint32_t lm = near ? m_near : m_far, lk = near ? k_near : k_far, ll = near ? l_near : l_far;
+                            if (SimX::kExt && S.link_table) {
+                                if (comm && near) { const uint4 e = mem.links[m.local_of(dev_a, node_a) * G + local_c]; lm = e.x; lk = e.y; ll = e.z; }
+                            }
+                            if (SimX::kExt && S.node_table) {
+                                if (comm && !near) { const uint4 e = mem.links[G * G + node_a * S.n_nodes + node_c]; lm = e.x; lk = e.y; ll = e.z; }
+                            }
+                            const uint32_t ns = (__umulhi((elems << elem_sh) - 1u, lm) >> lk) + ll;
+                            const u64 far_m = comm_m & ~near_m;
+                            uint32_t end;
+                            if (REG) {
+                                const uint32_t fr = mem.lrow[row];         // in range for every lane
+                                // consumer parts on one node are consecutive lanes: a running sum along them is the FIFO
+                                // order on the link row they share (rows between GPUs of one node are private)
+                                const uint32_t x = lanes_of(far_m) ? ns : 0u;
+                                uint32_t y = wave_shr1_u32(x) & c1;
+                                uint32_t acc = x + y;
+                                if (SimX::kGpn == 4) {
+                                    y = wave_shr1_u32(y) & c2; acc += y;
+                                    y = wave_shr1_u32(y) & c3; acc += y;
+                                } else {
+                                    for (uint32_t s = 2; s < G; s++) { y = wave_shr1_u32(y) & (uint32_t)((int32_t)(f << (12 - s)) >> 31); acc += y; }
+                                }
+                                if (wrapped) acc += readlane_u32(acc, (int)first_len) & last_run;
+                                end = __builtin_elementwise_add_sat(fr > now_kp ? fr : now_kp, near ? ns : acc);
+                                row_max(mem.lrow, row, end, comm_m);
+                                wave_sync();
+                            } else {
+                                // transfers to another node queue on the link row of the node pair in consumer-part order:
+                                // a running sum along the consumer's parts taken in (node, part) order
+                                end = 0;
+                                if (far_m) {
+                                    uint32_t incl = ns;
+                                    const uint32_t fr = mem.lrow[row];
+                                    if (far_m & (far_m - 1)) {
+                                        const uint32_t x = gather_u32(lanes_of(far_m) ? ns : 0u, sortw & 63u);
+                                        incl = gather_u32(seg_running_sum(x, (sortw >> 22) & 1u), (sortw >> 6) & 63u);
+                                    }
+                                    end = __builtin_elementwise_add_sat(fr > now_kp ? fr : now_kp, incl);
+                                    row_max(mem.lrow, row, end, far_m);
+                                    wave_sync();
+                                }
+                                const u64 here_m = comm_m & near_m;
+                                if (here_m) {
+                                    const bool here = lanes_of(here_m);
+                                    const uint32_t e = fifo_links(here, row, ns, now_kp, (here_m & dup_m) != 0, mem);
+                                    end = here ? e : end;
+                                }
+                            }
+                            arrive = comm ? end : now_kp;
+                            if (STATS) {
+                                cnt.n_comm += __popcll(comm_m);
+                                if (comm) cnt.sum_comm_ns += ns;     // per-lane partial sums, reduced by the caller
+                            }
+                        }
+                        const uint32_t came = lanes_of(hit_m) ? arrive : 0u;
+                        ready = came > ready ? came : ready;
+                        hits = count_lanes(hits, hit_m);
+                        if (STATS) cnt.n_pairs += __popcll(hit_m);
+                    } while (todo);
+                };
+                if (!(el & EL_FOUR)) {
+                    passes(std::integral_constant<int, 0>{});
+                } else if ((el & EL_CONTRIB) || (hflags & (HDR_SPLIT01 | HDR_SPLIT23)) == (HDR_SPLIT01 | HDR_SPLIT23)) {
+                    passes(std::integral_constant<int, 2>{});
+                } else {
+                    if (hflags & HDR_SPLIT23) {
+                        factor = pair_product(as_u16x2(chi) - as_u16x2(clo));
+                        clo = clo2; chi = chi2; plo = plo2; phi = phi2;
+                    } else {
+                        factor = pair_product(as_u16x2(chi2) - as_u16x2(clo2));
+                    }
+                    passes(std::integral_constant<int, 1>{});
+                }
+                PROF_MARK(6)
+                const bool touched = hits != 0;
+                const u64 touched_m = ballot(touched);
+                if (touched_m) {
+                    const uint32_t left = pending - hits;
+                    const u64 abs = st.E + ready;
+                    retry_m |= touched_m & ballot(ready == 0xffffffffu);
+                    overflow_m |= touched_m & ballot(abs >= TIME_LIMIT);
+                    const u64 ready_m = touched_m & ballot(left == 0);
+                    if (touched) words[(size_t)j * ROWL + lane] = left == 0 ? (abs << 1) | 1u : (W_WAIT | ((u64)left << 48) | (abs & (TIME_LIMIT - 1)));
+                    if (ready_m) {
+                        const uint32_t first = part_min_of<ROWL>(ready, ready_m);
+                        queue_insert<Q, ROWL>(mem, st, j, first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1);
+                    }
+                }
+                PROF_MARK(7)
+            }
+            if (SimX::kExt && S.sync) {
+                // parameter synchronisation (see run_events): a replica that has finished sends its gradient of the shard
+                // to the owner's device, queued on its link row after the op's transfers to consumers
+                const uint32_t pbytes = lite.param_bytes;
+                if (pbytes) {
+                    const OpCfg cfull = m.cfg(i);
+                    const uint32_t pdims = m.T.ops[i].param_dims;
+                    const uint32_t digits = part_digits(cfull, lane, m.magic_v);
+                    uint32_t owner = 0, shards = 1;
+#pragma unroll
+                    for (int dd = 0; dd < 4; dd++) {
+                        const bool indexes = (pdims >> dd) & 1u;
+                        owner = owner * cfull.deg[dd] + (indexes ? (digits >> (8 * dd)) & 0xffu : 0u);
+                        if (indexes) shards *= cfull.deg[dd];
+                    }
+                    const uint32_t shard_bytes = (pbytes - 1) / shards + 1;
+                    const uint32_t dev_o = m.template device_of_part<REG>(i, ci, in_mask ? owner : 0u);
+                    const bool act = in_mask && owner != lane && dev_o != dev_p;
+                    if (ballot(act)) {
+                        const uint32_t node_o = m.node_of(dev_o);
+                        const uint32_t local_o = m.local_of(dev_o, node_o);
+                        const bool same_node = node_o == node_p;
+                        const uint32_t row_i = same_node ? dev_p * G + local_o : S.n_nodes * G * G + node_p * S.n_nodes + node_o;
+                        uint32_t bw = same_node ? S.bw_intra : S.bw_inter, m_bw = same_node ? S.m_bw_intra : S.m_bw_inter;
+                        uint32_t lat = same_node ? S.lat_intra : S.lat_inter;
+                        if (S.link_table && act && same_node) {
+                            const uint4 e = m.links[m.local_of(dev_p, node_p) * G + local_o];
+                            bw = e.x; m_bw = e.y; lat = e.z;
+                        }
+                        if (S.node_table && act && !same_node) {
+                            const uint4 e = m.node_links[node_p * S.n_nodes + node_o];
+                            bw = e.x; m_bw = e.y; lat = e.z;
+                        }
+                        const uint32_t ns = ceil_div_u32(shard_bytes, bw, m_bw) + lat;
+                        const uint32_t end = fifo_links(act, act ? row_i : 0u, ns, now, true, mem);
+                        const u64 act_m = ballot(act);
+                        retry_m |= act_m & ballot(end == 0xffffffffu);
+                        overflow_m |= act_m & ballot(st.E + end >= TIME_LIMIT);
+                        if (STATS) {
+                            cnt.n_comm += __popcll(act_m);
+                            if (act) cnt.sum_comm_ns += ns;
+                        }
+                    }
+                }
+            }
+            d_new = in_mask ? KEY_NONE : d;
+            if (in_mask) k0 = W_NONE;
+        }
+        if (in_mask) words[(size_t)i * ROWL + lane] = k0;
+        // ---- the op's next event
+        const uint32_t nd = part_min_u32<ROWL>(d_new);
+        uint32_t nk = __builtin_elementwise_add_sat(kmin, nd);
+        if (nk >= KEY_FAR) nk = ballot((int32_t)(uint32_t)(k0 >> 32) >= 0) ? KEY_FAR : KEY_NONE;
+        {
+            const bool me = lanes_of(at);
+            q.key = me ? nk : q.key;
+            if (Q == Q_SLOT && nk == KEY_NONE) q.op = me ? NO_OP : q.op;
+        }
+        if (retry_m) return RESULT_RETRY;
+        PROF_MARK(7)
+    }
+    PROF_STORE(cnt)
+    return overflow_m ? RESULT_OVERFLOW : 0;
+}
+
+}  // namespace ffsim

@@ -240,9 +240,11 @@ struct SimT {
     const uint4* node_links = nullptr;   // per ordered pair of nodes: the same three figures (S.node_table)
     const uint16_t* devmap = nullptr;    // [n_ops][64] device of every part given explicitly, or null
     const uint32_t* tie = nullptr;       // [n_ops] tied configurations (S.ties), or null
+    uint32_t ov_in = 0;                  // in-edges of ov_op (the rows of its out-edges come behind those of its in-edges)
     bool want_sort = false;              // the set-up of an edge includes the consumer's parts in (node, part) order (general event loop)
     static constexpr bool kOvr = OVR;
     static constexpr bool kExt = EXT >= 1;      // refinements of the inputs: link tables, explicit devices, parameter traffic
+    static constexpr int kGpn = GPN;
     static constexpr bool kTrain = EXT >= 2;    // training-iteration graphs: contributing edges, tied configurations
     static_assert(GPN == 0 || GPN == 4, "compiled node sizes");
     __device__ __forceinline__ uint32_t gpn() const { return GPN ? (uint32_t)GPN : S.gpus_per_node; }
@@ -476,12 +478,13 @@ __device__ __forceinline__ uint32_t count_pending(const SimX& m, uint32_t j, con
     return pending;
 }
 
-// Section 4: every configuration valid?  Also fills exe_of.  A valid strategy is REGULAR if
+// Section 4: every configuration valid?  A valid strategy is REGULAR if
 // every op puts its parts on consecutive, distinct devices (stride 1, no more parts than
 // devices) and a node has at most MAX_RUN GPUs: the event loop has a faster form for those.
 enum StrategyClass : uint32_t { STRATEGY_INVALID = 0, STRATEGY_GENERAL = 1, STRATEGY_REGULAR = 2 };
-template <class SimX>
-__device__ __forceinline__ StrategyClass validate_strategy(const SimX& m) {
+// store(i, c, exe): what to keep of op i's configuration and exeTime (per lane).
+template <class SimX, class Store>
+__device__ __forceinline__ StrategyClass validate_with(const SimX& m, Store store) {
     bool bad = false, irregular = false;
     for (uint32_t i = lane_id(); i < m.S.n_ops; i += WAVE) {
         OpCfg c = unpack_cfg_lane(m.cfg_raw(i));
@@ -489,7 +492,7 @@ __device__ __forceinline__ StrategyClass validate_strategy(const SimX& m) {
         if (!cfg_ok(m.T.ops[i], c, m.S)) {
             bad = true;
         } else if (m.S.n_cols) {
-            m.exe_of[i] = m.T.cost[(size_t)i * m.S.n_cols + (c.parts - 1)];
+            store(i, c, m.T.cost[(size_t)i * m.S.n_cols + (c.parts - 1)]);
         } else {
             // costs keyed by the whole degree tuple: ptr[n_ops+1], tuples (ascending per op), times;
             // a tuple that is not listed has no cost: invalid
@@ -501,7 +504,7 @@ __device__ __forceinline__ StrategyClass validate_strategy(const SimX& m) {
                 const uint32_t mid = (lo + hi) / 2;
                 if (tuples[mid] < c.x) lo = mid + 1; else hi = mid;
             }
-            if (lo < ptr[i + 1] && tuples[lo] == c.x) m.exe_of[i] = ns[lo];
+            if (lo < ptr[i + 1] && tuples[lo] == c.x) store(i, c, ns[lo]);
             else bad = true;
         }
         irregular = irregular || c.stride != 1 || c.parts > m.S.n_dev;
@@ -511,6 +514,10 @@ __device__ __forceinline__ StrategyClass validate_strategy(const SimX& m) {
     if (ballot(bad)) return STRATEGY_INVALID;
     if (SimX::kExt && m.devmap) return STRATEGY_GENERAL;      // the regular form assumes consecutive devices
     return (ballot(irregular) || m.gpn() > MAX_RUN) ? STRATEGY_GENERAL : STRATEGY_REGULAR;
+}
+template <class SimX>
+__device__ __forceinline__ StrategyClass validate_strategy(const SimX& m) {
+    return validate_with(m, [&](uint32_t i, const OpCfg&, uint32_t exe) __attribute__((always_inline)) { m.exe_of[i] = exe; });
 }
 
 }  // namespace ffsim

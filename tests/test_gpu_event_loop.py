@@ -1,0 +1,154 @@
+"""The event loop on kept set-up at the sizes where it changes form: rows of 16 and 64 lanes, queues of up to 16, up
+to 64 and more ops, more ops with events than the queue has slots, events and link bookings too far ahead for 32-bit
+times, and the constants of the link-time division.  Everything against the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1807_05358_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1807_05358_amd import binding
+    return binding
+
+
+def draw(rng, ops, n, D, parts, choices, strides=False):
+    cfgs = np.zeros((n, len(ops)), W.CFG_DT)
+    for i in range(len(ops)):
+        t = W.valid_degree_tuples(ops[i], parts, choices)
+        cfgs["deg"][:, i] = t[rng.integers(len(t), size=n)]
+    cfgs["dev_offset"] = rng.integers(0, D, size=cfgs.shape)
+    cfgs["dev_stride"] = 1
+    if strides:
+        cfgs["dev_stride"][n // 2:] = rng.integers(0, 5, size=cfgs[n // 2:].shape)
+    return cfgs
+
+
+def check(B, ops, edges, mach, cost, cfgs, kernel=None, chain_steps=0):
+    want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8)
+    sim = B.Simulator(ops, edges, mach, cost)
+    if kernel is not None:
+        assert B.ff_sim_batch_kernel_name(sim.handle, len(cfgs)).startswith(kernel), B.ff_sim_batch_kernel_name(sim.handle, len(cfgs))
+    got = sim.simulate(cfgs)
+    assert np.array_equal(got, want), (np.nonzero(got != want)[0][:5], got[got != want][:3], want[got != want][:3])
+    again, st = sim.simulate(cfgs, stats=True)
+    assert np.array_equal(again, want) and not st["exit_code"].any()
+    if chain_steps:
+        # a chain of changes from the first strategy to parts of the second, op by op
+        muts = np.zeros((chain_steps, 1), W.MUT_DT)
+        muts["op"][:, 0] = np.arange(chain_steps) * 7 % len(ops)
+        muts["cfg"][:, 0] = cfgs[1, muts["op"][:, 0]]
+        ch = B.Chains(sim, cfgs[:1])
+        d = ch.delta(ch.upload_mutations(muts), chain_steps).cpu().numpy().view("<u8")
+        ref = oracle.simulate_delta_chain(ops, edges, mach, cost, cfgs[0], muts[:, 0])
+        assert np.array_equal(d[:, 0], ref)
+        t = ch.try_mutations(ch.upload_mutations(muts[::-1].copy()), chain_steps).cpu().numpy().view("<u8")
+        cur = cfgs[0].copy()
+        for s in range(chain_steps):
+            cur[int(muts[s, 0]["op"])] = muts[s, 0]["cfg"]
+        cand = np.repeat(cur[None], chain_steps, 0)
+        for s in range(chain_steps):
+            cand[s, int(muts[chain_steps - 1 - s, 0]["op"])] = muts[chain_steps - 1 - s, 0]["cfg"]
+        assert np.array_equal(t[:, 0], oracle.simulate_batch(ops, edges, mach, cost, cand, n_threads=8))
+        ch.close()
+    sim.close()
+    return want
+
+
+@pytest.mark.parametrize("n_ops", [1, 15, 16, 17, 64, 65, 66])
+@pytest.mark.parametrize("parts", [1, 15, 16, 17, 64])
+def test_queue_and_row_shapes(B, n_ops, parts):
+    """every combination of queue shape and lanes per row, at the edges of both, tensors of one to four dims"""
+    rng = np.random.default_rng(100 * n_ops + parts)
+    g = W.GraphBuilder()
+    shapes = [(48,), (24, 16), (16, 5, 9), (12, 8, 7, 6)]
+    for i in range(n_ops):
+        nd = int(rng.integers(1, 5))
+        o = g.op(W.T_ELEM, shapes[nd - 1], tuple(range(nd)), 1)
+        for s in sorted(set(int(x) for x in rng.integers(0, o, size=min(o, 2)))) if o else ():
+            sd = g.ops[s][0]
+            g.edge(s, o, [W.ident(d) if d < nd and rng.random() < 0.7 else W.ALL for d in range(sd)])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(5, 4, 7, 3, 2, 31)
+    cost = rng.integers(1, 5000, size=(n_ops, parts)).astype("<u4")
+    cfgs = draw(rng, ops, 24, mach.n_devices, parts, (1, 2, 3, 4, 5, 8, 12, 16, 48), strides=True)
+    check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=min(n_ops, 6))
+
+
+@pytest.mark.parametrize("parts", [4, 32])
+@pytest.mark.parametrize("equal", [False, True])
+def test_more_ops_with_events_than_slots(B, parts, equal):
+    """300 ops without inputs are READY at time 0 (and feed 30 others): the queue's 64 slots overflow.  equal: all
+    tasks take the same time, so that long stretches of events tie."""
+    rng = np.random.default_rng(7)
+    g = W.GraphBuilder()
+    src = [g.op(W.T_ELEM, (32, 16), (0, 1), 1) for _ in range(300)]
+    for k in range(30):
+        o = g.op(W.T_ELEM, (32, 16), (0, 1), 1)
+        for s in src[k * 10:k * 10 + 10]:
+            g.edge(s, o, [W.ident(0), W.ident(1)])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(4, 4, 3, 2)
+    cost = (np.full((len(ops), parts), 1000) if equal else rng.integers(1, 90000, size=(len(ops), parts))).astype("<u4")
+    cfgs = draw(rng, ops, 12, 16, parts, (1, 2, 3, 4, 8, 16), strides=True)
+    check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=4)
+
+
+@pytest.mark.parametrize("n_ops", [12, 80])
+def test_tasks_longer_than_32_bits_of_time(B, n_ops):
+    """tasks of up to 2^32 - 1 ns, next to short ones: events beyond the reach of 32-bit keys, an epoch that moves often"""
+    rng = np.random.default_rng(n_ops)
+    g = W.GraphBuilder()
+    for i in range(n_ops):
+        o = g.op(W.T_ELEM, (64, 8), (0, 1), 1)
+        for s in sorted(set(int(x) for x in rng.integers(max(0, o - 5), o, size=2))) if o else ():
+            g.edge(s, o, [W.ident(0), W.ident(1)])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(4, 4)
+    cost = rng.choice([5, 70000, 2 ** 31 - 1, 2 ** 31, 2 ** 32 - 1, 3 * 10 ** 9], size=(n_ops, 16)).astype("<u4")
+    want = check(B, ops, edges, mach, cost, draw(rng, ops, 64, 16, 16, (1, 2, 4, 8, 16), strides=True), kernel="k_loop_batch", chain_steps=5)
+    assert want.max() > 2 ** 33
+
+
+def test_links_booked_beyond_32_bits_of_time(B):
+    """one tensor of 1 GiB read whole by 64 parts of several ops: its transfers queue for more than 2^32 ns on the same
+    links, and the candidate is simulated with 64-bit link rows"""
+    g = W.GraphBuilder()
+    a = g.op(W.T_ELEM, (16384, 16384), (0, 1), 1)
+    for _ in range(70):
+        b = g.op(W.T_ELEM, (64, 64), (0, 1), 1)
+        if b <= 8:
+            g.edge(a, b, [W.ALL, W.ALL])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(16, 4, 6, 5)
+    cost = np.full((len(ops), 64), 1000, "<u4")
+    rng = np.random.default_rng(3)
+    cfgs = draw(rng, ops, 16, 64, 64, (1, 2, 4, 8, 16, 32, 64))
+    cfgs["deg"][:8, 1:9] = (8, 8, 1, 1)
+    cfgs["deg"][:8, 0] = (1, 1, 1, 1)
+    cfgs["deg"][12:, 1:] = (1, 1, 1, 1)
+    want = check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=4)
+    assert want.max() > 5 * 10 ** 9
+
+
+@pytest.mark.parametrize("elem_bytes", [1, 2, 3, 4, 8, 12])
+def test_link_time_constants(B, elem_bytes):
+    """ceil(elements * element size / bandwidth) for bandwidths that divide, share a factor with, or have none in common
+    with the element size, from 1 B/ns to the largest, with transfers of one element up to 2^27"""
+    rng = np.random.default_rng(elem_bytes)
+    g = W.GraphBuilder()
+    a = g.op(W.T_ELEM, (4096, 32768), (0, 1), 1)
+    for k in range(3):
+        b = g.op(W.T_ELEM, (4096, 32768), (0, 1), 1)
+        g.edge(a, b, [W.ident(0), W.ident(1)])
+        c = g.op(W.T_ELEM, (61, 7), (0, 1), 1)
+        g.edge(b, c, [(0, 1, 3 * k, 5 * k), (1, 2, 0, k)])
+    ops, edges, _ = g.finish()
+    cost = rng.integers(1, 100, size=(len(ops), 64)).astype("<u4")
+    for near, far in [(1, 1), (2, 3), (20, 12), (5, 7), (24, 36), (255, 256), (65537, 1000003), (2 ** 31, 2 ** 32 - 1), (1, 2 ** 32 - 1)]:
+        mach = W.Machine(4, 4, near, far, 1, 2, elem_bytes)
+        check(B, ops, edges, mach, cost, draw(rng, ops, 24, 16, 64, (1, 2, 3, 5, 7, 16, 61)))
