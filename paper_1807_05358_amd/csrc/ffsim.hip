@@ -53,7 +53,7 @@ struct ff_sim {
     // the batch kernel may keep the per-edge set-up of a candidate (all extents must fit 16 bits):
     // behind the task words, in the HBM slot, or in LDS for graphs whose words live there
     bool cache_ok = false;
-    bool chain_cache = false;     // the same for chains: only the extents matter, the set-up lives in the chain's memory
+    bool chain_cache = false;     // the same for chains (those on run_events): only the extents matter, the set-up lives in the chain's memory
     size_t batch_slot_bytes = 0;  // slot_bytes, plus the kept set-up where it lives in HBM
     size_t lds_cached = 0;        // dynamic LDS of the caching variant (= lds if the set-up lives in HBM)
     uint32_t max_slots_cached = 0;
@@ -68,6 +68,10 @@ struct ff_sim {
     size_t loop_slot_bytes = 0;   // HBM per resident wavefront
     size_t loop_lds = 0;
     uint32_t max_slots_loop = 0;
+    LoopChoice chain_choice{};    // the same for chains and trials
+    size_t chain_loop_lds = 0, try_loop_lds = 0;
+    uint32_t max_try_slots_loop = 0;
+    uint32_t max_adjacent = 0;    // most in- and out-edges of an op together
     uint32_t max_parts = 0;       // most parts any op can have
     uint64_t max_elems = 0;       // of the largest tensor
     uint64_t sum_edge_bytes = 0;  // over all edges, of the producer's tensor (saturating)
@@ -87,6 +91,7 @@ struct ff_chains {
     uint32_t C = 0;
     uint32_t n_snaps = 0;
     size_t stride = 0;             // bytes per chain
+    size_t meta_at = 0;            // offset of the ChainMeta record in a chain's block
     unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots
     uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation
     uint32_t* d_counter = nullptr; // work counter of the trial-mutation kernel
@@ -142,12 +147,18 @@ static batch_kernel_t batch_kernel(const ff_sim* s, bool cached, int ext = 0) {
     if (s->dev.gpus_per_node == 4) return ext == 2 ? batch_kernels<2, 4>(k) : (ext == 1 ? batch_kernels<1, 4>(k) : batch_kernels<0, 4>(k));
     return ext == 2 ? batch_kernels<2, 0>(k) : (ext == 1 ? batch_kernels<1, 0>(k) : batch_kernels<0, 0>(k));
 }
+template <int EXT, int GPN> static chain_kernel_t pick_chain(const ff_sim* s, bool loop) {
+    return loop ? loop_chain_kernels<EXT, GPN>(s->chain_choice) : chain_kernels<EXT, GPN>(choice(s, s->wide && s->chain_cache));
+}
+template <int EXT, int GPN> static try_kernel_t pick_try(const ff_sim* s, bool loop) {
+    return loop ? loop_try_kernels<EXT, GPN>(s->chain_choice) : try_kernels<EXT, GPN>(choice(s, s->wide && s->chain_cache));
+}
 // chains keep the per-edge set-up in their own memory whenever the extents allow it
 static chain_kernel_t chain_kernel(const ff_sim* s) {
-    const KernelChoice k = choice(s, s->chain_cache);
+    const bool k = s->loop;
     const int ext = ext_level(s);
-    if (s->dev.gpus_per_node == 4) return ext == 2 ? chain_kernels<2, 4>(k) : (ext == 1 ? chain_kernels<1, 4>(k) : chain_kernels<0, 4>(k));
-    return ext == 2 ? chain_kernels<2, 0>(k) : (ext == 1 ? chain_kernels<1, 0>(k) : chain_kernels<0, 0>(k));
+    if (s->dev.gpus_per_node == 4) return ext == 2 ? pick_chain<2, 4>(s, k) : (ext == 1 ? pick_chain<1, 4>(s, k) : pick_chain<0, 4>(s, k));
+    return ext == 2 ? pick_chain<2, 0>(s, k) : (ext == 1 ? pick_chain<1, 0>(s, k) : pick_chain<0, 0>(s, k));
 }
 static loop_kernel_t loop_kernel(const ff_sim* s, int ext) {
     LoopChoice k = s->loop_choice;
@@ -155,11 +166,21 @@ static loop_kernel_t loop_kernel(const ff_sim* s, int ext) {
     if (s->dev.gpus_per_node == 4) return ext == 2 ? loop_kernels<2, 4>(k) : (ext == 1 ? loop_kernels<1, 4>(k) : loop_kernels<0, 4>(k));
     return ext == 2 ? loop_kernels<2, 0>(k) : (ext == 1 ? loop_kernels<1, 0>(k) : loop_kernels<0, 0>(k));
 }
-static try_kernel_t try_kernel(const ff_sim* s) {
-    const KernelChoice k = choice(s, s->chain_cache);
+static try_kernel_t try_kernel(const ff_sim* s, bool k) {
     const int ext = ext_level(s);
-    if (s->dev.gpus_per_node == 4) return ext == 2 ? try_kernels<2, 4>(k) : (ext == 1 ? try_kernels<1, 4>(k) : try_kernels<0, 4>(k));
-    return ext == 2 ? try_kernels<2, 0>(k) : (ext == 1 ? try_kernels<1, 0>(k) : try_kernels<0, 0>(k));
+    if (s->dev.gpus_per_node == 4) return ext == 2 ? pick_try<2, 4>(s, k) : (ext == 1 ? pick_try<1, 4>(s, k) : pick_try<0, 4>(s, k));
+    return ext == 2 ? pick_try<2, 0>(s, k) : (ext == 1 ? pick_try<1, 0>(s, k) : pick_try<0, 0>(s, k));
+}
+
+// Trials: LDS and workspace bytes per resident wavefront, and how many the device holds.  (Where the state is in LDS nothing
+// is written to the workspace; it is asked for all the same, at its smallest, so that callers need not know.)
+static size_t try_lds(const ff_sim* s) { return s->loop ? s->try_loop_lds : s->lds_common; }
+static uint32_t try_slots(const ff_sim* s) { return s->loop ? s->max_try_slots_loop : s->max_try_slots; }
+static size_t try_slot_bytes(const ff_sim* s) {
+    if (!s->loop) return s->slot_bytes;
+    if (s->chain_choice.lds) return 256;
+    const uint32_t own_rows = s->dev.ties ? s->dev.n_kept : s->max_adjacent * (uint32_t)KEPT_ROWS;
+    return slot_layout(s->dev.n_ops, s->dev.n_ops_pad, own_rows, s->chain_choice.rowl, false).bytes;
 }
 
 // A launch with more than 64 KB of dynamic LDS (gfx950 allows a workgroup up to 160 KB) has to be
@@ -492,7 +513,7 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         }
     }
 
-    if (!allow_lds((const void*)batch_kernel(s, false), s->lds) || !allow_lds((const void*)try_kernel(s), s->lds_common) ||
+    if (!allow_lds((const void*)batch_kernel(s, false), s->lds) || !allow_lds((const void*)try_kernel(s, false), s->lds_common) ||
         (s->cache_ok && !allow_lds((const void*)batch_kernel(s, true), s->lds_cached))) { release(s); return FF_EHIP; }
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel(s, false), WAVE, s->lds);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
@@ -521,9 +542,25 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         s->max_slots_loop = (uint32_t)cus * (uint32_t)per_cu;
     }
     per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, try_kernel(s), WAVE, s->lds_common);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, try_kernel(s, false), WAVE, s->lds_common);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     s->max_try_slots = (uint32_t)cus * (uint32_t)per_cu;
+    if (s->loop_extents) {
+        LoopChoice& k = s->chain_choice;
+        k = s->loop_choice;
+        k.stats = false;
+        k.lds = S.n_ops <= 64 && loop_chain_lds_bytes(S, k.rowl, true, true) <= 40 * 1024;
+        k.queue = k.lds ? (S.n_ops <= 16 && k.rowl == 16 ? Q_OP16 : Q_OP) : Q_SLOT;
+        s->chain_loop_lds = loop_chain_lds_bytes(S, k.rowl, k.lds, true);
+        s->try_loop_lds = loop_chain_lds_bytes(S, k.rowl, k.lds, false);
+        for (uint32_t i = 0; i < S.n_ops; i++)
+            s->max_adjacent = std::max(s->max_adjacent, ops[i].out_end - ops[i].out_begin + ops[i].in_end - ops[i].in_begin);
+        if (!allow_lds((const void*)try_kernel(s, true), s->try_loop_lds)) { release(s); return FF_EHIP; }
+        per_cu = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, try_kernel(s, true), WAVE, s->try_loop_lds);
+        if (e != hipSuccess || per_cu < 1) per_cu = 1;
+        s->max_try_slots_loop = (uint32_t)cus * (uint32_t)per_cu;
+    }
     // the address of this device's scratch array (ff_sim_neighbours_noalloc) is looked up here, once per device
     if (!neighbour_scratch_of_current_device()) { release(s); return FF_EHIP; }
     *out = s;
@@ -776,9 +813,10 @@ static int launch_chain_steps(ff_chains* c, const ff_mutation_t* d_muts, uint32_
                               const SearchDev& search) {
     ff_sim* s = c->sim;
     static_assert(sizeof(ff_mutation_t) == 12, "mutation layout");
-    if (!allow_lds((const void*)chain_kernel(s), s->lds_chain)) return FF_EHIP;
-    hipLaunchKernelGGL(chain_kernel(s), dim3(c->C), dim3(WAVE), s->lds_chain, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges,
-                       s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, (const uint32_t*)d_muts, n_steps,
+    const size_t lds = s->loop ? s->chain_loop_lds : s->lds_chain;
+    if (!allow_lds((const void*)chain_kernel(s), lds)) return FF_EHIP;
+    hipLaunchKernelGGL(chain_kernel(s), dim3(c->C), dim3(WAVE), lds, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges, s->d_op_lite,
+                       s->d_edge_lite, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, (const uint32_t*)d_muts, n_steps,
                        (u64*)d_out, c->d_flags, search);
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
@@ -793,15 +831,16 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     c->sim = s;
     c->C = C;
     c->n_snaps = CHAIN_SNAPSHOTS;
-    c->stride = chain_bytes(s->dev.n_ops, s->dev.n_ops_pad, s->dev.n_rows, c->n_snaps, s->dev.n_edges);
+    const ChainLayout cl = chain_layout(s->dev, c->n_snaps, s->loop ? s->chain_choice.rowl : 0);
+    c->stride = cl.bytes;
+    c->meta_at = cl.meta;
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t row_bytes = (size_t)s->dev.n_ops * sizeof(uint2);
     if (hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess ||
         hipMalloc((void**)&c->d_flags, (size_t)C * 4) != hipSuccess ||
         hipMalloc((void**)&c->d_counter, 256) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
-    // zero everything (snapshot bookkeeping starts empty), then drop each chain's strategy at
-    // the head of its block
-    if (hipMemsetAsync(c->d_mem, 0, (size_t)C * c->stride, st) != hipSuccess ||
+    // the bookkeeping and the tags of endTimes start empty; each chain's strategy goes to the head of its block
+    if (hipMemset2DAsync(c->d_mem + cl.meta, c->stride, 0, cl.clear_bytes, C, st) != hipSuccess ||
         hipMemsetAsync(c->d_flags, 0, (size_t)C * 4, st) != hipSuccess ||
         hipMemcpy2DAsync(c->d_mem, c->stride, d_strategies, row_bytes, row_bytes, C, hipMemcpyDeviceToDevice, st) != hipSuccess) {
         ff_sim_chains_destroy(c);
@@ -859,12 +898,13 @@ int ff_sim_search(ff_chains_t* c, const ff_search_t* p, uint32_t n_steps, uint64
 static int launch_trials(ff_chains* c, const uint32_t* d_muts, uint32_t M, uint64_t* d_out_ns, hipStream_t st) {
     ff_sim* s = c->sim;
     const uint32_t total = M * c->C;
-    const uint32_t slots = std::min(total, s->max_try_slots);
+    const uint32_t slots = std::min(total, try_slots(s));
+    const try_kernel_t kernel = try_kernel(s, s->loop);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(WAVE), 0, st, c->d_counter);
-    if (!allow_lds((const void*)try_kernel(s), s->lds_common)) return FF_EHIP;
-    hipLaunchKernelGGL(try_kernel(s), dim3(slots), dim3(WAVE), s->lds_common, st, s->dev, s->d_ops, s->d_edges,
-                       s->d_in_edges, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, d_muts, M,
-                       (u64*)d_out_ns, c->d_flags, c->d_counter, (unsigned char*)s->ws, s->slot_bytes);
+    if (!allow_lds((const void*)kernel, try_lds(s))) return FF_EHIP;
+    hipLaunchKernelGGL(kernel, dim3(slots), dim3(WAVE), try_lds(s), st, s->dev, s->d_ops, s->d_edges,
+                       s->d_in_edges, s->d_op_lite, s->d_edge_lite, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, d_muts, M,
+                       (u64*)d_out_ns, c->d_flags, c->d_counter, (unsigned char*)s->ws, try_slot_bytes(s));
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
 
@@ -881,11 +921,11 @@ int ff_sim_search_ahead(ff_chains_t* c, const ff_search_t* p, uint32_t n_steps, 
     ff_sim* s = c->sim;
     hipStream_t st = (hipStream_t)hip_stream;
     // no more proposals in flight than the trial kernel has wavefronts for
-    const uint64_t fit = std::max<uint64_t>(1, (uint64_t)s->max_try_slots / c->C);
+    const uint64_t fit = std::max<uint64_t>(1, (uint64_t)try_slots(s) / c->C);
     const uint32_t cap = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(max_ahead, fit), n_steps);
     {
-        const uint32_t slots = (uint32_t)std::min<uint64_t>((uint64_t)cap * c->C, s->max_try_slots);
-        if (!s->ws || s->ws_bytes < (size_t)slots * s->slot_bytes) return FF_EWORKSPACE;
+        const uint32_t slots = (uint32_t)std::min<uint64_t>((uint64_t)cap * c->C, try_slots(s));
+        if (!s->ws || s->ws_bytes < (size_t)slots * try_slot_bytes(s)) return FF_EWORKSPACE;
     }
     if (cap < 4 && !always) {
         // the chains alone fill the device (or the caller allows no look-ahead worth a round): ff_sim_search
@@ -1044,7 +1084,7 @@ int ff_sim_neighbours_noalloc(ff_chains_t* c, const uint32_t* d_tuple_ptr, const
 size_t ff_sim_delta_try_workspace_bytes(const ff_chains_t* c, uint32_t M) {
     if (!c) return 0;
     const uint64_t total = (uint64_t)M * c->C;
-    return (size_t)std::max<uint64_t>(1, std::min<uint64_t>(total, c->sim->max_try_slots)) * c->sim->slot_bytes;
+    return (size_t)std::max<uint64_t>(1, std::min<uint64_t>(total, try_slots(c->sim))) * try_slot_bytes(c->sim);
 }
 
 int ff_sim_delta_try(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t M, uint64_t* d_out_ns, void* hip_stream) {
@@ -1054,8 +1094,8 @@ int ff_sim_delta_try(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t M, ui
     if ((uint64_t)M * c->C > 0xffffffffull) return FF_ERANGE;
     ff_sim* s = c->sim;
     const uint32_t total = M * c->C;
-    const uint32_t slots = std::min(total, s->max_try_slots);
-    if (!s->ws || s->ws_bytes < (size_t)slots * s->slot_bytes) return FF_EWORKSPACE;
+    const uint32_t slots = std::min(total, try_slots(s));
+    if (!s->ws || s->ws_bytes < (size_t)slots * try_slot_bytes(s)) return FF_EWORKSPACE;
     return launch_trials(c, (const uint32_t*)d_muts, M, d_out_ns, (hipStream_t)hip_stream);
 }
 
@@ -1064,7 +1104,7 @@ int ff_sim_chains_get_stats(ff_chains_t* c, ff_chain_stats_t* h_out) {
     if (hipDeviceSynchronize() != hipSuccess) return FF_EHIP;
     for (uint32_t k = 0; k < c->C; k++) {
         ChainMeta meta;
-        const unsigned char* p = c->d_mem + (size_t)k * c->stride + chain_meta_offset(c->sim->dev.n_ops, c->sim->dev.n_ops_pad, c->sim->dev.n_rows, c->n_snaps, c->sim->dev.n_edges);
+        const unsigned char* p = c->d_mem + (size_t)k * c->stride + c->meta_at;
         if (hipMemcpy(&meta, p, sizeof(meta), hipMemcpyDeviceToHost) != hipSuccess) return FF_EHIP;
         h_out[k].n_steps = meta.n_steps;
         h_out[k].n_resumed = meta.n_resumed;

@@ -1,7 +1,11 @@
 // Chains of strategies: delta simulation (Section 5.3), trial proposals, the search loop
 // (Section 6) and the neighbour sweep (Section 8.4).
+//
+// The bookkeeping here is the same for both event loops; what depends on the loop (state in memory, kept set-up, the run
+// itself) is an engine: EventsEngine (below, run_events) and LoopEngine (ffsim_loop_chain.h, run_loop).
 #pragma once
 #include "ffsim_events.h"
+#include "ffsim_kept.h"
 
 namespace ffsim {
 
@@ -33,46 +37,79 @@ struct ChainMeta {
     uint32_t tag;       // tag of the last recorded run (1..0xffff; 0 marks entries never written)
 };
 
-struct ChainMem {       // all pointers are per chain
+// all pointers are per chain; what only one of the engines has is null with the other
+struct ChainMem {
     uint2* cfgs;
-    u64* words;
-    uint32_t* exe_of;
-    u64* end_of;        // accepted timeline
-    u64* end_try;       // tag<<48 | endTime, written by recorded runs
-    u64* snap_words;    // [2][n_snaps][n_ops*64]
-    u64* snap_l1;       // [2][n_snaps][n_ops_pad]
-    u64* snap_free;     // [2][n_snaps][n_rows, padded to even]
-    uint32_t* ecache;   // kept per-edge set-up of the chain's current strategy (see EdgeLane)
     ChainMeta* meta;
+    u64* end_try;       // tag<<48 | endTime, written by recorded runs
+    u64* end_of;        // accepted timeline
+    u64* words;
+    u64* snap_words;    // [2][n_snaps][n_ops*row]
+    u64* snap_free;     // [2][n_snaps][n_rows, padded to even]
+    // EventsEngine
+    u64* snap_l1;       // [2][n_snaps][n_ops_pad]
+    uint32_t* exe_of;
+    uint32_t* ecache;   // kept per-edge set-up of the chain's current strategy (see EdgeLane)
+    // LoopEngine
+    uint4* hdr;
+    u64* spill_key;
+    uint32_t* spill_op;
+    uint32_t* rows;     // kept rows of all edges for the chain's current strategy (ffsim_kept.h)
 };
 
-// byte offset of the ChainMeta record inside a chain block (it comes last)
-__host__ __device__ inline size_t chain_meta_offset(uint32_t n_ops, uint32_t n_ops_pad, uint32_t n_rows, uint32_t n_snaps,
-                                                    uint32_t n_edges) {
-    size_t b = (size_t)n_ops_pad * 8;                       // cfgs
-    b += ecache_bytes(n_edges);
-    b += (size_t)n_ops * WAVE * 8 * 3;                      // words, end_of, end_try
-    b += 2 * (size_t)n_snaps * ((size_t)n_ops * WAVE * 8 + (size_t)n_ops_pad * 8 + (size_t)((n_rows + 1) & ~1u) * 8);
-    b += (size_t)n_ops_pad * 4;                             // exe_of
-    return b;
-}
-__host__ __device__ inline size_t chain_bytes(uint32_t n_ops, uint32_t n_ops_pad, uint32_t n_rows, uint32_t n_snaps, uint32_t n_edges) {
-    return (chain_meta_offset(n_ops, n_ops_pad, n_rows, n_snaps, n_edges) + sizeof(ChainMeta) + 255) & ~(size_t)255;
+// byte offsets inside a chain block; rowl: lanes per row of the event loop on kept set-up, 0 = EventsEngine (rows of 64).
+// The block must be zero from `meta` for clear_bytes before its first simulation.
+struct ChainLayout {
+    size_t cfgs, meta, end_try, end_of, words, snap_words, snap_free, snap_l1, exe_of, ecache, hdr, spill_key, spill_op, rows;
+    size_t clear_bytes, bytes;
+};
+__host__ __device__ inline ChainLayout chain_layout(const SimDev& S, uint32_t n_snaps, uint32_t rowl) {
+    ChainLayout l = {};
+    const size_t pad = S.n_ops_pad, nw = (size_t)S.n_ops * (rowl ? rowl : (uint32_t)WAVE) * 8;
+    size_t b = 0;
+    l.cfgs = b; b += pad * 8;
+    l.meta = b; b += (sizeof(ChainMeta) + 15) & ~(size_t)15;
+    l.end_try = b; b += nw;
+    l.clear_bytes = b - l.meta;
+    l.end_of = b; b += nw;
+    l.words = b; b += nw;
+    l.snap_words = b; b += 2 * (size_t)n_snaps * nw;
+    l.snap_free = b; b += 2 * (size_t)n_snaps * ((S.n_rows + 1) & ~1u) * 8;
+    if (rowl) {
+        l.hdr = b; b += pad * 16;
+        l.spill_key = b; b += pad * 8;
+        l.spill_op = b; b += pad * 4;
+        l.rows = b; b += (size_t)S.n_kept * rowl * 4;
+    } else {
+        l.snap_l1 = b; b += 2 * (size_t)n_snaps * pad * 8;
+        l.exe_of = b; b += pad * 4;
+        l.ecache = b; b += ecache_bytes(S.n_edges);
+        l.clear_bytes = b - l.meta;
+    }
+    l.bytes = (b + 255) & ~(size_t)255;
+    return l;
 }
 
-__device__ __forceinline__ ChainMem carve_chain(unsigned char* base, const SimDev& S, uint32_t n_snaps) {
-    ChainMem c;
-    const size_t nw = (size_t)S.n_ops * WAVE;
-    c.cfgs = (uint2*)base; base += (size_t)S.n_ops_pad * 8;
-    c.ecache = (uint32_t*)base; base += ecache_bytes(S.n_edges);
-    c.words = (u64*)base; base += nw * 8;
-    c.end_of = (u64*)base; base += nw * 8;
-    c.end_try = (u64*)base; base += nw * 8;
-    c.snap_words = (u64*)base; base += 2 * (size_t)n_snaps * nw * 8;
-    c.snap_l1 = (u64*)base; base += 2 * (size_t)n_snaps * S.n_ops_pad * 8;
-    c.snap_free = (u64*)base; base += 2 * (size_t)n_snaps * ((S.n_rows + 1) & ~1u) * 8;
-    c.exe_of = (uint32_t*)base; base += (size_t)S.n_ops_pad * 4;
-    c.meta = (ChainMeta*)base;
+__device__ __forceinline__ ChainMem carve_chain(unsigned char* base, const SimDev& S, uint32_t n_snaps, uint32_t rowl) {
+    const ChainLayout l = chain_layout(S, n_snaps, rowl);
+    ChainMem c = {};
+    c.cfgs = (uint2*)(base + l.cfgs);
+    c.meta = (ChainMeta*)(base + l.meta);
+    c.end_try = (u64*)(base + l.end_try);
+    c.end_of = (u64*)(base + l.end_of);
+    c.words = (u64*)(base + l.words);
+    c.snap_words = (u64*)(base + l.snap_words);
+    c.snap_free = (u64*)(base + l.snap_free);
+    if (rowl) {
+        c.hdr = (uint4*)(base + l.hdr);
+        c.spill_key = (u64*)(base + l.spill_key);
+        c.spill_op = (uint32_t*)(base + l.spill_op);
+        c.rows = (uint32_t*)(base + l.rows);
+    } else {
+        c.snap_l1 = (u64*)(base + l.snap_l1);
+        c.exe_of = (uint32_t*)(base + l.exe_of);
+        c.ecache = (uint32_t*)(base + l.ecache);
+    }
     return c;
 }
 
@@ -82,7 +119,7 @@ __device__ __forceinline__ ChainMem carve_chain(unsigned char* base, const SimDe
 // if op mo has no producer or has a part without inputs.  Returns the index of the last
 // snapshot at or before that time (0 = start from time 0) and, in pend_new, the number of
 // inputs every part of op mo waits for under the new configuration.
-template <class SimX>
+template <int ROWL, class SimX>
 __device__ __forceinline__ uint32_t resume_point(const SimX& m, const u64* end_of, const ChainMeta& meta, uint32_t mo, uint2 ocfg,
                                                  uint32_t& pend_new) {
     const int lane = lane_id();
@@ -93,7 +130,7 @@ __device__ __forceinline__ uint32_t resume_point(const SimX& m, const u64* end_o
     for (uint32_t q = in_begin; q < in_end; q++) {
         const uint32_t p = m.T.in_edges[q].src;
         const OpCfg cp = m.cfg(p);
-        const u64 t = wave_min_u64((uint32_t)lane < cp.parts ? end_of[p * WAVE + lane] : W_NONE);
+        const u64 t = wave_min_u64((uint32_t)lane < cp.parts ? end_of[p * ROWL + lane] : W_NONE);
         tau = t < tau ? t : tau;
     }
     pend_new = count_pending(m, mo, cn);
@@ -129,17 +166,16 @@ __device__ __forceinline__ uint32_t resume_point(const SimX& m, const u64* end_o
 
 // A simulation state taken before anything depended on op mo's configuration holds two static
 // things about it: the op's own tasks (all still waiting for all their inputs) and, in its
-// consumers' waiting tasks, how many inputs come from op mo.  Rewrites both for the new
-// configuration.  words / l1: the state to patch (a stored snapshot, or live state).
-template <class SimX>
-__device__ __forceinline__ void patch_state_for_op(const SimX& m, u64* words, u64* l1, uint32_t mo, uint2 ocfg, uint32_t pend_new) {
-    const int lane = lane_id();
+// consumers' waiting tasks, how many inputs come from op mo.  Rewrites both, for the new configuration, in n states:
+// words_of(s) for s = 0..n-1 (a chain's stored snapshots, or one live state).  Neither is an event: the queue stands.
+template <int ROWL, class SimX, class WordsOf>
+__device__ __forceinline__ void patch_states_for_op(const SimX& m, uint32_t n, WordsOf words_of, uint32_t mo, uint2 ocfg, uint32_t pend_new) {
+    const uint32_t lane = lane_id();
     const OpCfg cn = m.cfg(mo);
     const OpCfg co = unpack_cfg(ocfg);
-    const u64 w_own = (uint32_t)lane >= cn.parts ? W_NONE : (W_WAIT | ((u64)pend_new << 48));
-    words[mo * WAVE + lane] = w_own;
-    const u64 w_own_min = wave_min_u64(w_own);
-    if (lane == 0) l1[mo] = w_own_min;
+    const u64 w_own = lane >= cn.parts ? W_NONE : (W_WAIT | ((u64)pend_new << 48));
+    if (lane < (uint32_t)ROWL)
+        for (uint32_t s = 0; s < n; s++) words_of(s)[(size_t)mo * ROWL + lane] = w_own;
     const uint32_t ob = m.T.ops[mo].out_begin, oe = m.T.ops[mo].out_end;
     for (uint32_t ei = ob; ei < oe; ei++) {
         const DEdge e = m.T.edges[ei];
@@ -148,15 +184,26 @@ __device__ __forceinline__ void patch_state_for_op(const SimX& m, u64* words, u6
         const uint32_t digits = part_digits(cj, lane, m.magic_v);
         const uint32_t was = count_inputs<SimX::kTrain>(e, co, cj.x, digits, m.magic_v);
         const uint32_t is = count_inputs<SimX::kTrain>(e, cn, cj.x, digits, m.magic_v);
-        if (!ballot((uint32_t)lane < cj.parts && was != is)) continue;
-        const u64 w = words[j * WAVE + lane];
-        // a part of op j that reads op mo at all is still waiting in such a state
-        const bool waiting = (uint32_t)lane < cj.parts && (w >> 63) && w != W_NONE;
-        if (waiting && was != is) {
-            const uint32_t pending = ((uint32_t)(w >> 48) & PENDING_LIMIT) - was + is;
-            words[j * WAVE + lane] = W_WAIT | ((u64)pending << 48) | (w & (TIME_LIMIT - 1));
+        if (!ballot(lane < cj.parts && was != is)) continue;
+        // (a few states at a time, their loads in flight together)
+        constexpr uint32_t FEW = 8;
+        for (uint32_t s0 = 0; s0 < n; s0 += FEW) {
+            u64 w[FEW];
+#pragma unroll
+            for (uint32_t t = 0; t < FEW; t++) {
+                const uint32_t s = s0 + t < n ? s0 + t : n - 1;
+                w[t] = load_word<ROWL>(words_of(s), j);
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < FEW; t++) {
+                // a part of op j that reads op mo at all is still waiting in such a state
+                const bool waiting = lane < cj.parts && (w[t] >> 63) && w[t] != W_NONE;
+                if (s0 + t < n && waiting && was != is) {
+                    const uint32_t pending = ((uint32_t)(w[t] >> 48) & PENDING_LIMIT) - was + is;
+                    words_of(s0 + t)[(size_t)j * ROWL + lane] = W_WAIT | ((u64)pending << 48) | (w[t] & (TIME_LIMIT - 1));
+                }
+            }
         }
-        // level 1 of op j is unaffected: waiting words are not events
     }
 }
 
@@ -268,49 +315,73 @@ __device__ __forceinline__ void commit_run(const ChainMem& cm, ChainMeta& meta, 
     meta.loc ^= written;
     if (!converged) meta.n_valid = rec.next;
     const u64 tag = rec.tag;
-    for (uint32_t t = lane_id(); t < n_words; t += WAVE) {
-        const u64 v = cm.end_try[t];
-        if ((v & ~(TIME_LIMIT - 1)) == tag) cm.end_of[t] = v & (TIME_LIMIT - 1);
+    constexpr uint32_t FEW = 16;         // loads in flight
+    for (uint32_t b = 0; b < n_words; b += FEW * WAVE) {
+        u64 v[FEW];
+#pragma unroll
+        for (uint32_t u = 0; u < FEW; u++) { const uint32_t t = b + u * WAVE + lane_id(); v[u] = cm.end_try[t < n_words ? t : n_words - 1]; }
+#pragma unroll
+        for (uint32_t u = 0; u < FEW; u++) {
+            const uint32_t t = b + u * WAVE + lane_id();
+            if (t < n_words && (v[u] & ~(TIME_LIMIT - 1)) == tag) cm.end_of[t] = v[u] & (TIME_LIMIT - 1);
+        }
     }
     __threadfence_block();
     wave_sync();
 }
 
-// One kernel drives a chain through a sequence of steps.  Three sources of steps:
+// What the steps of a chain ask of run_events: state and kept set-up of one chain.
+// CACHE: the chain keeps the per-edge set-up of its current strategy (all extents fit 16 bits).
+template <bool WIDE, bool TREE, bool CACHE, class SimX>
+struct EventsEngine {
+    SimX& m;
+    const ChainMem& cm;
+    uint32_t n_snaps;
+    static constexpr int kRowl = WAVE;
+    __device__ __forceinline__ StrategyClass validate() const { return validate_strategy(m); }
+    // op mo has the configuration now in m.cfgs (`kept`: simulate is not called before the next change)
+    __device__ __forceinline__ void op_changed(uint32_t) {}
+    __device__ __forceinline__ void op_reverted(uint32_t mo) const { if (CACHE) refresh_ecache_for_group(m, mo); }
+    // one simulation, from time 0 (k = 0) or from snapshot k with op mo changed from configuration ocfg
+    __device__ __forceinline__ u64 simulate(StrategyClass cls, Counters& cnt, Recorder& rec, uint32_t k, uint32_t mo, uint2 ocfg, uint32_t pend_new) {
+        if (k == 0) {
+            init_state(m, cnt);
+        } else {
+            if (CACHE) refresh_ecache_for_op(m, mo);
+            load_snapshot(m, rec, k);
+            // the loaded state still describes the op under its old configuration
+            patch_states_for_op<kRowl>(m, 1, [&](uint32_t) { return m.words; }, mo, ocfg, pend_new);
+            if (lane_id() == 0) m.L.l1[mo] = W_WAIT;
+            wave_sync();
+            rebuild_l2(m);
+        }
+        return cls == STRATEGY_REGULAR ? run_events<WIDE, true, true, false, TREE ? Q_TREE : Q_FLAT, CACHE>(m, cnt, rec)
+                                       : run_events<WIDE, true, false, false, TREE ? Q_TREE : Q_FLAT, CACHE>(m, cnt, rec);
+    }
+    __device__ __forceinline__ u64 makespan() const { return ffsim::makespan(m); }
+    __device__ __forceinline__ void finish() const {}
+};
+
+// The steps of one chain.  Three sources of steps:
 //   muts == nullptr and no search: simulate the chain's starting strategy (n_steps is 1);
 //   muts: forced mutations, [n_steps][C] records {op, cfg.x, cfg.y}, always committed;
 //   search: per step one proposal (random op, random configuration from its list, random
 //           device offset), committed if it is not slower, else with the tabulated probability.
 // A step is one recorded simulation (resumed from the last snapshot before the change can
 // matter), then either commit_run or nothing.  Every simulation goes through the single
-// run_events call site below, including the pass that only finds the makespan when no
+// Engine::simulate call site below, including the pass that only finds the makespan when no
 // snapshot spacing is set yet.
 // A forced mutation that names an op outside the graph poisons the chain: this and all
 // later results are RESULT_INVALID.  out_ns[s][c] is the time of the chain's strategy after
-// step s.
-// CACHE: the chain keeps the per-edge set-up of its current strategy (all extents fit 16 bits).
-// EXT: 0 plain, 1 with the refinements of the inputs, 2 also training-iteration graphs.  GPN: compiled for this many GPUs per node (0 = any).
-template <bool WIDE, bool TREE, bool CACHE, int EXT, int GPN>
-__global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ edges,
-                                                          const DEdge* __restrict__ in_edges, const uint32_t* __restrict__ cost,
-                                                          const uint32_t* __restrict__ magic, unsigned char* chain_mem,
-                                                          size_t chain_stride, uint32_t n_snaps, uint32_t C,
-                                                          const uint32_t* __restrict__ muts, uint32_t n_steps,
-                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    const Tables T{ops, edges, in_edges, cost};
-    // the chain's strategy is worked on in LDS (and written through to HBM), so that the many
-    // uniform configuration look-ups do not queue behind the wavefront's stores to HBM
-    uint2* cfg_lds = (uint2*)lds_raw;
-    const WaveLds L = carve_lds(lds_raw + (size_t)S.n_ops_pad * 8, S);
-    const uint32_t c = blockIdx.x;
-    if (c >= C) return;
+// step s.  cfg_lds: the chain's strategy, worked on in LDS (and written through to HBM), so that the many
+// uniform configuration look-ups do not queue behind the wavefront's stores to HBM.
+template <class Engine, class SimX>
+__device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S, const ChainMem& cm, uint2* cfg_lds, uint32_t n_snaps, uint32_t c,
+                                            uint32_t C, const uint32_t* __restrict__ muts, uint32_t n_steps, u64* __restrict__ out_ns,
+                                            uint32_t* chain_flags, const SearchDev& search) {
+    constexpr int ROWL = Engine::kRowl;
     const int lane = lane_id();
-    const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps);
-    const uint32_t magic_v = load_magic(magic);
-    const uint32_t n_words = S.n_ops * WAVE;
-    for (uint32_t i = lane; i < S.n_ops; i += WAVE) cfg_lds[i] = cm.cfgs[i];
-    wave_sync();
+    const uint32_t n_words = S.n_ops * ROWL;
     bool poisoned = first_u32(chain_flags[c]) != 0;
     ChainMeta meta = *cm.meta;
     meta.step = first_u64(meta.step);
@@ -326,12 +397,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
     meta.loc = first_u32(meta.loc);
     meta.tag = first_u32(meta.tag);
     Recorder rec{cm.end_try, cm.snap_words, cm.snap_l1, cm.snap_free, meta.step, 0, meta.loc, n_snaps, 1, 0, 0};
-    SimT<false, EXT, GPN> m{S, T, cfg_lds, cm.words, cm.exe_of, L, magic_v, 0, false, NO_OVERRIDE, make_uint2(0, 0), CACHE ? cm.ecache : nullptr, true};
-    if (EXT) { m.links = (const uint4*)(magic + LINK_TABLE_AT); m.node_links = m.links + (size_t)S.gpus_per_node * S.gpus_per_node; }
-    if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
     // With tied configurations a mutation changes several ops at once: such steps are simulated from time 0.
-    const bool tied = EXT >= 2 && S.ties;
-    m.want_sort = true;          // a later step may make the strategy a general one: the kept set-up is always complete
+    const bool tied = SimX::kTrain && S.ties;
     u64 best = search.enabled ? first_u64(search.best_ns[c]) : 0;
     if (search.enabled && !poisoned && !meta.stale && meta.cur_ns < best) {
         // the strategy the search starts from counts as seen
@@ -386,12 +453,13 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                     cm.cfgs[op] = ncfg;
                 }
                 wave_sync();
+                en.op_changed(op);
             }
         }
         u64 mk = RESULT_INVALID;
         StrategyClass cls = STRATEGY_INVALID;
         // (a proposal known to be rejected changes nothing: the strategy in force was validated when it was taken)
-        if (!poisoned && !known_rejected) cls = validate_strategy(m);
+        if (!poisoned && !known_rejected) cls = en.validate();
         valid = known_rejected || cls != STRATEGY_INVALID;
         if (!poisoned && !valid && !proposal) { meta.stale = 1; meta.cur_ns = RESULT_INVALID; }
         const bool changed = muts != nullptr || proposal;
@@ -403,7 +471,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
         } else if (!poisoned && valid) {
             // where the simulation may start (0 = time 0)
             uint32_t k = 0, pend_new = 0;
-            if (changed && !meta.stale && meta.n_valid > 1 && meta.step != 0 && !tied) k = resume_point(m, cm.end_of, meta, op, ocfg, pend_new);
+            if (proposal) en.op_changed(op);
+            if (changed && !meta.stale && meta.n_valid > 1 && meta.step != 0 && !tied) k = resume_point<ROWL>(m, cm.end_of, meta, op, ocfg, pend_new);
             const uint32_t capacity = n_snaps;
             // phase 1: makespan only, to fix the snapshot spacing (no snapshots yet);
             // phase 2: the recorded simulation
@@ -432,20 +501,9 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                 // a resumed run of a changed strategy may re-join the accepted timeline
                 rec.check_below = (record && k > 0 && changed) ? meta.n_valid : 0u;
                 rec.check_op = op;
-                if (k == 0) {
-                    init_state(m, cnt);
-                } else {
-                    if (CACHE && record) refresh_ecache_for_op(m, op);
-                    load_snapshot(m, rec, k);
-                    // the loaded state still describes the op under its old configuration
-                    patch_state_for_op(m, m.words, L.l1, op, ocfg, pend_new);
-                    wave_sync();
-                    rebuild_l2(m);
-                }
-                rc = cls == STRATEGY_REGULAR ? run_events<WIDE, true, true, false, TREE ? Q_TREE : Q_FLAT, CACHE>(m, cnt, rec)
-                                             : run_events<WIDE, true, false, false, TREE ? Q_TREE : Q_FLAT, CACHE>(m, cnt, rec);
+                rc = en.simulate(cls, cnt, rec, k, op, ocfg, pend_new);
                 if (rc == RUN_CONVERGED) { converged = true; rc = 0; mk = meta.cur_ns; break; }
-                mk = rc ? rc : makespan(m);
+                mk = rc ? rc : en.makespan();
                 if (rc) break;
                 if (phase == 1) { meta.step = (2 * mk) / capacity + 1; phase = 2; continue; }
                 if (k == 0) meta.n_events_full = cnt.n_events - before;
@@ -460,10 +518,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                 if (k > 0) {
                     meta.n_resumed++;
                     // what the snapshots that stay hold about the op is rewritten for its new configuration
-                    for (uint32_t sn = 1; sn <= k; sn++) {
-                        const size_t at = (size_t)(((meta.loc >> sn) & 1u) * n_snaps + sn);
-                        patch_state_for_op(m, cm.snap_words + at * n_words, cm.snap_l1 + at * S.n_ops_pad, op, ocfg, pend_new);
-                    }
+                    patch_states_for_op<ROWL>(m, k, [&](uint32_t t) { return cm.snap_words + (size_t)(((meta.loc >> (t + 1)) & 1u) * n_snaps + t + 1) * n_words; },
+                                              op, ocfg, pend_new);
                 }
                 commit_run(cm, meta, rec, k + 1, n_words, converged);
                 if (converged) meta.n_converged++;
@@ -478,7 +534,7 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                 wave_sync();
                 if (lane == 0) cfg_lds[op] = ocfg;
                 wave_sync();
-                if (CACHE) refresh_ecache_for_group(m, op);
+                en.op_reverted(op);
                 mk = meta.cur_ns;
             } else {
                 // a forced step whose simulation failed (overflow): no timeline for this strategy
@@ -512,6 +568,36 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
         if (search.enabled) search.best_ns[c] = best;
         if (own_position) { search.done[c] = s; search.n_accepted[c] += n_taken; }
     }
+    en.finish();
+}
+
+// One wavefront per chain.  EXT: 0 plain, 1 with the refinements of the inputs, 2 also training-iteration graphs.  GPN: compiled for
+// this many GPUs per node (0 = any).
+template <bool WIDE, bool TREE, bool CACHE, int EXT, int GPN>
+__global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ edges,
+                                                          const DEdge* __restrict__ in_edges, const OpLite* __restrict__,
+                                                          const EdgeLite* __restrict__, const uint32_t* __restrict__ cost,
+                                                          const uint32_t* __restrict__ magic, unsigned char* chain_mem,
+                                                          size_t chain_stride, uint32_t n_snaps, uint32_t C,
+                                                          const uint32_t* __restrict__ muts, uint32_t n_steps,
+                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const Tables T{ops, edges, in_edges, cost};
+    uint2* cfg_lds = (uint2*)lds_raw;
+    const WaveLds L = carve_lds(lds_raw + (size_t)S.n_ops_pad * 8, S);
+    const uint32_t c = blockIdx.x;
+    if (c >= C) return;
+    const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, 0);
+    const uint32_t magic_v = load_magic(magic);
+    for (uint32_t i = lane_id(); i < S.n_ops; i += WAVE) cfg_lds[i] = cm.cfgs[i];
+    wave_sync();
+    typedef SimT<false, EXT, GPN> SimX;
+    SimX m{S, T, cfg_lds, cm.words, cm.exe_of, L, magic_v, 0, false, NO_OVERRIDE, make_uint2(0, 0), CACHE ? cm.ecache : nullptr, true};
+    if (EXT) { m.links = (const uint4*)(magic + LINK_TABLE_AT); m.node_links = m.links + (size_t)S.gpus_per_node * S.gpus_per_node; }
+    if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
+    m.want_sort = true;          // a later step may make the strategy a general one: the kept set-up is always complete
+    EventsEngine<WIDE, TREE, CACHE, SimX> en{m, cm, n_snaps};
+    chain_steps(en, m, S, cm, cfg_lds, n_snaps, c, C, muts, n_steps, out_ns, chain_flags, search);
 }
 
 // Trial mutations (the proposals of Section 6.2 before acceptance): evaluates M alternative
@@ -520,7 +606,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
 // live in a private workspace slot, the chain's snapshots are only read.
 template <bool WIDE, bool TREE, bool CACHE, int EXT, int GPN>
 __global__ __launch_bounds__(WAVE) void k_sim_chain_try(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ edges,
-                                                        const DEdge* __restrict__ in_edges, const uint32_t* __restrict__ cost,
+                                                        const DEdge* __restrict__ in_edges, const OpLite* __restrict__,
+                                                        const EdgeLite* __restrict__, const uint32_t* __restrict__ cost,
                                                         const uint32_t* __restrict__ magic, const unsigned char* __restrict__ chain_mem,
                                                         size_t chain_stride, uint32_t n_snaps, uint32_t C,
                                                         const uint32_t* __restrict__ muts, uint32_t M, u64* __restrict__ out_ns,
@@ -543,7 +630,7 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_try(SimDev S, const DOp* __r
         if (id >= total) break;
         const uint32_t c = id % C;
         // the chain is only read here
-        const ChainMem cm = carve_chain(const_cast<unsigned char*>(chain_mem) + (size_t)c * chain_stride, S, n_snaps);
+        const ChainMem cm = carve_chain(const_cast<unsigned char*>(chain_mem) + (size_t)c * chain_stride, S, n_snaps, 0);
         ChainMeta meta = *cm.meta;
         meta.step = first_u64(meta.step);
         meta.n_valid = first_u32(meta.n_valid);
@@ -563,12 +650,13 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_try(SimDev S, const DOp* __r
                 Counters cnt = {};
                 Recorder rec{nullptr, cm.snap_words, cm.snap_l1, cm.snap_free, meta.step, 0, first_u32(meta.loc), n_snaps, 1, 0, 0};
                 uint32_t k = 0, pend_new = 0;
-                if (!meta.stale && meta.n_valid > 1 && meta.step != 0 && !(EXT >= 2 && S.ties)) k = resume_point(m, cm.end_of, meta, op, ocfg, pend_new);
+                if (!meta.stale && meta.n_valid > 1 && meta.step != 0 && !(EXT >= 2 && S.ties)) k = resume_point<WAVE>(m, cm.end_of, meta, op, ocfg, pend_new);
                 if (k == 0) {
                     init_state(m, cnt);
                 } else {
                     load_snapshot(m, rec, k);
-                    patch_state_for_op(m, m.words, L.l1, op, ocfg, pend_new);
+                    patch_states_for_op<WAVE>(m, 1, [&](uint32_t) { return words; }, op, ocfg, pend_new);
+                    if (lane_id() == 0) L.l1[op] = W_WAIT;
                     wave_sync();
                     rebuild_l2(m);
                 }

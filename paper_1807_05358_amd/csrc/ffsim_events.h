@@ -155,6 +155,16 @@ __device__ __forceinline__ void init_state(SimX& m, Counters& cnt) {
     m.overflow = false;
 }
 
+// the words of an op's parts, rows of ROWL words (lanes beyond them: W_NONE)
+template <int ROWL>
+__device__ __forceinline__ u64 load_word(const u64* words, uint32_t op) {
+    const uint32_t lane = lane_id();
+    if (ROWL == WAVE) return words[(size_t)op * WAVE + lane];
+    u64 w = W_NONE;
+    if (lane < (uint32_t)ROWL) w = words[(size_t)op * ROWL + lane];
+    return w;
+}
+
 // wavefront-wide copy of n 64-bit words between 16-byte aligned HBM buffers, n a multiple of
 // 64: 16 bytes per lane and eight loads in flight before the first store
 __device__ __forceinline__ void copy_words(u64* __restrict__ dst, const u64* __restrict__ src, uint32_t n) {

@@ -7,18 +7,29 @@
 
 namespace ffsim {
 
-template <bool CACHE>
+template <bool WIDE, bool CACHE>
 static chain_kernel_t chain_kernel_of(const KernelChoice& k) {
     constexpr int EXT = FFSIM_EXT;
     constexpr int GPN = FFSIM_GPN;
-    const bool tree = k.n_groups > FLAT_GROUPS;
-    if (k.wide) return tree ? k_sim_chain_steps<true, true, CACHE, EXT, GPN> : k_sim_chain_steps<true, false, CACHE, EXT, GPN>;
-    return tree ? k_sim_chain_steps<false, true, CACHE, EXT, GPN> : k_sim_chain_steps<false, false, CACHE, EXT, GPN>;
+    return k.n_groups > FLAT_GROUPS ? k_sim_chain_steps<WIDE, true, CACHE, EXT, GPN> : k_sim_chain_steps<WIDE, false, CACHE, EXT, GPN>;
 }
 
 template <>
 chain_kernel_t chain_kernels<FFSIM_EXT, FFSIM_GPN>(const KernelChoice& k) {
-    return k.cache ? chain_kernel_of<true>(k) : chain_kernel_of<false>(k);
+    // (extents that fit 16 bits without the need for 64-bit arithmetic: k_loop_chain_steps)
+    if (k.cache) return chain_kernel_of<true, true>(k);
+    return k.wide ? chain_kernel_of<true, false>(k) : chain_kernel_of<false, false>(k);
+}
+
+template <>
+chain_kernel_t loop_chain_kernels<FFSIM_EXT, FFSIM_GPN>(const LoopChoice& k) {
+    constexpr int EXT = FFSIM_EXT;
+    constexpr int GPN = FFSIM_GPN;
+    if (k.lds) {
+        if (k.rowl == WAVE) return k_loop_chain_steps<true, Q_OP, WAVE, EXT, GPN>;
+        return k.queue == Q_OP16 ? k_loop_chain_steps<true, Q_OP16, 16, EXT, GPN> : k_loop_chain_steps<true, Q_OP, 16, EXT, GPN>;
+    }
+    return k.rowl == WAVE ? k_loop_chain_steps<false, Q_SLOT, WAVE, EXT, GPN> : k_loop_chain_steps<false, Q_SLOT, 16, EXT, GPN>;
 }
 
 }  // namespace ffsim

@@ -46,6 +46,7 @@ struct LoopMem {
     uint32_t* spill_op;         // [n_ops_pad]
     u64* crow;                  // LDS [n_dev]: endTime of the last task of every compute device
     uint32_t* lrow;             // LDS [n_links]: endTime of the last transfer of every link row, relative to E
+    u64* lrow64;                // the same memory as absolute times (the form with 64-bit link rows; null where there is none)
     uint8_t* tag;               // LDS [n_rows]: see fifo_commit
     const uint4* links;         // {m, k, lat1, 0} per ordered pair of local GPUs, then per ordered pair of nodes; or null
     const OpLite* op_lite;      // static records (ffsim_kept.h)
@@ -63,14 +64,6 @@ __device__ __forceinline__ uint32_t part_min_of(uint32_t v, u64 mask) {
     return part_min_u32<ROWL>(lanes_of(mask) ? v : KEY_NONE);
 }
 
-template <int ROWL>
-__device__ __forceinline__ u64 load_word(const u64* words, uint32_t op) {
-    const uint32_t lane = lane_id();
-    if (ROWL == WAVE) return words[(size_t)op * WAVE + lane];
-    u64 w = W_NONE;
-    if (lane < (uint32_t)ROWL) w = words[(size_t)op * ROWL + lane];
-    return w;
-}
 // smallest pending event of an op, from its words in memory (W_NONE: none)
 template <int ROWL>
 __device__ __forceinline__ u64 op_min_word(const u64* words, uint32_t op) {
@@ -192,7 +185,7 @@ __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st)
 
 // Moves the epoch to the next pending event.  Returns false if there is none.
 // (What a link row holds below the epoch no longer matters: nothing becomes ready before it.)
-template <int Q, int ROWL>
+template <int Q, int ROWL, bool L64>
 __device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st, uint32_t n_links) {
     Queue& q = st.q;
     u64 word = q.key >= KEY_FAR ? W_NONE : 2 * st.E + q.key;      // this lane's event in full
@@ -211,18 +204,28 @@ __device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st,
     const u64 delta = E - st.E;
     st.E = E;
     q.key = word >> 63 ? KEY_NONE : rel_key(word, E);
-    const uint32_t d32 = delta >> 32 ? 0xffffffffu : (uint32_t)delta;
-    for (uint32_t r = lane_id(); r < n_links; r += WAVE) mem.lrow[r] = __builtin_elementwise_sub_sat(mem.lrow[r], d32);
-    wave_sync();
+    if (!L64) {
+        const uint32_t d32 = delta >> 32 ? 0xffffffffu : (uint32_t)delta;
+        for (uint32_t r = lane_id(); r < n_links; r += WAVE) mem.lrow[r] = __builtin_elementwise_sub_sat(mem.lrow[r], d32);
+        wave_sync();
+    }
     return true;
 }
 
 // ---- state: start, snapshots, result -------------------------------------------------------
 
-// Writes the next snapshot: the task words, and endTimes of all device and link rows (absolute).  Result: see save_snapshot
-// (ffsim_events.h).  The queue is not stored: it follows from the words.
-template <int ROWL, class SimX>
-__device__ __forceinline__ bool save_loop_snapshot(const SimX& m, const LoopMem& mem, const LoopState& st, Recorder& rec) {
+// endTime of device row or link row t (device rows first), absolute; a link row idle before the epoch reads as the epoch or less
+template <bool L64>
+__device__ __forceinline__ u64 row_time(const LoopMem& mem, const LoopState& st, uint32_t t, uint32_t n_dev) {
+    return t < n_dev ? mem.crow[t] : (L64 ? mem.lrow64[t - n_dev] : st.E + mem.lrow[t - n_dev]);
+}
+
+// Writes the next snapshot: the task words, and endTimes of all device and link rows (absolute).  The queue is not
+// stored: it follows from the words.  next_ns: time of the first pending event.  Returns true if the comparison is on and the
+// state equals the accepted timeline's snapshot of the same index for everything that can still matter: all words, and
+// the rows, where rows that are idle when the first event comes count as equal (with equal words it is the same event).
+template <int ROWL, bool L64, class SimX>
+__device__ __forceinline__ bool save_loop_snapshot(const SimX& m, const LoopMem& mem, const LoopState& st, Recorder& rec, u64 next_ns) {
     const uint32_t lane = lane_id();
     const uint32_t idx = rec.next, n_rows = m.S.n_rows, n_dev = m.S.n_dev;
     const size_t k = (size_t)((((rec.loc >> idx) & 1u) ^ 1u) * rec.n_snaps + idx);   // the place the accepted timeline does not use
@@ -233,25 +236,24 @@ __device__ __forceinline__ bool save_loop_snapshot(const SimX& m, const LoopMem&
     if (check) {
         const size_t old = (size_t)(((rec.loc >> idx) & 1u) * rec.n_snaps + idx);
         differs = copy_words_compare(rec.snap_words + k * nw, mem.words, rec.snap_words + old * nw, (uint32_t)nw);
-        const u64 t_snap = ((u64)idx * rec.step) >> 1;
         const u64* ofr = rec.snap_free + old * (size_t)n_rows;
         for (uint32_t t = lane; t < n_rows; t += WAVE) {
-            const u64 a = t < n_dev ? mem.crow[t] : st.E + mem.lrow[t - n_dev], b = ofr[t];
-            differs = differs || (a > t_snap ? a : t_snap) != (b > t_snap ? b : t_snap);
+            const u64 a = row_time<L64>(mem, st, t, n_dev), b = ofr[t];
+            differs = differs || (a > next_ns ? a : next_ns) != (b > next_ns ? b : next_ns);
         }
         // a task of the changed op still pending would make equal words mean different things
         differs = differs || load_word<ROWL>(mem.words, rec.check_op) != W_NONE;
     } else {
         copy_words(rec.snap_words + k * nw, mem.words, (uint32_t)nw);
     }
-    for (uint32_t t = lane; t < n_rows; t += WAVE) fr[t] = t < n_dev ? mem.crow[t] : st.E + mem.lrow[t - n_dev];
+    for (uint32_t t = lane; t < n_rows; t += WAVE) fr[t] = row_time<L64>(mem, st, t, n_dev);
     rec.next++;
     return check && !ballot(differs);
 }
 
 // The state of snapshot k of the accepted timeline: words copied, rows and queue rebuilt.  False if a link row is booked
-// beyond 32 bits after the snapshot's time.
-template <int Q, int ROWL, class SimX>
+// beyond 32 bits after the snapshot's time (and the rows are not 64-bit ones).
+template <int Q, int ROWL, bool L64, class SimX>
 __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem& mem, LoopState& st, const Recorder& rec, uint32_t k) {
     const uint32_t lane = lane_id();
     const uint32_t n_rows = m.S.n_rows, n_dev = m.S.n_dev, n_ops = m.S.n_ops;
@@ -263,15 +265,18 @@ __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem&
     for (uint32_t t = lane; t < n_rows; t += WAVE) {
         const u64 a = fr[t];
         if (t < n_dev) { mem.crow[t] = a; continue; }
+        if (L64) { mem.lrow64[t - n_dev] = a; continue; }
         const u64 r = a > E ? a - E : 0;
         beyond = beyond || r >= 0xffffffffull;
         mem.lrow[t - n_dev] = (uint32_t)r;
     }
     queue_clear(st.q);
     const u64* src = rec.snap_words + at * (size_t)n_ops * ROWL;
-    // eight rows of 64 words in flight; a row of ROWL = 16 holds the words of four ops
+    // eight rows of 64 words in flight; a row of ROWL = 16 holds the words of four ops.  Q_SLOT: ops with an event are listed
+    // first (where the queue's spill list will be) and get their slots afterwards.
     constexpr uint32_t PER = WAVE / ROWL;
     const uint32_t n_words = n_ops * ROWL;
+    uint32_t n_listed = 0;
     for (uint32_t b = 0; b < n_words; b += 8 * WAVE) {
         u64 v[8];
 #pragma unroll
@@ -284,24 +289,38 @@ __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem&
                 for (uint32_t g = 0; g < PER; g++) {
                     const u64 mine = lane / ROWL == g ? v[u] : W_NONE;
                     const u64 mn = wave_min_u64(mine);
-                    if (!(mn >> 63)) queue_insert<Q, ROWL>(mem, st, (b + u * WAVE) / ROWL + g, rel_key(mn, E));
+                    if (mn >> 63) continue;
+                    const uint32_t op = (b + u * WAVE) / ROWL + g;
+                    if (Q == Q_SLOT) {
+                        if (lane == 0) { mem.spill_key[n_listed] = mn; mem.spill_op[n_listed] = op; }
+                        n_listed++;
+                    } else {
+                        queue_insert<Q, ROWL>(mem, st, op, rel_key(mn, E));
+                    }
                 }
             }
         }
     }
     wave_sync();
+    if (Q == Q_SLOT) {
+        n_listed = first_u32(n_listed);
+        // (an insertion puts at most one entry back on the list, over one already read)
+        for (uint32_t t = 0; t < n_listed; t++) queue_insert<Q, ROWL>(mem, st, first_u32(mem.spill_op[t]), rel_key(first_u64(mem.spill_key[t]), E));
+    }
     return !ballot(beyond);
 }
 
 // Section 5.1 step 1 and the start of Algorithm 1: the tasks, how many inputs each waits for, the initial READY set,
 // idle devices.  FILL: computes and keeps the set-up of every edge; otherwise the kept rows are valid and only read.
 // Configurations are loaded 64 at a time and read from registers, so that no op waits for its own loads.
-template <int Q, int ROWL, class SimX>
+template <int Q, int ROWL, bool L64 = false, class SimX>
 __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, bool fill) {
     const uint32_t lane = lane_id();
     const uint32_t n_ops = m.S.n_ops, n_edges = m.S.n_edges;
     for (uint32_t r = lane; r < m.S.n_dev; r += WAVE) mem.crow[r] = 0;
-    for (uint32_t r = lane; r < m.S.n_rows - m.S.n_dev; r += WAVE) mem.lrow[r] = 0;
+    for (uint32_t r = lane; r < m.S.n_rows - m.S.n_dev; r += WAVE) {
+        if (L64) mem.lrow64[r] = 0; else mem.lrow[r] = 0;
+    }
     queue_clear(st.q);
     st.E = 0;
     uint2 sc = make_uint2(0, 0);                    // configurations of the producers of the next 64 in-edges
@@ -365,13 +384,13 @@ __device__ __forceinline__ StrategyClass validate_loop(const SimX& m, const Loop
 }
 
 // Algorithm 1, result: see makespan (ffsim_events.h)
-template <class SimX>
+template <bool L64 = false, class SimX>
 __device__ __forceinline__ u64 loop_makespan(const SimX& m, const LoopMem& mem, const LoopState& st) {
     u64 mk = 0;
     for (uint32_t d = lane_id(); d < m.S.n_dev; d += WAVE) mk = mem.crow[d] > mk ? mem.crow[d] : mk;
     if (SimX::kExt && m.S.sync) {
         for (uint32_t r = lane_id(); r < m.S.n_rows - m.S.n_dev; r += WAVE) {
-            const u64 t = mem.lrow[r] ? st.E + mem.lrow[r] : 0;
+            const u64 t = L64 ? mem.lrow64[r] : (mem.lrow[r] ? st.E + mem.lrow[r] : 0);
             mk = t > mk ? t : mk;
         }
     }
@@ -458,9 +477,12 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
 // ResNet-101-shaped 20.1 -> 13.9, 1024 x NMT-shaped 98.9 -> 74.2, 1024 x AlexNet-shaped 0.232 -> 0.219; general
 // strategies (777 x ResNet-101-shaped on 5 x 3 devices) 31.2 -> 22.4; training iterations (1024 x Inception-v3-shaped)
 // 24.6 -> 18.5.
-template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, class SimX>
-__device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec) {
+// L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
+template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX>
+__device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec) {
+    static_assert(!(REG && L64), "64-bit link rows go with the general form");
     constexpr bool RUNS = Q == Q_SLOT;       // runs of events (see run_events): on graphs of more than 64 ops
+    typedef typename std::conditional<L64, u64, uint32_t>::type T;      // times of transfers: absolute, or relative to the epoch
     const uint32_t lane = lane_id();
     PROF_DECL
     const SimDev& S = m.S;
@@ -475,6 +497,11 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
     const uint32_t l_near = vector_copy(S.near_link.lat1), l_far = vector_copy(S.far_link.lat1);
     const uint32_t elem_sh = vector_copy(S.elem_sh);
     Queue& q = st.q;
+    // (uniform already, which the compiler does not always see where the state was rebuilt from memory)
+    st.E = first_u64(st.E);
+    q.n_spill = first_u32(q.n_spill);
+    q.spill_min = first_u64(q.spill_min);
+    if (RECORD) { rec.step = first_u64(rec.step); rec.next = first_u32(rec.next); rec.n_snaps = first_u32(rec.n_snaps); rec.check_below = first_u32(rec.check_below); }
     const u64 max_events = 2ull * S.n_ops * WAVE + 8;
     uint32_t snap_key = KEY_NONE;            // RECORD: key of the next snapshot boundary
     auto set_snap_key = [&]() {
@@ -488,7 +515,7 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
         // ---- pop
         uint32_t kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
         if (kmin >= KEY_REFRESH) {
-            if (!advance_epoch<Q, ROWL>(mem, st, n_links)) break;
+            if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
             set_snap_key();
             kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
         }
@@ -511,7 +538,7 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
         if (RECORD) {
             // the state before the first event at or after a multiple of `step` is a snapshot
             while (kmin >= snap_key) {
-                if (save_loop_snapshot<ROWL>(m, mem, st, rec)) return RUN_CONVERGED;
+                if (save_loop_snapshot<ROWL, L64>(m, mem, st, rec, st.E + (kmin >> 1))) return RUN_CONVERGED;
                 set_snap_key();
             }
         }
@@ -649,8 +676,10 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                 const uint32_t local_c = m.local_of(dev_c, node_c);
                 const uint32_t far_base = S.n_nodes * G * G + node_c;
                 u64 ready64 = w & (TIME_LIMIT - 1);
-                uint32_t ready;                             // relative to the epoch; what lies before it no longer matters
-                {
+                T ready;                                    // relative to the epoch; what lies before it no longer matters
+                if constexpr (L64) {
+                    ready = ready64;
+                } else {
                     const u64 rr = ready64 - st.E;
                     ready = (int32_t)(uint32_t)(rr >> 32) < 0 ? 0u : (uint32_t)rr;
                 }
@@ -692,7 +721,8 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                         const uint32_t dev_a = readlane_u32(dev_v, kp), now_kp = readlane_u32(now_v, kp);
                         const uint32_t node_a = SimX::kGpn == 4 ? dev_a >> 2 : m.node_of(dev_a);
                         const u64 comm_m = hit_m & ballot(dev_c != dev_a);
-                        uint32_t arrive = now_kp;
+                        const T from = L64 ? (T)(st.E + now_kp) : (T)now_kp;
+                        T arrive = from;
                         if (comm_m) {
                             // Section 5.1: the link device between the two devices; assumption A2: transfer time
                             const u64 near_m = ballot(node_c == node_a);
@@ -708,8 +738,10 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                             }
                             const uint32_t ns = (__umulhi((elems << elem_sh) - 1u, lm) >> lk) + ll;
                             const u64 far_m = comm_m & ~near_m;
-                            uint32_t end;
-                            if (REG) {
+                            T end;
+                            if constexpr (L64) {
+                                end = fifo_commit(comm, row, ns, from, true, WaveLds{mem.lrow64, nullptr, nullptr, mem.tag});
+                            } else if (REG) {
                                 const uint32_t fr = mem.lrow[row];         // in range for every lane
                                 // consumer parts on one node are consecutive lanes: a running sum along them is the FIFO
                                 // order on the link row they share (rows between GPUs of one node are private)
@@ -748,13 +780,13 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                                     end = here ? e : end;
                                 }
                             }
-                            arrive = comm ? end : now_kp;
+                            arrive = comm ? end : from;
                             if (STATS) {
                                 cnt.n_comm += __popcll(comm_m);
                                 if (comm) cnt.sum_comm_ns += ns;     // per-lane partial sums, reduced by the caller
                             }
                         }
-                        const uint32_t came = lanes_of(hit_m) ? arrive : 0u;
+                        const T came = lanes_of(hit_m) ? arrive : 0u;
                         ready = came > ready ? came : ready;
                         hits = count_lanes(hits, hit_m);
                         if (STATS) cnt.n_pairs += __popcll(hit_m);
@@ -778,13 +810,15 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                 const u64 touched_m = ballot(touched);
                 if (touched_m) {
                     const uint32_t left = pending - hits;
-                    const u64 abs = st.E + ready;
-                    retry_m |= touched_m & ballot(ready == 0xffffffffu);
+                    const u64 abs = L64 ? (u64)ready : st.E + ready;
+                    if (!L64) retry_m |= touched_m & ballot(ready == 0xffffffffu);
                     overflow_m |= touched_m & ballot(abs >= TIME_LIMIT);
                     const u64 ready_m = touched_m & ballot(left == 0);
                     if (touched) words[(size_t)j * ROWL + lane] = left == 0 ? (abs << 1) | 1u : (W_WAIT | ((u64)left << 48) | (abs & (TIME_LIMIT - 1)));
                     if (ready_m) {
-                        const uint32_t first = part_min_of<ROWL>(ready, ready_m);
+                        uint32_t rel = (uint32_t)ready;
+                        if constexpr (L64) { const u64 r = ready - st.E; rel = r >= KEY_FAR ? KEY_FAR : (uint32_t)r; }
+                        const uint32_t first = part_min_of<ROWL>(rel, ready_m);
                         queue_insert<Q, ROWL>(mem, st, j, first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1);
                     }
                 }
@@ -824,10 +858,15 @@ __device__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cn
                             bw = e.x; m_bw = e.y; lat = e.z;
                         }
                         const uint32_t ns = ceil_div_u32(shard_bytes, bw, m_bw) + lat;
-                        const uint32_t end = fifo_links(act, act ? row_i : 0u, ns, now, true, mem);
                         const u64 act_m = ballot(act);
-                        retry_m |= act_m & ballot(end == 0xffffffffu);
-                        overflow_m |= act_m & ballot(st.E + end >= TIME_LIMIT);
+                        if constexpr (L64) {
+                            const u64 end = fifo_commit(act, act ? row_i : 0u, ns, st.E + now, true, WaveLds{mem.lrow64, nullptr, nullptr, mem.tag});
+                            overflow_m |= act_m & ballot(end >= TIME_LIMIT);
+                        } else {
+                            const uint32_t end = fifo_links(act, act ? row_i : 0u, ns, now, true, mem);
+                            retry_m |= act_m & ballot(end == 0xffffffffu);
+                            overflow_m |= act_m & ballot(st.E + end >= TIME_LIMIT);
+                        }
                         if (STATS) {
                             cnt.n_comm += __popcll(act_m);
                             if (act) cnt.sum_comm_ns += ns;

@@ -152,3 +152,52 @@ def test_link_time_constants(B, elem_bytes):
     for near, far in [(1, 1), (2, 3), (20, 12), (5, 7), (24, 36), (255, 256), (65537, 1000003), (2 ** 31, 2 ** 32 - 1), (1, 2 ** 32 - 1)]:
         mach = W.Machine(4, 4, near, far, 1, 2, elem_bytes)
         check(B, ops, edges, mach, cost, draw(rng, ops, 24, 16, 64, (1, 2, 3, 5, 7, 16, 61)))
+
+
+@pytest.mark.parametrize("n_ops", [12, 70])
+@pytest.mark.parametrize("parts", [16, 64])
+def test_chain_that_starts_from_an_invalid_strategy(B, n_ops, parts):
+    """two ops with degrees their tensors do not have, mended one after the other, by changes and by a trial: the kept set-up of
+    every edge is complete as soon as the strategy is valid"""
+    rng = np.random.default_rng(n_ops + parts)
+    g = W.GraphBuilder()
+    for i in range(n_ops):
+        o = g.op(W.T_ELEM, (16, 6, 8) if i % 3 else (64, 8), (0, 1, 2) if i % 3 else (0, 1), 1)
+        for s in sorted(set(int(x) for x in rng.integers(max(0, o - 4), o, size=2))) if o else ():
+            g.edge(s, o, [W.ident(0), W.ident(1)] + ([W.ALL] if s % 3 else []))
+    ops, edges, _ = g.finish()
+    mach = W.Machine(4, 4)
+    cost = rng.integers(1, 9000, size=(n_ops, parts)).astype("<u4")
+    cfgs = draw(rng, ops, 3, 16, parts, (1, 2, 3, 4, 8), strides=True)
+    good = cfgs[0].copy()
+    a, b = 3, n_ops - 2
+    cfgs[0]["deg"][a] = (255, 1, 1, 1)
+    cfgs[0]["deg"][b] = (0, 2, 1, 1)
+    # a step that leaves it invalid, one that mends the first op, the second, and an ordinary one
+    muts = np.zeros((4, 1), W.MUT_DT)
+    muts["op"][:, 0] = (5, a, b, 1)
+    for t, cfg in enumerate((cfgs[1, 5], good[a], cfgs[1, b], cfgs[1, 1])):
+        muts[t, 0]["cfg"] = cfg
+    sim = B.Simulator(ops, edges, mach, cost)
+    ch = B.Chains(sim, cfgs[:1])
+    invalid = np.iinfo(np.uint64).max
+    assert ch.start_ns()[0] == invalid
+    d = ch.delta(ch.upload_mutations(muts[:2].copy()), 2).cpu().numpy().view("<u8")
+    assert (d == invalid).all()
+    # a trial that mends the last op, against the chain's (invalid) strategy
+    cur = cfgs[0].copy()
+    cur[5], cur[a] = cfgs[1, 5], good[a]
+    trial = np.zeros((2, 1), W.MUT_DT)
+    trial["op"][:, 0] = (b, 2)
+    trial[0, 0]["cfg"], trial[1, 0]["cfg"] = good[b], cfgs[1, 2]
+    t = ch.try_mutations(ch.upload_mutations(trial), 2).cpu().numpy().view("<u8")
+    mended = cur.copy()
+    mended[b] = good[b]
+    assert t[0, 0] == oracle.simulate_batch(ops, edges, mach, cost, mended[None])[0] and t[1, 0] == invalid
+    d = ch.delta(ch.upload_mutations(muts[2:].copy()), 2).cpu().numpy().view("<u8")
+    steps = np.repeat(cur[None], 2, 0)
+    steps[:, b] = cfgs[1, b]
+    steps[1, 1] = cfgs[1, 1]
+    assert np.array_equal(d[:, 0], oracle.simulate_batch(ops, edges, mach, cost, steps))
+    ch.close()
+    sim.close()
