@@ -180,7 +180,7 @@ static size_t try_slot_bytes(const ff_sim* s) {
     if (!s->loop) return s->slot_bytes;
     if (s->chain_choice.lds) return 256;
     const uint32_t own_rows = s->dev.ties ? s->dev.n_kept : s->max_adjacent * (uint32_t)KEPT_ROWS;
-    return slot_layout(s->dev.n_ops, s->dev.n_ops_pad, own_rows, s->chain_choice.rowl, false).bytes;
+    return slot_layout(s->dev.n_ops, s->dev.n_ops_pad, s->dev.n_edges, own_rows, s->chain_choice.rowl, false).bytes;
 }
 
 // A launch with more than 64 KB of dynamic LDS (gfx950 allows a workgroup up to 160 KB) has to be
@@ -530,11 +530,11 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         LoopChoice& k = s->loop_choice;
         k.rowl = S.max_parts <= 16 ? 16 : 64;
         const size_t rows_lds = loop_lds_bytes(S.n_rows, S.n_dev);
-        const size_t lds_all = slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, k.rowl, true).bytes + rows_lds;
+        const size_t lds_all = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, k.rowl, true).bytes + rows_lds;
         k.lds = S.n_ops <= 64 && lds_all <= 40 * 1024;
         k.queue = k.lds ? (S.n_ops <= 16 && k.rowl == 16 ? Q_OP16 : Q_OP) : Q_SLOT;
         s->loop_lds = k.lds ? lds_all : rows_lds;
-        s->loop_slot_bytes = k.lds ? 0 : slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, k.rowl, false).bytes;
+        s->loop_slot_bytes = k.lds ? 0 : slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, k.rowl, false).bytes;
         if (!allow_lds((const void*)loop_kernel(s, 0), s->loop_lds)) { release(s); return FF_EHIP; }
         per_cu = 0;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, loop_kernel(s, 0), WAVE, s->loop_lds);

@@ -114,7 +114,7 @@ __device__ __forceinline__ void queue_spill(const LoopMem& mem, LoopState& st, u
     if ((uint32_t)lane_id() == slot) { q.key = key; q.op = j; }
 }
 
-// gives op j the event `key` if it is earlier than what it has
+// gives op j the event `key` if it is earlier than what it has (it may end up on the spill list: only with n_spill > 0)
 template <int Q, int ROWL>
 __device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
     Queue& q = st.q;
@@ -511,13 +511,14 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         }
     };
     set_snap_key();
+    auto keys_min = [&](uint32_t key) __attribute__((always_inline)) { return Q == Q_OP16 ? row0_min_u32(key) : wave_min_u32(key); };
+    uint32_t kmin = keys_min(q.key);
     for (u64 ev = 0; ev < max_events; ev++) {
-        // ---- pop
-        uint32_t kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
+        // ---- pop.  kmin: smallest key of the slots
         if (kmin >= KEY_REFRESH) {
             if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
             set_snap_key();
-            kmin = Q == Q_OP16 ? row0_min_u32(q.key) : wave_min_u32(q.key);
+            kmin = keys_min(q.key);
         }
         if (Q == Q_SLOT && q.n_spill) {
             for (uint32_t guard = 0; q.n_spill && guard < S.n_ops + WAVE; guard++) {
@@ -557,12 +558,21 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         }
         const u64 K = 2 * st.E + kmin;       // the popped word
         PROF_MARK(1)
-        const OpLite lite = mem.op_lite[i];
+        // Everything that depends only on i is requested together, the static record through the vector unit as well (a
+        // scalar load of it would be sunk below the wait for the words and be waited for once more), and the smallest key
+        // of the other ops is found while that is on its way.  It and the keys that come up in this step make the next kmin.
         u64 k0 = load_word<ROWL>(words, i);
-        uint4 h = mem.hdr[i];
+        const uint4 h = mem.hdr[i];
+        const uint4* lite_at = (const uint4*)mem.op_lite + 2 * (size_t)vector_copy(i);
+        const uint4 lite0 = lite_at[0], lite1 = lite_at[1];
+        const uint32_t other_key = keys_min(lanes_of(at) ? KEY_NONE : q.key);
+        uint32_t next_kmin = other_key;
         const uint32_t exe = first_u32(h.x), offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
         OpCfg ci;
         ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
+        OpLite lite;
+        lite.out_begin = first_u32(lite0.x); lite.out_end = first_u32(lite0.y); lite.param_bytes = first_u32(lite0.z);
+        lite.first.word = first_u32(lite1.x); lite.first.in_pos = SimX::kOvr ? first_u32(lite1.y) : 0u; lite.first.row = first_u32(lite1.z);
         const uint32_t out_begin = lite.out_begin, out_end = lite.out_end;
         const uint32_t dev_p = m.template device_of<REG>(i, ci);
         PROF_MARK(1)
@@ -581,14 +591,16 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         if (RUNS && ((kmin & 1) ? REG : (out_end - out_begin == 1 && !(SimX::kExt && S.sync)))) {
             const u64 kind_m = ballot((d & 1u) == 0u);
             if (kind_m != mask_same) {
-                const uint32_t other_key = wave_min_u32(lanes_of(at) ? KEY_NONE : q.key);
                 uint32_t bound = other_key >= KEY_FAR ? KEY_NONE : other_key - kmin;
                 if (Q == Q_SLOT && q.n_spill) {
                     const u64 s = q.spill_min - K;
                     if (s < bound) bound = (uint32_t)s;
                 }
-                const uint32_t odd = part_min_u32<ROWL>((d & 1u) ? d : KEY_NONE);
-                bound = odd < bound ? odd : bound;
+                const bool is_odd = (d & 1u) && d != KEY_NONE;
+                if (ballot(is_odd)) {
+                    const uint32_t odd = part_min_u32<ROWL>(is_odd ? d : KEY_NONE);
+                    bound = odd < bound ? odd : bound;
+                }
                 const uint32_t e = (kmin & 1) ? exe : next_exe;
                 const uint32_t first_new = e >= RUN_SPAN / 2 ? RUN_SPAN : 2 * e;
                 bound = first_new < bound ? first_new : bound;
@@ -649,9 +661,22 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             }
             uint32_t now_v = (kmin + d) >> 1, dev_v = dev_p;
             if (mixed) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
+            // the records of the op's edges behind the first, a lane per edge, requested before the first edge is gone through
+            uint4 lits = make_uint4(0, 0, 0, 0);
+            auto load_lits = [&](uint32_t from) __attribute__((always_inline)) {
+                const uint32_t t = from + lane < out_end ? from + lane : out_end - 1;
+                lits = ((const uint4*)mem.edge_lite)[t];
+            };
+            if (out_end - out_begin > 1) load_lits(out_begin);
             for (uint32_t ei = out_begin; ei < out_end; ei++) {
                 EdgeLite lit = lite.first;
-                if (ei != out_begin) lit = mem.edge_lite[ei];
+                if (ei != out_begin) {
+                    const uint32_t l = (ei - out_begin) & (WAVE - 1);
+                    if (l == 0) load_lits(ei);
+                    lit.word = readlane_u32(lits.x, l);
+                    lit.in_pos = SimX::kOvr ? readlane_u32(lits.y, l) : 0u;
+                    lit.row = readlane_u32(lits.z, l);
+                }
                 const uint32_t el = lit.word;
                 const uint32_t j = el & EL_DST;
                 const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
@@ -819,7 +844,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                         uint32_t rel = (uint32_t)ready;
                         if constexpr (L64) { const u64 r = ready - st.E; rel = r >= KEY_FAR ? KEY_FAR : (uint32_t)r; }
                         const uint32_t first = part_min_of<ROWL>(rel, ready_m);
-                        queue_insert<Q, ROWL>(mem, st, j, first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1);
+                        const uint32_t key = first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1;
+                        queue_insert<Q, ROWL>(mem, st, j, key);
+                        next_kmin = key < next_kmin ? key : next_kmin;
                     }
                 }
                 PROF_MARK(7)
@@ -887,6 +914,8 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             q.key = me ? nk : q.key;
             if (Q == Q_SLOT && nk == KEY_NONE) q.op = me ? NO_OP : q.op;
         }
+        kmin = nk < next_kmin ? nk : next_kmin;
+        if (Q == Q_SLOT && q.n_spill) kmin = wave_min_u32(q.key);        // (what came up may have gone to the spill list)
         if (retry_m) return RESULT_RETRY;
         PROF_MARK(7)
     }

@@ -15,7 +15,7 @@ namespace ffsim {
 // LDS of one wavefront: (chains: the strategy,) the state if it is kept there, device and link rows (64 bits each: the form
 // with 64-bit link rows uses the same memory), tags
 __host__ __device__ inline size_t loop_chain_lds_bytes(const SimDev& S, uint32_t rowl, bool lds, bool strategy) {
-    return (strategy ? (size_t)S.n_ops_pad * 8 : 0) + (lds ? slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, rowl, true).bytes : 0) +
+    return (strategy ? (size_t)S.n_ops_pad * 8 : 0) + (lds ? slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, rowl, true).bytes : 0) +
            (size_t)S.n_rows * 8 + ((S.n_rows + 15) & ~15u);
 }
 
@@ -89,18 +89,6 @@ __device__ __forceinline__ u64 simulate_loop(SimX& m, const LoopMem& mem, Strate
     return rc;
 }
 
-// n words of 32 bits between LDS and HBM
-__device__ __forceinline__ void copy_u32(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, uint32_t n) {
-    constexpr uint32_t FEW = 8;
-    for (uint32_t b = 0; b < n; b += FEW * WAVE) {
-        uint32_t v[FEW];
-#pragma unroll
-        for (uint32_t u = 0; u < FEW; u++) { const uint32_t t = b + u * WAVE + lane_id(); v[u] = src[t < n ? t : n - 1]; }
-#pragma unroll
-        for (uint32_t u = 0; u < FEW; u++) { const uint32_t t = b + u * WAVE + lane_id(); if (t < n) dst[t] = v[u]; }
-    }
-}
-
 template <bool LDSW, int Q, int ROWL, class SimX>
 struct LoopEngine {
     SimX& m;
@@ -152,12 +140,8 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
     mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
     const bool first_launch = !muts && !search.enabled;
     if (LDSW) {
-        const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, ROWL, true);
-        mem.words = (u64*)(lds + sl.words);
-        mem.hdr = (uint4*)(lds + sl.hdr);
-        mem.rows = (uint32_t*)(lds + sl.rows);
-        mem.spill_key = nullptr;
-        mem.spill_op = nullptr;
+        const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, true);
+        carve_lds_state(mem, lds, sl, S, op_lite, edge_lite);
         carve_rows64(mem, lds + sl.bytes, S);
         if (!first_launch) copy_u32(mem.rows, cm.rows, S.n_kept * ROWL);
     } else {
@@ -193,19 +177,23 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_try(SimDev S, const DOp* __
                                                          uint32_t* __restrict__ next_item, unsigned char* __restrict__ ws, size_t slot_stride) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
-    const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, ROWL, LDSW);
+    const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, LDSW);
     unsigned char* slot = LDSW ? lds_raw : ws + (size_t)blockIdx.x * slot_stride;
     const bool tied = EXT >= 2 && S.ties;
     LoopMem mem;
     mem.op_lite = op_lite;
     mem.edge_lite = edge_lite;
     mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
-    mem.words = (u64*)(slot + sl.words);
-    mem.hdr = (uint4*)(slot + sl.hdr);
-    mem.rows = (uint32_t*)(slot + sl.rows);
+    if (LDSW) {
+        carve_lds_state(mem, lds_raw, sl, S, op_lite, edge_lite);
+    } else {
+        mem.words = (u64*)(slot + sl.words);
+        mem.hdr = (uint4*)(slot + sl.hdr);
+        mem.rows = (uint32_t*)(slot + sl.rows);
+        mem.spill_key = (u64*)(slot + sl.spill_key);
+        mem.spill_op = (uint32_t*)(slot + sl.spill_op);
+    }
     mem.priv = (LDSW || tied) ? nullptr : mem.rows;
-    mem.spill_key = LDSW ? nullptr : (u64*)(slot + sl.spill_key);
-    mem.spill_op = LDSW ? nullptr : (uint32_t*)(slot + sl.spill_op);
     carve_rows64(mem, LDSW ? lds_raw + sl.bytes : lds_raw, S);
     const WaveLds L{mem.crow, nullptr, nullptr, mem.tag};
     const uint32_t magic_v = load_magic(magic);

@@ -7,15 +7,17 @@ namespace ffsim {
 
 // ---- memory of one candidate -----------------------------------------------------------------
 //
-// In LDS (small graphs): words, kept rows, kept op records, then device and link rows and the tags.
+// In LDS (small graphs): words, op records (kept and static), edge records, kept rows, then device and link rows and the tags.
 // In HBM (a slot of the caller's workspace per resident wavefront): words, op records, spill list, kept rows; only
 // device and link rows and the tags are in LDS.
-struct SlotLayout { size_t words, hdr, spill_key, spill_op, rows, bytes; };
-__host__ __device__ inline SlotLayout slot_layout(uint32_t n_ops, uint32_t n_ops_pad, uint32_t n_kept, uint32_t rowl, bool lds) {
+struct SlotLayout { size_t words, hdr, op_lite, edge_lite, spill_key, spill_op, rows, bytes; };
+__host__ __device__ inline SlotLayout slot_layout(uint32_t n_ops, uint32_t n_ops_pad, uint32_t n_edges, uint32_t n_kept, uint32_t rowl, bool lds) {
     SlotLayout s;
     size_t b = 0;
     s.words = b; b += (size_t)n_ops * rowl * 8;
     s.hdr = b; b += (size_t)(lds ? n_ops : n_ops_pad) * 16;
+    s.op_lite = b; b += lds ? (size_t)n_ops * sizeof(OpLite) : 0;
+    s.edge_lite = b; b += lds ? (size_t)n_edges * sizeof(EdgeLite) : 0;
     s.spill_key = b; b += lds ? 0 : (size_t)n_ops_pad * 8;
     s.spill_op = b; b += lds ? 0 : (size_t)n_ops_pad * 4;
     s.rows = b; b += (size_t)n_kept * rowl * 4;
@@ -32,6 +34,33 @@ __device__ __forceinline__ void carve_rows(LoopMem& mem, unsigned char* lds, con
     mem.tag = (uint8_t*)(lds + loop_rows_bytes(S.n_rows, S.n_dev));
 }
 
+// n words of 32 bits between LDS and HBM
+__device__ __forceinline__ void copy_u32(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, uint32_t n) {
+    constexpr uint32_t FEW = 8;
+    for (uint32_t b = 0; b < n; b += FEW * WAVE) {
+        uint32_t v[FEW];
+#pragma unroll
+        for (uint32_t u = 0; u < FEW; u++) { const uint32_t t = b + u * WAVE + lane_id(); v[u] = src[t < n ? t : n - 1]; }
+#pragma unroll
+        for (uint32_t u = 0; u < FEW; u++) { const uint32_t t = b + u * WAVE + lane_id(); if (t < n) dst[t] = v[u]; }
+    }
+}
+
+// the parts of a candidate's state that live in LDS with it, and copies of the static records
+__device__ __forceinline__ void carve_lds_state(LoopMem& mem, unsigned char* lds, const SlotLayout& sl, const SimDev& S, const OpLite* op_lite,
+                                                const EdgeLite* edge_lite) {
+    mem.words = (u64*)(lds + sl.words);
+    mem.hdr = (uint4*)(lds + sl.hdr);
+    mem.rows = (uint32_t*)(lds + sl.rows);
+    mem.spill_key = nullptr;
+    mem.spill_op = nullptr;
+    copy_u32((uint32_t*)(lds + sl.op_lite), (const uint32_t*)op_lite, S.n_ops * (uint32_t)(sizeof(OpLite) / 4));
+    copy_u32((uint32_t*)(lds + sl.edge_lite), (const uint32_t*)edge_lite, S.n_edges * (uint32_t)(sizeof(EdgeLite) / 4));
+    mem.op_lite = (const OpLite*)(lds + sl.op_lite);
+    mem.edge_lite = (const EdgeLite*)(lds + sl.edge_lite);
+    wave_sync();
+}
+
 // LDSW: the candidate's whole state is in LDS.  Q: LoopQueue.  ROWL: lanes per row (16 where no op has more parts).
 template <bool STATS, bool LDSW, int Q, int ROWL, int EXT, int GPN>
 __global__ __launch_bounds__(WAVE) void k_loop_batch(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ in_edges,
@@ -42,18 +71,14 @@ __global__ __launch_bounds__(WAVE) void k_loop_batch(SimDev S, const DOp* __rest
                                                      const DEdge* __restrict__ edges, const uint16_t* __restrict__ devmaps) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
-    const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_kept, ROWL, LDSW);
+    const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, LDSW);
     LoopMem mem;
     mem.priv = nullptr;
     mem.op_lite = op_lite;
     mem.edge_lite = edge_lite;
     mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
     if (LDSW) {
-        mem.words = (u64*)(lds_raw + sl.words);
-        mem.hdr = (uint4*)(lds_raw + sl.hdr);
-        mem.rows = (uint32_t*)(lds_raw + sl.rows);
-        mem.spill_key = nullptr;
-        mem.spill_op = nullptr;
+        carve_lds_state(mem, lds_raw, sl, S, op_lite, edge_lite);
         carve_rows(mem, lds_raw + sl.bytes, S);
     } else {
         unsigned char* slot = ws + (size_t)blockIdx.x * slot_stride;
