@@ -452,6 +452,21 @@ __device__ __forceinline__ uint32_t count_lanes(uint32_t n, u64 mask) {
 }
 // a uniform value the compiler is not to recompute (or to move into a branch of its own)
 __device__ __forceinline__ uint32_t opaque(uint32_t uniform) { asm("" : "+s"(uniform)); return uniform; }
+// LDS addresses as numbers
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ uint32_t lds_addr(uint32_t* p) { return (uint32_t)(uintptr_t)(lds_u32*)p; }
+__device__ __forceinline__ lds_u32* lds_at(uint32_t addr) { return (lds_u32*)(uintptr_t)addr; }
+// *at = max(*at, v) on the lanes of both masks, which are combined at the last moment (see reg_passes), without a branch around
+// it.  Call with all 64 lanes active; at must be in range on every lane of the masks.
+__device__ __forceinline__ void row_max_of(uint32_t at, uint32_t v, u64 mask_a, u64 mask_b) {
+    asm volatile("s_and_b64 exec, %2, %3\n\tds_max_u32 %0, %1\n\ts_mov_b64 exec, -1" : : "v"(at), "v"(v), "s"(mask_a), "s"(mask_b) : "memory", "scc");
+}
+// a & ~b, not before v is there
+__device__ __forceinline__ u64 mask_without(u64 a, u64 b, uint32_t v) {
+    u64 r;
+    asm("s_andn2_b64 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b), "v"(v) : "scc");
+    return r;
+}
 // lrow[row] = max(lrow[row], v) on the lanes of a mask, without a branch around it.  Call with all 64 lanes active; row must
 // be in range on every lane of the mask.
 __device__ __forceinline__ void row_max(uint32_t* lrow, uint32_t row, uint32_t v, u64 mask) {
@@ -661,6 +676,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             }
             uint32_t now_v = (kmin + d) >> 1, dev_v = dev_p;
             if (mixed) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
+            // REG: what a pass needs of its producer part, ready to be read out of the part's lane
+            const uint32_t node_v = m.node_of(dev_v);
+            const uint32_t near_at_v = lds_addr(mem.lrow) + 4 * (dev_v * G), far_at_v = lds_addr(mem.lrow) + 4 * (S.n_nodes * G * G + node_v * S.n_nodes);
             // the records of the op's edges behind the first, a lane per edge, requested before the first edge is gone through
             uint4 lits = make_uint4(0, 0, 0, 0);
             auto load_lits = [&](uint32_t from) __attribute__((always_inline)) {
@@ -720,6 +738,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                     wrapped = (u >> 28) & 1u;
                     first_len = u >> 29;
                 }
+                const uint32_t local_c4 = 4 * local_c, node_c4 = 4 * node_c;
                 const u64 dup_m = REG ? 0 : ballot((sortw >> 23) & 1u);
                 PROF_MARK(4)
                 PROF_VMWAIT(5)
@@ -732,8 +751,69 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 // One pass per producer part.  FORM 0: the parts' boxes meet in one pair of dims; 1: in one pair of dims, the
                 // other contributes the same factor for every producer part (which does not split it); 2: in both.
                 uint32_t factor = 1;
+                // The regular form's passes avoid what a lone wavefront waits for: about 20 cycles wherever the scalar unit needs what
+                // the vector unit has just found, 25 for a taken branch.  Lane masks are used as the comparisons leave them, or
+                // combined long after; what the part brings is read from its lane ready for use, and the next part's
+                // number is known a pass ahead.
+                auto reg_passes = [&](auto form_) __attribute__((always_inline)) {
+                    constexpr int FORM = decltype(form_)::value;
+                    u64 todo = parts_m;
+                    int next = __builtin_ctzll(todo);
+                    do {
+                        const int kp = next;
+                        todo &= todo - 1;
+                        next = __builtin_ctzll(todo);
+                        uint32_t elems = pair_product(meet(clo, chi, readlane_u32(plo, kp), readlane_u32(phi, kp)));
+                        if (FORM == 2) elems *= pair_product(meet(clo2, chi2, readlane_u32(plo2, kp), readlane_u32(phi2, kp)));
+                        const uint32_t dev_a = readlane_u32(dev_v, kp), node_a = readlane_u32(node_v, kp), now_kp = readlane_u32(now_v, kp);
+                        const u64 hit_m = ballot(elems != 0), near_m = ballot(node_c == node_a), diff_m = ballot(dev_c != dev_a);
+                        const bool near = lanes_of(near_m);
+                        if (FORM == 1) elems *= factor;
+                        // Section 5.1: the link device between the two devices (in range for every lane); assumption A2: transfer time
+                        const uint32_t near_at = readlane_u32(near_at_v, kp) + local_c4, far_at = readlane_u32(far_at_v, kp) + node_c4;
+                        const uint32_t at_row = near ? near_at : far_at;
+                        const uint32_t fr = *lds_at(at_row);
+                        uint32_t lm = near ? m_near : m_far, lk = near ? k_near : k_far, ll = near ? l_near : l_far;
+                        if (SimX::kExt && S.link_table) {
+                            if (lanes_of(hit_m & diff_m & near_m)) { const uint4 e = mem.links[(dev_a - node_a * G) * G + local_c]; lm = e.x; lk = e.y; ll = e.z; }
+                        }
+                        if (SimX::kExt && S.node_table) {
+                            if (lanes_of(hit_m & ~near_m)) { const uint4 e = mem.links[G * G + node_a * S.n_nodes + node_c]; lm = e.x; lk = e.y; ll = e.z; }
+                        }
+                        const uint32_t ns = (__umulhi((elems << elem_sh) - 1u, lm) >> lk) + ll;
+                        // consumer parts on one node are consecutive lanes: a running sum along them is the FIFO order on the
+                        // link row they share (rows between GPUs of one node are private)
+                        uint32_t acc = lanes_of(mask_without(hit_m, near_m, ns)) ? ns : 0u;
+                        uint32_t y = wave_shr1_u32(acc) & c1;
+                        acc += y;
+                        if (SimX::kGpn == 4) {
+                            y = wave_shr1_u32(y) & c2; acc += y;
+                            y = wave_shr1_u32(y) & c3; acc += y;
+                        } else {
+                            for (uint32_t s = 2; s < G; s++) { y = wave_shr1_u32(y) & (uint32_t)((int32_t)(f << (12 - s)) >> 31); acc += y; }
+                        }
+                        if (__builtin_expect(wrapped, 0)) acc += readlane_u32(acc, (int)first_len) & last_run;
+                        const uint32_t end = __builtin_elementwise_add_sat(fr > now_kp ? fr : now_kp, near ? ns : acc);
+                        row_max_of(at_row, end, hit_m, diff_m);
+                        wave_sync();
+                        uint32_t came = lanes_of(diff_m) ? end : now_kp;
+                        came = lanes_of(hit_m) ? came : 0u;
+                        ready = came > ready ? came : ready;
+                        hits = count_lanes(hits, hit_m);
+                        if (STATS) {
+                            cnt.n_pairs += __popcll(hit_m);
+                            cnt.n_comm += __popcll(hit_m & diff_m);
+                            if (lanes_of(hit_m & diff_m)) cnt.sum_comm_ns += ns;     // per-lane partial sums, reduced by the caller
+                        }
+                    } while (todo);
+                };
                 auto passes = [&](auto form_) __attribute__((always_inline)) {
                     constexpr int FORM = decltype(form_)::value;
+                    if constexpr (REG) {
+                        if (FORM == 1) chi = factor ? chi : clo;         // (nothing is read)
+                        reg_passes(form_);
+                        return;
+                    }
                     u64 todo = parts_m;
                     do {
                         const int kp = __builtin_ctzll(todo);
@@ -766,23 +846,6 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                             T end;
                             if constexpr (L64) {
                                 end = fifo_commit(comm, row, ns, from, true, WaveLds{mem.lrow64, nullptr, nullptr, mem.tag});
-                            } else if (REG) {
-                                const uint32_t fr = mem.lrow[row];         // in range for every lane
-                                // consumer parts on one node are consecutive lanes: a running sum along them is the FIFO
-                                // order on the link row they share (rows between GPUs of one node are private)
-                                const uint32_t x = lanes_of(far_m) ? ns : 0u;
-                                uint32_t y = wave_shr1_u32(x) & c1;
-                                uint32_t acc = x + y;
-                                if (SimX::kGpn == 4) {
-                                    y = wave_shr1_u32(y) & c2; acc += y;
-                                    y = wave_shr1_u32(y) & c3; acc += y;
-                                } else {
-                                    for (uint32_t s = 2; s < G; s++) { y = wave_shr1_u32(y) & (uint32_t)((int32_t)(f << (12 - s)) >> 31); acc += y; }
-                                }
-                                if (wrapped) acc += readlane_u32(acc, (int)first_len) & last_run;
-                                end = __builtin_elementwise_add_sat(fr > now_kp ? fr : now_kp, near ? ns : acc);
-                                row_max(mem.lrow, row, end, comm_m);
-                                wave_sync();
                             } else {
                                 // transfers to another node queue on the link row of the node pair in consumer-part order:
                                 // a running sum along the consumer's parts taken in (node, part) order

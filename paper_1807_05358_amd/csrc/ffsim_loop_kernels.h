@@ -31,6 +31,7 @@ __host__ __device__ inline size_t loop_lds_bytes(uint32_t n_rows, uint32_t n_dev
 __device__ __forceinline__ void carve_rows(LoopMem& mem, unsigned char* lds, const SimDev& S) {
     mem.crow = (u64*)lds;
     mem.lrow = (uint32_t*)(mem.crow + S.n_dev);
+    mem.lrow64 = nullptr;
     mem.tag = (uint8_t*)(lds + loop_rows_bytes(S.n_rows, S.n_dev));
 }
 
