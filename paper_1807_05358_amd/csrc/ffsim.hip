@@ -142,8 +142,9 @@ static int ext_level(const ff_sim* s, bool devmaps = false) {
     if (s->dev.ties || s->has_contributing) return 2;
     return (s->dev.link_table || s->dev.node_table || s->dev.sync || devmaps) ? 1 : 0;
 }
-static batch_kernel_t batch_kernel(const ff_sim* s, bool cached, int ext = 0) {
-    const KernelChoice k = choice(s, cached);
+static batch_kernel_t batch_kernel(const ff_sim* s, bool cached, int ext = 0, bool wide = false) {
+    KernelChoice k = choice(s, cached);
+    k.wide = k.wide || wide;
     if (s->dev.gpus_per_node == 4) return ext == 2 ? batch_kernels<2, 4>(k) : (ext == 1 ? batch_kernels<1, 4>(k) : batch_kernels<0, 4>(k));
     return ext == 2 ? batch_kernels<2, 0>(k) : (ext == 1 ? batch_kernels<1, 0>(k) : batch_kernels<0, 0>(k));
 }
@@ -250,12 +251,13 @@ static std::vector<uint32_t> constants_image(const ff_machine_t& m, const std::v
 }
 
 // The narrow kernels count elements, bytes and a link row's running sum of transfer times in
-// 32 bits: every tensor must stay below 2^32 bytes, and gpus_per_node transfers of the largest tensor
-// (the most one producer part can queue on one row) below 2^32 ns.  Everything else runs in the
+// 32 bits: every tensor must stay below 2^32 bytes, and the transfers of the largest tensor that one producer part can queue on one
+// row below 2^32 ns: gpus_per_node of them in a regular strategy, as many as an op has parts in a general one (several parts
+// on a device; there run_loop notices and has the candidate simulated again with 64-bit rows, run_events does not).  Everything else runs in the
 // 64-bit (WIDE) kernels.
-static bool needs_wide(bool big_tensors, uint64_t max_bytes, uint32_t bw_min, uint32_t lat_max, uint32_t gpus_per_node) {
+static bool needs_wide(bool big_tensors, uint64_t max_bytes, uint32_t bw_min, uint32_t lat_max, uint32_t on_a_row) {
     const uint64_t ns_max = (max_bytes + bw_min - 1) / bw_min + lat_max;
-    return big_tensors || ns_max * gpus_per_node >= (1ull << 32);
+    return big_tensors || ns_max * on_a_row >= (1ull << 32);
 }
 
 // What the event loop on kept set-up needs to know about link times: elem_sh and per link (inside a node, between nodes, then
@@ -320,7 +322,7 @@ static std::vector<uint32_t> derive(ff_sim* s) {
             lat.push_back(given ? s->node_lat[a * N + b] : lat[1]);
         }
     const uint32_t bw_min = *std::min_element(bw.begin(), bw.end()), lat_max = *std::max_element(lat.begin(), lat.end());
-    s->wide = needs_wide(s->big_tensors, s->max_elems * m.elem_bytes, bw_min, lat_max, G);
+    s->wide = needs_wide(s->big_tensors, s->max_elems * m.elem_bytes, bw_min, lat_max, s->loop_extents ? G : std::max(G, s->max_parts));
     std::vector<LinkTime> lt;
     SimDev& S = s->dev;
     uint32_t sh = 0;
@@ -737,8 +739,9 @@ static uint32_t batch_slots(const ff_sim* s, uint32_t B) {
 
 static int launch_batch(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_t* d_devmaps, uint32_t B, uint64_t* d_out_ns,
                         hipStream_t st, int ext, bool cached, uint32_t slots, size_t slot_stride, uint32_t only_marked) {
-    if (!allow_lds((const void*)batch_kernel(s, cached, ext), cached ? s->lds_cached : s->lds)) return FF_EHIP;
-    hipLaunchKernelGGL(batch_kernel(s, cached, ext), dim3(slots), dim3(WAVE), cached ? s->lds_cached : s->lds, st, s->dev, s->d_ops,
+    const batch_kernel_t kernel = batch_kernel(s, cached, ext, only_marked != 0);
+    if (!allow_lds((const void*)kernel, cached ? s->lds_cached : s->lds)) return FF_EHIP;
+    hipLaunchKernelGGL(kernel, dim3(slots), dim3(WAVE), cached ? s->lds_cached : s->lds, st, s->dev, s->d_ops,
                        s->d_edges, s->d_in_edges, s->d_cost, s->d_magic, (const uint2*)d_strategies, B, (u64*)d_out_ns,
                        (Counters*)s->d_stats, (unsigned char*)s->ws, slot_stride, d_devmaps, only_marked);
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;

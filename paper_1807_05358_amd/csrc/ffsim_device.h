@@ -169,7 +169,7 @@ __device__ __forceinline__ uint32_t scatter_u32(uint32_t v, uint32_t dst) {
 }
 
 // Segmented inclusive running sum along the 64 lanes: lane l gets the sum of v over the lanes from the
-// last lane <= l whose `head` is set up to l (lane 0 counts as a head).  Six DPP steps on the pair
+// last lane <= l whose `head` is set up to l (lane 0 counts as a head); sums that do not fit stick at 2^32 - 1.  Six DPP steps on the pair
 // (head seen so far, sum): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the last lane of
 // rows 0 / 2 into rows 1 / 3 and lane 31 into rows 2 and 3.  Lanes that a step gives no source keep
 // their value (old = 0 is the identity of both components).  All 64 lanes active.
@@ -177,7 +177,7 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ void seg_step(uint32_t& f, uint32_t& v) {
     const uint32_t tv = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
     const uint32_t tf = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)f, CTRL, ROW_MASK, 0xf, false);
-    v += f ? 0u : tv;
+    v = __builtin_elementwise_add_sat(v, f ? 0u : tv);
     f |= tf;
 }
 __device__ __forceinline__ uint32_t seg_running_sum(uint32_t v, bool head) {

@@ -201,3 +201,24 @@ def test_chain_that_starts_from_an_invalid_strategy(B, n_ops, parts):
     assert np.array_equal(d[:, 0], oracle.simulate_batch(ops, edges, mach, cost, steps))
     ch.close()
     sim.close()
+
+
+@pytest.mark.parametrize("shape", [(16384, 16384), (131072, 2048)])
+def test_general_strategies_queue_for_longer_than_32_bits_on_one_link(B, shape):
+    """64 parts on one device read a tensor of 1 GiB whole, one after the other over one link: fewer than 2^32 ns for as many
+    of them as a node has GPUs, more for all; extents within and beyond 16 bits"""
+    g = W.GraphBuilder()
+    a = g.op(W.T_ELEM, shape, (0, 1), 1)
+    for _ in range(6):
+        b = g.op(W.T_ELEM, (64, 64), (0, 1), 1)
+        g.edge(a, b, [W.ALL, W.ALL])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(16, 4, 6, 5)
+    cost = np.full((len(ops), 64), 1000, "<u4")
+    rng = np.random.default_rng(8)
+    cfgs = draw(rng, ops, 6, 64, 64, (1, 2, 4, 8), strides=True)
+    cfgs["deg"][:, 0] = (1, 1, 1, 1)
+    cfgs["deg"][:4, 1:] = (8, 8, 1, 1)
+    cfgs["dev_stride"][:2] = 0
+    want = check(B, ops, edges, mach, cost, cfgs, chain_steps=3)
+    assert want.max() > 10 * 2 ** 30
