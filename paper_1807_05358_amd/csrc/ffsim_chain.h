@@ -339,7 +339,7 @@ struct EventsEngine {
     uint32_t n_snaps;
     static constexpr int kRowl = WAVE;
     __device__ __forceinline__ StrategyClass validate() const { return validate_strategy(m); }
-    // op mo has the configuration now in m.cfgs (`kept`: simulate is not called before the next change)
+    // op mo now has the configuration in m.cfgs: a change about to be simulated, or one taken back
     __device__ __forceinline__ void op_changed(uint32_t) {}
     __device__ __forceinline__ void op_reverted(uint32_t mo) const { if (CACHE) refresh_ecache_for_group(m, mo); }
     // one simulation, from time 0 (k = 0) or from snapshot k with op mo changed from configuration ocfg

@@ -21,7 +21,7 @@
 //
 // Files: ffsim_device.h (word encoding, wavefront primitives), ffsim_strategy.h (configurations,
 // geometry, kept per-edge set-up, validity), ffsim_events.h (FIFO, recording, initial state, event
-// loop), this file (the batch kernel), ffsim_kept.h, ffsim_loop.h, ffsim_loop_kernels.h (the form on kept set-up), ffsim_chain.h (delta simulation, search), ffsim_sweep.h
+// loop), this file (the batch kernel), ffsim_kept.h, ffsim_loop.h, ffsim_loop_kernels.h (the form on kept set-up), ffsim_chain.h, ffsim_loop_chain.h (delta simulation, search), ffsim_sweep.h
 // (neighbour list and reduction), ffsim_select.h + ffsim_k_*.hip (the instantiations, compiled
 // side by side), ffsim.hip (host side of the C boundary).
 #pragma once
