@@ -132,7 +132,7 @@ __device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, 
                 const u64 hit = ballot(t < q.n_spill && mem.spill_op[t < q.n_spill ? t : 0] == j);
                 if (hit) {
                     const uint32_t at_t = b + __builtin_ctzll(hit);
-                    const u64 word = key >= KEY_FAR ? W_NONE : 2 * st.E + key;
+                    const u64 word = key >= KEY_FAR ? op_min_word<ROWL>(mem.words, j) : 2 * st.E + key;
                     if (lane_id() == 0 && word < mem.spill_key[at_t]) mem.spill_key[at_t] = word;
                     wave_sync();
                     spill_scan(mem, q);
@@ -184,7 +184,8 @@ __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st)
 }
 
 // Moves the epoch to the next pending event.  Returns false if there is none.
-// (What a link row holds below the epoch no longer matters: nothing becomes ready before it.)
+// (What a link row holds below the epoch no longer matters: nothing becomes ready before it.  So the epoch never moves back; an event
+// before it would be one that the queue has lost, keeps the key KEY_FAR and ends the run as an internal error where it is popped.)
 template <int Q, int ROWL, bool L64>
 __device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st, uint32_t n_links) {
     Queue& q = st.q;
@@ -200,7 +201,7 @@ __device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st,
     u64 next = wave_min_u64(word);
     if (Q == Q_SLOT) next = q.spill_min < next ? q.spill_min : next;
     if (next >> 63) return false;
-    const u64 E = next >> 1;
+    const u64 E = (next >> 1) > st.E ? next >> 1 : st.E;
     const u64 delta = E - st.E;
     st.E = E;
     q.key = word >> 63 ? KEY_NONE : rel_key(word, E);
@@ -530,7 +531,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     uint32_t kmin = keys_min(q.key);
     for (u64 ev = 0; ev < max_events; ev++) {
         // ---- pop.  kmin: smallest key of the slots
-        if (kmin >= KEY_REFRESH) {
+        if (__builtin_expect(kmin >= KEY_REFRESH, 0)) {
             if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
             set_snap_key();
             kmin = keys_min(q.key);

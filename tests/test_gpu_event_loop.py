@@ -222,3 +222,63 @@ def test_general_strategies_queue_for_longer_than_32_bits_on_one_link(B, shape):
     cfgs["dev_stride"][:2] = 0
     want = check(B, ops, edges, mach, cost, cfgs, chain_steps=3)
     assert want.max() > 10 * 2 ** 30
+
+
+def far_fan_out(n_consumers):
+    """One tensor of 1 GB in two parts of unequal size, read by consumers in two parts each over the two links between four
+    nodes of one GPU: the larger part is sent first and arrives up to 4 s later, the smaller one is sent 10 us later and
+    arrives earlier, so that an op with an event gets an earlier one, both too far ahead for a 32-bit key.  Behind the
+    last consumer a task of 3 s, beside all of it a chain of tasks that keeps simulated time moving in between."""
+    g = W.GraphBuilder()
+    cost, cfg = [], []
+
+    def op(extent, deg, dev, ns):
+        o = g.op(W.T_ELEM, extent, tuple(range(len(extent))), 1)
+        cost.append(ns)
+        cfg.append((tuple(deg) + (1,) * (4 - len(deg)), dev))
+        return o
+    same = [W.ident(0), W.ident(1), W.ident(2)]
+    op((1,), (1,), 0, 10000)
+    big = op((5, 5000, 10000), (2,), 0, 1000)
+    readers = [op((5, 5000, 10000), (2,), 2, 1000) for _ in range(n_consumers)]
+    for r in readers:
+        g.edge(big, r, same)
+    g.edge(readers[-1], op((1, 1, 10000), (1,), 0, 3 * 10 ** 9), same)
+    last = None
+    for _ in range(60):
+        o = op((1,), (1,), 2, 90 * 10 ** 6)
+        if last is not None:
+            g.edge(last, o, [W.ident(0)])
+        last = o
+    ops, edges, _ = g.finish()
+    cfgs = np.zeros((1, len(ops)), W.CFG_DT)
+    cfgs["deg"][0], cfgs["dev_offset"][0] = [c[0] for c in cfg], [c[1] for c in cfg]
+    cfgs["dev_stride"] = 1
+    return ops, edges, W.Machine(4, 1, 12, 12), np.repeat(np.array(cost, "<u4")[:, None], 4, 1), cfgs
+
+
+@pytest.mark.parametrize("strides", [1, 5])
+@pytest.mark.parametrize("n_consumers", [60, 66, 72, 84])
+def test_earlier_far_event_of_an_op_without_a_slot(B, n_consumers, strides):
+    """as a batch, as a chain and as trials; strides 5 = 1 modulo the number of devices, the same strategy in the general form"""
+    ops, edges, mach, cost, cfgs = far_fan_out(n_consumers)
+    cfgs["dev_stride"] = strides
+    # the second strategy has the 3 s task elsewhere: what a chain's steps and the trials change
+    cfgs = np.repeat(cfgs, 3, 0)
+    cfgs["dev_offset"][1, n_consumers + 2] = 1
+    cfgs["dev_offset"][1, 7], cfgs["dev_offset"][2, 0] = 1, 1
+    check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=8)
+    # the op ahead of the smaller part goes and comes back: every simulation starts from time 0 or from a snapshot before it matters
+    muts = np.zeros((4, 1), W.MUT_DT)
+    muts["op"][:, 0] = (0, n_consumers + 2, 0, n_consumers + 2)
+    muts["cfg"][:, 0] = cfgs[(2, 1, 0, 0), muts["op"][:, 0]]
+    sim = B.Simulator(ops, edges, mach, cost)
+    ch = B.Chains(sim, cfgs[:1])
+    t = ch.try_mutations(ch.upload_mutations(muts), 4).cpu().numpy().view("<u8")
+    cand = np.repeat(cfgs[:1], 4, 0)
+    cand[np.arange(4), muts["op"][:, 0]] = muts["cfg"][:, 0]
+    assert np.array_equal(t[:, 0], oracle.simulate_batch(ops, edges, mach, cost, cand))
+    d = ch.delta(ch.upload_mutations(muts), 4).cpu().numpy().view("<u8")
+    assert np.array_equal(d[:, 0], oracle.simulate_delta_chain(ops, edges, mach, cost, cfgs[0], muts[:, 0]))
+    ch.close()
+    sim.close()
