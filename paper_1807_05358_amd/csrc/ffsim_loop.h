@@ -948,7 +948,11 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                             const uint4 e = m.node_links[node_p * S.n_nodes + node_o];
                             bw = e.x; m_bw = e.y; lat = e.z;
                         }
-                        const uint32_t ns = ceil_div_u32(shard_bytes, bw, m_bw) + lat;
+                        // (parameters may be larger than any tensor: the time of one transfer may take more than 32 bits)
+                        const uint32_t send = ceil_div_u32(shard_bytes, bw, m_bw);
+                        T ns;
+                        if constexpr (L64) ns = (u64)send + lat;
+                        else ns = __builtin_elementwise_add_sat(send, lat);
                         const u64 act_m = ballot(act);
                         if constexpr (L64) {
                             const u64 end = fifo_commit(act, act ? row_i : 0u, ns, st.E + now, true, WaveLds{mem.lrow64, nullptr, nullptr, mem.tag});

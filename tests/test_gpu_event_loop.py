@@ -28,9 +28,10 @@ def draw(rng, ops, n, D, parts, choices, strides=False):
     return cfgs
 
 
-def check(B, ops, edges, mach, cost, cfgs, kernel=None, chain_steps=0):
-    want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8)
-    sim = B.Simulator(ops, edges, mach, cost)
+def check(B, ops, edges, mach, cost, cfgs, kernel=None, chain_steps=0, **refined):
+    """refined: params and ties, as the simulator and the oracle take them"""
+    want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8, **refined)
+    sim = B.Simulator(ops, edges, mach, cost, **refined)
     if kernel is not None:
         assert B.ff_sim_batch_kernel_name(sim.handle, len(cfgs)).startswith(kernel), B.ff_sim_batch_kernel_name(sim.handle, len(cfgs))
     got = sim.simulate(cfgs)
@@ -44,7 +45,7 @@ def check(B, ops, edges, mach, cost, cfgs, kernel=None, chain_steps=0):
         muts["cfg"][:, 0] = cfgs[1, muts["op"][:, 0]]
         ch = B.Chains(sim, cfgs[:1])
         d = ch.delta(ch.upload_mutations(muts), chain_steps).cpu().numpy().view("<u8")
-        ref = oracle.simulate_delta_chain(ops, edges, mach, cost, cfgs[0], muts[:, 0])
+        ref = oracle.simulate_delta_chain(ops, edges, mach, cost, cfgs[0], muts[:, 0], **refined)
         assert np.array_equal(d[:, 0], ref)
         t = ch.try_mutations(ch.upload_mutations(muts[::-1].copy()), chain_steps).cpu().numpy().view("<u8")
         cur = cfgs[0].copy()
@@ -53,7 +54,7 @@ def check(B, ops, edges, mach, cost, cfgs, kernel=None, chain_steps=0):
         cand = np.repeat(cur[None], chain_steps, 0)
         for s in range(chain_steps):
             cand[s, int(muts[chain_steps - 1 - s, 0]["op"])] = muts[chain_steps - 1 - s, 0]["cfg"]
-        assert np.array_equal(t[:, 0], oracle.simulate_batch(ops, edges, mach, cost, cand, n_threads=8))
+        assert np.array_equal(t[:, 0], oracle.simulate_batch(ops, edges, mach, cost, cand, n_threads=8, **refined))
         ch.close()
     sim.close()
     return want
@@ -282,3 +283,26 @@ def test_earlier_far_event_of_an_op_without_a_slot(B, n_consumers, strides):
     assert np.array_equal(d[:, 0], oracle.simulate_delta_chain(ops, edges, mach, cost, cfgs[0], muts[:, 0]))
     ch.close()
     sim.close()
+
+
+@pytest.mark.parametrize("n_ops", [12, 80])
+@pytest.mark.parametrize("mach", [W.Machine(2, 2, 1, 1, 700, 900), W.Machine(4, 1, 1, 1, 0, 3 * 10 ** 9), W.Machine(1, 4, 1, 1, 10 ** 9, 0),
+                                  W.Machine(2, 2, 9, 9, 0, 0, 4, np.array([[1, 1], [2, 1]], "<u4"), np.array([[0, 5], [800, 0]], "<u4"),
+                                            np.array([[1, 1], [1, 1]], "<u4"), np.array([[0, 7], [2 ** 30, 0]], "<u4"))])
+def test_parameter_transfers_longer_than_32_bits_of_time(B, n_ops, mach):
+    """parameters of up to 2^32 - 1 bytes over links of 1 byte per ns, and latencies of seconds: the time of one transfer, not
+    only when it ends, takes more than 32 bits"""
+    rng = np.random.default_rng(n_ops)
+    g = W.GraphBuilder()
+    for i in range(n_ops):
+        o = g.op(W.T_ELEM, (8, 6), (0, 1), 1)
+        for s in sorted(set(int(x) for x in rng.integers(max(0, o - 4), o, size=2))) if o else ():
+            g.edge(s, o, [W.ident(0), W.ident(1)])
+    ops, edges, _ = g.finish()
+    cost = rng.integers(1, 9000, size=(n_ops, 16)).astype("<u4")
+    params = (rng.choice([0, 0, 1000, 3 * 10 ** 9, 2 ** 32 - 2, 2 ** 32 - 1], size=n_ops).astype("<u4"), rng.integers(0, 4, size=n_ops).astype(np.uint8))
+    params[0][1], params[1][1] = 2 ** 32 - 1, 0
+    cfgs = draw(rng, ops, 16, mach.n_devices, 16, (1, 2, 4), strides=True)
+    cfgs["deg"][:4, 1] = (2, 1, 1, 1)
+    want = check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=6, params=params)
+    assert want.max() > 2 ** 32
