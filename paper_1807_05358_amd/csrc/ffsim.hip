@@ -757,7 +757,10 @@ static int batch_impl(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_
     if (s->loop) {
         const uint32_t slots = std::min(B, s->max_slots_loop);
         const size_t need = s->loop_choice.lds ? 0 : (size_t)slots * s->loop_slot_bytes;
-        if (need && (!s->ws || s->ws_bytes < need)) return FF_EWORKSPACE;
+        // wavefronts of the launch behind it, which may need memory where this one needs none
+        uint32_t again = std::min(B, s->max_slots);
+        if (s->loop_retry && !s->lds_words) again = (uint32_t)std::min<size_t>(again, (s->ws ? s->ws_bytes : 0) / s->slot_bytes);
+        if ((need && (!s->ws || s->ws_bytes < need)) || again < 1) return FF_EWORKSPACE;      // nothing launched, no result touched
         if (!allow_lds((const void*)loop_kernel(s, ext), s->loop_lds)) return FF_EHIP;
         hipLaunchKernelGGL(loop_kernel(s, ext), dim3(slots), dim3(WAVE), s->loop_lds, st, s->dev, s->d_ops, s->d_in_edges, s->d_op_lite,
                            s->d_edge_lite, s->d_cost, s->d_magic, (const uint2*)d_strategies, B, (u64*)d_out_ns, (Counters*)s->d_stats,
@@ -765,9 +768,6 @@ static int batch_impl(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint16_
         if (hipGetLastError() != hipSuccess) return FF_EHIP;
         if (!s->loop_retry) return FF_OK;
         // candidates that book a link more than four seconds ahead (hardly ever one) are left to the kernel with 64-bit rows
-        uint32_t again = std::min(B, s->max_slots);
-        if (!s->lds_words) again = (uint32_t)std::min<size_t>(again, s->ws_bytes / s->slot_bytes);
-        if (again < 1) return FF_EWORKSPACE;
         return launch_batch(s, d_strategies, d_devmaps, B, d_out_ns, st, ext, false, again, s->slot_bytes, 1);
     }
     const bool cached = batch_cached(s, B);

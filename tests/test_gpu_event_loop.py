@@ -3,6 +3,7 @@ to 64 and more ops, more ops with events than the queue has slots, events and li
 times, and the constants of the link-time division.  Everything against the oracle, bit for bit."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_1807_05358_amd import workloads as W
@@ -306,3 +307,34 @@ def test_parameter_transfers_longer_than_32_bits_of_time(B, n_ops, mach):
     cfgs["deg"][:4, 1] = (2, 1, 1, 1)
     want = check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=6, params=params)
     assert want.max() > 2 ** 32
+
+
+def test_refused_workspace_leaves_the_results_alone(B):
+    """rows of 16 lanes fit LDS and need no workspace, the 64-bit kernel behind them (transfers of seconds) does: without one
+    the call is refused and nothing has been launched"""
+    rng = np.random.default_rng(5)
+    g = W.GraphBuilder()
+    for i in range(64):
+        o = g.op(W.T_ELEM, (16384, 16384) if i == 0 else (64, 64), (0, 1), 1)
+        if 0 < o < 31:
+            g.edge(0 if o < 4 else o - 3, o, [W.ALL, W.ALL])
+    ops, edges, _ = g.finish()
+    mach = W.Machine(8, 9, 6, 5)
+    cost = rng.integers(1, 9000, size=(len(ops), 16)).astype("<u4")
+    cfgs = draw(rng, ops, 8, 72, 16, (1, 2, 4, 8, 16))
+    cfgs["deg"][:, 0] = 1
+    cfgs["deg"][:4, 1:4] = (4, 4, 1, 1)
+    sim = B.Simulator(ops, edges, mach, cost)
+    assert B.ff_sim_batch_kernel_name(sim.handle, len(cfgs)).startswith("k_loop_batch<false, true")
+    need = B.ff_sim_workspace_bytes(sim.handle, len(cfgs))
+    assert need > 0
+    d = sim.upload_strategies(cfgs)
+    out = torch.full((len(cfgs),), 12345, dtype=torch.int64, device="cuda")
+    B.ff_sim_set_stats(sim.handle, None)
+    with pytest.raises(B.FFSimError):
+        B.ff_sim_batch(sim.handle, d.data_ptr(), len(cfgs), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert (out == 12345).all()
+    want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8)
+    assert want.max() > 2 ** 32 and np.array_equal(sim.simulate(cfgs), want)
+    sim.close()
