@@ -263,16 +263,23 @@ static bool needs_wide(bool big_tensors, uint64_t max_bytes, uint32_t bw_min, ui
 // What the event loop on kept set-up needs to know about link times: elem_sh and per link (inside a node, between nodes, then
 // every pair of the tables in force) m, k, lat1 with
 //     (umulhi((elems << elem_sh) - 1, m) >> k) + lat1 == ceil(elems * elem_bytes / bandwidth) + latency
-// for 1 <= elems <= max_elems.  With g a common divisor of elem_bytes and all bandwidths, q = bandwidth / g and x =
-// elems * elem_bytes / g - 1, the right side is floor(x / q) + 1 + latency; floor(x / q) = umulhi(x, m) >> k for
-// m = floor(2^(32+k) / q) + 1 as long as x * (m * q - 2^(32+k)) < 2^(32+k).  False: no such constants.
-static bool link_time(uint64_t q, uint64_t x_max, uint32_t lat, LinkTime* out) {
+// for 1 <= elems <= max_elems.  With g a common divisor of elem_bytes and all bandwidths, mul = elem_bytes / g and q =
+// bandwidth / g, the right side is floor((elems * mul - 1) / q) + 1 + latency.  Let x = (elems << elem_sh) - 1, Q = q << elem_sh, P =
+// 2^(32+k), and 1 << elem_sh >= mul.  Then x * mul / Q = (elems * mul - mul / (1 << elem_sh)) / q lies at least (1 - mul / (1 << elem_sh)) / q
+// above that floor and at least mul / Q below the next whole number, so m may be P * mul / Q rounded up by r / Q as long as x * r < mul * P, or
+// rounded down by r / Q as long as x * r <= ((1 << elem_sh) - mul) * P.  Both fail for the largest P whose m fits 32 bits only if max_elems * mul >
+// 2^31: the constants exist for every element size and all bandwidths below 2^30 B/ns if no tensor is larger than 2 GiB, and for most if one
+// has up to 4 GiB.
+static bool link_time(uint64_t mul, uint64_t q, uint64_t max_elems, uint32_t sh, uint32_t lat, LinkTime* out) {
+    typedef unsigned __int128 u128;
     if (lat == 0xffffffffu) return false;
+    const u128 Q = (u128)q << sh, x_max = ((u128)max_elems << sh) - 1;
     for (uint32_t k = 0; k < 32; k++) {
-        const uint64_t P = 1ull << (32 + k), mm = P / q + 1;
-        if (mm >> 32) return false;
-        const uint64_t e = mm * q - P;                      // 1..q
-        if ((unsigned __int128)x_max * e < P) { *out = LinkTime{(uint32_t)mm, k, lat + 1}; return true; }
+        const u128 P = (u128)1 << (32 + k), down = P * mul / Q, up = down + 1;
+        if (down >> 32) return false;
+        const bool down_ok = down && x_max * (P * mul - down * Q) <= (((u128)1 << sh) - mul) * P;
+        const bool up_ok = !(up >> 32) && x_max * (up * Q - P * mul) < P * mul;
+        if (down_ok || up_ok) { *out = LinkTime{(uint32_t)(down_ok ? down : up), k, lat + 1}; return true; }
     }
     return false;
 }
@@ -280,17 +287,15 @@ static bool link_times(const ff_machine_t& m, uint64_t max_elems, const std::vec
                        uint32_t* elem_sh, std::vector<LinkTime>* out) {
     uint64_t g = m.elem_bytes;
     for (uint32_t b : bw) g = std::__gcd<uint64_t>(g, b);
-    uint64_t mul = m.elem_bytes / g, scale = 1;
-    if (mul & (mul - 1)) return false;
-    for (uint32_t b : bw) if (b / g < 2) scale = 2;         // (m of q = 1 would not fit 32 bits)
-    mul *= scale;
-    const unsigned __int128 x_max = (unsigned __int128)max_elems * mul - 1;
-    if (x_max >> 32) return false;
-    *elem_sh = (uint32_t)__builtin_ctzll(mul);
+    const uint64_t mul = m.elem_bytes / g;
     out->resize(bw.size());
-    for (size_t p = 0; p < bw.size(); p++)
-        if (!link_time(bw[p] / g * scale, (uint64_t)x_max, lat[p], &(*out)[p])) return false;
-    return true;
+    for (uint32_t sh = 0; sh < 32 && ((max_elems << sh) - 1) >> 32 == 0; sh++) {
+        if (1ull << sh < mul) continue;
+        size_t p = 0;
+        while (p < bw.size() && link_time(mul, bw[p] / g, max_elems, sh, lat[p], &(*out)[p])) p++;
+        if (p == bw.size()) { *elem_sh = sh; return true; }
+    }
+    return false;
 }
 
 static uint64_t sat_add(uint64_t a, uint64_t b) { return a + b < a ? ~0ull : a + b; }
@@ -327,7 +332,7 @@ static std::vector<uint32_t> derive(ff_sim* s) {
     SimDev& S = s->dev;
     uint32_t sh = 0;
     s->loop = !s->wide && s->loop_extents && link_times(m, s->max_elems, bw, lat, &sh, &lt);
-    if (s->loop_extents && !s->loop) s->wide = true;       // (no such constants: odd element sizes, extreme bandwidths)
+    if (s->loop_extents && !s->loop) s->wide = true;       // (no such constants: tensors of 2 to 4 GiB with some bandwidths)
     if (s->loop) { S.near_link = lt[0]; S.far_link = lt[1]; S.elem_sh = sh; lt.erase(lt.begin(), lt.begin() + 2); }
     // No simulated time can pass the sum of all tasks and transfers: every consumer part reads at most the whole tensor of
     // every edge, in at most parts^2 transfers, and (parameters in step) sends at most the op's parameters once.

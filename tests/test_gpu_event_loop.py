@@ -338,3 +338,24 @@ def test_refused_workspace_leaves_the_results_alone(B):
     want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8)
     assert want.max() > 2 ** 32 and np.array_equal(sim.simulate(cfgs), want)
     sim.close()
+
+
+@pytest.mark.parametrize("gib", [0.01, 1.99, 3.99])
+@pytest.mark.parametrize("elem_bytes", [1, 2, 3, 4, 5, 6, 12, 20])
+def test_link_time_constants_for_any_element_size(B, elem_bytes, gib):
+    """element sizes with and without common divisors with the bandwidths, largest tensors well below 2 GiB, at 2 GiB and at 4 GiB:
+    up to 2 GiB the event loop on kept set-up serves all of them (at less than 2^30 bytes per ns)"""
+    rng = np.random.default_rng(elem_bytes)
+    rows = int(gib * 2 ** 30 / elem_bytes / 16384)
+    g = W.GraphBuilder()
+    a = g.op(W.T_ELEM, (rows // 64 + 1, 64, 16384), (0, 1, 2), 1)
+    for k in range(3):
+        b = g.op(W.T_ELEM, (rows // 64 + 1, 64, 16384 - 1000 * k), (0, 1, 2), 1)
+        g.edge(a, b, [W.ident(0), W.ident(1), W.ident(2)])
+        c = g.op(W.T_ELEM, (61, 7), (0, 1), 1)
+        g.edge(b, c, [(0, 1, k, 5 * k), (1, 2, 0, k), (1, 1 + 100 * k, 0, 17 * k)])
+    ops, edges, _ = g.finish()
+    cost = rng.integers(1, 100, size=(len(ops), 64)).astype("<u4")
+    for near, far in [(20, 14), (25, 7), (101, 97), (127, 255), (12345, 65537), (2 ** 31 - 1, 2 ** 32 - 1), (1000003, 64)]:
+        mach = W.Machine(4, 4, near, far, 1, 2, elem_bytes)
+        check(B, ops, edges, mach, cost, draw(rng, ops, 16, 16, 64, (1, 2, 3, 5, 7, 16, 61)), kernel="k_loop_batch" if gib < 2 and far < 2 ** 30 else None)
