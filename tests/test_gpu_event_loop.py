@@ -359,3 +359,42 @@ def test_link_time_constants_for_any_element_size(B, elem_bytes, gib):
     for near, far in [(20, 14), (25, 7), (101, 97), (127, 255), (12345, 65537), (2 ** 31 - 1, 2 ** 32 - 1), (1000003, 64)]:
         mach = W.Machine(4, 4, near, far, 1, 2, elem_bytes)
         check(B, ops, edges, mach, cost, draw(rng, ops, 16, 16, 64, (1, 2, 3, 5, 7, 16, 61)), kernel="k_loop_batch" if gib < 2 and far < 2 ** 30 else None)
+
+
+@pytest.mark.parametrize("refinement", ["params", "links", "node_links", "ties", "devmaps"])
+@pytest.mark.parametrize("n_ops", [10, 70])
+def test_bookings_beyond_32_bits_with_refined_inputs(B, n_ops, refinement):
+    """what is simulated again with 64-bit link rows: parameter traffic, links that differ per pair, tied configurations with
+    contributing edges, explicit devices; batches, and chains and trials where they take such inputs"""
+    rng = np.random.default_rng(n_ops)
+    g = W.GraphBuilder()
+    a = g.op(W.T_ELEM, (16384, 16384), (0, 1), 1)
+    for _ in range(n_ops - 1):
+        b = g.op(W.T_ELEM, (64, 64), (0, 1), 1)
+        if b <= 6:
+            g.edge(a, b, [W.ALL, W.ALL])
+        elif rng.random() < 0.5:
+            g.edge(b - 6, b, [W.ident(0), W.ident(1)])
+    ops, edges, flops = g.finish()
+    mach, refined = W.Machine(4, 4, 6, 5), {}
+    if refinement == "links":
+        mach = W.Machine(4, 4, 6, 5, 0, 0, 4, *W.paired_links(4, 9, 4, 0, 300))
+    elif refinement == "node_links":
+        mach = W.Machine(4, 4, 6, 5, 0, 0, 4, None, None, *W.ring_node_links(4, 7, 4, 1000))
+    elif refinement == "params":
+        refined["params"] = (rng.choice([0, 5000, 10 ** 9, 2 ** 32 - 1], size=len(ops)).astype("<u4"), rng.integers(0, 4, size=len(ops)).astype(np.uint8))
+    elif refinement == "ties":
+        ops, edges, flops, refined["ties"], _ = W.training_graph(ops, edges, flops)
+        refined["params"] = (rng.choice([0, 5000, 10 ** 9], size=len(ops)).astype("<u4"), np.ones(len(ops), np.uint8))
+    cost = rng.integers(1, 9000, size=(len(ops), 16)).astype("<u4")
+    cfgs = draw(rng, ops, 12, 16, 16, (1, 2, 4, 8, 16), strides=True)
+    cfgs["deg"][:, 0] = 1
+    cfgs["deg"][:9, 1:7] = (4, 4, 1, 1)
+    want = check(B, ops, edges, mach, cost, cfgs, kernel="k_loop_batch", chain_steps=6, **refined)
+    if refinement == "devmaps":
+        maps = W.device_maps(cfgs, 16, 3)
+        want = oracle.simulate_batch(ops, edges, mach, cost, cfgs, n_threads=8, devmaps=maps)
+        sim = B.Simulator(ops, edges, mach, cost)
+        assert np.array_equal(sim.simulate(cfgs, devmaps=maps), want)
+        sim.close()
+    assert want.max() > 2 ** 32
