@@ -26,7 +26,7 @@ HEADLINE = 4
 VALU_PEAK_G_PER_S = 256 * 4 * 2.4e9 / 4 / 1e9
 # rocprofv3 counter readings per launch (HBM traffic from FETCH_SIZE / WRITE_SIZE, instruction
 # counts from SQ_INSTS_*), one line per workload with the kernel instantiation they were read for
-COUNTER_FILE = os.path.join(ROOT, "profiles", "k_sim_batch_pmc_counters.txt")
+COUNTER_FILE = os.path.join(ROOT, "profiles", "k_loop_batch_pmc_counters.txt")
 
 
 def profiled_counters():

@@ -165,12 +165,12 @@ __device__ __forceinline__ u64 load_word(const u64* words, uint32_t op) {
     return w;
 }
 
-// wavefront-wide copy of n 64-bit words between 16-byte aligned HBM buffers, n a multiple of
-// 64: 16 bytes per lane and eight loads in flight before the first store
+// wavefront-wide copy of n 64-bit words between 16-byte aligned buffers, n even (a state has 16 or 64 words per op):
+// 16 bytes per lane and eight loads in flight before the first store
 __device__ __forceinline__ void copy_words(u64* __restrict__ dst, const u64* __restrict__ src, uint32_t n) {
     const uint4* __restrict__ s4 = (const uint4*)src;
     uint4* __restrict__ d4 = (uint4*)dst;
-    const uint32_t n4 = n / 2;          // multiple of 32
+    const uint32_t n4 = n / 2;
     uint32_t t = lane_id();
     for (; t + 7 * WAVE < n4; t += 8 * WAVE) {
         uint4 v[8];

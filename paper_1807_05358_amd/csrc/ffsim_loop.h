@@ -485,12 +485,12 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
 // Returns 0, RUN_CONVERGED, RESULT_RETRY or a RESULT_* code.
 //
 // What bounds it: one wavefront is one chain of instructions.  With one wavefront per SIMD the chain is the time; with four
-// the vector unit is busy 85 % of it.  Both ask for fewer instructions per event (boxes of parts as pairs of 16-bit values, times in
-// 32 bits, the queue in a register: a pass over the consumer parts took 95 instructions in run_events, it takes about 50
+// the vector unit is busy 91 to 99 % of it.  Both ask for fewer instructions per event (boxes of parts as pairs of 16-bit values, times in
+// 32 bits, the queue in a register: a pass over the consumer parts took 95 instructions in run_events, it takes 51 to 58
 // here), the former also for fewer crossings from the vector to the scalar unit and fewer taken branches: on a lone wavefront any
 // instruction takes 4.6 to 6.4 cycles, dependent or not, but a scalar instruction that reads a mask or a lane's value
 // just found waits 20, a taken branch 25.  Per launch, against run_events: 4096 x Inception-v3-shaped 9.28 -> 7.01 ms, 4096 x
-// ResNet-101-shaped 20.2 -> 13.9, 1024 x NMT-shaped 98.6 -> 69.4, 1024 x AlexNet-shaped 0.227 -> 0.183; general
+// ResNet-101-shaped 20.2 -> 13.9, 1024 x NMT-shaped 98.6 -> 67.9, 1024 x AlexNet-shaped 0.227 -> 0.183; general
 // strategies (777 x ResNet-101-shaped on 5 x 3 devices) 30.9 -> 22.1; training iterations (1024 x Inception-v3-shaped)
 // 24.3 -> 16.4.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
