@@ -81,6 +81,7 @@ struct ff_sim {
     size_t lds_chain = 0;         // dynamic LDS per wavefront, chain kernel (adds the strategy; words in HBM)
     uint32_t max_slots = 0;       // wavefronts the device can hold at once (batch kernel)
     uint32_t max_try_slots = 0;   // same for the trial-mutation kernel
+    uint32_t n_simds = 0;         // of the device
     void* ws = nullptr;
     size_t ws_bytes = 0;
     ff_stats_t* d_stats = nullptr;
@@ -94,7 +95,7 @@ struct ff_chains {
     size_t meta_at = 0;            // offset of the ChainMeta record in a chain's block
     unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots
     uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation
-    uint32_t* d_counter = nullptr; // work counter of the trial-mutation kernel
+    uint32_t* d_counter = nullptr; // [TRIAL_WORDS] work counter of the trial-mutation kernel, and what k_trial_class counts
     uint32_t links_gen = 0;        // sim->links_gen when the chains were created
     const uint32_t* checked_ptr = nullptr;   // the proposal ranges ff_sim_search has checked last
     uint32_t checked_n = 0;
@@ -131,6 +132,8 @@ static uint32_t batch_slots(const ff_sim* s, uint32_t B);
 
 constexpr uint32_t CHAIN_SNAPSHOTS = 32;
 static_assert(CHAIN_SNAPSHOTS <= MAX_SNAPSHOTS, "one bit per snapshot in ChainMeta::loc");
+static_assert(CHAIN_SNAPSHOTS <= TRIAL_CLASSES, "one class of trials per snapshot");
+constexpr uint32_t TRIAL_COUNTS_AT = 32, TRIAL_WORDS = TRIAL_COUNTS_AT + TRIAL_CLASSES;
 
 static KernelChoice choice(const ff_sim* s, bool cache) {
     return KernelChoice{s->wide, s->lds_words, s->d_stats != nullptr, cache, s->dev.n_ops, s->dev.n_groups, s->dev.max_parts};
@@ -182,6 +185,12 @@ static size_t try_slot_bytes(const ff_sim* s) {
     if (s->chain_choice.lds) return 256;
     const uint32_t own_rows = s->dev.ties ? s->dev.n_kept : s->max_adjacent * (uint32_t)KEPT_ROWS;
     return slot_layout(s->dev.n_ops, s->dev.n_ops_pad, s->dev.n_edges, own_rows, s->chain_choice.rowl, false).bytes;
+}
+
+// Trials are ordered by length where SIMDs get several of them (up to one per SIMD there is nothing to balance: the two kernels would only cost
+// their launches).  Bytes behind the slots of the workspace: two words per trial.
+static size_t try_plan_bytes(const ff_sim* s, uint64_t total) {
+    return total > s->n_simds && total <= MAX_PLANNED_TRIALS ? ((size_t)total * 8 + 255) & ~(size_t)255 : 0;
 }
 
 // A launch with more than 64 KB of dynamic LDS (gfx950 allows a workgroup up to 160 KB) has to be
@@ -524,6 +533,7 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         (s->cache_ok && !allow_lds((const void*)batch_kernel(s, true), s->lds_cached))) { release(s); return FF_EHIP; }
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel(s, false), WAVE, s->lds);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
+    s->n_simds = (uint32_t)cus * 4u;
     s->max_slots = (uint32_t)cus * (uint32_t)per_cu;
     per_cu = 0;
     if (s->cache_ok) {
@@ -846,7 +856,7 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     const size_t row_bytes = (size_t)s->dev.n_ops * sizeof(uint2);
     if (hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess ||
         hipMalloc((void**)&c->d_flags, (size_t)C * 4) != hipSuccess ||
-        hipMalloc((void**)&c->d_counter, 256) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
+        hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
     // the bookkeeping and the tags of endTimes start empty; each chain's strategy goes to the head of its block
     if (hipMemset2DAsync(c->d_mem + cl.meta, c->stride, 0, cl.clear_bytes, C, st) != hipSuccess ||
         hipMemsetAsync(c->d_flags, 0, (size_t)C * 4, st) != hipSuccess ||
@@ -908,11 +918,22 @@ static int launch_trials(ff_chains* c, const uint32_t* d_muts, uint32_t M, uint6
     const uint32_t total = M * c->C;
     const uint32_t slots = std::min(total, try_slots(s));
     const try_kernel_t kernel = try_kernel(s, s->loop);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(WAVE), 0, st, c->d_counter);
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, st, c->d_counter, TRIAL_WORDS);
+    // (a workspace with room for the slots alone will do: the trials are then drawn as they come)
+    uint32_t* order = nullptr;
+    const size_t plan = try_plan_bytes(s, total), used = (size_t)slots * try_slot_bytes(s);
+    if (plan && s->ws_bytes >= used + plan) {
+        order = (uint32_t*)((unsigned char*)s->ws + used);
+        uint32_t* key = order + total;
+        uint32_t* counts = c->d_counter + TRIAL_COUNTS_AT;
+        hipLaunchKernelGGL(k_trial_class, dim3((total + TRIALS_PER_BLOCK - 1) / TRIALS_PER_BLOCK), dim3(TRIALS_PER_BLOCK * WAVE), 0, st, s->dev, s->d_ops, s->d_in_edges, c->d_mem, c->stride, c->n_snaps,
+                           s->loop ? s->chain_choice.rowl : 0u, c->C, d_muts, total, c->d_flags, counts, key);
+        hipLaunchKernelGGL(k_trial_place, dim3((total + 255) / 256), dim3(256), 0, st, counts, key, total, order);
+    }
     if (!allow_lds((const void*)kernel, try_lds(s))) return FF_EHIP;
     hipLaunchKernelGGL(kernel, dim3(slots), dim3(WAVE), try_lds(s), st, s->dev, s->d_ops, s->d_edges,
                        s->d_in_edges, s->d_op_lite, s->d_edge_lite, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, d_muts, M,
-                       (u64*)d_out_ns, c->d_flags, c->d_counter, (unsigned char*)s->ws, try_slot_bytes(s));
+                       (u64*)d_out_ns, c->d_flags, c->d_counter, (unsigned char*)s->ws, try_slot_bytes(s), order, s->n_simds);
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
 
@@ -1092,7 +1113,7 @@ int ff_sim_neighbours_noalloc(ff_chains_t* c, const uint32_t* d_tuple_ptr, const
 size_t ff_sim_delta_try_workspace_bytes(const ff_chains_t* c, uint32_t M) {
     if (!c) return 0;
     const uint64_t total = (uint64_t)M * c->C;
-    return (size_t)std::max<uint64_t>(1, std::min<uint64_t>(total, try_slots(c->sim))) * try_slot_bytes(c->sim);
+    return (size_t)std::max<uint64_t>(1, std::min<uint64_t>(total, try_slots(c->sim))) * try_slot_bytes(c->sim) + try_plan_bytes(c->sim, total);
 }
 
 int ff_sim_delta_try(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t M, uint64_t* d_out_ns, void* hip_stream) {

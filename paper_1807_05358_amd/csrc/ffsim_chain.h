@@ -600,6 +600,21 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
     chain_steps(en, m, S, cm, cfg_lds, n_snaps, c, C, muts, n_steps, out_ns, chain_flags, search);
 }
 
+// The order trials are drawn in.  With `order` (see k_trial_place: longest first) the first trial of a wavefront follows its place on the chip:
+// workgroups are dealt out over the SIMDs in turn, so that workgroups b and b + n_simds share one (seen on the card with
+// 4096 of them: every SIMD holds b, b + 1024, b + 2048 and b + 3072), and the list is dealt out there and back, so that a SIMD with one of the
+// longest gets one of the shortest as well.  Whatever is left is drawn from a counter, longest first.
+__device__ __forceinline__ uint32_t trial_first_place(uint32_t b, uint32_t n, uint32_t n_simds) {
+    const uint32_t round = b / n_simds, begin = round * n_simds;
+    const uint32_t here = n - begin < n_simds ? n - begin : n_simds;
+    return (round & 1u) ? begin + (here - 1 - (b - begin)) : b;
+}
+__device__ __forceinline__ uint32_t trial_next_place(uint32_t* next_item, uint32_t from) {
+    uint32_t at = 0;
+    if (lane_id() == 0) at = from + atomicAdd(next_item, 1u);
+    return first_u32(at);
+}
+
 // Trial mutations (the proposals of Section 6.2 before acceptance): evaluates M alternative
 // single-op mutations per chain, each against the chain's current strategy and stored
 // timeline, without changing the chain.  One wavefront per (proposal, chain); its task words
@@ -612,7 +627,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_try(SimDev S, const DOp* __r
                                                         size_t chain_stride, uint32_t n_snaps, uint32_t C,
                                                         const uint32_t* __restrict__ muts, uint32_t M, u64* __restrict__ out_ns,
                                                         const uint32_t* __restrict__ chain_flags, uint32_t* __restrict__ next_item,
-                                                        unsigned char* __restrict__ ws, size_t slot_stride) {
+                                                        unsigned char* __restrict__ ws, size_t slot_stride,
+                                                        const uint32_t* __restrict__ order, uint32_t n_simds) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     const WaveLds L = carve_lds(lds_raw, S);
@@ -623,11 +639,11 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_try(SimDev S, const DOp* __r
     const uint32_t total = M * C;
     // proposals differ a lot in cost (how much of the timeline they keep): wavefronts draw the
     // next one from a counter instead of striding
-    for (;;) {
-        uint32_t id = 0;
-        if (lane_id() == 0) id = atomicAdd(next_item, 1u);
-        id = first_u32(id);
-        if (id >= total) break;
+    for (bool first = order != nullptr;;) {
+        const uint32_t at = first ? trial_first_place(blockIdx.x, gridDim.x, n_simds) : trial_next_place(next_item, order ? gridDim.x : 0u);
+        first = false;
+        if (at >= total) break;
+        const uint32_t id = order ? first_u32(order[at]) : at;
         const uint32_t c = id % C;
         // the chain is only read here
         const ChainMem cm = carve_chain(const_cast<unsigned char*>(chain_mem) + (size_t)c * chain_stride, S, n_snaps, 0);

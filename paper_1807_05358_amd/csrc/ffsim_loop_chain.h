@@ -174,7 +174,8 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_try(SimDev S, const DOp* __
                                                          const uint32_t* __restrict__ magic, const unsigned char* __restrict__ chain_mem,
                                                          size_t chain_stride, uint32_t n_snaps, uint32_t C, const uint32_t* __restrict__ muts,
                                                          uint32_t M, u64* __restrict__ out_ns, const uint32_t* __restrict__ chain_flags,
-                                                         uint32_t* __restrict__ next_item, unsigned char* __restrict__ ws, size_t slot_stride) {
+                                                         uint32_t* __restrict__ next_item, unsigned char* __restrict__ ws, size_t slot_stride,
+                                                         const uint32_t* __restrict__ order, uint32_t n_simds) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, LDSW);
@@ -198,11 +199,11 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_try(SimDev S, const DOp* __
     const WaveLds L{mem.crow, nullptr, nullptr, mem.tag};
     const uint32_t magic_v = load_magic(magic);
     const uint32_t total = M * C;
-    for (;;) {
-        uint32_t id = 0;
-        if (lane_id() == 0) id = atomicAdd(next_item, 1u);
-        id = first_u32(id);
-        if (id >= total) break;
+    for (bool first = order != nullptr;;) {
+        const uint32_t at = first ? trial_first_place(blockIdx.x, gridDim.x, n_simds) : trial_next_place(next_item, order ? gridDim.x : 0u);
+        first = false;
+        if (at >= total) break;
+        const uint32_t id = order ? first_u32(order[at]) : at;
         const uint32_t c = id % C;
         // the chain is only read here
         const ChainMem cm = carve_chain(const_cast<unsigned char*>(chain_mem) + (size_t)c * chain_stride, S, n_snaps, ROWL);

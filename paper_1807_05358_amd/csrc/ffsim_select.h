@@ -11,7 +11,7 @@ typedef void (*batch_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, c
 typedef void (*chain_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, unsigned char*, size_t,
                                uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, uint32_t*, SearchDev);
 typedef void (*try_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const unsigned char*, size_t,
-                             uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, const uint32_t*, uint32_t*, unsigned char*, size_t);
+                             uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, const uint32_t*, uint32_t*, unsigned char*, size_t, const uint32_t*, uint32_t);
 
 typedef void (*loop_kernel_t)(SimDev, const DOp*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const uint2*,
                               uint32_t, u64*, Counters*, unsigned char*, size_t, const DEdge*, const uint16_t*);
