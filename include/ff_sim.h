@@ -274,12 +274,16 @@ int ff_sim_batch_devmaps(ff_sim_t* sim, const ff_opcfg_t* d_strategies, const ui
  * d_out_ns0[c] receives the time of the starting strategies.  The library owns the
  * chains' state and allocates it here with hipMalloc: per chain the strategy, one word and two
  * endTimes per possible task, and two places for each of 32 snapshots of the simulation state
- * (about 67 * 512 * n_ops bytes: 80 MB for a 2321-op graph).  Destroy only after the work queued on the stream has finished. */
+ * (about 67 * 512 * n_ops bytes: 80 MB for a 2321-op graph).  Where C is small, up to 31 more such blocks per
+ * chain, 8 GiB in all (64 MiB for small graphs) and no more than a 16th of the memory that is free: ff_sim_delta
+ * uses them; without room for them there are none.  Destroy only after the work queued on the stream has finished. */
 int ff_sim_chains_create(ff_sim_t* sim, const ff_opcfg_t* d_strategies, uint32_t C, uint64_t* d_out_ns0,
                          void* hip_stream, ff_chains_t** out);
 /* Applies d_muts[s][c] (step-major, [n_steps][C]) to chain c for s = 0..n_steps-1,
  * cumulatively, and writes the simulated time after every step to d_out_ns[s][c]
- * (FF_INVALID_NS while the chain's strategy is invalid). */
+ * (FF_INVALID_NS while the chain's strategy is invalid).  The mutations are known beforehand, so from three
+ * steps on the steps of a chain are cut into segments that are simulated side by side, as far as the chain set has
+ * blocks and the device has room for them; the first step of a segment is a full simulation. */
 int ff_sim_delta(ff_chains_t* chains, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out_ns,
                  void* hip_stream);
 void ff_sim_chains_destroy(ff_chains_t* chains);

@@ -82,6 +82,7 @@ struct ff_sim {
     uint32_t max_slots = 0;       // wavefronts the device can hold at once (batch kernel)
     uint32_t max_try_slots = 0;   // same for the trial-mutation kernel
     uint32_t n_simds = 0;         // of the device
+    uint32_t max_chain_slots = 0; // wavefronts the device can hold at once (chain kernel)
     void* ws = nullptr;
     size_t ws_bytes = 0;
     ff_stats_t* d_stats = nullptr;
@@ -93,8 +94,9 @@ struct ff_chains {
     uint32_t n_snaps = 0;
     size_t stride = 0;             // bytes per chain
     size_t meta_at = 0;            // offset of the ChainMeta record in a chain's block
-    unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots
-    uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation
+    unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots; then [n_spare][C] more for segments of ff_sim_delta
+    uint32_t* d_flags = nullptr;   // per block: nonzero once a chain saw an out-of-range mutation
+    uint32_t n_spare = 0;
     uint32_t* d_counter = nullptr; // [TRIAL_WORDS] work counter of the trial-mutation kernel, and what k_trial_class counts
     uint32_t links_gen = 0;        // sim->links_gen when the chains were created
     const uint32_t* checked_ptr = nullptr;   // the proposal ranges ff_sim_search has checked last
@@ -578,6 +580,9 @@ static int create_impl(const ff_opgraph_t* g, const ff_machine_t* m, std::vector
         if (e != hipSuccess || per_cu < 1) per_cu = 1;
         s->max_try_slots_loop = (uint32_t)cus * (uint32_t)per_cu;
     }
+    // (chains: two wavefronts per SIMD run nearly as fast as one, four do not)
+    const size_t chain_lds = s->loop_extents ? std::max(s->chain_loop_lds, s->lds_chain) : s->lds_chain;
+    s->max_chain_slots = (uint32_t)std::min<size_t>(2 * s->n_simds, (size_t)cus * std::max<size_t>(1, (size_t)lds_limit / std::max<size_t>(1, chain_lds)));
     // the address of this device's scratch array (ff_sim_neighbours_noalloc) is looked up here, once per device
     if (!neighbour_scratch_of_current_device()) { release(s); return FF_EHIP; }
     *out = s;
@@ -827,15 +832,30 @@ int ff_sim_batch_devmaps(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint
     return batch_impl(s, d_strategies, d_devmaps, B, d_out_ns, hip_stream);
 }
 
+// Blocks per chain besides its own, for the segments of ff_sim_delta: as many as let the chains together fill the device, within MAX_SPARE per chain
+// and SPARE_BYTES (and no more than a 16th of what is free) in all.  Graphs that are simulated in LDS take a fraction of a millisecond per step, and
+// to get and give back more than 64 MiB takes 0.3 ms (up to there 35 us): their chain sets stay below that.
+constexpr uint32_t MAX_SPARE = 31;
+constexpr size_t SPARE_BYTES = (size_t)8 << 30, CHEAP_BYTES = (size_t)64 << 20;
+static uint32_t spare_blocks(const ff_sim* s, uint32_t C, size_t stride) {
+    const uint32_t fit = std::min(s->max_chain_slots / C, MAX_SPARE + 1);
+    if (fit < 2) return 0;
+    const bool in_lds = s->loop ? s->chain_choice.lds : s->lds_words;
+    if (in_lds) { const size_t sets = CHEAP_BYTES / ((size_t)C * stride); return sets < 2 ? 0u : (uint32_t)std::min<size_t>(fit - 1, sets - 1); }
+    size_t avail = 0, all = 0;
+    if (hipMemGetInfo(&avail, &all) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    return (uint32_t)std::min<size_t>(fit - 1, std::min(SPARE_BYTES, avail / 16) / ((size_t)C * stride));
+}
+
 static int launch_chain_steps(ff_chains* c, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out, hipStream_t st,
-                              const SearchDev& search) {
+                              const SearchDev& search, uint32_t n_segs = 1) {
     ff_sim* s = c->sim;
     static_assert(sizeof(ff_mutation_t) == 12, "mutation layout");
     const size_t lds = s->loop ? s->chain_loop_lds : s->lds_chain;
     if (!allow_lds((const void*)chain_kernel(s), lds)) return FF_EHIP;
-    hipLaunchKernelGGL(chain_kernel(s), dim3(c->C), dim3(WAVE), lds, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges, s->d_op_lite,
+    hipLaunchKernelGGL(chain_kernel(s), dim3(c->C * n_segs), dim3(WAVE), lds, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges, s->d_op_lite,
                        s->d_edge_lite, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, (const uint32_t*)d_muts, n_steps,
-                       (u64*)d_out, c->d_flags, search);
+                       (u64*)d_out, c->d_flags, search, n_segs);
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
 
@@ -853,17 +873,20 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     c->stride = cl.bytes;
     c->meta_at = cl.meta;
     hipStream_t st = (hipStream_t)hip_stream;
-    const size_t row_bytes = (size_t)s->dev.n_ops * sizeof(uint2);
-    if (hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess ||
-        hipMalloc((void**)&c->d_flags, (size_t)C * 4) != hipSuccess ||
-        hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
-    // the bookkeeping and the tags of endTimes start empty; each chain's strategy goes to the head of its block
-    if (hipMemset2DAsync(c->d_mem + cl.meta, c->stride, 0, cl.clear_bytes, C, st) != hipSuccess ||
-        hipMemsetAsync(c->d_flags, 0, (size_t)C * 4, st) != hipSuccess ||
-        hipMemcpy2DAsync(c->d_mem, c->stride, d_strategies, row_bytes, row_bytes, C, hipMemcpyDeviceToDevice, st) != hipSuccess) {
-        ff_sim_chains_destroy(c);
-        return FF_EHIP;
+    c->n_spare = spare_blocks(s, C, c->stride);
+    if (c->n_spare && hipMalloc((void**)&c->d_mem, (size_t)(1 + c->n_spare) * C * c->stride) != hipSuccess) {
+        (void)hipGetLastError();
+        c->d_mem = nullptr;
+        c->n_spare = 0;
     }
+    const uint32_t blocks = (1 + c->n_spare) * C;
+    if ((!c->d_mem && hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess) ||
+        hipMalloc((void**)&c->d_flags, (size_t)blocks * 4) != hipSuccess ||
+        hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
+    static_assert(sizeof(ff_opcfg_t) == sizeof(uint2), "strategy layout");
+    hipLaunchKernelGGL(k_chain_blocks, dim3(blocks), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
+                       s->dev.n_ops, C, c->d_flags);
+    if (hipGetLastError() != hipSuccess) { ff_sim_chains_destroy(c); return FF_EHIP; }
     int rc = launch_chain_steps(c, nullptr, 1, d_out_ns0, st, SearchDev{});
     if (rc) { ff_sim_chains_destroy(c); return rc; }
     c->links_gen = s->links_gen;
@@ -875,7 +898,17 @@ int ff_sim_delta(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t n_steps, 
     if (!c || (n_steps && (!d_muts || !d_out_ns))) return FF_EINVAL;
     if (c->links_gen != c->sim->links_gen) return FF_EINVAL;
     if (n_steps == 0) return FF_OK;
-    return launch_chain_steps(c, d_muts, n_steps, d_out_ns, (hipStream_t)hip_stream, SearchDev{});
+    // Segments side by side: as many as there are blocks and the device has room for, from three steps on.  The first step of a segment is a full simulation, one
+    // that resumes costs anything between none and a full one, half of it on the mean: n steps in P segments last for about
+    // (n / P + 1) / 2 full simulations instead of n / 2.
+    ff_sim* s = c->sim;
+    const uint32_t n_segs = n_steps < 3 ? 1u : std::max(1u, std::min(std::min(1 + c->n_spare, n_steps), s->max_chain_slots / c->C));
+    if (n_segs > 1) {
+        hipLaunchKernelGGL(k_chain_split, dim3(c->C), dim3(256), (size_t)s->dev.n_ops * sizeof(uint2), (hipStream_t)hip_stream, s->dev, c->d_mem,
+                           c->stride, c->n_snaps, s->loop ? s->chain_choice.rowl : 0u, c->C, n_segs, (const uint32_t*)d_muts, n_steps, c->d_flags);
+        if (hipGetLastError() != hipSuccess) return FF_EHIP;
+    }
+    return launch_chain_steps(c, d_muts, n_steps, d_out_ns, (hipStream_t)hip_stream, SearchDev{}, n_segs);
 }
 
 // checks the search parameters and fills what the kernels take of them
@@ -1131,15 +1164,19 @@ int ff_sim_delta_try(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t M, ui
 int ff_sim_chains_get_stats(ff_chains_t* c, ff_chain_stats_t* h_out) {
     if (!c || !h_out) return FF_EINVAL;
     if (hipDeviceSynchronize() != hipSuccess) return FF_EHIP;
+    // a chain's own block and those its segments ran in
+    const size_t blocks = (size_t)(1 + c->n_spare) * c->C;
+    std::vector<ChainMeta> meta(blocks);
+    if (hipMemcpy2D(meta.data(), sizeof(ChainMeta), c->d_mem + c->meta_at, c->stride, sizeof(ChainMeta), blocks, hipMemcpyDeviceToHost) != hipSuccess)
+        return FF_EHIP;
     for (uint32_t k = 0; k < c->C; k++) {
-        ChainMeta meta;
-        const unsigned char* p = c->d_mem + (size_t)k * c->stride + c->meta_at;
-        if (hipMemcpy(&meta, p, sizeof(meta), hipMemcpyDeviceToHost) != hipSuccess) return FF_EHIP;
-        h_out[k].n_steps = meta.n_steps;
-        h_out[k].n_resumed = meta.n_resumed;
-        h_out[k].n_events = meta.n_events;
-        h_out[k].n_events_full = meta.n_events_full;
-        h_out[k].n_converged = meta.n_converged;
+        h_out[k] = ff_chain_stats_t{0, 0, 0, meta[k].n_events_full, 0};
+        for (size_t b = k; b < blocks; b += c->C) {
+            h_out[k].n_steps += meta[b].n_steps;
+            h_out[k].n_resumed += meta[b].n_resumed;
+            h_out[k].n_events += meta[b].n_events;
+            h_out[k].n_converged += meta[b].n_converged;
+        }
     }
     return FF_OK;
 }

@@ -362,6 +362,16 @@ struct EventsEngine {
     __device__ __forceinline__ void finish() const {}
 };
 
+// Forced mutations do not depend on what the simulations before them find, so the steps of one chain may be cut into n_segs segments of
+// consecutive steps that run side by side, each in a block of its own with the strategy it starts from (k_chain_split): the last one in the
+// chain's own block, which it leaves as the chain's state, segment p before it in block C + p * C + c.  The first step of a segment simulates from
+// time 0, the ones behind it resume as ever.
+struct ChainSeg { uint32_t c, blk, s_begin, s_end; };
+__device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32_t n_segs, uint32_t n_steps) {
+    const uint32_t p = b / C, c = b - p * C;
+    return ChainSeg{c, p + 1 < n_segs ? C + b : c, (uint32_t)((u64)n_steps * p / n_segs), (uint32_t)((u64)n_steps * (p + 1) / n_segs)};
+}
+
 // The steps of one chain.  Three sources of steps:
 //   muts == nullptr and no search: simulate the chain's starting strategy (n_steps is 1);
 //   muts: forced mutations, [n_steps][C] records {op, cfg.x, cfg.y}, always committed;
@@ -373,16 +383,17 @@ struct EventsEngine {
 // snapshot spacing is set yet.
 // A forced mutation that names an op outside the graph poisons the chain: this and all
 // later results are RESULT_INVALID.  out_ns[s][c] is the time of the chain's strategy after
-// step s.  cfg_lds: the chain's strategy, worked on in LDS (and written through to HBM), so that the many
+// step s.  seg: the part of the steps that this wavefront makes.  cfg_lds: the chain's strategy, worked on in LDS (and written through to HBM), so that the many
 // uniform configuration look-ups do not queue behind the wavefront's stores to HBM.
 template <class Engine, class SimX>
-__device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S, const ChainMem& cm, uint2* cfg_lds, uint32_t n_snaps, uint32_t c,
+__device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S, const ChainMem& cm, uint2* cfg_lds, uint32_t n_snaps, const ChainSeg& seg,
                                             uint32_t C, const uint32_t* __restrict__ muts, uint32_t n_steps, u64* __restrict__ out_ns,
                                             uint32_t* chain_flags, const SearchDev& search) {
     constexpr int ROWL = Engine::kRowl;
     const int lane = lane_id();
+    const uint32_t c = seg.c;
     const uint32_t n_words = S.n_ops * ROWL;
-    bool poisoned = first_u32(chain_flags[c]) != 0;
+    bool poisoned = first_u32(chain_flags[seg.blk]) != 0;
     ChainMeta meta = *cm.meta;
     meta.step = first_u64(meta.step);
     meta.n_valid = first_u32(meta.n_valid);
@@ -409,7 +420,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
     // look-ahead: this launch takes the chain from step done[c] up to its first accepted proposal, at most n_ahead steps
     const bool own_position = search.enabled && search.done != nullptr;
     const bool ahead = own_position && search.ahead_ns != nullptr;
-    uint32_t s_begin = 0, s_end = n_steps, n_taken = 0;
+    uint32_t s_begin = seg.s_begin, s_end = seg.s_end, n_taken = 0;
     if (own_position) {
         s_begin = first_u32(search.done[c]);
         s_begin = s_begin < n_steps ? s_begin : n_steps;
@@ -480,7 +491,8 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
             u64 rc = 0;
             bool converged = false;
             while (phase < 3) {
-                const bool record = phase == 2;
+                // (a full simulation nothing follows in a segment whose block is not the chain's: only its result is wanted)
+                const bool record = phase == 2 && !(k == 0 && seg.blk != c && s + 1 == s_end);
                 const u64 before = cnt.n_events;
                 if (record) {
                     meta.tag = meta.tag >= 0xffffu ? 0u : meta.tag;
@@ -563,7 +575,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
         if (own_position && search.time_limit && first_u64(wall_clock64() - clock_begin) >= search.time_limit) { s++; break; }
     }
     if (lane == 0) {
-        chain_flags[c] = poisoned ? 1u : 0u;
+        chain_flags[seg.blk] = poisoned ? 1u : 0u;
         *cm.meta = meta;
         if (search.enabled) search.best_ns[c] = best;
         if (own_position) { search.done[c] = s; search.n_accepted[c] += n_taken; }
@@ -580,14 +592,14 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                                                           const uint32_t* __restrict__ magic, unsigned char* chain_mem,
                                                           size_t chain_stride, uint32_t n_snaps, uint32_t C,
                                                           const uint32_t* __restrict__ muts, uint32_t n_steps,
-                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search) {
+                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     uint2* cfg_lds = (uint2*)lds_raw;
     const WaveLds L = carve_lds(lds_raw + (size_t)S.n_ops_pad * 8, S);
-    const uint32_t c = blockIdx.x;
-    if (c >= C) return;
-    const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, 0);
+    if (blockIdx.x >= C * n_segs) return;
+    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps);
+    const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, 0);
     const uint32_t magic_v = load_magic(magic);
     for (uint32_t i = lane_id(); i < S.n_ops; i += WAVE) cfg_lds[i] = cm.cfgs[i];
     wave_sync();
@@ -597,7 +609,7 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
     if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
     m.want_sort = true;          // a later step may make the strategy a general one: the kept set-up is always complete
     EventsEngine<WIDE, TREE, CACHE, SimX> en{m, cm, n_snaps};
-    chain_steps(en, m, S, cm, cfg_lds, n_snaps, c, C, muts, n_steps, out_ns, chain_flags, search);
+    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, chain_flags, search);
 }
 
 // The order trials are drawn in.  With `order` (see k_trial_place: longest first) the first trial of a wavefront follows its place on the chip:

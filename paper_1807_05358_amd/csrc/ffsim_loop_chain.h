@@ -125,25 +125,26 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
                                                            const EdgeLite* __restrict__ edge_lite, const uint32_t* __restrict__ cost,
                                                            const uint32_t* __restrict__ magic, unsigned char* chain_mem, size_t chain_stride,
                                                            uint32_t n_snaps, uint32_t C, const uint32_t* __restrict__ muts, uint32_t n_steps,
-                                                           u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search) {
+                                                           u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
-    const uint32_t c = blockIdx.x;
-    if (c >= C) return;
+    if (blockIdx.x >= C * n_segs) return;
+    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps);
     uint2* cfg_lds = (uint2*)lds_raw;
     unsigned char* lds = lds_raw + (size_t)S.n_ops_pad * 8;
-    const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, ROWL);
+    const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, ROWL);
     LoopMem mem;
     mem.priv = nullptr;
     mem.op_lite = op_lite;
     mem.edge_lite = edge_lite;
     mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
-    const bool first_launch = !muts && !search.enabled;
+    // the kept rows do not belong to the strategy yet: a chain's first launch, and segments of its steps
+    const bool fresh = (!muts && !search.enabled) || n_segs > 1;
     if (LDSW) {
         const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, true);
         carve_lds_state(mem, lds, sl, S, op_lite, edge_lite);
         carve_rows64(mem, lds + sl.bytes, S);
-        if (!first_launch) copy_u32(mem.rows, cm.rows, S.n_kept * ROWL);
+        if (!fresh) copy_u32(mem.rows, cm.rows, S.n_kept * ROWL);
     } else {
         mem.words = cm.words;
         mem.hdr = cm.hdr;
@@ -161,8 +162,8 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
     if (EXT) { m.links = (const uint4*)(magic + LINK_TABLE_AT); m.node_links = m.links + (size_t)S.gpus_per_node * S.gpus_per_node; }
     if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
     m.want_sort = true;          // a later step may make the strategy a general one: the kept rows are always complete
-    LoopEngine<LDSW, Q, ROWL, SimX> en{m, cm, mem, EXT >= 2 && S.ties, !first_launch, 0};
-    chain_steps(en, m, S, cm, cfg_lds, n_snaps, c, C, muts, n_steps, out_ns, chain_flags, search);
+    LoopEngine<LDSW, Q, ROWL, SimX> en{m, cm, mem, EXT >= 2 && S.ties, !fresh, 0};
+    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, chain_flags, search);
 }
 
 // Trial mutations (see k_sim_chain_try).  The rows of the changed op's edges are the trial's own: in LDS with a copy of all

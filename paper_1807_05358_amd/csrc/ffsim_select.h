@@ -9,7 +9,7 @@ namespace ffsim {
 typedef void (*batch_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const uint32_t*, const uint32_t*, const uint2*,
                                uint32_t, u64*, Counters*, unsigned char*, size_t, const uint16_t*, uint32_t);
 typedef void (*chain_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, unsigned char*, size_t,
-                               uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, uint32_t*, SearchDev);
+                               uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, uint32_t*, SearchDev, uint32_t);
 typedef void (*try_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const unsigned char*, size_t,
                              uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, const uint32_t*, uint32_t*, unsigned char*, size_t, const uint32_t*, uint32_t);
 

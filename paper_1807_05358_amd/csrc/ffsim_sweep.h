@@ -123,6 +123,64 @@ __global__ void k_zero_words(uint32_t* p, uint32_t n) {
     if (i < n) p[i] = 0;
 }
 
+// ---- forced mutations in segments (chain_segment) ------------------------------------------
+//
+// The blocks of a new chain set: bookkeeping and tags of endTimes empty (clear_bytes from clear_at on, both multiples of 16), the strategies at the
+// heads of the first C blocks.  One workgroup per block.
+__global__ __launch_bounds__(256) void k_chain_blocks(unsigned char* __restrict__ chain_mem, size_t chain_stride, size_t clear_at, size_t clear_bytes,
+                                                      const uint2* __restrict__ strategies, uint32_t n_ops, uint32_t C, uint32_t* __restrict__ chain_flags) {
+    unsigned char* block = chain_mem + (size_t)blockIdx.x * chain_stride;
+    uint4* p = (uint4*)(block + clear_at);
+    for (size_t i = threadIdx.x; i < clear_bytes / 16; i += 256) p[i] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x < C)
+        for (uint32_t i = threadIdx.x; i < n_ops; i += 256) ((uint2*)block)[i] = strategies[(size_t)blockIdx.x * n_ops + i];
+    if (threadIdx.x == 0) chain_flags[blockIdx.x] = 0;
+}
+
+// Writes into the block of every segment the strategy that its steps start from: the chain's with all mutations before them applied.  The stored
+// timelines of the blocks belong to other strategies from then on.  One workgroup per chain; the mutations are applied in order by one lane.
+__global__ __launch_bounds__(256) void k_chain_split(SimDev S, unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps,
+                                                     uint32_t rowl, uint32_t C, uint32_t n_segs, const uint32_t* __restrict__ muts,
+                                                     uint32_t n_steps, uint32_t* __restrict__ chain_flags) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    uint2* cfgs = (uint2*)lds_raw;                       // [n_ops]
+    constexpr uint32_t FEW = 256;
+    __shared__ uint32_t mu[FEW * 3];
+    __shared__ uint32_t poisoned;
+    const uint32_t c = blockIdx.x, t = threadIdx.x;
+    const ChainMem own = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, rowl);
+    for (uint32_t i = t; i < S.n_ops; i += 256) cfgs[i] = own.cfgs[i];
+    const u64 step = own.meta->step;
+    if (t == 0) poisoned = chain_flags[c];
+    __syncthreads();
+    for (uint32_t p = 0; p < n_segs; p++) {
+        const ChainSeg seg = chain_segment(p * C + c, C, n_segs, n_steps);
+        const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, rowl);
+        for (uint32_t i = t; i < S.n_ops; i += 256) cm.cfgs[i] = cfgs[i];
+        if (t == 0) {
+            cm.meta->step = step;
+            cm.meta->n_valid = 0;
+            cm.meta->stale = 1;
+            cm.meta->cur_ns = RESULT_INVALID;
+            chain_flags[seg.blk] = poisoned;
+        }
+        for (uint32_t s = seg.s_begin; s < seg.s_end; s += FEW) {
+            const uint32_t n = seg.s_end - s < FEW ? seg.s_end - s : FEW;
+            __syncthreads();
+            if (t < n)
+                for (uint32_t k = 0; k < 3; k++) mu[t * 3 + k] = muts[((size_t)(s + t) * C + c) * 3 + k];
+            __syncthreads();
+            if (t == 0) {
+                for (uint32_t k = 0; k < n && !poisoned; k++) {
+                    if (mu[k * 3] >= S.n_ops) poisoned = 1;
+                    else cfgs[mu[k * 3]] = make_uint2(mu[k * 3 + 1], mu[k * 3 + 2]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // ---- trials, longest first ------------------------------------------------------------------
 //
 // How long a trial takes follows from where it may resume: from nothing (the last snapshot) to a full simulation.  A launch lasts as long as its

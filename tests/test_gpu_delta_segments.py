@@ -1,0 +1,141 @@
+"""ff_sim_delta with its steps in segments side by side (chain_segment, k_chain_split): every step's time is the full simulation of the chain's
+strategy after it (Section 5.3), and the chains are left as if the steps had been made one after the other.  Compared with calls of two steps, which
+are never cut, and with the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import random_graph
+from paper_1807_05358_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+INVALID = np.uint64(2 ** 64 - 1)
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1807_05358_amd import binding
+    return binding
+
+
+def _steps(ch, muts, per_call):
+    out = []
+    for a in range(0, len(muts), per_call):
+        n = min(per_call, len(muts) - a)
+        out.append(ch.delta(ch.upload_mutations(muts[a:a + n]), n).cpu().numpy().view("<u8"))
+    return np.concatenate(out)
+
+
+def _setup(form, seed):
+    """ops, edges, machine, cost, Simulator keywords, choices of degrees"""
+    rng = np.random.default_rng(seed)
+    if form == "tiny" or form == "wide":
+        w = W.workload(0)
+        ops = w.ops.copy()
+        if form == "wide":
+            ops["extent"][:, 0] = 70000          # beyond 16 bits: the other event loop
+        return ops, w.edges, w.machine, w.cost, {}, w.choices
+    if form == "inception":
+        w = W.workload(2)
+        return w.ops, w.edges, w.machine, w.cost, {}, w.choices
+    if form == "train":
+        w = W.workload(1)
+        ops, edges, flops, ties, params = W.training_graph(w.ops, w.edges, w.flops)
+        return ops, edges, w.machine, np.ascontiguousarray(W.cost_table(1, flops, seed)[:, :w.max_parts]), {"params": params, "ties": ties}, w.choices
+    ops, edges, flops = random_graph(rng, 90 if form == "memory" else 40)
+    mach = W.Machine(3, 3, 11, 7, 20, 400)
+    cost = rng.integers(1, 9000, size=(len(ops), 16)).astype("<u4")
+    return ops, edges, mach, cost, {}, (1, 2, 3, 4, 5, 7)
+
+
+# three steps are the fewest that are cut; one segment per step; segments of unequal lengths; more segments than a chain has blocks
+@pytest.mark.parametrize("form,C,n", [("tiny", 1, 3), ("tiny", 5, 33), ("tiny", 300, 40), ("inception", 2, 9), ("inception", 1, 70), ("train", 3, 11),
+                                      ("general", 4, 19), ("memory", 3, 35), ("wide", 2, 13)])
+def test_segments_equal_steps_in_turn(B, form, C, n):
+    ops, edges, mach, cost, kw, choices = _setup(form, 31 * n + C)
+    parts = cost.shape[1]
+    cfg0 = W.strategies(ops, C, 5, mach.n_devices, parts, choices)
+    muts = W.mutation_chains(ops, 2 * n, C, 6, mach.n_devices, parts, choices).copy()
+    rng = np.random.default_rng(n)
+    if form in ("general", "memory", "wide"):
+        cfg0["dev_stride"] = rng.integers(0, 5, cfg0.shape)
+        muts["cfg"]["dev_stride"] = rng.integers(0, 5, muts.shape)
+    if kw.get("ties") is not None:
+        muts["op"] = kw["ties"][muts["op"]]      # changes of leaders
+    print(f"segments: {form}, {C} chains x {n} steps, twice", flush=True)
+    sim = B.Simulator(ops, edges, mach, cost, **kw)
+    one, two = B.Chains(sim, cfg0), B.Chains(sim, cfg0)
+    probe = one.upload_mutations(muts[:2 * n][::-1].copy())
+    for call in (muts[:n], muts[n:]):
+        got, want = _steps(one, call, n), _steps(two, call, 2)
+        assert np.array_equal(got, want)
+        # what trials see of the chains afterwards
+        assert np.array_equal(one.try_mutations(probe, 4).cpu().numpy(), two.try_mutations(probe, 4).cpu().numpy())
+    a, b = one.stats(), two.stats()
+    assert np.array_equal(a["n_steps"], b["n_steps"]) and (a["n_resumed"] <= a["n_steps"]).all()
+    for c in {0, C - 1}:
+        ref = oracle.simulate_delta_chain(ops, edges, mach, cost, cfg0[c], muts[:, c], steps=[0, n - 1, n, 2 * n - 1], **kw)
+        mine = np.concatenate([_steps(B.Chains(sim, cfg0[c:c + 1]), muts[:, c:c + 1].copy(), n)])[[0, n - 1, n, 2 * n - 1], 0]
+        assert np.array_equal(mine, ref)
+    one.close()
+    two.close()
+    sim.close()
+
+
+@pytest.mark.parametrize("config_id", [0, 2])
+def test_invalid_and_foreign_mutations_in_segments(B, config_id):
+    """a strategy that is invalid for a few steps (from the start, across the bounds of segments) and mended later; a mutation that names no op:
+    its step and all later ones are invalid, in this call and in the next"""
+    w = W.workload(config_id)
+    C, n = 3, 24
+    cfg0 = w.strategies(C).copy()
+    muts = w.mutations(n, C).copy()
+    cfg0["deg"][0, 2, 0] = 0                                     # chain 0 starts invalid ...
+    muts["op"][3, 0], muts["cfg"][3, 0] = 2, w.strategies(1)[0, 2]        # ... and is mended in step 3
+    good = w.strategies(1)[0]
+    muts["op"][:3, 0], muts["cfg"][:3, 0] = 1, good[1]
+    muts["cfg"]["deg"][7, 1] = 255                               # chain 1 is invalid from step 7 until step 15
+    muts["op"][7, 1] = 4
+    muts["cfg"][8:15, 1][muts["op"][8:15, 1] == 4] = good[1]
+    muts["op"][8:15, 1][muts["op"][8:15, 1] == 4] = 1
+    muts["op"][15, 1], muts["cfg"][15, 1] = 4, good[4]
+    muts["op"][11, 2] = w.n_ops                                  # chain 2 is lost from step 11 on
+    print(f"segments with invalid steps: config {config_id}", flush=True)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    one, two = B.Chains(sim, cfg0), B.Chains(sim, cfg0)
+    got, want = _steps(one, muts, n), _steps(two, muts, 2)
+    assert np.array_equal(got, want)
+    assert (got[:3, 0] == INVALID).all() and (got[4:, 0] != INVALID).all()
+    assert (got[7:15, 1] == INVALID).all() and got[6, 1] != INVALID and got[15, 1] != INVALID
+    assert (got[11:, 2] == INVALID).all() and (got[:11, 2] != INVALID).all()
+    assert np.array_equal(_steps(one, muts[:7], 7), _steps(two, muts[:7], 2))
+    one.close()
+    two.close()
+    sim.close()
+
+
+def test_run_tags_start_over_in_one_block(B):
+    """calls of two steps are never cut, so one block records more runs than the 16-bit tag of an endTime can count"""
+    w = W.workload(0)
+    n = 66000
+    cfg0 = w.strategies(1)
+    muts = w.mutations(n, 1)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    ch = B.Chains(sim, cfg0)
+    import torch
+    d = ch.upload_mutations(muts)
+    out = torch.empty((n, 1), dtype=torch.int64, device="cuda")
+    for a in range(0, n, 2):
+        B.ff_sim_delta(ch.handle, d.data_ptr() + a * 12, 2, out.data_ptr() + a * 8, torch.cuda.current_stream().cuda_stream)
+        if a % 22000 == 0:
+            torch.cuda.synchronize()
+            print(f"{a} steps queued", flush=True)
+    cfgs = np.repeat(cfg0, n, 0)
+    cur = cfg0[0].copy()
+    for s in range(n):
+        cur[muts["op"][s, 0]] = muts["cfg"][s, 0]
+        cfgs[s] = cur
+    want = oracle.simulate_batch(w.ops, w.edges, w.machine, w.cost, cfgs, n_threads=16)
+    assert np.array_equal(out.cpu().numpy().view("<u8")[:, 0], want)
+    ch.close()
+    sim.close()
