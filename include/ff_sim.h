@@ -247,7 +247,7 @@ int ff_sim_set_stats(ff_sim_t* sim, ff_stats_t* d_stats);
 int ff_sim_batch(ff_sim_t* sim, const ff_opcfg_t* d_strategies, uint32_t B, uint64_t* d_out_ns,
                  void* hip_stream);
 /* ff_sim_batch, ff_sim_batch_devmaps, ff_sim_delta and ff_sim_delta_try put nothing but kernel
- * launches on the stream (no allocation, no memset, no copy): they may be recorded into a HIP
+ * launches on the stream (no memset, no copy; while it captures no allocation either): they may be recorded into a HIP
  * graph.  So may ff_sim_search from the second call with the same d_tuple_ptr / n_tuples on (the
  * first one reads the ranges back to check them; they must not change afterwards).
  * ff_sim_neighbours allocates and waits: not for capture. */
@@ -274,16 +274,16 @@ int ff_sim_batch_devmaps(ff_sim_t* sim, const ff_opcfg_t* d_strategies, const ui
  * d_out_ns0[c] receives the time of the starting strategies.  The library owns the
  * chains' state and allocates it here with hipMalloc: per chain the strategy, one word and two
  * endTimes per possible task, and two places for each of 32 snapshots of the simulation state
- * (about 67 * 512 * n_ops bytes: 80 MB for a 2321-op graph).  Where C is small, up to 31 more such blocks per
- * chain, 8 GiB in all (64 MiB for small graphs) and no more than a 16th of the memory that is free: ff_sim_delta
- * uses them; without room for them there are none.  Destroy only after the work queued on the stream has finished. */
+ * (about 67 * 512 * n_ops bytes: 80 MB for a 2321-op graph).  Destroy only after the work queued on the stream has finished. */
 int ff_sim_chains_create(ff_sim_t* sim, const ff_opcfg_t* d_strategies, uint32_t C, uint64_t* d_out_ns0,
                          void* hip_stream, ff_chains_t** out);
 /* Applies d_muts[s][c] (step-major, [n_steps][C]) to chain c for s = 0..n_steps-1,
  * cumulatively, and writes the simulated time after every step to d_out_ns[s][c]
  * (FF_INVALID_NS while the chain's strategy is invalid).  The mutations are known beforehand, so from three
- * steps on the steps of a chain are cut into segments that are simulated side by side, as far as the chain set has
- * blocks and the device has room for them; the first step of a segment is a full simulation. */
+ * steps on the steps of a chain are cut into segments that are simulated side by side, as far as the device has room
+ * for them; the first step of a segment is a full simulation.  The first such call outside a capture gets the memory for
+ * it with hipMalloc, up to 31 blocks of the above size per chain, 8 GiB in all (64 MiB for small graphs) and no more than a 16th of
+ * what is free; without it, and in graphs captured before it, the steps are made in turn. */
 int ff_sim_delta(ff_chains_t* chains, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out_ns,
                  void* hip_stream);
 void ff_sim_chains_destroy(ff_chains_t* chains);
@@ -356,7 +356,11 @@ int ff_sim_neighbours_noalloc(ff_chains_t* chains, const uint32_t* d_tuple_ptr, 
  * d_trace_ns[s][c] receives the time of chain c's strategy after step s; d_best_ns[c] /
  * d_best[c][n_ops] are updated whenever a step ends with a better time than d_best_ns[c]
  * (initialise it to UINT64_MAX).  All d_* are device pointers.  The call copies n_ops+1
- * integers back to validate d_tuple_ptr (it synchronises the stream's device). */
+ * integers back to validate d_tuple_ptr (it synchronises the stream's device).
+ * Where the device has room for four simulations per chain or more, calls of 8 steps or more (16 or 32 with many chains) simulate
+ * the strategies of steps to come side by side and then follow the path that the decisions take: the same chains, step for
+ * step, sooner; the time goes by rounds of full simulations.  The first such call gets up to 1 GiB with hipMalloc for it; calls on a stream that
+ * is being captured make their steps in turn.  ff_sim_chains_get_stats counts such steps, not the queue pops of what was simulated for them. */
 typedef struct {
     uint64_t seed;
     uint64_t first_step;

@@ -8,10 +8,10 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 HOST_UNIT = "ffsim.hip"
-KERNEL_UNITS = ["ffsim_k_loop.hip", "ffsim_k_batch.hip", "ffsim_k_chain.hip", "ffsim_k_try.hip"]   # each compiled per (EXT, GPN)
+KERNEL_UNITS = ["ffsim_k_loop.hip", "ffsim_k_batch.hip", "ffsim_k_chain.hip", "ffsim_k_try.hip", "ffsim_k_nodes.hip"]   # each compiled per (EXT, GPN)
 VARIANTS = [(0, 4), (0, 0), (1, 4), (1, 0), (2, 4), (2, 0)]
 UNITS = [HOST_UNIT] + KERNEL_UNITS
-HEADERS = ["ffsim_select.h", "ffsim_loop_chain.h", "ffsim_loop_kernels.h", "ffsim_loop.h", "ffsim_kept.h", "ffsim_sweep.h", "ffsim_kernels.h", "ffsim_chain.h", "ffsim_events.h", "ffsim_strategy.h",
+HEADERS = ["ffsim_select.h", "ffsim_loop_chain.h", "ffsim_loop_kernels.h", "ffsim_loop.h", "ffsim_kept.h", "ffsim_sweep.h", "ffsim_ahead.h", "ffsim_kernels.h", "ffsim_chain.h", "ffsim_events.h", "ffsim_strategy.h",
            "ffsim_device.h"]
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libffsim.so")

@@ -14,6 +14,7 @@
 
 #include "ffsim_select.h"
 #include "ffsim_sweep.h"
+#include "ffsim_ahead.h"
 
 using namespace ffsim;
 
@@ -94,9 +95,12 @@ struct ff_chains {
     uint32_t n_snaps = 0;
     size_t stride = 0;             // bytes per chain
     size_t meta_at = 0;            // offset of the ChainMeta record in a chain's block
-    unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots; then [n_spare][C] more for segments of ff_sim_delta
-    uint32_t* d_flags = nullptr;   // per block: nonzero once a chain saw an out-of-range mutation
+    unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots
+    uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation
+    // more blocks [n_spare][C] for the segments of ff_sim_delta, got when they are first wanted, and their flags behind them
+    SpareBlocks spare{};
     uint32_t n_spare = 0;
+    bool spare_asked = false;
     uint32_t* d_counter = nullptr; // [TRIAL_WORDS] work counter of the trial-mutation kernel, and what k_trial_class counts
     uint32_t links_gen = 0;        // sim->links_gen when the chains were created
     const uint32_t* checked_ptr = nullptr;   // the proposal ranges ff_sim_search has checked last
@@ -106,6 +110,12 @@ struct ff_chains {
     uint64_t* d_ahead_ns = nullptr;
     uint32_t* d_ahead_done = nullptr;
     uint32_t ahead_cap = 0;
+    // ff_sim_search with the steps to come simulated side by side (ffsim_ahead.h): one allocation for all of it
+    bool tree_asked = false;
+    unsigned char* d_tree = nullptr;
+    AheadDev tree{};               // pointers into it; capacity 0: the search makes its steps one after the other
+    NodeSlots node_slots{};
+    u64* d_tree_out = nullptr;     // [C]
 };
 
 // Scratch of ff_sim_neighbours_noalloc: the index of every op's first neighbour (one entry per op of the
@@ -176,6 +186,13 @@ static try_kernel_t try_kernel(const ff_sim* s, bool k) {
     const int ext = ext_level(s);
     if (s->dev.gpus_per_node == 4) return ext == 2 ? pick_try<2, 4>(s, k) : (ext == 1 ? pick_try<1, 4>(s, k) : pick_try<0, 4>(s, k));
     return ext == 2 ? pick_try<2, 0>(s, k) : (ext == 1 ? pick_try<1, 0>(s, k) : pick_try<0, 0>(s, k));
+}
+
+static nodes_kernel_t nodes_kernel(const ff_sim* s) {
+    const LoopChoice& k = s->chain_choice;
+    const int ext = ext_level(s);
+    if (s->dev.gpus_per_node == 4) return ext == 2 ? loop_nodes_kernels<2, 4>(k) : (ext == 1 ? loop_nodes_kernels<1, 4>(k) : loop_nodes_kernels<0, 4>(k));
+    return ext == 2 ? loop_nodes_kernels<2, 0>(k) : (ext == 1 ? loop_nodes_kernels<1, 0>(k) : loop_nodes_kernels<0, 0>(k));
 }
 
 // Trials: LDS and workspace bytes per resident wavefront, and how many the device holds.  (Where the state is in LDS nothing
@@ -832,19 +849,45 @@ int ff_sim_batch_devmaps(ff_sim_t* s, const ff_opcfg_t* d_strategies, const uint
     return batch_impl(s, d_strategies, d_devmaps, B, d_out_ns, hip_stream);
 }
 
+// Memory the library can do without: null if there is none.  (Another thread may be capturing a stream of its own, and this is no business of that graph.)
+static unsigned char* get_memory(size_t bytes) {
+    unsigned char* mem = nullptr;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t e = hipMalloc((void**)&mem, bytes);
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) return mem;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
 // Blocks per chain besides its own, for the segments of ff_sim_delta: as many as let the chains together fill the device, within MAX_SPARE per chain
-// and SPARE_BYTES (and no more than a 16th of what is free) in all.  Graphs that are simulated in LDS take a fraction of a millisecond per step, and
-// to get and give back more than 64 MiB takes 0.3 ms (up to there 35 us): their chain sets stay below that.
+// and SPARE_BYTES (and no more than a 16th of what is free) in all.  They are got with the first call that has use for them: memory of this size costs
+// little to get (0.3 ms; up to 64 MiB 0.02 ms), but is wiped by the driver when it is given back, at about 80 GB/s, and chain sets that only search or price
+// trials would wait for that.  Graphs that are simulated in LDS take a fraction of a millisecond per step: their chain sets stay below 64 MiB.
 constexpr uint32_t MAX_SPARE = 31;
 constexpr size_t SPARE_BYTES = (size_t)8 << 30, CHEAP_BYTES = (size_t)64 << 20;
-static uint32_t spare_blocks(const ff_sim* s, uint32_t C, size_t stride) {
-    const uint32_t fit = std::min(s->max_chain_slots / C, MAX_SPARE + 1);
-    if (fit < 2) return 0;
-    const bool in_lds = s->loop ? s->chain_choice.lds : s->lds_words;
-    if (in_lds) { const size_t sets = CHEAP_BYTES / ((size_t)C * stride); return sets < 2 ? 0u : (uint32_t)std::min<size_t>(fit - 1, sets - 1); }
-    size_t avail = 0, all = 0;
-    if (hipMemGetInfo(&avail, &all) != hipSuccess) { (void)hipGetLastError(); return 0; }
-    return (uint32_t)std::min<size_t>(fit - 1, std::min(SPARE_BYTES, avail / 16) / ((size_t)C * stride));
+static void get_spare_blocks(ff_chains* c, hipStream_t st) {
+    ff_sim* s = c->sim;
+    c->spare_asked = true;
+    const uint32_t fit = std::min(s->max_chain_slots / c->C, MAX_SPARE + 1);
+    const size_t set = (size_t)c->C * c->stride;
+    if (fit < 2) return;
+    size_t most = CHEAP_BYTES;
+    if (!(s->loop ? s->chain_choice.lds : s->lds_words)) {
+        size_t avail = 0, all = 0;
+        if (hipMemGetInfo(&avail, &all) != hipSuccess) { (void)hipGetLastError(); return; }
+        most = std::min(SPARE_BYTES, avail / 16);
+    }
+    const uint32_t n = (uint32_t)std::min<size_t>(fit - 1, most / (set + c->C * 4));
+    if (!n) return;
+    unsigned char* mem = get_memory(n * (set + (size_t)c->C * 4));
+    if (!mem) return;
+    c->spare = SpareBlocks{mem, (uint32_t*)(mem + n * set)};
+    c->n_spare = n;
+    const ChainLayout cl = chain_layout(s->dev, c->n_snaps, s->loop ? s->chain_choice.rowl : 0);
+    hipLaunchKernelGGL(k_chain_blocks, dim3(n * c->C), dim3(256), 0, st, mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)nullptr, s->dev.n_ops, 0u,
+                       c->spare.flags);
 }
 
 static int launch_chain_steps(ff_chains* c, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out, hipStream_t st,
@@ -855,7 +898,7 @@ static int launch_chain_steps(ff_chains* c, const ff_mutation_t* d_muts, uint32_
     if (!allow_lds((const void*)chain_kernel(s), lds)) return FF_EHIP;
     hipLaunchKernelGGL(chain_kernel(s), dim3(c->C * n_segs), dim3(WAVE), lds, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges, s->d_op_lite,
                        s->d_edge_lite, s->d_cost, s->d_magic, c->d_mem, c->stride, c->n_snaps, c->C, (const uint32_t*)d_muts, n_steps,
-                       (u64*)d_out, c->d_flags, search, n_segs);
+                       (u64*)d_out, c->d_flags, search, n_segs, c->spare);
     return hipGetLastError() == hipSuccess ? FF_OK : FF_EHIP;
 }
 
@@ -873,18 +916,11 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     c->stride = cl.bytes;
     c->meta_at = cl.meta;
     hipStream_t st = (hipStream_t)hip_stream;
-    c->n_spare = spare_blocks(s, C, c->stride);
-    if (c->n_spare && hipMalloc((void**)&c->d_mem, (size_t)(1 + c->n_spare) * C * c->stride) != hipSuccess) {
-        (void)hipGetLastError();
-        c->d_mem = nullptr;
-        c->n_spare = 0;
-    }
-    const uint32_t blocks = (1 + c->n_spare) * C;
-    if ((!c->d_mem && hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess) ||
-        hipMalloc((void**)&c->d_flags, (size_t)blocks * 4) != hipSuccess ||
+    if (hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess ||
+        hipMalloc((void**)&c->d_flags, (size_t)C * 4) != hipSuccess ||
         hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
     static_assert(sizeof(ff_opcfg_t) == sizeof(uint2), "strategy layout");
-    hipLaunchKernelGGL(k_chain_blocks, dim3(blocks), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
+    hipLaunchKernelGGL(k_chain_blocks, dim3(C), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
                        s->dev.n_ops, C, c->d_flags);
     if (hipGetLastError() != hipSuccess) { ff_sim_chains_destroy(c); return FF_EHIP; }
     int rc = launch_chain_steps(c, nullptr, 1, d_out_ns0, st, SearchDev{});
@@ -902,13 +938,61 @@ int ff_sim_delta(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t n_steps, 
     // that resumes costs anything between none and a full one, half of it on the mean: n steps in P segments last for about
     // (n / P + 1) / 2 full simulations instead of n / 2.
     ff_sim* s = c->sim;
-    const uint32_t n_segs = n_steps < 3 ? 1u : std::max(1u, std::min(std::min(1 + c->n_spare, n_steps), s->max_chain_slots / c->C));
+    hipStream_t st = (hipStream_t)hip_stream;
+    uint32_t n_segs = 1;
+    if (n_steps >= 3) {
+        if (!c->spare_asked) {
+            hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(st, &capturing) != hipSuccess) return FF_EHIP;
+            if (capturing == hipStreamCaptureStatusNone) get_spare_blocks(c, st);
+        }
+        n_segs = std::max(1u, std::min(std::min(1 + c->n_spare, n_steps), s->max_chain_slots / c->C));
+    }
     if (n_segs > 1) {
-        hipLaunchKernelGGL(k_chain_split, dim3(c->C), dim3(256), (size_t)s->dev.n_ops * sizeof(uint2), (hipStream_t)hip_stream, s->dev, c->d_mem,
-                           c->stride, c->n_snaps, s->loop ? s->chain_choice.rowl : 0u, c->C, n_segs, (const uint32_t*)d_muts, n_steps, c->d_flags);
+        hipLaunchKernelGGL(k_chain_split, dim3(c->C), dim3(256), (size_t)s->dev.n_ops * sizeof(uint2), st, s->dev, c->d_mem,
+                           c->stride, c->n_snaps, s->loop ? s->chain_choice.rowl : 0u, c->C, n_segs, (const uint32_t*)d_muts, n_steps, c->d_flags,
+                           c->spare);
         if (hipGetLastError() != hipSuccess) return FF_EHIP;
     }
-    return launch_chain_steps(c, d_muts, n_steps, d_out_ns, (hipStream_t)hip_stream, SearchDev{}, n_segs);
+    return launch_chain_steps(c, d_muts, n_steps, d_out_ns, st, SearchDev{}, n_segs);
+}
+
+// Memory for searches that look ahead, got with the first call that has use for it.  Nodes: two wavefronts per SIMD, which take little longer than one, or four where that is what it takes to have four nodes per
+// chain; none with fewer (with chains enough to fill the device steps one after the other cost less).  The nodes of large graphs keep their state
+// where the chains have their snapshots, about eight per chain; few chains get up to TREE_BYTES more.
+constexpr uint32_t AHEAD_LEAST = 4;
+constexpr size_t TREE_BYTES = (size_t)1 << 30;
+static void get_tree(ff_chains* c) {
+    ff_sim* s = c->sim;
+    c->tree_asked = true;
+    if (!s->loop) return;
+    uint64_t n = std::min<uint64_t>(std::max<uint64_t>(2ull * s->n_simds, (uint64_t)AHEAD_LEAST * c->C), s->max_try_slots_loop);
+    n = std::min<uint64_t>(n, (uint64_t)MAX_TREE * c->C);
+    const uint32_t rowl = s->chain_choice.rowl;
+    NodeSlots& ns = c->node_slots;
+    uint64_t more = 0;
+    if (!s->chain_choice.lds) {
+        const ChainLayout cl = chain_layout(s->dev, c->n_snaps, rowl);
+        ns.bytes = slot_layout(s->dev.n_ops, s->dev.n_ops_pad, s->dev.n_edges, s->dev.n_kept, rowl, false).bytes;
+        ns.blocks = c->d_mem + cl.snap_words;
+        ns.stride = c->stride;
+        ns.per_chain = (uint32_t)((cl.snap_free - cl.snap_words) / ns.bytes);
+        const uint64_t in_blocks = std::min<uint64_t>(n, (uint64_t)ns.per_chain * c->C);
+        ns.in_blocks = (uint32_t)in_blocks;
+        more = std::min<uint64_t>(n - in_blocks, TREE_BYTES / ns.bytes);
+        n = in_blocks + more;
+    }
+    if (n < (uint64_t)AHEAD_LEAST * c->C) return;
+    size_t at = 0;
+    auto take = [&](size_t bytes) { const size_t a = at; at = (at + bytes + 255) & ~(size_t)255; return a; };
+    const size_t slots = take(more * ns.bytes), nodes = take(n * sizeof(AheadNode)), times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)),
+                 counters = take(AHEAD_RING * 2 * 4), tree = take((size_t)c->C * 8), done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
+    c->d_tree = get_memory(at);
+    if (!c->d_tree) return;
+    c->tree = AheadDev{(AheadNode*)(c->d_tree + nodes), (u64*)(c->d_tree + times), (uint2*)(c->d_tree + strategies), (uint32_t*)(c->d_tree + counters),
+                       (uint32_t*)(c->d_tree + tree), (uint32_t*)(c->d_tree + done), (uint32_t)n};
+    ns.more = c->d_tree + slots;
+    c->d_tree_out = (u64*)(c->d_tree + out);
 }
 
 // checks the search parameters and fills what the kernels take of them
@@ -936,13 +1020,56 @@ static int search_params(ff_chains_t* c, const ff_search_t* p, SearchDev* out) {
     return FF_OK;
 }
 
+// A search that looks ahead: rounds of k_search_walk and k_loop_nodes, as many as chains with a middling share of accepted proposals need and a third
+// more (rounds that find nothing to do cost their launches, 5 to 10 us); then the timelines of the chains that have moved are recorded, and chains that are not
+// through yet make the rest of their steps one after the other.
+constexpr uint32_t AHEAD_STEPS = 8;
+static int launch_ahead(ff_chains* c, uint32_t n_steps, uint64_t* d_trace_ns, hipStream_t st, SearchDev sd) {
+    ff_sim* s = c->sim;
+    const AheadDev& ah = c->tree;
+    const size_t lds = s->try_loop_lds;
+    const nodes_kernel_t kernel = nodes_kernel(s);
+    if (!allow_lds((const void*)kernel, lds)) return FF_EHIP;
+    const uint32_t rowl = s->chain_choice.rowl;
+    const double per_round = std::log2(1.0 + std::min<double>(MAX_TREE, (double)ah.capacity / c->C));
+    const uint32_t rounds = (uint32_t)std::min<double>(n_steps, 3.0 + 4.0 / 3.0 * n_steps / per_round);
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, st, ah.counters, AHEAD_RING * 2);
+    for (uint32_t r = 0; r <= rounds; r++) {
+        hipLaunchKernelGGL(k_search_walk, dim3(c->C), dim3(WAVE), 0, st, s->dev, c->d_mem, c->stride, c->n_snaps, rowl, c->C, n_steps, (u64*)d_trace_ns,
+                           c->d_flags, sd, ah, c->node_slots.in_blocks, r);
+        if (r < rounds)
+            hipLaunchKernelGGL(kernel, dim3(ah.capacity), dim3(WAVE), lds, st, s->dev, s->d_ops, s->d_edges, s->d_in_edges, s->d_op_lite, s->d_edge_lite,
+                               s->d_cost, s->d_magic, (const uint2*)ah.strategies, ah.counters + (r % AHEAD_RING) * 2 + 1, ah.capacity, ah.ns,
+                               c->node_slots);
+    }
+    if (hipGetLastError() != hipSuccess) return FF_EHIP;
+    const int rc = launch_chain_steps(c, nullptr, 1, (uint64_t*)c->d_tree_out, st, SearchDev{});
+    if (rc || rounds >= n_steps) return rc;
+    sd.done = ah.done;
+    sd.n_accepted = ah.done + c->C;
+    sd.n_ahead = n_steps;
+    return launch_chain_steps(c, nullptr, n_steps, d_trace_ns, st, sd);
+}
+
 int ff_sim_search(ff_chains_t* c, const ff_search_t* p, uint32_t n_steps, uint64_t* d_trace_ns, void* hip_stream) {
     if (!c || !p || (n_steps && !d_trace_ns)) return FF_EINVAL;
     if (n_steps == 0) return c->links_gen != c->sim->links_gen ? FF_EINVAL : FF_OK;
     SearchDev sd{};
     const int rc = search_params(c, p, &sd);
     if (rc) return rc;
-    return launch_chain_steps(c, nullptr, n_steps, d_trace_ns, (hipStream_t)hip_stream, sd);
+    hipStream_t st = (hipStream_t)hip_stream;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capturing) != hipSuccess) return FF_EHIP;
+    // (a graph is to hold the search in one node, not in two per round)
+    const bool try_ahead = n_steps >= AHEAD_STEPS && capturing == hipStreamCaptureStatusNone;
+    if (try_ahead && !c->tree_asked) get_tree(c);
+    // What a call costs besides its rounds, one recorded simulation, takes more steps to get back with few nodes per chain: from 16 nodes on 8 steps, with
+    // fewer 16, and where the nodes are four to a SIMD 32 (Inception-v3-shaped, chains created and closed included, in turn -> ahead: 20 chains x 8 steps
+    // 33.2 -> 24.1 ms, 130 x 8 37.8 -> 37.9, 500 x 16 61.0 -> 50.0, 1024 x 16 65.7 -> 66.5, 1024 x 64 201 -> 171).
+    const uint32_t least = c->tree.capacity > 2 * c->sim->n_simds ? 4 * AHEAD_STEPS : (c->tree.capacity / c->C < 16 ? 2 * AHEAD_STEPS : AHEAD_STEPS);
+    if (!try_ahead || !c->tree.capacity || n_steps < least)
+        return launch_chain_steps(c, nullptr, n_steps, d_trace_ns, st, sd);
+    return launch_ahead(c, n_steps, d_trace_ns, st, sd);
 }
 
 // the trial kernel on M proposals per chain (d_muts [M][C]); the caller has checked the workspace
@@ -1165,13 +1292,14 @@ int ff_sim_chains_get_stats(ff_chains_t* c, ff_chain_stats_t* h_out) {
     if (!c || !h_out) return FF_EINVAL;
     if (hipDeviceSynchronize() != hipSuccess) return FF_EHIP;
     // a chain's own block and those its segments ran in
-    const size_t blocks = (size_t)(1 + c->n_spare) * c->C;
+    const size_t C = c->C, blocks = (1 + (size_t)c->n_spare) * C;
     std::vector<ChainMeta> meta(blocks);
-    if (hipMemcpy2D(meta.data(), sizeof(ChainMeta), c->d_mem + c->meta_at, c->stride, sizeof(ChainMeta), blocks, hipMemcpyDeviceToHost) != hipSuccess)
-        return FF_EHIP;
-    for (uint32_t k = 0; k < c->C; k++) {
+    if (hipMemcpy2D(meta.data(), sizeof(ChainMeta), c->d_mem + c->meta_at, c->stride, sizeof(ChainMeta), C, hipMemcpyDeviceToHost) != hipSuccess ||
+        (c->n_spare && hipMemcpy2D(meta.data() + C, sizeof(ChainMeta), c->spare.mem + c->meta_at, c->stride, sizeof(ChainMeta), blocks - C,
+                                   hipMemcpyDeviceToHost) != hipSuccess)) return FF_EHIP;
+    for (size_t k = 0; k < C; k++) {
         h_out[k] = ff_chain_stats_t{0, 0, 0, meta[k].n_events_full, 0};
-        for (size_t b = k; b < blocks; b += c->C) {
+        for (size_t b = k; b < blocks; b += C) {
             h_out[k].n_steps += meta[b].n_steps;
             h_out[k].n_resumed += meta[b].n_resumed;
             h_out[k].n_events += meta[b].n_events;
@@ -1189,6 +1317,8 @@ void ff_sim_chains_destroy(ff_chains_t* c) {
     hipFree(c->d_ahead_muts);
     hipFree(c->d_ahead_ns);
     hipFree(c->d_ahead_done);
+    hipFree(c->d_tree);
+    hipFree(c->spare.mem);
     delete c;
 }
 

@@ -35,6 +35,10 @@ struct ChainMeta {
     u64 n_converged;    // committed steps whose run stopped early because it re-joined the accepted timeline
     uint32_t loc;       // bit k: which of its two places holds snapshot k of the accepted timeline
     uint32_t tag;       // tag of the last recorded run (1..0xffff; 0 marks entries never written)
+    // searches that look ahead (ffsim_ahead.h)
+    uint32_t moved;     // the strategy has changed since its timeline was recorded
+    uint32_t n_tried, n_taken;   // proposals lately decided, and taken
+    uint32_t unused;
 };
 
 // all pointers are per chain; what only one of the engines has is null with the other
@@ -364,12 +368,16 @@ struct EventsEngine {
 
 // Forced mutations do not depend on what the simulations before them find, so the steps of one chain may be cut into n_segs segments of
 // consecutive steps that run side by side, each in a block of its own with the strategy it starts from (k_chain_split): the last one in the
-// chain's own block, which it leaves as the chain's state, segment p before it in block C + p * C + c.  The first step of a segment simulates from
+// chain's own block, which it leaves as the chain's state, segment p before it in spare block p * C + c.  The first step of a segment simulates from
 // time 0, the ones behind it resume as ever.
-struct ChainSeg { uint32_t c, blk, s_begin, s_end; };
-__device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32_t n_segs, uint32_t n_steps) {
+struct SpareBlocks { unsigned char* mem; uint32_t* flags; };
+struct ChainSeg { uint32_t c, s_begin, s_end; bool spare; unsigned char* block; uint32_t* flag; };
+__device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32_t n_segs, uint32_t n_steps, unsigned char* chain_mem, size_t stride,
+                                                  uint32_t* chain_flags, const SpareBlocks& spare) {
     const uint32_t p = b / C, c = b - p * C;
-    return ChainSeg{c, p + 1 < n_segs ? C + b : c, (uint32_t)((u64)n_steps * p / n_segs), (uint32_t)((u64)n_steps * (p + 1) / n_segs)};
+    const bool sp = p + 1 < n_segs;
+    return ChainSeg{c, (uint32_t)((u64)n_steps * p / n_segs), (uint32_t)((u64)n_steps * (p + 1) / n_segs), sp,
+                    (sp ? spare.mem + (size_t)b * stride : chain_mem + (size_t)c * stride), sp ? spare.flags + b : chain_flags + c};
 }
 
 // The steps of one chain.  Three sources of steps:
@@ -388,12 +396,12 @@ __device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32
 template <class Engine, class SimX>
 __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S, const ChainMem& cm, uint2* cfg_lds, uint32_t n_snaps, const ChainSeg& seg,
                                             uint32_t C, const uint32_t* __restrict__ muts, uint32_t n_steps, u64* __restrict__ out_ns,
-                                            uint32_t* chain_flags, const SearchDev& search) {
+                                            const SearchDev& search) {
     constexpr int ROWL = Engine::kRowl;
     const int lane = lane_id();
     const uint32_t c = seg.c;
     const uint32_t n_words = S.n_ops * ROWL;
-    bool poisoned = first_u32(chain_flags[seg.blk]) != 0;
+    bool poisoned = first_u32(*seg.flag) != 0;
     ChainMeta meta = *cm.meta;
     meta.step = first_u64(meta.step);
     meta.n_valid = first_u32(meta.n_valid);
@@ -407,6 +415,8 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
     meta.n_converged = first_u64(meta.n_converged);
     meta.loc = first_u32(meta.loc);
     meta.tag = first_u32(meta.tag);
+    // (a launch that only brings stored timelines up to date has nothing to do for this one)
+    if (!muts && !search.enabled && (meta.stale || (meta.n_valid > 0 && !first_u32(meta.moved)))) return;
     Recorder rec{cm.end_try, cm.snap_words, cm.snap_l1, cm.snap_free, meta.step, 0, meta.loc, n_snaps, 1, 0, 0};
     // With tied configurations a mutation changes several ops at once: such steps are simulated from time 0.
     const bool tied = SimX::kTrain && S.ties;
@@ -492,7 +502,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
             bool converged = false;
             while (phase < 3) {
                 // (a full simulation nothing follows in a segment whose block is not the chain's: only its result is wanted)
-                const bool record = phase == 2 && !(k == 0 && seg.blk != c && s + 1 == s_end);
+                const bool record = phase == 2 && !(k == 0 && seg.spare && s + 1 == s_end);
                 const u64 before = cnt.n_events;
                 if (record) {
                     meta.tag = meta.tag >= 0xffffu ? 0u : meta.tag;
@@ -534,6 +544,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
                                               op, ocfg, pend_new);
                 }
                 commit_run(cm, meta, rec, k + 1, n_words, converged);
+                meta.moved = 0;
                 if (converged) meta.n_converged++;
                 meta.stale = 0;
                 meta.cur_ns = mk;
@@ -575,7 +586,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
         if (own_position && search.time_limit && first_u64(wall_clock64() - clock_begin) >= search.time_limit) { s++; break; }
     }
     if (lane == 0) {
-        chain_flags[seg.blk] = poisoned ? 1u : 0u;
+        *seg.flag = poisoned ? 1u : 0u;
         *cm.meta = meta;
         if (search.enabled) search.best_ns[c] = best;
         if (own_position) { search.done[c] = s; search.n_accepted[c] += n_taken; }
@@ -592,14 +603,15 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
                                                           const uint32_t* __restrict__ magic, unsigned char* chain_mem,
                                                           size_t chain_stride, uint32_t n_snaps, uint32_t C,
                                                           const uint32_t* __restrict__ muts, uint32_t n_steps,
-                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs) {
+                                                          u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs,
+                                                          SpareBlocks spare) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     uint2* cfg_lds = (uint2*)lds_raw;
     const WaveLds L = carve_lds(lds_raw + (size_t)S.n_ops_pad * 8, S);
     if (blockIdx.x >= C * n_segs) return;
-    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps);
-    const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, 0);
+    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
+    const ChainMem cm = carve_chain(seg.block, S, n_snaps, 0);
     const uint32_t magic_v = load_magic(magic);
     for (uint32_t i = lane_id(); i < S.n_ops; i += WAVE) cfg_lds[i] = cm.cfgs[i];
     wave_sync();
@@ -609,7 +621,7 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
     if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
     m.want_sort = true;          // a later step may make the strategy a general one: the kept set-up is always complete
     EventsEngine<WIDE, TREE, CACHE, SimX> en{m, cm, n_snaps};
-    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, chain_flags, search);
+    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, search);
 }
 
 // The order trials are drawn in.  With `order` (see k_trial_place: longest first) the first trial of a wavefront follows its place on the chip:

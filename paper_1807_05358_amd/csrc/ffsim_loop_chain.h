@@ -125,14 +125,15 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
                                                            const EdgeLite* __restrict__ edge_lite, const uint32_t* __restrict__ cost,
                                                            const uint32_t* __restrict__ magic, unsigned char* chain_mem, size_t chain_stride,
                                                            uint32_t n_snaps, uint32_t C, const uint32_t* __restrict__ muts, uint32_t n_steps,
-                                                           u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs) {
+                                                           u64* __restrict__ out_ns, uint32_t* chain_flags, SearchDev search, uint32_t n_segs,
+                                                           SpareBlocks spare) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     if (blockIdx.x >= C * n_segs) return;
-    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps);
+    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
     uint2* cfg_lds = (uint2*)lds_raw;
     unsigned char* lds = lds_raw + (size_t)S.n_ops_pad * 8;
-    const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, ROWL);
+    const ChainMem cm = carve_chain(seg.block, S, n_snaps, ROWL);
     LoopMem mem;
     mem.priv = nullptr;
     mem.op_lite = op_lite;
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
     if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
     m.want_sort = true;          // a later step may make the strategy a general one: the kept rows are always complete
     LoopEngine<LDSW, Q, ROWL, SimX> en{m, cm, mem, EXT >= 2 && S.ties, !fresh, 0};
-    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, chain_flags, search);
+    chain_steps(en, m, S, cm, cfg_lds, n_snaps, seg, C, muts, n_steps, out_ns, search);
 }
 
 // Trial mutations (see k_sim_chain_try).  The rows of the changed op's edges are the trial's own: in LDS with a copy of all
@@ -245,6 +246,75 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_try(SimDev S, const DOp* __
         if (lane_id() == 0) out_ns[id] = mk;
         wave_sync();
     }
+}
+
+// Where the nodes of large graphs keep their state: where the chains have their snapshots (per_chain slots in every block; the search leaves the
+// timelines to be recorded again), then in memory of their own.
+struct NodeSlots {
+    unsigned char* blocks;     // the first chain's snapshots
+    size_t stride, bytes;      // from chain to chain; of a slot
+    uint32_t per_chain, in_blocks;
+    unsigned char* more;
+    __device__ __forceinline__ unsigned char* of(uint32_t b) const {
+        return b < in_blocks ? blocks + (size_t)(b / per_chain) * stride + (size_t)(b % per_chain) * bytes : more + (size_t)(b - in_blocks) * bytes;
+    }
+};
+
+// One full simulation per strategy and wavefront: the first *n of the strategies of a search that looks ahead (ffsim_ahead.h).  As k_loop_batch, but
+// strategies that book a link more than 2^32 ns ahead are simulated again here.
+template <bool LDSW, int Q, int ROWL, int EXT, int GPN>
+__global__ __launch_bounds__(WAVE) void k_loop_nodes(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ edges, const DEdge* __restrict__ in_edges,
+                                                     const OpLite* __restrict__ op_lite, const EdgeLite* __restrict__ edge_lite,
+                                                     const uint32_t* __restrict__ cost, const uint32_t* __restrict__ magic,
+                                                     const uint2* __restrict__ strategies, const uint32_t* __restrict__ n, uint32_t capacity,
+                                                     u64* __restrict__ out_ns, NodeSlots slots) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const uint32_t b = blockIdx.x;
+    if (b >= *n || b >= capacity) return;
+    const Tables T{ops, edges, in_edges, cost};
+    const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, LDSW);
+    LoopMem mem;
+    mem.priv = nullptr;
+    mem.op_lite = op_lite;
+    mem.edge_lite = edge_lite;
+    mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
+    if (LDSW) {
+        carve_lds_state(mem, lds_raw, sl, S, op_lite, edge_lite);
+        carve_rows64(mem, lds_raw + sl.bytes, S);
+    } else {
+        unsigned char* slot = slots.of(b);
+        mem.words = (u64*)(slot + sl.words);
+        mem.hdr = (uint4*)(slot + sl.hdr);
+        mem.rows = (uint32_t*)(slot + sl.rows);
+        mem.spill_key = (u64*)(slot + sl.spill_key);
+        mem.spill_op = (uint32_t*)(slot + sl.spill_op);
+        carve_rows64(mem, lds_raw, S);
+    }
+    const WaveLds L{mem.crow, nullptr, nullptr, mem.tag};
+    const uint32_t magic_v = load_magic(magic);
+    SimT<false, EXT, GPN> m{S, T, strategies + (size_t)b * S.n_ops, mem.words, nullptr, L, magic_v, 0, false, NO_OVERRIDE, make_uint2(0, 0), nullptr, true};
+    if (EXT) { m.links = (const uint4*)(magic + LINK_TABLE_AT); m.node_links = m.links + (size_t)S.gpus_per_node * S.gpus_per_node; }
+    if (EXT >= 2 && S.ties) m.tie = magic + tie_table_at(S.gpus_per_node, S.n_nodes);
+    u64 mk = RESULT_INVALID;
+    const StrategyClass cls = validate_loop<Q>(m, mem);
+    if (cls != STRATEGY_INVALID) {
+        Counters cnt = {};
+        Recorder none = {};
+        LoopState st;
+        m.want_sort = cls != STRATEGY_REGULAR;
+        init_loop<Q, ROWL>(m, mem, st, cnt, true);
+        u64 rc = cls == STRATEGY_REGULAR ? run_loop<false, true, false, Q, ROWL>(m, mem, st, cnt, none)
+                                         : run_loop<false, false, false, Q, ROWL>(m, mem, st, cnt, none);
+        if (!rc) mk = loop_makespan(m, mem, st);
+        if (rc == RESULT_RETRY) {
+            m.want_sort = true;          // (the general form's rows)
+            init_loop<Q, ROWL, true>(m, mem, st, cnt, true);
+            rc = run_loop<false, false, false, Q, ROWL, true>(m, mem, st, cnt, none);
+            if (!rc) mk = loop_makespan<true>(m, mem, st);
+        }
+        if (rc) mk = rc;
+    }
+    if (lane_id() == 0) out_ns[b] = mk;
 }
 
 }  // namespace ffsim

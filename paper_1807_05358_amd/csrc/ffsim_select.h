@@ -9,12 +9,15 @@ namespace ffsim {
 typedef void (*batch_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const uint32_t*, const uint32_t*, const uint2*,
                                uint32_t, u64*, Counters*, unsigned char*, size_t, const uint16_t*, uint32_t);
 typedef void (*chain_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, unsigned char*, size_t,
-                               uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, uint32_t*, SearchDev, uint32_t);
+                               uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, uint32_t*, SearchDev, uint32_t, SpareBlocks);
 typedef void (*try_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const unsigned char*, size_t,
                              uint32_t, uint32_t, const uint32_t*, uint32_t, u64*, const uint32_t*, uint32_t*, unsigned char*, size_t, const uint32_t*, uint32_t);
 
 typedef void (*loop_kernel_t)(SimDev, const DOp*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const uint2*,
                               uint32_t, u64*, Counters*, unsigned char*, size_t, const DEdge*, const uint16_t*);
+
+typedef void (*nodes_kernel_t)(SimDev, const DOp*, const DEdge*, const DEdge*, const OpLite*, const EdgeLite*, const uint32_t*, const uint32_t*, const uint2*,
+                               const uint32_t*, uint32_t, u64*, NodeSlots);
 
 // kernels on kept set-up: where the state lives, shape of the queue, lanes per row, (batch) per-candidate counters
 struct LoopChoice {
@@ -25,6 +28,7 @@ struct LoopChoice {
 template <int EXT, int GPN> loop_kernel_t loop_kernels(const LoopChoice& k);
 template <int EXT, int GPN> chain_kernel_t loop_chain_kernels(const LoopChoice& k);
 template <int EXT, int GPN> try_kernel_t loop_try_kernels(const LoopChoice& k);
+template <int EXT, int GPN> nodes_kernel_t loop_nodes_kernels(const LoopChoice& k);
 
 // What fixes the instantiation inside one object.  Batch kernels: four layouts -- task words in
 // LDS (small graphs; never a queue level 2; up to 64 ops the whole queue in a register, with a

@@ -126,7 +126,7 @@ __global__ void k_zero_words(uint32_t* p, uint32_t n) {
 // ---- forced mutations in segments (chain_segment) ------------------------------------------
 //
 // The blocks of a new chain set: bookkeeping and tags of endTimes empty (clear_bytes from clear_at on, both multiples of 16), the strategies at the
-// heads of the first C blocks.  One workgroup per block.
+// heads of the first C blocks (0: spare blocks, without one).  One workgroup per block.
 __global__ __launch_bounds__(256) void k_chain_blocks(unsigned char* __restrict__ chain_mem, size_t chain_stride, size_t clear_at, size_t clear_bytes,
                                                       const uint2* __restrict__ strategies, uint32_t n_ops, uint32_t C, uint32_t* __restrict__ chain_flags) {
     unsigned char* block = chain_mem + (size_t)blockIdx.x * chain_stride;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) void k_chain_blocks(unsigned char* __restrict_
 // timelines of the blocks belong to other strategies from then on.  One workgroup per chain; the mutations are applied in order by one lane.
 __global__ __launch_bounds__(256) void k_chain_split(SimDev S, unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps,
                                                      uint32_t rowl, uint32_t C, uint32_t n_segs, const uint32_t* __restrict__ muts,
-                                                     uint32_t n_steps, uint32_t* __restrict__ chain_flags) {
+                                                     uint32_t n_steps, uint32_t* __restrict__ chain_flags, SpareBlocks spare) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     uint2* cfgs = (uint2*)lds_raw;                       // [n_ops]
     constexpr uint32_t FEW = 256;
@@ -154,15 +154,15 @@ __global__ __launch_bounds__(256) void k_chain_split(SimDev S, unsigned char* __
     if (t == 0) poisoned = chain_flags[c];
     __syncthreads();
     for (uint32_t p = 0; p < n_segs; p++) {
-        const ChainSeg seg = chain_segment(p * C + c, C, n_segs, n_steps);
-        const ChainMem cm = carve_chain(chain_mem + (size_t)seg.blk * chain_stride, S, n_snaps, rowl);
+        const ChainSeg seg = chain_segment(p * C + c, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
+        const ChainMem cm = carve_chain(seg.block, S, n_snaps, rowl);
         for (uint32_t i = t; i < S.n_ops; i += 256) cm.cfgs[i] = cfgs[i];
         if (t == 0) {
             cm.meta->step = step;
             cm.meta->n_valid = 0;
             cm.meta->stale = 1;
             cm.meta->cur_ns = RESULT_INVALID;
-            chain_flags[seg.blk] = poisoned;
+            *seg.flag = poisoned;
         }
         for (uint32_t s = seg.s_begin; s < seg.s_end; s += FEW) {
             const uint32_t n = seg.s_end - s < FEW ? seg.s_end - s : FEW;
