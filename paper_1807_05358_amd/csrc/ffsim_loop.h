@@ -324,6 +324,34 @@ __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState
     }
     queue_clear(st.q);
     st.E = 0;
+    if constexpr (ROWL == 16 && Q != Q_SLOT && !SimX::kTrain) {
+        if (fill) {
+            uint32_t own = lane;
+            asm volatile("" : "+v"(own));         // (see kept_edges16)
+            for (uint32_t t = own; t < n_ops * 16; t += WAVE) mem.words[t] = 0;
+            wave_sync();
+            kept_edges16(m, [&](uint32_t eid) { return mem.rows + (size_t)mem.edge_lite[eid].row * 16; }, mem.words);
+            wave_sync();
+            // the tasks, four ops at a time
+            const uint32_t k = own & 15u, g = own >> 4;
+            for (uint32_t base = 0; base < n_ops; base += 4) {
+                const bool live = base + g < n_ops;
+                const uint32_t j = live ? base + g : n_ops - 1;
+                const uint32_t parts = unpack_cfg_lane(m.cfg_raw(j)).parts;
+                const uint32_t pending = (uint32_t)mem.words[(size_t)j * 16 + k];
+                const bool task = live && k < parts;
+                const u64 w = !task ? W_NONE : (pending == 0 ? 1ull : (W_WAIT | ((u64)pending << 48)));
+                wave_sync();
+                if (live) mem.words[(size_t)j * 16 + k] = w;
+                const u64 now_m = ballot(w == 1ull);
+                const uint32_t mine = own - base;              // op `lane` is the mine-th of these four
+                if (mine < 4 && ((uint32_t)(now_m >> (16 * mine)) & 0xffffu)) st.q.key = 1u;
+                cnt.n_compute += __popcll(ballot(task));
+            }
+            wave_sync();
+            return;
+        }
+    }
     uint2 sc = make_uint2(0, 0);                    // configurations of the producers of the next 64 in-edges
     uint32_t seid = 0, ssrc = 0;                    // their edge ids and producers
     for (uint32_t base = 0; base < n_ops; base += WAVE) {
