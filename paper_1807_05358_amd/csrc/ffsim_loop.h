@@ -114,8 +114,8 @@ __device__ __forceinline__ void queue_spill(const LoopMem& mem, LoopState& st, u
     if ((uint32_t)lane_id() == slot) { q.key = key; q.op = j; }
 }
 
-// gives op j the event `key` if it is earlier than what it has (it may end up on the spill list: only with n_spill > 0)
-template <int Q, int ROWL>
+// gives op j the event `key` if it is earlier than what it has (it may end up on the spill list: only with n_spill > 0).  LEAN: see run_loop
+template <int Q, int ROWL, bool LEAN = false>
 __device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
     Queue& q = st.q;
     if (Q != Q_SLOT) {
@@ -123,23 +123,33 @@ __device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, 
         q.key = k < q.key ? k : q.key;
         return;
     }
-    u64 at = ballot(q.op == j);
-    if (!at) {
-        if (q.n_spill) {
-            // on the spill list already?
-            for (uint32_t b = 0; b < q.n_spill; b += WAVE) {
-                const uint32_t t = b + lane_id();
-                const u64 hit = ballot(t < q.n_spill && mem.spill_op[t < q.n_spill ? t : 0] == j);
-                if (hit) {
-                    const uint32_t at_t = b + __builtin_ctzll(hit);
-                    const u64 word = key >= KEY_FAR ? op_min_word<ROWL>(mem.words, j) : 2 * st.E + key;
-                    if (lane_id() == 0 && word < mem.spill_key[at_t]) mem.spill_key[at_t] = word;
-                    wave_sync();
-                    spill_scan(mem, q);
-                    return;
-                }
+    // on the spill list already?
+    auto spilled = [&]() __attribute__((always_inline)) {
+        for (uint32_t b = 0; b < q.n_spill; b += WAVE) {
+            const uint32_t t = b + lane_id();
+            const u64 hit = ballot(t < q.n_spill && mem.spill_op[t < q.n_spill ? t : 0] == j);
+            if (hit) {
+                const uint32_t at_t = b + __builtin_ctzll(hit);
+                const u64 word = key >= KEY_FAR ? op_min_word<ROWL>(mem.words, j) : 2 * st.E + key;
+                if (lane_id() == 0 && word < mem.spill_key[at_t]) mem.spill_key[at_t] = word;
+                wave_sync();
+                spill_scan(mem, q);
+                return true;
             }
         }
+        return false;
+    };
+    // its slot, else the first free one
+    u64 at = ballot(q.op == j);
+    if (LEAN) {
+        const u64 open = ballot(q.op == NO_OP);
+        if (__builtin_expect(at == 0 && (q.n_spill != 0 || open == 0), 0)) {
+            if (spilled()) return;
+            if (!open) { queue_spill<ROWL>(mem, st, j, key); return; }
+        }
+        at = at ? at : open & (0 - open);
+    } else if (!at) {
+        if (q.n_spill && spilled()) return;
         at = ballot(q.op == NO_OP);
         if (!at) { queue_spill<ROWL>(mem, st, j, key); return; }
         at &= 0 - at;
@@ -474,13 +484,27 @@ __device__ __forceinline__ uint32_t pair_product(u16x2 v) {
     asm("v_mul_u32_u24_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(r) : "v"(v));
     return r;
 }
+// Nothing is moved across: loads asked for above are all on their way before the first of them is waited for below.
+__device__ __forceinline__ void in_flight() { __builtin_amdgcn_sched_barrier(0); }
+// a distance in 32 bits, all ones where it does not fit (LEAN: the high half is looked at by itself; a comparison of all 64 bits wants its bound in
+// two scalar registers, and the loop has none to spare)
+template <bool LEAN>
+__device__ __forceinline__ uint32_t near_u32(u64 d) {
+    uint32_t hi = (uint32_t)(d >> 32);
+    if (LEAN) asm("" : "+v"(hi));
+    return hi ? KEY_NONE : (uint32_t)d;
+}
 // n + 1 on the lanes of a mask
 __device__ __forceinline__ uint32_t count_lanes(uint32_t n, u64 mask) {
     asm("v_addc_co_u32 %0, vcc, 0, %0, %1" : "+v"(n) : "s"(mask) : "vcc");
     return n;
 }
+// Behind a rarely taken branch with loads: nothing is in flight where it joins the main path, which would otherwise wait there for
+// whatever this branch may have left in the air -- and with it for the stores of the step before.
+__device__ __forceinline__ void vector_loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 // a uniform value the compiler is not to recompute (or to move into a branch of its own)
 __device__ __forceinline__ uint32_t opaque(uint32_t uniform) { asm("" : "+s"(uniform)); return uniform; }
+__device__ __forceinline__ u64 opaque64(u64 uniform) { asm("" : "+s"(uniform)); return uniform; }
 // LDS addresses as numbers
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 __device__ __forceinline__ uint32_t lds_addr(uint32_t* p) { return (uint32_t)(uintptr_t)(lds_u32*)p; }
@@ -509,6 +533,9 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
     return __builtin_elementwise_sub_sat(hi, lo);
 }
 
+// what a release has of an edge in registers: the consumer's words, the kept rows of both sides
+struct EdgeLoad { u64 w; uint32_t f, clo, chi, plo, phi, clo2, chi2, plo2, phi2, sortw; };
+
 // Algorithm 1 from the current state to the end.  RECORD, REG, STATS as for run_events; Q: LoopQueue; ROWL: lanes per row.
 // Returns 0, RUN_CONVERGED, RESULT_RETRY or a RESULT_* code.
 //
@@ -521,11 +548,17 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
 // ResNet-101-shaped 20.2 -> 13.9, 1024 x NMT-shaped 98.6 -> 67.9, 1024 x AlexNet-shaped 0.227 -> 0.183; general
 // strategies (777 x ResNet-101-shaped on 5 x 3 devices) 30.9 -> 22.1; training iterations (1024 x Inception-v3-shaped)
 // 24.3 -> 16.4.
+// LEAN (kernels without the refinements): what keeps the compiler from waiting for one load before it asks for the next (in_flight; left to itself it does
+// now and then, which costs a trip to memory per step, 3 to 7 % of a batch), the first edge of a release asked for as soon as it is known that there is one,
+// and a few forms that need fewer scalar registers.  4096 x Inception-v3-shaped 7.17 -> 6.98 ms, 4096 x ResNet-101-shaped 13.88 -> 13.46, 1024 x
+// NMT-shaped 68.5 -> 67.2, 1024 x AlexNet-shaped 0.196 -> 0.191 (with the set-up of four edges at a time 0.188).  With the refinements the same costs 1 to 2 % (their loops have fewer registers
+// left), so they keep the plain forms.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
 template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX>
 __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec) {
     static_assert(!(REG && L64), "64-bit link rows go with the general form");
     constexpr bool RUNS = Q == Q_SLOT;       // runs of events (see run_events): on graphs of more than 64 ops
+    constexpr bool LEAN = !SimX::kExt;
     typedef typename std::conditional<L64, u64, uint32_t>::type T;      // times of transfers: absolute, or relative to the epoch
     const uint32_t lane = lane_id();
     PROF_DECL
@@ -579,6 +612,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 queue_unspill<ROWL>(mem, st);
                 kmin = wave_min_u32(q.key);
             }
+            if (LEAN) vector_loads_done();
         }
         if (RECORD) {
             // the state before the first event at or after a multiple of `step` is a snapshot
@@ -609,7 +643,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         const uint4 h = mem.hdr[i];
         const uint4* lite_at = (const uint4*)mem.op_lite + 2 * (size_t)vector_copy(i);
         const uint4 lite0 = lite_at[0], lite1 = lite_at[1];
+        if (LEAN) in_flight();
         const uint32_t other_key = keys_min(lanes_of(at) ? KEY_NONE : q.key);
+        if (LEAN) in_flight();
         uint32_t next_kmin = other_key;
         const uint32_t exe = first_u32(h.x), offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
         OpCfg ci;
@@ -618,20 +654,41 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         lite.out_begin = first_u32(lite0.x); lite.out_end = first_u32(lite0.y); lite.param_bytes = first_u32(lite0.z);
         lite.first.word = first_u32(lite1.x); lite.first.in_pos = SimX::kOvr ? first_u32(lite1.y) : 0u; lite.first.row = first_u32(lite1.z);
         const uint32_t out_begin = lite.out_begin, out_end = lite.out_end;
+        // What a release needs of an edge: the consumer's words and the kept rows of both sides.
+        auto load_edge = [&](const EdgeLite& lit, uint32_t ei) __attribute__((always_inline)) {
+            const uint32_t j = lit.word & EL_DST;
+            const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
+            if (SimX::kOvr && mem.priv) {
+                // a trial mutation's own edges have rows of their own
+                if (i == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (ei - out_begin)) * (KEPT_ROWS * ROWL);
+                else if (j == m.ov_op) row = mem.priv + (size_t)lit.in_pos * (KEPT_ROWS * ROWL);
+            }
+            const uint32_t* p = row + (ROWL < WAVE ? (lane & (ROWL - 1)) : lane);
+            EdgeLoad v;
+            v.w = load_word<ROWL>(words, j);
+            v.f = p[KR_F * ROWL]; v.clo = p[KR_CLO * ROWL]; v.chi = p[KR_CHI * ROWL]; v.plo = p[KR_PLO * ROWL]; v.phi = p[KR_PHI * ROWL];
+            v.clo2 = 0; v.chi2 = 0; v.plo2 = 0; v.phi2 = 0; v.sortw = 0;
+            if (lit.word & EL_FOUR) { v.clo2 = p[KR_CLO2 * ROWL]; v.chi2 = p[KR_CHI2 * ROWL]; v.plo2 = p[KR_PLO2 * ROWL]; v.phi2 = p[KR_PHI2 * ROWL]; }
+            if (!REG) v.sortw = p[KR_SORT * ROWL];
+            if (LEAN) in_flight();
+            return v;
+        };
+        // (from memory the first edge's are asked for now, and are there when it has been found out which parts are released)
+        constexpr bool EARLY = LEAN && Q == Q_SLOT;
+        EdgeLite lit = lite.first;
+        EdgeLoad ed;
         const uint32_t dev_p = m.template device_of<REG>(i, ci);
         PROF_MARK(1)
         PROF_VMWAIT(2)
         // distance of every event of the op from the popped one (words that are no events: all ones, an odd value)
-        uint32_t d;
-        {
-            const u64 dd = k0 - K;
-            d = (uint32_t)(dd >> 32) ? KEY_NONE : (uint32_t)dd;
-        }
+        uint32_t d = near_u32<LEAN>(k0 - K);
         const u64 mask_same = ballot(d == 0);
         if (!mask_same) { cnt.exit_code = 2; return RESULT_INTERNAL; }
+        if (EARLY && !(kmin & 1) && out_end > out_begin) ed = load_edge(lit, out_begin);
         cnt.n_events++;
         u64 mask = mask_same;
-        bool mixed = false;
+        // events at several times (asked anew where it matters: kept, the answer would be a lane mask)
+        auto mixed = [&]() __attribute__((always_inline)) { return RUNS && (LEAN ? opaque64(mask & ~mask_same) != 0 : mask != mask_same); };
         if (RUNS && ((kmin & 1) ? REG : (out_end - out_begin == 1 && !(SimX::kExt && S.sync)))) {
             const u64 kind_m = ballot((d & 1u) == 0u);
             if (kind_m != mask_same) {
@@ -640,17 +697,16 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                     const u64 s = q.spill_min - K;
                     if (s < bound) bound = (uint32_t)s;
                 }
-                const bool is_odd = (d & 1u) && d != KEY_NONE;
-                if (ballot(is_odd)) {
-                    const uint32_t odd = part_min_u32<ROWL>(is_odd ? d : KEY_NONE);
+                const u64 odd_m = ~kind_m & ballot(d != KEY_NONE);
+                if (odd_m) {
+                    const uint32_t odd = part_min_u32<ROWL>(lanes_of(odd_m) ? d : KEY_NONE);
                     bound = odd < bound ? odd : bound;
                 }
                 const uint32_t e = (kmin & 1) ? exe : next_exe;
                 const uint32_t first_new = e >= RUN_SPAN / 2 ? RUN_SPAN : 2 * e;
                 bound = first_new < bound ? first_new : bound;
                 if (RECORD && snap_key < KEY_FAR) { const uint32_t s = snap_key - kmin; bound = s < bound ? s : bound; }
-                mask = mask_same | ballot((d & 1u) == 0u && d < bound);
-                mixed = mask != mask_same;
+                mask = mask_same | (kind_m & ballot(d < bound));
             }
         }
         const bool in_mask = lanes_of(mask);
@@ -673,9 +729,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             const bool releases = out_end > out_begin || (SimX::kExt && S.sync && lite.param_bytes != 0);
             const u64 w = end << 1;
             if (releases) {
-                const u64 dd = w - K;
-                const uint32_t dn = (uint32_t)(dd >> 32) ? KEY_NONE : (uint32_t)dd;
-                d_new = in_mask ? dn : d;
+                d_new = in_mask ? near_u32<LEAN>(w - K) : d;
             } else {
                 d_new = in_mask ? KEY_NONE : d;
             }
@@ -689,7 +743,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             // first brought into that order (lane t then stands for the t-th part).
             uint32_t order = lane;
             u64 parts_m = mask;
-            if (mixed) {
+            if (mixed()) {
                 uint32_t rank = 0;
                 u64 t = mask;
                 while (t) {
@@ -704,7 +758,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 parts_m = __popcll(mask) == 64 ? ~0ull : (1ull << __popcll(mask)) - 1;
             }
             uint32_t now_v = (kmin + d) >> 1, dev_v = dev_p;
-            if (mixed) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
+            if (mixed()) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
             // REG: what a pass needs of its producer part, ready to be read out of the part's lane
             const uint32_t node_v = m.node_of(dev_v);
             const uint32_t near_at_v = lds_addr(mem.lrow) + 4 * (dev_v * G), far_at_v = lds_addr(mem.lrow) + 4 * (S.n_nodes * G * G + node_v * S.n_nodes);
@@ -715,29 +769,22 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 lits = ((const uint4*)mem.edge_lite)[t];
             };
             if (out_end - out_begin > 1) load_lits(out_begin);
-            for (uint32_t ei = out_begin; ei < out_end; ei++) {
-                EdgeLite lit = lite.first;
-                if (ei != out_begin) {
-                    const uint32_t l = (ei - out_begin) & (WAVE - 1);
-                    if (l == 0) load_lits(ei);
-                    lit.word = readlane_u32(lits.x, l);
-                    lit.in_pos = SimX::kOvr ? readlane_u32(lits.y, l) : 0u;
-                    lit.row = readlane_u32(lits.z, l);
-                }
+            auto next_edge = [&](uint32_t ei) __attribute__((always_inline)) {
+                const uint32_t l = (ei - out_begin) & (WAVE - 1);
+                if (l == 0) load_lits(ei);
+                lit.word = readlane_u32(lits.x, l);
+                lit.in_pos = SimX::kOvr ? readlane_u32(lits.y, l) : 0u;
+                lit.row = readlane_u32(lits.z, l);
+            };
+            // (LEAN: without parameter traffic only ops with an edge have anything to release, so there is a first one)
+            for (uint32_t ei = out_begin; LEAN || ei < out_end; ei++) {
+                if (!LEAN && ei != out_begin) next_edge(ei);
+                if (!EARLY) ed = load_edge(lit, ei);
                 const uint32_t el = lit.word;
                 const uint32_t j = el & EL_DST;
-                const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
-                if (SimX::kOvr && mem.priv) {
-                    // a trial mutation's own edges have rows of their own
-                    if (i == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (ei - out_begin)) * (KEPT_ROWS * ROWL);
-                    else if (j == m.ov_op) row = mem.priv + (size_t)lit.in_pos * (KEPT_ROWS * ROWL);
-                }
-                const uint32_t* p = row + (ROWL < WAVE ? (lane & (ROWL - 1)) : lane);
-                uint32_t f = 0, clo = 0, chi = 0, plo = 0, phi = 0, clo2 = 0, chi2 = 0, plo2 = 0, phi2 = 0, sortw = 0;
-                u64 w = load_word<ROWL>(words, j);
-                f = p[KR_F * ROWL]; clo = p[KR_CLO * ROWL]; chi = p[KR_CHI * ROWL]; plo = p[KR_PLO * ROWL]; phi = p[KR_PHI * ROWL];
-                if (el & EL_FOUR) { clo2 = p[KR_CLO2 * ROWL]; chi2 = p[KR_CHI2 * ROWL]; plo2 = p[KR_PLO2 * ROWL]; phi2 = p[KR_PHI2 * ROWL]; }
-                if (!REG) sortw = p[KR_SORT * ROWL];
+                const u64 w = ed.w;
+                const uint32_t f = ed.f, sortw = ed.sortw;
+                uint32_t clo = ed.clo, chi = ed.chi, plo = ed.plo, phi = ed.phi, clo2 = ed.clo2, chi2 = ed.chi2, plo2 = ed.plo2, phi2 = ed.phi2;
                 if (ROWL < WAVE) {
                     // (no part there: an empty range)
                     chi = lane < (uint32_t)ROWL ? chi : 0u;
@@ -772,7 +819,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 PROF_MARK(4)
                 PROF_VMWAIT(5)
 
-                if (mixed) {
+                if (mixed()) {
                     plo = gather_u32(plo, order); phi = gather_u32(phi, order);
                     if (el & EL_FOUR) { plo2 = gather_u32(plo2, order); phi2 = gather_u32(phi2, order); }
                 }
@@ -937,11 +984,16 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                         if constexpr (L64) { const u64 r = ready - st.E; rel = r >= KEY_FAR ? KEY_FAR : (uint32_t)r; }
                         const uint32_t first = part_min_of<ROWL>(rel, ready_m);
                         const uint32_t key = first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1;
-                        queue_insert<Q, ROWL>(mem, st, j, key);
+                        queue_insert<Q, ROWL, LEAN>(mem, st, j, key);
                         next_kmin = key < next_kmin ? key : next_kmin;
                     }
                 }
                 PROF_MARK(7)
+                if (LEAN) {
+                    if (ei + 1 >= out_end) break;
+                    next_edge(ei + 1);
+                    if (EARLY) ed = load_edge(lit, ei + 1);
+                }
             }
             // (chains: code that inputs without parameters do not run is laid out behind the rest -- 64 chains x 16 changes with unequal links on the
             // AlexNet-shaped graph 3.42 -> 3.32 ms, and 0.5 % less with parameters; in batches it costs 1 % with parameters and gives nothing)
