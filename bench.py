@@ -549,8 +549,8 @@ def main():
                            "median_start_ns": float(np.median(start)), "median_best_ns": float(np.median(best_ns))})
             ch.close()
         line["search"] = search
-        # one chain is one wavefront in ff_sim_search; ff_sim_search_ahead simulates the proposals of the coming
-        # steps side by side (the same chain, step for step).  It pays when few proposals are accepted.
+        # one chain: ff_sim_search ("one_by_one"; it prices a tree of the steps to come) and ff_sim_search_ahead, which
+        # simulates the proposals of the coming steps against the current strategy (the same chain, step for step).
         few = []
         for cid, n_steps, start_kind in ((1, 4000, "data parallelism"), (1, 2000, "random strategy"), (2, 600, "data parallelism")):
             if cid not in results:

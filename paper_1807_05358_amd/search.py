@@ -43,8 +43,8 @@ def find_strategy(sim: B.Simulator, ops, machine, max_parts, choices, n_chains=6
                   accept_scale=None, n_buckets=256, seed=1, start=None, ahead=0) -> SearchResult:
     """runs n_chains independent Markov chains for `steps` steps each and returns the best
     strategy any of them has seen.  `start`: [n_chains][n_ops] starting strategies (default: see
-    starting_strategies).  `ahead`: with few chains, let ff_sim_search_ahead simulate up to that many
-    proposals per chain side by side (the same chains, step for step; only faster)."""
+    starting_strategies).  `ahead`: let ff_sim_search_ahead simulate up to that many proposals per chain
+    side by side (the same chains, step for step; slower than 0 wherever ff_sim_search itself looks ahead: see ff_sim.h)."""
     if accept_scale is None:
         # one op moves the iteration time by about its share of it: the tolerance follows the number of ops
         accept_scale = 0.25 / max(1, len(ops))
