@@ -985,7 +985,7 @@ static void get_tree(ff_chains* c) {
     if (n < (uint64_t)AHEAD_LEAST * c->C) return;
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t a = at; at = (at + bytes + 255) & ~(size_t)255; return a; };
-    const size_t slots = take(more * ns.bytes), nodes = take(n * sizeof(AheadNode)), times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)),
+    const size_t slots = take(more * ns.bytes), nodes = take((size_t)c->C * MAX_TREE * sizeof(AheadNode)), times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)),
                  counters = take(AHEAD_RING * 2 * 4), tree = take((size_t)c->C * 8), done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
     c->d_tree = get_memory(at);
     if (!c->d_tree) return;

@@ -29,7 +29,7 @@ constexpr uint32_t MAX_TREE = 63;            // nodes of a chain in one round: a
 constexpr uint32_t AHEAD_RING = 4;           // rounds whose counters are kept
 
 struct AheadDev {
-    AheadNode* nodes;        // [capacity]
+    AheadNode* nodes;        // [C][MAX_TREE]: a chain's tree is its own, since the chains walk side by side and some lay out their next tree while others still read theirs
     u64* ns;                 // [capacity] simulated time of every node
     uint2* strategies;       // [capacity][n_ops]
     uint32_t* counters;      // [AHEAD_RING][2]: chains with a tree, slots given out
@@ -52,6 +52,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     ChainMeta meta = *cm.meta;
     const bool poisoned = first_u32(chain_flags[c]) != 0;
     u64 best = first_u64(search.best_ns[c]), cur = first_u64(meta.cur_ns), idle = first_u64(meta.idle_steps);
+    AheadNode* mine = ah.nodes + (size_t)c * MAX_TREE;
     auto keep_best = [&]() {
         best = cur;
         __threadfence_block();
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     if (round) {
         const uint32_t base = first_u32(ah.tree[2 * c]), count = first_u32(ah.tree[2 * c + 1]);
         for (uint32_t k = 0; k < count;) {
-            const AheadNode node = ah.nodes[base + k];
+            const AheadNode node = mine[k];
             const uint32_t at = first_u32(node.step);
             while (pos < at) step_done(cur);                  // steps without a proposal
             if (search.patience && idle >= search.patience) break;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
         if (lane < quota) {
             AheadNode node = tree[lane];
             if (lane >= n) node.chain = NO_NODE;
-            ah.nodes[base + lane] = node;
+            mine[lane] = node;
         }
         if (lane == 0) ah.tree[2 * c] = base;
         // the strategies of the nodes: the chain's, then the proposals on the way down from the root
@@ -144,14 +145,14 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
         __threadfence_block();
         wave_sync();
         if (lane < n) {
-            uint2* mine = ah.strategies + (size_t)(base + lane) * S.n_ops;
+            uint2* strategy = ah.strategies + (size_t)(base + lane) * S.n_ops;
             u64 made = 1ull << lane;
             for (uint32_t k = lane; tree[k].parent != NO_NODE; k = tree[k].parent)
                 if (tree[k].via) made |= 1ull << tree[k].parent;
             // (a node comes after the one above it: in ascending order, so that the last proposal for an op holds)
             for (; made; made &= made - 1) {
                 const AheadNode& node = tree[__builtin_ctzll(made)];
-                mine[node.op] = make_uint2(node.x, node.y);
+                strategy[node.op] = make_uint2(node.x, node.y);
             }
         }
     }

@@ -108,3 +108,38 @@ def test_a_captured_search_after_one_that_looked_ahead(B):
     one.close()
     two.close()
     sim.close()
+
+
+@pytest.mark.parametrize("config_id,C", [(0, 256), (1, 200)])
+def test_chains_that_walk_different_ways(B, config_id, C):
+    """chains side by side that read long paths of their trees, next to chains that are at their next tree already: half of them have settled (long
+    runs of rejections), the others start over (every other proposal taken, the best strategy copied at most steps), two are out"""
+    w = W.workload(config_id)
+    tp, tu = w.search_space()
+    cfg0 = w.strategies(C)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    one, two = B.Chains(sim, cfg0), B.Chains(sim, cfg0)
+    t0 = int(one.start_ns()[0])
+    bucket = max(1, t0 // 4096)
+    table = B.ff_sim_accept_table(500.0 / t0, bucket, 256)
+    over = np.zeros((w.n_ops, C), W.MUT_DT)
+    fresh = W.strategies(w.ops, C, 91, w.machine.n_devices, w.max_parts, w.choices)
+    for ch in (one, two):
+        ch.search_setup(tp, tu, table, bucket, 13)
+    print(f"search: chains that differ, config {config_id}", flush=True)
+    assert np.array_equal(_search(one, 210, 210), _search(two, 210, 7))
+    now = one.best()[1]
+    for s in range(w.n_ops):
+        over[s]["op"] = s
+        over[s]["cfg"] = np.where(np.arange(C) % 2 == 0, now[:, s], fresh[:, s])
+    over["op"][0, [5, 8]] = w.n_ops                  # these name no op: invalid from here on
+    for ch in (one, two):
+        ch.delta(ch.upload_mutations(over), w.n_ops)
+    for call in range(3):
+        got, want = _search(one, 70, 70), _search(two, 70, 7)
+        assert np.array_equal(got, want), np.argwhere(got != want)[:3]
+        (a_ns, a), (b_ns, b) = one.best(), two.best()
+        assert np.array_equal(a_ns, b_ns) and a.tobytes() == b.tobytes()
+    one.close()
+    two.close()
+    sim.close()
