@@ -21,9 +21,9 @@
 
 namespace ffsim {
 
-// parent: slot of the node above (NO_NODE: root), via: 1 if this node supposes that it was taken; child: numbers within the
+// parent: the node above in the chain's tree (NO_NODE: root), via: 1 if this node supposes that it was taken; child: numbers within the
 // chain's tree of the nodes after this one was taken (low half) and not (high half), 0xffff where there is none
-struct AheadNode { uint32_t chain, parent, via, step, op, x, y, child; };
+struct AheadNode { uint32_t parent, via, step, op, x, y, child; };
 constexpr uint32_t NO_NODE = 0xffffffffu;
 constexpr uint32_t MAX_TREE = 63;            // nodes of a chain in one round: a lane per node and one more for what may come next
 constexpr uint32_t AHEAD_RING = 4;           // rounds whose counters are kept
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
             if (!top) break;
             const int l = __builtin_ctzll(ballot(chance == top));
             const uint32_t n_up = readlane_u32(up, l), n_via = readlane_u32(via, l), n_t = readlane_u32(t, l);
-            const AheadNode node{c, n_up, n_via, pos + n_t, readlane_u32(op, n_t), readlane_u32(cfg.x, n_t), readlane_u32(cfg.y, n_t), NO_NODE};
+            const AheadNode node{n_up, n_via, pos + n_t, readlane_u32(op, n_t), readlane_u32(cfg.x, n_t), readlane_u32(cfg.y, n_t), NO_NODE};
             if (lane == 0) {
                 tree[n] = node;
                 if (n_up != NO_NODE) tree[n_up].child = n_via ? (tree[n_up].child & 0xffff0000u) | n : (tree[n_up].child & 0xffffu) | (n << 16);
@@ -128,14 +128,11 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
         }
         wave_sync();
         uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&ah.counters[(round % AHEAD_RING) * 2 + 1], quota);
+        // (a slot per node and no more: whatever a slot holds is simulated, and the round lasts as long.  What the quotas add up to does not exceed
+        // the capacity: no more chains have a tree than in the round before)
+        if (lane == 0) base = atomicAdd(&ah.counters[(round % AHEAD_RING) * 2 + 1], n);
         base = first_u32(base);
-        // (what the quotas add up to does not exceed the capacity: no more chains have a tree than in the round before)
-        if (lane < quota) {
-            AheadNode node = tree[lane];
-            if (lane >= n) node.chain = NO_NODE;
-            mine[lane] = node;
-        }
+        if (lane < n) mine[lane] = tree[lane];
         if (lane == 0) ah.tree[2 * c] = base;
         // the strategies of the nodes: the chain's, then the proposals on the way down from the root
         for (uint32_t i = lane; i < S.n_ops; i += WAVE) {
