@@ -153,6 +153,12 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
             }
         }
     }
+    // (the timeline of a chain that has moved is recorded anew behind the last round: with snapshots as far apart as chain_steps wants them for the
+    // time the chain has now, or the run would drop them again)
+    if (meta.moved) {
+        const u64 ideal = (2 * cur) / n_snaps + 1;
+        if (ideal * 2 < meta.step || ideal > meta.step * 2) meta.step = ideal;
+    }
     if (lane == 0) {
         ah.tree[2 * c + 1] = n;
         ah.done[c] = pos;

@@ -184,3 +184,28 @@ def test_only_the_nodes_of_a_tree_are_simulated(B):
         ch.close()
     sim.close()
     assert took[1] < 1.7 * took[0], took
+
+
+@pytest.mark.parametrize("form,C", [("alexnet", 2), ("inception", 2)])
+def test_snapshots_follow_the_time_a_search_has_reached(B, form, C):
+    """a search that more than halves the time leaves a timeline that the next change resumes from"""
+    ops, edges, mach, cost, kw, choices = _setup(form, 1)
+    parts = cost.shape[1]
+    cfg0 = W.strategies(ops, C, 3, mach.n_devices, parts, choices)
+    sim = B.Simulator(ops, edges, mach, cost, **kw)
+    ch = B.Chains(sim, cfg0)
+    start = ch.start_ns().copy()
+    t0 = int(np.median(start))
+    bucket = max(1, t0 // 4096)
+    tp, tu = W.search_space(ops, parts, choices)
+    ch.search_setup(tp, tu, B.ff_sim_accept_table(2000.0 / t0, bucket, 256), bucket, 5)
+    last = ch.search(1500).cpu().numpy().view("<u8")[-1]
+    assert (2 * last < start).all()
+    before = ch.stats()
+    late = np.zeros((1, C), W.MUT_DT)
+    late["op"] = len(ops) - 1
+    late["cfg"] = cfg0[:, -1]
+    ch.delta(ch.upload_mutations(late), 1)
+    assert np.array_equal(ch.stats()["n_resumed"], before["n_resumed"] + 1)
+    ch.close()
+    sim.close()
