@@ -986,7 +986,7 @@ static void get_tree(ff_chains* c) {
     size_t at = 0;
     auto take = [&](size_t bytes) { const size_t a = at; at = (at + bytes + 255) & ~(size_t)255; return a; };
     const size_t slots = take(more * ns.bytes), nodes = take((size_t)c->C * MAX_TREE * sizeof(AheadNode)), times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)),
-                 counters = take(AHEAD_RING * 2 * 4), tree = take((size_t)c->C * 8), done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
+                 counters = take(AHEAD_WORDS * 4), tree = take((size_t)c->C * 8), done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
     c->d_tree = get_memory(at);
     if (!c->d_tree) return;
     c->tree = AheadDev{(AheadNode*)(c->d_tree + nodes), (u64*)(c->d_tree + times), (uint2*)(c->d_tree + strategies), (uint32_t*)(c->d_tree + counters),
@@ -1033,7 +1033,8 @@ static int launch_ahead(ff_chains* c, uint32_t n_steps, uint64_t* d_trace_ns, hi
     const uint32_t rowl = s->chain_choice.rowl;
     const double per_round = std::log2(1.0 + std::min<double>(MAX_TREE, (double)ah.capacity / c->C));
     const uint32_t rounds = (uint32_t)std::min<double>(n_steps, 3.0 + 4.0 / 3.0 * n_steps / per_round);
-    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, st, ah.counters, AHEAD_RING * 2);
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, st, ah.counters, AHEAD_WORDS);
+    hipLaunchKernelGGL(k_search_plan, dim3((c->C + 255) / 256), dim3(256), 0, st, c->d_mem, c->stride, c->meta_at, c->C, c->d_flags, sd, ah.counters + AHEAD_PLAN);
     for (uint32_t r = 0; r <= rounds; r++) {
         hipLaunchKernelGGL(k_search_walk, dim3(c->C), dim3(WAVE), 0, st, s->dev, c->d_mem, c->stride, c->n_snaps, rowl, c->C, n_steps, (u64*)d_trace_ns,
                            c->d_flags, sd, ah, c->node_slots.in_blocks, r);

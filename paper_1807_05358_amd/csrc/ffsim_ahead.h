@@ -32,11 +32,26 @@ struct AheadDev {
     AheadNode* nodes;        // [C][MAX_TREE]: a chain's tree is its own, since the chains walk side by side and some lay out their next tree while others still read theirs
     u64* ns;                 // [capacity] simulated time of every node
     uint2* strategies;       // [capacity][n_ops]
-    uint32_t* counters;      // [AHEAD_RING][2]: chains with a tree, slots given out
+    uint32_t* counters;      // [AHEAD_RING][2]: chains with a tree, slots given out; then what k_search_plan counts
     uint32_t* tree;          // [C][2]: first slot, nodes
     uint32_t* done;          // [C] steps of the call a chain has finished
     uint32_t capacity;
 };
+
+constexpr uint32_t AHEAD_PLAN = AHEAD_RING * 2, AHEAD_WORDS = AHEAD_PLAN + 4;
+
+// a chain whose strategy is valid and whose patience has not run out
+__device__ __forceinline__ bool search_goes_on(const SearchDev& search, const ChainMeta& meta, uint32_t flag) {
+    return flag == 0 && meta.stale == 0 && !(search.patience && meta.idle_steps >= search.patience);
+}
+
+// Is there anything to look ahead at?  Counts the chains that still propose.  If there are none (all have run out of patience, say) there will be no
+// tree, so that no timeline has to be recorded again for its sake: 32 steps of 64 such chains on the ResNet-101-shaped graph 9.9 -> 0.17 ms.
+__global__ __launch_bounds__(256) void k_search_plan(unsigned char* __restrict__ chain_mem, size_t chain_stride, size_t meta_at, uint32_t C,
+                                                     const uint32_t* __restrict__ chain_flags, SearchDev search, uint32_t* __restrict__ plan) {
+    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
+    if (c < C && search_goes_on(search, *(const ChainMeta*)(chain_mem + (size_t)c * chain_stride + meta_at), chain_flags[c])) atomicAdd(&plan[0], 1u);
+}
 
 // One wavefront per chain: the decisions that the round before allows, then the chain's next tree.
 __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps, uint32_t rowl,
@@ -47,7 +62,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     if (c == 0 && lane < 2) ah.counters[((round + 2) % AHEAD_RING) * 2 + lane] = 0;
     uint32_t pos = round ? first_u32(ah.done[c]) : 0u;
     if (pos >= n_steps) return;
-    // (with slots in the chains' blocks every stored timeline is lost, whether its chain moves or not)
+    // (with slots in the chains' blocks every stored timeline is lost, whether its chain moves or not -- if there is to be any tree at all)
     const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, rowl);
     ChainMeta meta = *cm.meta;
     const bool poisoned = first_u32(chain_flags[c]) != 0;
@@ -63,7 +78,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     const bool live = !poisoned && first_u32(meta.stale) == 0;
     if (round == 0 && live) {
         if (cur < best) keep_best();       // the strategy the search starts from counts as seen
-        if (slots_in_blocks) meta.moved = 1;
+        if (slots_in_blocks && first_u32(ah.counters[AHEAD_PLAN])) meta.moved = 1;
     }
     if (round) {
         const uint32_t base = first_u32(ah.tree[2 * c]), count = first_u32(ah.tree[2 * c + 1]);
