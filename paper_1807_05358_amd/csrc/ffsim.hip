@@ -990,7 +990,8 @@ static void get_tree(ff_chains* c) {
     c->d_tree = get_memory(at);
     if (!c->d_tree) return;
     c->tree = AheadDev{(AheadNode*)(c->d_tree + nodes), (u64*)(c->d_tree + times), (uint2*)(c->d_tree + strategies), (uint32_t*)(c->d_tree + counters),
-                       (uint32_t*)(c->d_tree + tree), (uint32_t*)(c->d_tree + done), (uint32_t)n};
+                       (uint32_t*)(c->d_tree + tree), (uint32_t*)(c->d_tree + done), (uint32_t)n,
+                       (float)std::log2(1.0 + std::min<double>(MAX_TREE, (double)n / c->C)), s->chain_choice.lds ? WHOLE / 6.0f : 0.0f};
     ns.more = c->d_tree + slots;
     c->d_tree_out = (u64*)(c->d_tree + out);
 }
@@ -1031,10 +1032,10 @@ static int launch_ahead(ff_chains* c, uint32_t n_steps, uint64_t* d_trace_ns, hi
     const nodes_kernel_t kernel = nodes_kernel(s);
     if (!allow_lds((const void*)kernel, lds)) return FF_EHIP;
     const uint32_t rowl = s->chain_choice.rowl;
-    const double per_round = std::log2(1.0 + std::min<double>(MAX_TREE, (double)ah.capacity / c->C));
-    const uint32_t rounds = (uint32_t)std::min<double>(n_steps, 3.0 + 4.0 / 3.0 * n_steps / per_round);
+    const uint32_t rounds = (uint32_t)std::min<double>(n_steps, 3.0 + 4.0 / 3.0 * n_steps / ah.per_round);
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, st, ah.counters, AHEAD_WORDS);
-    hipLaunchKernelGGL(k_search_plan, dim3((c->C + 255) / 256), dim3(256), 0, st, c->d_mem, c->stride, c->meta_at, c->C, c->d_flags, sd, ah.counters + AHEAD_PLAN);
+    hipLaunchKernelGGL(k_search_plan, dim3(c->C), dim3(PLAN_WAVES * WAVE), 0, st, s->dev, s->d_ops, s->d_in_edges, c->d_mem, c->stride, c->n_snaps, rowl, n_steps,
+                       c->d_flags, sd, ah.counters + AHEAD_PLAN);
     for (uint32_t r = 0; r <= rounds; r++) {
         hipLaunchKernelGGL(k_search_walk, dim3(c->C), dim3(WAVE), 0, st, s->dev, c->d_mem, c->stride, c->n_snaps, rowl, c->C, n_steps, (u64*)d_trace_ns,
                            c->d_flags, sd, ah, c->node_slots.in_blocks, r);
@@ -1045,7 +1046,7 @@ static int launch_ahead(ff_chains* c, uint32_t n_steps, uint64_t* d_trace_ns, hi
     }
     if (hipGetLastError() != hipSuccess) return FF_EHIP;
     const int rc = launch_chain_steps(c, nullptr, 1, (uint64_t*)c->d_tree_out, st, SearchDev{});
-    if (rc || rounds >= n_steps) return rc;
+    if (rc) return rc;
     sd.done = ah.done;
     sd.n_accepted = ah.done + c->C;
     sd.n_ahead = n_steps;

@@ -32,10 +32,13 @@ struct AheadDev {
     AheadNode* nodes;        // [C][MAX_TREE]: a chain's tree is its own, since the chains walk side by side and some lay out their next tree while others still read theirs
     u64* ns;                 // [capacity] simulated time of every node
     uint2* strategies;       // [capacity][n_ops]
-    uint32_t* counters;      // [AHEAD_RING][2]: chains with a tree, slots given out; then what k_search_plan counts
+    uint32_t* counters;      // [AHEAD_RING][2]: chains with a tree, slots given out; then what k_search_plan finds: chains that go on, the
+                             // most that a chain's steps take in turn (1024ths of a simulation), the most proposals
     uint32_t* tree;          // [C][2]: first slot, nodes
     uint32_t* done;          // [C] steps of the call a chain has finished
     uint32_t capacity;
+    float per_round;         // steps that a round takes a chain further where the share of accepted proposals is middling
+    float per_step;          // what a step in turn takes besides its simulation, in 1024ths of one
 };
 
 constexpr uint32_t AHEAD_PLAN = AHEAD_RING * 2, AHEAD_WORDS = AHEAD_PLAN + 4;
@@ -45,12 +48,41 @@ __device__ __forceinline__ bool search_goes_on(const SearchDev& search, const Ch
     return flag == 0 && meta.stale == 0 && !(search.patience && meta.idle_steps >= search.patience);
 }
 
-// Is there anything to look ahead at?  Counts the chains that still propose.  If there are none (all have run out of patience, say) there will be no
-// tree, so that no timeline has to be recorded again for its sake: 32 steps of 64 such chains on the ResNet-101-shaped graph 9.9 -> 0.17 ms.
-__global__ __launch_bounds__(256) void k_search_plan(unsigned char* __restrict__ chain_mem, size_t chain_stride, size_t meta_at, uint32_t C,
-                                                     const uint32_t* __restrict__ chain_flags, SearchDev search, uint32_t* __restrict__ plan) {
-    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
-    if (c < C && search_goes_on(search, *(const ChainMeta*)(chain_mem + (size_t)c * chain_stride + meta_at), chain_flags[c])) atomicAdd(&plan[0], 1u);
+// Is it worth looking ahead?  Counts the chains that still propose, and estimates what the call's steps take in turn (share_from, for the proposals of the
+// first steps) and as a tree (rounds of full simulations and one that is recorded), both for the chain with the most to do.  Without a
+// chain that proposes there will be no tree, so that no timeline has to be recorded again for its sake: 32 steps of 64 such chains on the
+// ResNet-101-shaped graph 9.9 -> 0.17 ms.  Proposals of late ops (the others have no list) resume late in the timeline, and their steps are made in turn where that
+// is less: 16 steps of one chain on the NMT-shaped graph (20 steps unrolled) with lists for the last 3 % of the ops 33 to 60 -> 0.5 to 2.5 ms.  (Graphs simulated in
+// LDS take about a sixth of a simulation per step besides: 64 steps of one chain on the AlexNet-shaped graph, lists for its last three ops, 1.1 ms in turn,
+// 0.6 as a tree.)
+constexpr uint32_t PLAN_STEPS = 64, PLAN_WAVES = 16;
+__device__ __forceinline__ bool worth_looking_ahead(const AheadDev& ah, uint32_t n_steps) {
+    const uint32_t* plan = ah.counters + AHEAD_PLAN;
+    const float scale = n_steps > PLAN_STEPS ? (float)n_steps / PLAN_STEPS : 1.0f;
+    const float rounds = scale * (float)first_u32(plan[2]) / ah.per_round;
+    return scale * (float)first_u32(plan[1]) + ah.per_step * (float)n_steps > (float)WHOLE * ((rounds > 1.0f ? rounds : 1.0f) + 1.0f);
+}
+__global__ __launch_bounds__(PLAN_WAVES * WAVE) void k_search_plan(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ in_edges,
+                                                                   unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps, uint32_t rowl,
+                                                                   uint32_t n_steps, const uint32_t* __restrict__ chain_flags, SearchDev search,
+                                                                   uint32_t* __restrict__ plan) {
+    __shared__ uint32_t share, proposals;
+    const uint32_t c = blockIdx.x;
+    const ChainMem cm = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, rowl);
+    const ChainMeta meta = *cm.meta;
+    if (!search_goes_on(search, meta, chain_flags[c])) return;
+    if (threadIdx.x == 0) { share = 0; proposals = 0; }
+    __syncthreads();
+    for (uint32_t s = first_u32(threadIdx.x / WAVE); s < (n_steps < PLAN_STEPS ? n_steps : PLAN_STEPS); s += PLAN_WAVES) {
+        uint32_t op;
+        uint2 cfg;
+        if (!search_proposal(search, S.n_ops, S.n_dev, c, search.first_step + s, op, cfg)) continue;   // (no list)
+        op = first_u32(op);
+        const uint32_t left = S.ties ? WHOLE : share_from(meta, first_input_at(ops, in_edges, cm, rowl, op));
+        if (lane_id() == 0) { atomicAdd(&share, left); atomicAdd(&proposals, 1u); }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) { atomicAdd(&plan[0], 1u); atomicMax(&plan[1], share); atomicMax(&plan[2], proposals); }
 }
 
 // One wavefront per chain: the decisions that the round before allows, then the chain's next tree.
@@ -60,6 +92,12 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     __shared__ AheadNode tree[WAVE];
     const uint32_t c = blockIdx.x, lane = lane_id();
     if (c == 0 && lane < 2) ah.counters[((round + 2) % AHEAD_RING) * 2 + lane] = 0;
+    const bool any = first_u32(ah.counters[AHEAD_PLAN]) != 0;
+    if (any && !worth_looking_ahead(ah, n_steps)) {
+        // (all steps are left to the launch behind the rounds)
+        if (lane == 0 && round == 0) ah.done[c] = 0;
+        return;
+    }
     uint32_t pos = round ? first_u32(ah.done[c]) : 0u;
     if (pos >= n_steps) return;
     // (with slots in the chains' blocks every stored timeline is lost, whether its chain moves or not -- if there is to be any tree at all)
@@ -78,7 +116,7 @@ __global__ __launch_bounds__(WAVE) void k_search_walk(SimDev S, unsigned char* _
     const bool live = !poisoned && first_u32(meta.stale) == 0;
     if (round == 0 && live) {
         if (cur < best) keep_best();       // the strategy the search starts from counts as seen
-        if (slots_in_blocks && first_u32(ah.counters[AHEAD_PLAN])) meta.moved = 1;
+        if (slots_in_blocks && any) meta.moved = 1;
     }
     if (round) {
         const uint32_t base = first_u32(ah.tree[2 * c]), count = first_u32(ah.tree[2 * c + 1]);

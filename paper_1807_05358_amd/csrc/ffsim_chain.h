@@ -168,6 +168,27 @@ __device__ __forceinline__ uint32_t resume_point(const SimX& m, const u64* end_o
     return (uint32_t)k64;
 }
 
+// The time before which a change of an op cannot matter, as resume_point finds it, for kernels that only estimate what a simulation will take: parts
+// without inputs are not looked for, and the timeline is the stored one, whatever has changed since.  All 64 lanes; row: words per op (64, or lanes per row).
+__device__ __forceinline__ u64 first_input_at(const DOp* __restrict__ ops, const DEdge* __restrict__ in_edges, const ChainMem& cm, uint32_t row, uint32_t op) {
+    const uint32_t ib = ops[op].in_begin, ie = ops[op].in_end;
+    u64 tau = ie > ib ? W_NONE : 0;
+    for (uint32_t q = ib; q < ie; q++) {
+        const uint32_t p = in_edges[q].src;
+        const uint32_t parts = unpack_cfg(cm.cfgs[p]).parts;
+        const u64 t = wave_min_u64((uint32_t)lane_id() < parts && (uint32_t)lane_id() < row ? cm.end_of[(size_t)p * row + lane_id()] : W_NONE);
+        tau = t < tau ? t : tau;
+    }
+    return tau >> 62 ? 0 : tau;
+}
+// what is left of the timeline from the last snapshot before that time, in 1024ths
+constexpr uint32_t WHOLE = 1024;
+__device__ __forceinline__ uint32_t share_from(const ChainMeta& meta, u64 tau) {
+    if (meta.step == 0 || meta.cur_ns == 0 || meta.cur_ns >= TIME_LIMIT) return WHOLE;
+    const u64 gone = (((2 * tau) / meta.step) * meta.step / 2) * WHOLE / meta.cur_ns;
+    return gone < WHOLE ? WHOLE - (uint32_t)gone : 0u;
+}
+
 // A simulation state taken before anything depended on op mo's configuration holds two static
 // things about it: the op's own tasks (all still waiting for all their inputs) and, in its
 // consumers' waiting tasks, how many inputs come from op mo.  Rewrites both, for the new configuration, in n states:

@@ -213,15 +213,7 @@ __global__ __launch_bounds__(TRIALS_PER_BLOCK * WAVE) void k_trial_class(SimDev 
         const ChainMeta meta = *cm.meta;
         k = 0;
         if (!meta.stale && meta.n_valid > 1 && meta.step != 0 && !S.ties) {
-            const uint32_t ib = ops[op].in_begin, ie = ops[op].in_end;
-            u64 tau = ie > ib ? W_NONE : 0;
-            for (uint32_t q = ib; q < ie; q++) {
-                const uint32_t p = in_edges[q].src;
-                const uint32_t parts = unpack_cfg(cm.cfgs[p]).parts;
-                const u64 t = wave_min_u64((uint32_t)lane_id() < parts ? cm.end_of[(size_t)p * row + lane_id()] : W_NONE);
-                tau = t < tau ? t : tau;
-            }
-            const u64 at = tau >> 62 ? 0 : (2 * tau) / meta.step;
+            const u64 at = (2 * first_input_at(ops, in_edges, cm, row, op)) / meta.step;
             const uint32_t last = meta.n_valid - 1 < TRIAL_CLASSES - 1 ? meta.n_valid - 1 : TRIAL_CLASSES - 1;
             k = at < last ? (uint32_t)at : last;
         }

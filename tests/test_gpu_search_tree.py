@@ -238,3 +238,27 @@ def test_chains_that_have_stopped_are_left_alone(B, C):
     ch.close()
     two.close()
     sim.close()
+
+
+def test_proposals_of_late_ops_are_made_in_turn(B):
+    """only the last ten ops have a list: their proposals resume late in the timeline, and 32 steps of them take less than one full simulation.
+    (Measured on the ResNet-101-shaped graph: 0.4 to 1 ms; 9 to 16 where every call looked ahead.)"""
+    w = W.workload(3)
+    n_ops = w.n_ops
+    tp, tu = w.search_space()
+    few_p = np.concatenate([np.zeros(n_ops - 10, "<u4"), tp[n_ops - 10:] - tp[n_ops - 10]]).astype("<u4")
+    cfg0 = w.strategies(1)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    one, two = B.Chains(sim, cfg0), B.Chains(sim, cfg0)
+    t0 = int(one.start_ns()[0])
+    bucket = max(1, t0 // 256)
+    for ch in (one, two):
+        ch.search_setup(few_p, tu[tp[n_ops - 10]:], B.ff_sim_accept_table(50.0 / t0, bucket, 256), bucket, 5)
+    assert np.array_equal(_search(one, 320, 32), _search(two, 320, 7))
+    (a_ns, a), (b_ns, b) = one.best(), two.best()
+    assert np.array_equal(a_ns, b_ns) and a.tobytes() == b.tobytes()
+    d = sim.upload_strategies(cfg0)
+    assert _seconds(lambda: one.search(32)) < 0.5 * _seconds(lambda: sim.batch(d, 1))
+    one.close()
+    two.close()
+    sim.close()
