@@ -359,8 +359,12 @@ int ff_sim_neighbours_noalloc(ff_chains_t* chains, const uint32_t* d_tuple_ptr, 
  * integers back to validate d_tuple_ptr (it synchronises the stream's device).
  * Where the device has room for four simulations per chain or more, calls of 8 steps or more (16 or 32 with many chains) simulate
  * the strategies of steps to come side by side and then follow the path that the decisions take: the same chains, step for
- * step, sooner; the time goes by rounds of full simulations.  The first such call gets up to 1 GiB with hipMalloc for it; calls on a stream that
- * is being captured make their steps in turn.  ff_sim_chains_get_stats counts such steps, not the queue pops of what was simulated for them. */
+ * step, sooner; the time goes by rounds of full simulations.  (Where the proposals resume so late in the timeline that steps in turn take less, they
+ * are made in turn: the estimate is made on the device.)  Such a call puts two launches per round on the stream instead of one in all, about n_steps / 2 for one
+ * chain and up to n_steps with many, so the host is busy for 4 us per launch, and long calls wait where the queue is full; a call in turn returns at once.
+ * The first such call gets memory with hipMalloc for it, 1 GiB at most and no more than a 16th of what is free, and the chain set keeps it
+ * until it is destroyed; calls on a stream that is being captured make their steps in turn, in one launch.  ff_sim_chains_get_stats counts such steps,
+ * not the queue pops of what was simulated for them. */
 typedef struct {
     uint64_t seed;
     uint64_t first_step;

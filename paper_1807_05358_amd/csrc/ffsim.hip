@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "ffsim_select.h"
@@ -957,19 +958,26 @@ int ff_sim_delta(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t n_steps, 
     return launch_chain_steps(c, d_muts, n_steps, d_out_ns, st, SearchDev{}, n_segs);
 }
 
-// Memory for searches that look ahead, got with the first call that has use for it.  Nodes: two wavefronts per SIMD, which take little longer than one, or four where that is what it takes to have four nodes per
+// Searches that look ahead.  Nodes: two wavefronts per SIMD, which take little longer than one, or four where that is what it takes to have four nodes per
 // chain; none with fewer (with chains enough to fill the device steps one after the other cost less).  The nodes of large graphs keep their state
-// where the chains have their snapshots, about eight per chain; few chains get up to TREE_BYTES more.
+// where the chains have their snapshots, about eight per chain; few chains get more as far as the memory that all of this takes stays within TREE_BYTES.
 constexpr uint32_t AHEAD_LEAST = 4;
 constexpr size_t TREE_BYTES = (size_t)1 << 30;
-static void get_tree(ff_chains* c) {
-    ff_sim* s = c->sim;
-    c->tree_asked = true;
-    if (!s->loop) return;
+// fills c->tree and c->node_slots as offsets into an allocation of at most `most` bytes and returns its size; 0: no tree
+static size_t plan_tree(const ff_chains* c, size_t most, AheadDev* tree, NodeSlots* slots, size_t* out_at) {
+    const ff_sim* s = c->sim;
+    if (!s->loop) return 0;
     uint64_t n = std::min<uint64_t>(std::max<uint64_t>(2ull * s->n_simds, (uint64_t)AHEAD_LEAST * c->C), s->max_try_slots_loop);
     n = std::min<uint64_t>(n, (uint64_t)MAX_TREE * c->C);
     const uint32_t rowl = s->chain_choice.rowl;
-    NodeSlots& ns = c->node_slots;
+    NodeSlots ns{};
+    size_t at = 0;
+    auto take = [&](size_t bytes) { const size_t a = at; at = (at + bytes + 255) & ~(size_t)255; return a; };
+    const size_t nodes = take((size_t)c->C * MAX_TREE * sizeof(AheadNode)), counters = take(AHEAD_WORDS * 4), trees = take((size_t)c->C * 8),
+                 done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
+    const size_t per_node = 8 + s->dev.n_ops * sizeof(uint2);            // its time and its strategy
+    if (at + 3 * 256 > most) return 0;
+    size_t left = most - at - 3 * 256;
     uint64_t more = 0;
     if (!s->chain_choice.lds) {
         const ChainLayout cl = chain_layout(s->dev, c->n_snaps, rowl);
@@ -977,23 +985,40 @@ static void get_tree(ff_chains* c) {
         ns.blocks = c->d_mem + cl.snap_words;
         ns.stride = c->stride;
         ns.per_chain = (uint32_t)((cl.snap_free - cl.snap_words) / ns.bytes);
-        const uint64_t in_blocks = std::min<uint64_t>(n, (uint64_t)ns.per_chain * c->C);
+        const uint64_t in_blocks = std::min<uint64_t>(std::min<uint64_t>(n, (uint64_t)ns.per_chain * c->C), left / per_node);
         ns.in_blocks = (uint32_t)in_blocks;
-        more = std::min<uint64_t>(n - in_blocks, TREE_BYTES / ns.bytes);
+        left -= in_blocks * per_node;
+        more = std::min<uint64_t>(n - in_blocks, left / (per_node + ns.bytes));
         n = in_blocks + more;
+    } else {
+        n = std::min<uint64_t>(n, left / per_node);
     }
-    if (n < (uint64_t)AHEAD_LEAST * c->C) return;
-    size_t at = 0;
-    auto take = [&](size_t bytes) { const size_t a = at; at = (at + bytes + 255) & ~(size_t)255; return a; };
-    const size_t slots = take(more * ns.bytes), nodes = take((size_t)c->C * MAX_TREE * sizeof(AheadNode)), times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)),
-                 counters = take(AHEAD_WORDS * 4), tree = take((size_t)c->C * 8), done = take((size_t)c->C * 8), out = take((size_t)c->C * 8);
-    c->d_tree = get_memory(at);
-    if (!c->d_tree) return;
-    c->tree = AheadDev{(AheadNode*)(c->d_tree + nodes), (u64*)(c->d_tree + times), (uint2*)(c->d_tree + strategies), (uint32_t*)(c->d_tree + counters),
-                       (uint32_t*)(c->d_tree + tree), (uint32_t*)(c->d_tree + done), (uint32_t)n,
-                       (float)std::log2(1.0 + std::min<double>(MAX_TREE, (double)n / c->C)), s->chain_choice.lds ? WHOLE / 6.0f : 0.0f};
-    ns.more = c->d_tree + slots;
-    c->d_tree_out = (u64*)(c->d_tree + out);
+    if (n < (uint64_t)AHEAD_LEAST * c->C) return 0;
+    const size_t times = take(n * 8), strategies = take(n * s->dev.n_ops * sizeof(uint2)), more_at = take(more * ns.bytes);
+    ns.more = (unsigned char*)more_at;
+    *tree = AheadDev{(AheadNode*)nodes, (u64*)times, (uint2*)strategies, (uint32_t*)counters, (uint32_t*)trees, (uint32_t*)done, (uint32_t)n,
+                     (float)std::log2(1.0 + std::min<double>(MAX_TREE, (double)n / c->C)), s->chain_choice.lds ? WHOLE / 6.0f : 0.0f};
+    *slots = ns;
+    *out_at = out;
+    return at;
+}
+// Gets the memory with the first call that has use for it; within a 16th of what is free, as ff_sim_delta's.
+static void get_tree(ff_chains* c) {
+    c->tree_asked = true;
+    size_t avail = 0, all = 0, out = 0;
+    if (hipMemGetInfo(&avail, &all) != hipSuccess) { (void)hipGetLastError(); return; }
+    AheadDev t{};
+    NodeSlots ns{};
+    const size_t bytes = plan_tree(c, std::min(TREE_BYTES, avail / 16), &t, &ns, &out);
+    if (!bytes) return;
+    unsigned char* mem = get_memory(bytes);
+    if (!mem) return;
+    auto at = [&](auto*& p) { p = (std::remove_reference_t<decltype(p)>)(mem + (size_t)p); };
+    at(t.nodes); at(t.ns); at(t.strategies); at(t.counters); at(t.tree); at(t.done); at(ns.more);
+    c->d_tree = mem;
+    c->tree = t;
+    c->node_slots = ns;
+    c->d_tree_out = (u64*)(mem + out);
 }
 
 // checks the search parameters and fills what the kernels take of them
@@ -1063,14 +1088,21 @@ int ff_sim_search(ff_chains_t* c, const ff_search_t* p, uint32_t n_steps, uint64
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &capturing) != hipSuccess) return FF_EHIP;
     // (a graph is to hold the search in one node, not in two per round)
-    const bool try_ahead = n_steps >= AHEAD_STEPS && capturing == hipStreamCaptureStatusNone;
-    if (try_ahead && !c->tree_asked) get_tree(c);
+    bool ahead = n_steps >= AHEAD_STEPS && capturing == hipStreamCaptureStatusNone && (!c->tree_asked || c->tree.capacity);
     // What a call costs besides its rounds, one recorded simulation, takes more steps to get back with few nodes per chain: from 16 nodes on 8 steps, with
     // fewer 16, and where the nodes are four to a SIMD 32 (Inception-v3-shaped, chains created and closed included, in turn -> ahead: 20 chains x 8 steps
     // 33.2 -> 24.1 ms, 130 x 8 37.8 -> 37.9, 500 x 16 61.0 -> 50.0, 1024 x 16 65.7 -> 66.5, 1024 x 64 201 -> 171).
-    const uint32_t least = c->tree.capacity > 2 * c->sim->n_simds ? 4 * AHEAD_STEPS : (c->tree.capacity / c->C < 16 ? 2 * AHEAD_STEPS : AHEAD_STEPS);
-    if (!try_ahead || !c->tree.capacity || n_steps < least)
-        return launch_chain_steps(c, nullptr, n_steps, d_trace_ns, st, sd);
+    auto enough = [&](uint32_t nodes) {
+        return nodes && n_steps >= (nodes > 2 * c->sim->n_simds ? 4 * AHEAD_STEPS : (nodes / c->C < 16 ? 2 * AHEAD_STEPS : AHEAD_STEPS));
+    };
+    if (ahead && !c->tree_asked) {
+        AheadDev t{};
+        NodeSlots ns{};
+        size_t out = 0;
+        ahead = plan_tree(c, TREE_BYTES, &t, &ns, &out) && enough(t.capacity);
+        if (ahead) get_tree(c);
+    }
+    if (!ahead || !enough(c->tree.capacity)) return launch_chain_steps(c, nullptr, n_steps, d_trace_ns, st, sd);
     return launch_ahead(c, n_steps, d_trace_ns, st, sd);
 }
 

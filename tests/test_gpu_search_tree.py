@@ -262,3 +262,25 @@ def test_proposals_of_late_ops_are_made_in_turn(B):
     one.close()
     two.close()
     sim.close()
+
+
+@pytest.mark.parametrize("config_id,C,n,most", [(2, 300, 12, 0), (4, 150, 15, 0), (4, 150, 16, 1 << 30)])
+def test_memory_of_searches_that_look_ahead(B, config_id, C, n, most):
+    """none for calls of too few steps to look ahead with that many chains; 1 GiB at most for the others"""
+    import torch
+    w = W.workload(config_id)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    ch = B.Chains(sim, w.strategies(C))
+    t0 = int(np.median(ch.start_ns()))
+    bucket = max(1, t0 // 256)
+    tp, tu = w.search_space()
+    ch.search_setup(tp, tu, B.ff_sim_accept_table(50.0 / t0, bucket, 256), bucket, 5)
+    trace = torch.empty((n, C), dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ch.search(n, d_trace=trace)
+    torch.cuda.synchronize()
+    got = before - torch.cuda.mem_get_info()[0]
+    assert got <= most and (most == 0 or got > most // 2), got
+    ch.close()
+    sim.close()
