@@ -280,8 +280,9 @@ int ff_sim_chains_create(ff_sim_t* sim, const ff_opcfg_t* d_strategies, uint32_t
 /* Applies d_muts[s][c] (step-major, [n_steps][C]) to chain c for s = 0..n_steps-1,
  * cumulatively, and writes the simulated time after every step to d_out_ns[s][c]
  * (FF_INVALID_NS while the chain's strategy is invalid).  The mutations are known beforehand, so from three
- * steps on the steps of a chain are cut into segments that are simulated side by side, as far as the device has room
- * for them; the first step of a segment is a full simulation.  The first such call outside a capture gets the memory for
+ * steps on the steps of a chain may be cut into segments that are simulated side by side, as far as the device has room
+ * for them; the first step of a segment is a full simulation.  Every chain is cut where that is estimated to take less than its steps in turn (from
+ * where the changes matter in the stored timeline: late ones resume there and are made in turn); the estimate is made on the device.  The first such call outside a capture gets the memory for
  * it with hipMalloc, up to 31 blocks of the above size per chain, 8 GiB in all (64 MiB for small graphs) and no more than a 16th of
  * what is free; without it, and in graphs captured before it, the steps are made in turn. */
 int ff_sim_delta(ff_chains_t* chains, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out_ns,

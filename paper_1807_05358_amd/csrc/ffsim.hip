@@ -97,7 +97,7 @@ struct ff_chains {
     size_t stride = 0;             // bytes per chain
     size_t meta_at = 0;            // offset of the ChainMeta record in a chain's block
     unsigned char* d_mem = nullptr; // [C] chain blocks: strategy, task words, endTimes, snapshots
-    uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation
+    uint32_t* d_flags = nullptr;   // [C] nonzero once a chain saw an out-of-range mutation; then [C] segments of the call at hand
     // more blocks [n_spare][C] for the segments of ff_sim_delta, got when they are first wanted, and their flags behind them
     SpareBlocks spare{};
     uint32_t n_spare = 0;
@@ -884,7 +884,7 @@ static void get_spare_blocks(ff_chains* c, hipStream_t st) {
     if (!n) return;
     unsigned char* mem = get_memory(n * (set + (size_t)c->C * 4));
     if (!mem) return;
-    c->spare = SpareBlocks{mem, (uint32_t*)(mem + n * set)};
+    c->spare = SpareBlocks{mem, (uint32_t*)(mem + n * set), c->d_flags + c->C};
     c->n_spare = n;
     const ChainLayout cl = chain_layout(s->dev, c->n_snaps, s->loop ? s->chain_choice.rowl : 0);
     hipLaunchKernelGGL(k_chain_blocks, dim3(n * c->C), dim3(256), 0, st, mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)nullptr, s->dev.n_ops, 0u,
@@ -918,7 +918,7 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     c->meta_at = cl.meta;
     hipStream_t st = (hipStream_t)hip_stream;
     if (hipMalloc((void**)&c->d_mem, (size_t)C * c->stride) != hipSuccess ||
-        hipMalloc((void**)&c->d_flags, (size_t)C * 4) != hipSuccess ||
+        hipMalloc((void**)&c->d_flags, (size_t)C * 8) != hipSuccess ||
         hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
     static_assert(sizeof(ff_opcfg_t) == sizeof(uint2), "strategy layout");
     hipLaunchKernelGGL(k_chain_blocks, dim3(C), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
@@ -931,13 +931,16 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
     return FF_OK;
 }
 
+// what a step of a chain takes besides its simulation, in 1024ths of one: small graphs in LDS (52 of about 95 us on the AlexNet-shaped one), others
+constexpr uint32_t STEP_LDS = WHOLE * 11 / 20, STEP_HBM = WHOLE / 50;
+
 int ff_sim_delta(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t n_steps, uint64_t* d_out_ns, void* hip_stream) {
     if (!c || (n_steps && (!d_muts || !d_out_ns))) return FF_EINVAL;
     if (c->links_gen != c->sim->links_gen) return FF_EINVAL;
     if (n_steps == 0) return FF_OK;
-    // Segments side by side: as many as there are blocks and the device has room for, from three steps on.  The first step of a segment is a full simulation, one
-    // that resumes costs anything between none and a full one, half of it on the mean: n steps in P segments last for about
-    // (n / P + 1) / 2 full simulations instead of n / 2.
+    // Segments side by side: up to as many as there are blocks and the device has room for, from three steps on, where that is estimated to take less than steps
+    // in turn (k_chain_split).  The first step of a segment is a full simulation, one that resumes costs anything between none and a full one: n steps
+    // that cost a half on the mean last for n / 2 full simulations in turn, for about (ceil(n / P) + 1) / 2 in P segments.
     ff_sim* s = c->sim;
     hipStream_t st = (hipStream_t)hip_stream;
     uint32_t n_segs = 1;
@@ -950,9 +953,11 @@ int ff_sim_delta(ff_chains_t* c, const ff_mutation_t* d_muts, uint32_t n_steps, 
         n_segs = std::max(1u, std::min(std::min(1 + c->n_spare, n_steps), s->max_chain_slots / c->C));
     }
     if (n_segs > 1) {
-        hipLaunchKernelGGL(k_chain_split, dim3(c->C), dim3(256), (size_t)s->dev.n_ops * sizeof(uint2), st, s->dev, c->d_mem,
-                           c->stride, c->n_snaps, s->loop ? s->chain_choice.rowl : 0u, c->C, n_segs, (const uint32_t*)d_muts, n_steps, c->d_flags,
-                           c->spare);
+        const uint32_t per_step = s->loop && s->chain_choice.lds ? STEP_LDS : STEP_HBM;
+        const bool cut = (uint64_t)n_steps * per_step > (uint64_t)((n_steps - 1) / n_segs + 1) * (WHOLE + per_step) + WHOLE / 16;
+        hipLaunchKernelGGL(k_chain_split, dim3(c->C), dim3(SPLIT_THREADS), (size_t)s->dev.n_ops * sizeof(uint2), st, s->dev, s->d_ops,
+                           s->d_in_edges, c->d_mem, c->stride, c->n_snaps, s->loop ? s->chain_choice.rowl : 0u, c->C, n_segs, (const uint32_t*)d_muts,
+                           n_steps, c->d_flags, c->spare, per_step, cut);
         if (hipGetLastError() != hipSuccess) return FF_EHIP;
     }
     return launch_chain_steps(c, d_muts, n_steps, d_out_ns, st, SearchDev{}, n_segs);

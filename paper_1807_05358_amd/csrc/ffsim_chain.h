@@ -387,18 +387,22 @@ struct EventsEngine {
     __device__ __forceinline__ void finish() const {}
 };
 
-// Forced mutations do not depend on what the simulations before them find, so the steps of one chain may be cut into n_segs segments of
+// Forced mutations do not depend on what the simulations before them find, so the steps of one chain may be cut into segments of
 // consecutive steps that run side by side, each in a block of its own with the strategy it starts from (k_chain_split): the last one in the
 // chain's own block, which it leaves as the chain's state, segment p before it in spare block p * C + c.  The first step of a segment simulates from
-// time 0, the ones behind it resume as ever.
-struct SpareBlocks { unsigned char* mem; uint32_t* flags; };
-struct ChainSeg { uint32_t c, s_begin, s_end; bool spare; unsigned char* block; uint32_t* flag; };
-__device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32_t n_segs, uint32_t n_steps, unsigned char* chain_mem, size_t stride,
+// time 0, the ones behind it resume as ever.  How many segments is each chain's own matter (segs[c], at most n_segs); one of them is steps in turn.
+struct SpareBlocks { unsigned char* mem; uint32_t* flags; uint32_t* segs; };
+struct ChainSeg { uint32_t c, p, n, s_begin, s_end; bool spare; unsigned char* block; uint32_t* flag; };
+__device__ __forceinline__ ChainSeg chain_segment(uint32_t b, uint32_t C, uint32_t n, uint32_t n_steps, unsigned char* chain_mem, size_t stride,
                                                   uint32_t* chain_flags, const SpareBlocks& spare) {
     const uint32_t p = b / C, c = b - p * C;
-    const bool sp = p + 1 < n_segs;
-    return ChainSeg{c, (uint32_t)((u64)n_steps * p / n_segs), (uint32_t)((u64)n_steps * (p + 1) / n_segs), sp,
+    const bool sp = p + 1 < n;
+    return ChainSeg{c, p, n, (uint32_t)((u64)n_steps * p / n), (uint32_t)((u64)n_steps * (p + 1) / n), sp,
                     (sp ? spare.mem + (size_t)b * stride : chain_mem + (size_t)c * stride), sp ? spare.flags + b : chain_flags + c};
+}
+// the number of segments of the chain of workgroup b
+__device__ __forceinline__ uint32_t chain_segments(uint32_t b, uint32_t C, uint32_t n_segs, const SpareBlocks& spare) {
+    return n_segs > 1 ? first_u32(spare.segs[b % C]) : 1u;
 }
 
 // The steps of one chain.  Three sources of steps:
@@ -631,7 +635,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_chain_steps(SimDev S, const DOp* _
     uint2* cfg_lds = (uint2*)lds_raw;
     const WaveLds L = carve_lds(lds_raw + (size_t)S.n_ops_pad * 8, S);
     if (blockIdx.x >= C * n_segs) return;
-    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
+    const ChainSeg seg = chain_segment(blockIdx.x, C, chain_segments(blockIdx.x, C, n_segs, spare), n_steps, chain_mem, chain_stride, chain_flags, spare);
+    if (seg.p >= seg.n) return;
     const ChainMem cm = carve_chain(seg.block, S, n_snaps, 0);
     const uint32_t magic_v = load_magic(magic);
     for (uint32_t i = lane_id(); i < S.n_ops; i += WAVE) cfg_lds[i] = cm.cfgs[i];

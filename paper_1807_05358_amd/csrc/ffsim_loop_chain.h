@@ -130,7 +130,8 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const Tables T{ops, edges, in_edges, cost};
     if (blockIdx.x >= C * n_segs) return;
-    const ChainSeg seg = chain_segment(blockIdx.x, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
+    const ChainSeg seg = chain_segment(blockIdx.x, C, chain_segments(blockIdx.x, C, n_segs, spare), n_steps, chain_mem, chain_stride, chain_flags, spare);
+    if (seg.p >= seg.n) return;
     uint2* cfg_lds = (uint2*)lds_raw;
     unsigned char* lds = lds_raw + (size_t)S.n_ops_pad * 8;
     const ChainMem cm = carve_chain(seg.block, S, n_snaps, ROWL);
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(WAVE) void k_loop_chain_steps(SimDev S, const DOp* 
     mem.edge_lite = edge_lite;
     mem.links = (const uint4*)(magic + loop_links_at(S.gpus_per_node, S.n_nodes, S.n_ops));
     // the kept rows do not belong to the strategy yet: a chain's first launch, and segments of its steps
-    const bool fresh = (!muts && !search.enabled) || n_segs > 1;
+    const bool fresh = (!muts && !search.enabled) || seg.n > 1;
     if (LDSW) {
         const SlotLayout sl = slot_layout(S.n_ops, S.n_ops_pad, S.n_edges, S.n_kept, ROWL, true);
         carve_lds_state(mem, lds, sl, S, op_lite, edge_lite);

@@ -137,28 +137,78 @@ __global__ __launch_bounds__(256) void k_chain_blocks(unsigned char* __restrict_
     if (threadIdx.x == 0) chain_flags[blockIdx.x] = 0;
 }
 
-// Writes into the block of every segment the strategy that its steps start from: the chain's with all mutations before them applied.  The stored
-// timelines of the blocks belong to other strategies from then on.  One workgroup per chain; the mutations are applied in order by one lane.
-__global__ __launch_bounds__(256) void k_chain_split(SimDev S, unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps,
+// How many segments the steps of a chain are cut into: the number with which the longest one is estimated to take least, 1 (steps in turn) where cutting gives
+// nothing.  A step takes what is left of the stored timeline from where the change can matter first (first_input_at; half of it without a timeline), the
+// first one of a segment all of it, and every step per_step besides.  With more than SPLIT_STEPS steps that many of them stand for all.  left: what each
+// of the m steps takes; called by one wavefront, a lane per number.  (Where per_step alone decides, the host says so and nothing is estimated.)
+constexpr uint32_t SPLIT_STEPS = 128;
+__device__ __forceinline__ uint32_t choose_segments(const uint32_t* left, uint32_t m, uint32_t n_steps, uint32_t most, uint32_t first, uint32_t per_step) {
+    const uint32_t P = (uint32_t)lane_id() + 1;
+    const float w = (float)n_steps / (float)m;
+    float longest = 0.0f, sum = 0.0f;
+    const uint32_t q = m / P, r = m - q * P;
+    uint32_t err = 0, end = 0;                           // the next segment begins at floor(m * p / P)
+    for (uint32_t i = 0; i < m; i++) {
+        const float f = (float)left[i] + (float)per_step;
+        if (i == end) {
+            sum = P > 1 || i ? (float)WHOLE + (float)per_step + (w - 1.0f) * f : (float)first + (float)per_step + (w - 1.0f) * f;
+            end += q;
+            err += r;
+            if (err >= P) { err -= P; end++; }
+        } else {
+            sum += w * f;
+        }
+        longest = sum > longest ? sum : longest;
+    }
+    // (below 2^25: compared as whole numbers, the smallest number of segments among equals)
+    const float capped = longest < 33000000.0f ? longest : 33000000.0f;
+    const uint32_t key = P <= most && P <= m ? ((uint32_t)capped << 6) | (P - 1) : 0xffffffffu;
+    const uint32_t in_turn = readlane_u32(key, 0) >> 6, best = wave_min_u32(key);
+    return (best >> 6) + WHOLE / 16 < in_turn ? (best & 63u) + 1 : 1u;
+}
+
+// Decides how many segments there are and writes into the block of each the strategy that its steps start from: the chain's with all mutations before them
+// applied.  The stored timelines of the blocks belong to other strategies from then on.  One workgroup per chain; the mutations are applied in order by one lane.
+// Cut by what the steps take rather than always, one chain, three changes: of the last 3 % of the ops of the NMT-shaped graph 69 -> 7.7 to 34 ms,
+// of the ResNet-101-shaped one 8.9 -> 0.7 to 1.2; 800 chains x 3 on the Inception-v3-shaped one 7.1 -> 3.0, of any ops there 11 as before (in turn 12.7).
+constexpr uint32_t SPLIT_THREADS = 256;       // (more only wait for one another at the barriers)
+__global__ __launch_bounds__(SPLIT_THREADS) void k_chain_split(SimDev S, const DOp* __restrict__ ops, const DEdge* __restrict__ in_edges,
+                                                     unsigned char* __restrict__ chain_mem, size_t chain_stride, uint32_t n_snaps,
                                                      uint32_t rowl, uint32_t C, uint32_t n_segs, const uint32_t* __restrict__ muts,
-                                                     uint32_t n_steps, uint32_t* __restrict__ chain_flags, SpareBlocks spare) {
+                                                     uint32_t n_steps, uint32_t* __restrict__ chain_flags, SpareBlocks spare, uint32_t per_step, bool cut) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     uint2* cfgs = (uint2*)lds_raw;                       // [n_ops]
     constexpr uint32_t FEW = 256;
     __shared__ uint32_t mu[FEW * 3];
-    __shared__ uint32_t poisoned;
-    const uint32_t c = blockIdx.x, t = threadIdx.x;
+    __shared__ uint32_t left[SPLIT_STEPS];
+    __shared__ uint32_t poisoned, chosen;
+    const uint32_t c = blockIdx.x, t = threadIdx.x, wave = first_u32(t / WAVE);
     const ChainMem own = carve_chain(chain_mem + (size_t)c * chain_stride, S, n_snaps, rowl);
-    for (uint32_t i = t; i < S.n_ops; i += 256) cfgs[i] = own.cfgs[i];
-    const u64 step = own.meta->step;
+    const ChainMeta meta = *own.meta;
+    for (uint32_t i = t; i < S.n_ops; i += SPLIT_THREADS) cfgs[i] = own.cfgs[i];
     if (t == 0) poisoned = chain_flags[c];
+    const uint32_t m = cut ? 0 : (n_steps < SPLIT_STEPS ? n_steps : SPLIT_STEPS);
+    for (uint32_t i = wave; i < m; i += SPLIT_THREADS / WAVE) {
+        const uint32_t op = first_u32(muts[((u64)n_steps * i / m * C + c) * 3]);
+        uint32_t share = WHOLE;
+        if (op >= S.n_ops) share = 0;                    // (neither it nor anything behind it is simulated)
+        else if (!S.ties) share = meta.stale ? WHOLE / 2 : share_from(meta, first_input_at(ops, in_edges, own, rowl ? rowl : (uint32_t)WAVE, op));
+        if (lane_id() == 0) left[i] = share;
+    }
     __syncthreads();
-    for (uint32_t p = 0; p < n_segs; p++) {
-        const ChainSeg seg = chain_segment(p * C + c, C, n_segs, n_steps, chain_mem, chain_stride, chain_flags, spare);
+    if (wave == 0) {
+        const uint32_t n = poisoned ? 1u : cut ? n_segs : choose_segments(left, m, n_steps, n_segs, meta.stale || meta.n_valid < 2 ? WHOLE : left[0], per_step);
+        if (t == 0) { chosen = n; spare.segs[c] = n; }
+    }
+    __syncthreads();
+    const uint32_t n_mine = chosen;
+    if (n_mine < 2) return;
+    for (uint32_t p = 0; p < n_mine; p++) {
+        const ChainSeg seg = chain_segment(p * C + c, C, n_mine, n_steps, chain_mem, chain_stride, chain_flags, spare);
         const ChainMem cm = carve_chain(seg.block, S, n_snaps, rowl);
-        for (uint32_t i = t; i < S.n_ops; i += 256) cm.cfgs[i] = cfgs[i];
+        for (uint32_t i = t; i < S.n_ops; i += SPLIT_THREADS) cm.cfgs[i] = cfgs[i];
         if (t == 0) {
-            cm.meta->step = step;
+            cm.meta->step = meta.step;
             cm.meta->n_valid = 0;
             cm.meta->stale = 1;
             cm.meta->cur_ns = RESULT_INVALID;
