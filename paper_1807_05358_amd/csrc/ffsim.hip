@@ -863,9 +863,9 @@ static unsigned char* get_memory(size_t bytes) {
 }
 
 // Blocks per chain besides its own, for the segments of ff_sim_delta: as many as let the chains together fill the device, within MAX_SPARE per chain
-// and SPARE_BYTES (and no more than a 16th of what is free) in all.  They are got with the first call that has use for them: memory of this size costs
-// little to get (0.3 ms; up to 64 MiB 0.02 ms), but is wiped by the driver when it is given back, at about 80 GB/s, and chain sets that only search or price
-// trials would wait for that.  Graphs that are simulated in LDS take a fraction of a millisecond per step: their chain sets stay below 64 MiB.
+// and SPARE_BYTES (and no more than a 16th of what is free) in all.  They are got with the first call that has use for them: memory of this size takes
+// 0.3 ms to get and as much to give back (up to 64 MiB 0.02 ms), which graphs that are simulated in LDS, with a fraction of a millisecond per step, would
+// notice: their chain sets stay below 64 MiB.
 constexpr uint32_t MAX_SPARE = 31;
 constexpr size_t SPARE_BYTES = (size_t)8 << 30, CHEAP_BYTES = (size_t)64 << 20;
 static void get_spare_blocks(ff_chains* c, hipStream_t st) {
@@ -887,7 +887,7 @@ static void get_spare_blocks(ff_chains* c, hipStream_t st) {
     c->spare = SpareBlocks{mem, (uint32_t*)(mem + n * set), c->d_flags + c->C};
     c->n_spare = n;
     const ChainLayout cl = chain_layout(s->dev, c->n_snaps, s->loop ? s->chain_choice.rowl : 0);
-    hipLaunchKernelGGL(k_chain_blocks, dim3(n * c->C), dim3(256), 0, st, mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)nullptr, s->dev.n_ops, 0u,
+    hipLaunchKernelGGL(k_chain_blocks, dim3(n * c->C, clear_pieces(cl.clear_bytes)), dim3(256), 0, st, mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)nullptr, s->dev.n_ops, 0u,
                        c->spare.flags);
 }
 
@@ -921,7 +921,7 @@ int ff_sim_chains_create(ff_sim_t* s, const ff_opcfg_t* d_strategies, uint32_t C
         hipMalloc((void**)&c->d_flags, (size_t)C * 8) != hipSuccess ||
         hipMalloc((void**)&c->d_counter, TRIAL_WORDS * 4) != hipSuccess) { ff_sim_chains_destroy(c); return FF_ENOMEM; }
     static_assert(sizeof(ff_opcfg_t) == sizeof(uint2), "strategy layout");
-    hipLaunchKernelGGL(k_chain_blocks, dim3(C), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
+    hipLaunchKernelGGL(k_chain_blocks, dim3(C, clear_pieces(cl.clear_bytes)), dim3(256), 0, st, c->d_mem, c->stride, cl.meta, cl.clear_bytes, (const uint2*)d_strategies,
                        s->dev.n_ops, C, c->d_flags);
     if (hipGetLastError() != hipSuccess) { ff_sim_chains_destroy(c); return FF_EHIP; }
     int rc = launch_chain_steps(c, nullptr, 1, d_out_ns0, st, SearchDev{});

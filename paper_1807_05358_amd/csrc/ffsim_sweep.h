@@ -126,12 +126,16 @@ __global__ void k_zero_words(uint32_t* p, uint32_t n) {
 // ---- forced mutations in segments (chain_segment) ------------------------------------------
 //
 // The blocks of a new chain set: bookkeeping and tags of endTimes empty (clear_bytes from clear_at on, both multiples of 16), the strategies at the
-// heads of the first C blocks (0: spare blocks, without one).  One workgroup per block.
+// heads of the first C blocks (0: spare blocks, without one).  Workgroups: blocks x pieces of what is to be cleared, which is 1 MB of a block of the NMT-shaped
+// graph, but with its extents beyond 16 bits all of it: 80 MB, 0.7 ms for a single workgroup.
+constexpr uint32_t CLEAR_PIECES = 64;
+inline uint32_t clear_pieces(size_t clear_bytes) { return (uint32_t)(clear_bytes >> 16 < CLEAR_PIECES ? (clear_bytes >> 16) + 1 : CLEAR_PIECES); }
 __global__ __launch_bounds__(256) void k_chain_blocks(unsigned char* __restrict__ chain_mem, size_t chain_stride, size_t clear_at, size_t clear_bytes,
                                                       const uint2* __restrict__ strategies, uint32_t n_ops, uint32_t C, uint32_t* __restrict__ chain_flags) {
     unsigned char* block = chain_mem + (size_t)blockIdx.x * chain_stride;
     uint4* p = (uint4*)(block + clear_at);
-    for (size_t i = threadIdx.x; i < clear_bytes / 16; i += 256) p[i] = make_uint4(0, 0, 0, 0);
+    for (size_t i = blockIdx.y * 256 + threadIdx.x; i < clear_bytes / 16; i += (size_t)gridDim.y * 256) p[i] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.y) return;
     if (blockIdx.x < C)
         for (uint32_t i = threadIdx.x; i < n_ops; i += 256) ((uint2*)block)[i] = strategies[(size_t)blockIdx.x * n_ops + i];
     if (threadIdx.x == 0) chain_flags[blockIdx.x] = 0;
