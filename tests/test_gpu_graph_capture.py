@@ -78,6 +78,51 @@ def test_delta_and_trial_mutations_in_a_graph(B):
     sim.close()
 
 
+@pytest.mark.parametrize("config_id,C", [(1, 3), (2, 2)])
+def test_delta_in_segments_in_a_graph(B, config_id, C):
+    """chains that have their blocks for segments when the graph is captured: every replay cuts the steps it finds in the buffer (changes of the first ops: side by
+    side; of the last ones: in turn where the graph is large; one that names no op), from where the chains are by then"""
+    import torch
+    w = W.workload(config_id)
+    sim = B.Simulator(w.ops, w.edges, w.machine, w.cost)
+    steps, n_ops = 6, w.n_ops
+    cfg0 = w.strategies(C)
+    calls = [w.mutations(5 * steps, C)[k * steps:(k + 1) * steps].copy() for k in range(5)]
+    good = w.strategies(steps)
+    for k, ops in ((1, np.arange(steps) % 2), (2, n_ops - 1 - np.arange(steps) % 3), (3, np.arange(steps) % 2)):
+        calls[k]["op"] = ops[:, None]
+        calls[k]["cfg"] = good[np.arange(steps), ops][:, None]
+    calls[4]["op"][3, 0] = n_ops
+    eager, ch = B.Chains(sim, cfg0), B.Chains(sim, cfg0)
+    trial = w.mutations(4, C)
+
+    def in_turn(muts):
+        return np.concatenate([eager.delta(eager.upload_mutations(muts[a:a + 2]), 2).cpu().numpy() for a in range(0, steps, 2)])
+
+    first = w.mutations(steps, C)
+    assert np.array_equal(ch.delta(ch.upload_mutations(first), steps).cpu().numpy(), in_turn(first))
+    d_m, d_t = ch.upload_mutations(calls[0]), ch.upload_mutations(trial)
+    out = torch.zeros((steps, C), dtype=torch.int64, device="cuda")
+    tried = torch.zeros((4, C), dtype=torch.int64, device="cuda")
+    ch.try_mutations(d_t, 4, d_out=tried)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ch.delta(d_m, steps, d_out=out)
+        ch.try_mutations(d_t, 4, d_out=tried)
+    for replay, muts in enumerate(calls):
+        d_m.copy_(ch.upload_mutations(muts))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), in_turn(muts)), f"replay {replay}"
+        assert np.array_equal(tried.cpu().numpy(), eager.try_mutations(d_t, 4).cpu().numpy()), f"replay {replay} (trials)"
+    assert (out.cpu().numpy()[3:, 0] == -1).all() and (out.cpu().numpy()[:, 1:] != -1).all()
+    assert np.array_equal(ch.stats()["n_steps"], eager.stats()["n_steps"])
+    ch.close()
+    eager.close()
+    sim.close()
+
+
 def test_search_steps_in_a_graph(B):
     """after one eager call (which checks the proposal lists) ff_sim_search only launches: a graph of
     search steps, replayed, continues the chains exactly as eager calls do"""
