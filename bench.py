@@ -549,7 +549,7 @@ def main():
                            "median_start_ns": float(np.median(start)), "median_best_ns": float(np.median(best_ns))})
             ch.close()
         line["search"] = search
-        # one chain: ff_sim_search ("one_by_one"; it prices a tree of the steps to come) and ff_sim_search_ahead, which
+        # one chain: ff_sim_search, which prices a tree of the steps to come, and ff_sim_search_ahead, which
         # simulates the proposals of the coming steps against the current strategy (the same chain, step for step).
         few = []
         for cid, n_steps, start_kind in ((1, 4000, "data parallelism"), (1, 2000, "random strategy"), (2, 600, "data parallelism")):
@@ -579,11 +579,11 @@ def main():
                     rec["ahead_rounds"], rec["ahead_proposals_simulated"] = int(ch.ahead_stats[0]), int(ch.ahead_stats[1])
                     rec["proposals_accepted"] = int(ch.ahead_stats[3])
                 else:
-                    rec["one_by_one_steps_per_s"] = n_steps / dt
+                    rec["search_steps_per_s"] = n_steps / dt
                 ch.close()
             rec["same_trace"] = bool(np.array_equal(traces[0], traces[1]))
             rec["steps_that_changed_the_time"] = int((np.diff(np.concatenate([[t_start], traces[0][:, 0].astype(np.float64)])) != 0).sum())
-            rec["speedup"] = rec["ahead_steps_per_s"] / rec["one_by_one_steps_per_s"]
+            rec["ahead_over_search"] = rec["ahead_steps_per_s"] / rec["search_steps_per_s"]
             few.append(rec)
         line["search_with_one_chain"] = few
         # the whole search with parameter-synchronisation traffic simulated (ff_sim_set_params): can it

@@ -549,8 +549,8 @@ struct EdgeLoad { u64 w; uint32_t f, clo, chi, plo, phi, clo2, chi2, plo2, phi2,
 // strategies (777 x ResNet-101-shaped on 5 x 3 devices) 30.9 -> 22.1; training iterations (1024 x Inception-v3-shaped)
 // 24.3 -> 16.4.
 // LEAN (kernels without the refinements): what keeps the compiler from waiting for one load before it asks for the next (in_flight; left to itself it does
-// now and then, which costs a trip to memory per step, 3 to 7 % of a batch), the first edge of a release asked for as soon as it is known that there is one,
-// and a few forms that need fewer scalar registers.  4096 x Inception-v3-shaped 7.17 -> 6.98 ms, 4096 x ResNet-101-shaped 13.88 -> 13.46, 1024 x
+// now and then, which costs a trip to memory per step), the first edge of a release asked for as soon as it is known that there is one,
+// and a few forms that need fewer scalar registers; together 2 to 3 % of a batch: 4096 x Inception-v3-shaped 7.17 -> 6.98 ms, 4096 x ResNet-101-shaped 13.88 -> 13.46, 1024 x
 // NMT-shaped 68.5 -> 67.2, 1024 x AlexNet-shaped 0.196 -> 0.191 (with the set-up of four edges at a time 0.188).  With the refinements the same costs 1 to 2 % (their loops have fewer registers
 // left), so they keep the plain forms.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
