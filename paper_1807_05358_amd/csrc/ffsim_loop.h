@@ -536,6 +536,35 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
 // what a release has of an edge in registers: the consumer's words, the kept rows of both sides
 struct EdgeLoad { u64 w; uint32_t f, clo, chi, plo, phi, clo2, chi2, plo2, phi2, sortw; };
 
+// ---- pace ----------------------------------------------------------------------------------
+//
+// Wavefronts that share a SIMD and have nothing behind them should finish together: with four the vector unit is busy, the last one alone leaves three
+// quarters of it idle, and how long a candidate takes is only known when it has been simulated.  So a wavefront gives way as it gets on: its priority
+// falls by one where half, three quarters and nine tenths of its ops are behind it (of all candidates it will simulate), and the others catch up.
+// They do so slowly, with no more than the difference between their share and a lone wavefront's pace (those ahead still get every slot that is
+// left), so the bounds come early: with the first at 0.7 or 0.8 half of the gain is lost; a quarter, a half and three quarters give 2 % less;
+// priorities that change hands by the clock give nothing (the shares are even enough, the lengths are not).  4096 x Inception-v3-shaped 6.99 -> 6.27 ms,
+// x ResNet-101-shaped 13.4 -> 11.4, 8192 x AlexNet-shaped 0.47 -> 0.41, 1024 searches x 32 steps (nodes four to a SIMD) 97.9 -> 90.9; with one
+// wavefront per SIMD nothing changes.  How far a wavefront is is looked at every 32 steps, where the loop's own bound is: a count of events costs such lone
+// wavefronts 1 to 4 %.  (Trials are dealt out by length already and gain nothing.)
+constexpr uint32_t PACE_STEPS = 32;      // queue steps between two looks at how far a wavefront is
+struct NoPace {
+    static constexpr bool kOn = false;
+    __device__ __forceinline__ void at(uint32_t) {}
+};
+struct Pace {
+    static constexpr bool kOn = true;
+    uint32_t before, all;                // ops of the candidates done, of all candidates of this wavefront
+    // op i is released or dequeued (ops are numbered in an order their tensors allow, so that is how far the candidate is)
+    __device__ __forceinline__ void at(uint32_t i) {
+        const u64 done = (u64)(before + i) * 256;
+        if (done < (u64)all * 128) __builtin_amdgcn_s_setprio(3);
+        else if (done < (u64)all * 192) __builtin_amdgcn_s_setprio(2);
+        else if (done < (u64)all * 232) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+    }
+};
+
 // Algorithm 1 from the current state to the end.  RECORD, REG, STATS as for run_events; Q: LoopQueue; ROWL: lanes per row.
 // Returns 0, RUN_CONVERGED, RESULT_RETRY or a RESULT_* code.
 //
@@ -554,8 +583,8 @@ struct EdgeLoad { u64 w; uint32_t f, clo, chi, plo, phi, clo2, chi2, plo2, phi2,
 // NMT-shaped 68.5 -> 67.2, 1024 x AlexNet-shaped 0.196 -> 0.191 (with the set-up of four edges at a time 0.188).  With the refinements the same costs 1 to 2 % (their loops have fewer registers
 // left), so they keep the plain forms.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
-template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX>
-__device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec) {
+template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX, class PaceX = NoPace>
+__device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec, PaceX pace = PaceX()) {
     static_assert(!(REG && L64), "64-bit link rows go with the general form");
     constexpr bool RUNS = Q == Q_SLOT;       // runs of events (see run_events): on graphs of more than 64 ops
     constexpr bool LEAN = !SimX::kExt;
@@ -579,7 +608,8 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     q.n_spill = first_u32(q.n_spill);
     q.spill_min = first_u64(q.spill_min);
     if (RECORD) { rec.step = first_u64(rec.step); rec.next = first_u32(rec.next); rec.n_snaps = first_u32(rec.n_snaps); rec.check_below = first_u32(rec.check_below); }
-    const u64 max_events = 2ull * S.n_ops * WAVE + 8;
+    const uint32_t max_steps = 2 * S.n_ops * WAVE + 8;
+    uint32_t stop = PaceX::kOn ? 0 : max_steps, last = 0;
     uint32_t snap_key = KEY_NONE;            // RECORD: key of the next snapshot boundary
     auto set_snap_key = [&]() {
         if (RECORD) {
@@ -590,7 +620,12 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     set_snap_key();
     auto keys_min = [&](uint32_t key) __attribute__((always_inline)) { return Q == Q_OP16 ? row0_min_u32(key) : wave_min_u32(key); };
     uint32_t kmin = keys_min(q.key);
-    for (u64 ev = 0; ev < max_events; ev++) {
+    for (uint32_t step = 0;; step++) {
+        if (__builtin_expect(step >= stop, 0)) {
+            if (step >= max_steps) break;
+            pace.at(first_u32(last));
+            stop = step + PACE_STEPS < max_steps ? step + PACE_STEPS : max_steps;
+        }
         // ---- pop.  kmin: smallest key of the slots
         if (__builtin_expect(kmin >= KEY_REFRESH, 0)) {
             if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
@@ -634,6 +669,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 i = readlane_u32(q.op, __builtin_ctzll(at));
             }
         }
+        if (PaceX::kOn) last = i;
         const u64 K = 2 * st.E + kmin;       // the popped word
         PROF_MARK(1)
         // Everything that depends only on i is requested together, the static record through the vector unit as well (a

@@ -304,8 +304,9 @@ __global__ __launch_bounds__(WAVE) void k_loop_nodes(SimDev S, const DOp* __rest
         LoopState st;
         m.want_sort = cls != STRATEGY_REGULAR;
         init_loop<Q, ROWL>(m, mem, st, cnt, true);
-        u64 rc = cls == STRATEGY_REGULAR ? run_loop<false, true, false, Q, ROWL>(m, mem, st, cnt, none)
-                                         : run_loop<false, false, false, Q, ROWL>(m, mem, st, cnt, none);
+        const Pace pace{0, S.n_ops};
+        u64 rc = cls == STRATEGY_REGULAR ? run_loop<false, true, false, Q, ROWL>(m, mem, st, cnt, none, pace)
+                                         : run_loop<false, false, false, Q, ROWL>(m, mem, st, cnt, none, pace);
         if (!rc) mk = loop_makespan(m, mem, st);
         if (rc == RESULT_RETRY) {
             m.want_sort = true;          // (the general form's rows)

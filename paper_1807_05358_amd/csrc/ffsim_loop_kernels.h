@@ -114,8 +114,9 @@ __global__ __launch_bounds__(WAVE) void k_loop_batch(SimDev S, const DOp* __rest
 #ifdef FFSIM_PROFILE
             cnt.exit_code = __builtin_readcyclecounter() - prof_t0;   // reported as section 0
 #endif
-            u64 rc = cls == STRATEGY_REGULAR ? run_loop<false, true, STATS, Q, ROWL>(m, mem, st, cnt, none)
-                                             : run_loop<false, false, STATS, Q, ROWL>(m, mem, st, cnt, none);
+            const Pace pace{b / gridDim.x * S.n_ops, ((B - 1 - blockIdx.x) / gridDim.x + 1) * S.n_ops};
+            u64 rc = cls == STRATEGY_REGULAR ? run_loop<false, true, STATS, Q, ROWL>(m, mem, st, cnt, none, pace)
+                                             : run_loop<false, false, STATS, Q, ROWL>(m, mem, st, cnt, none, pace);
             mk = rc == RESULT_RETRY ? RESULT_MARK_RETRY : rc ? rc : loop_makespan(m, mem, st);
             if (STATS)   // diagnostics: tasks that never ran (0 in a correct run)
                 for (uint32_t j = 0; j < S.n_ops; j++) cnt.n_stuck += __popcll(ballot(load_word<ROWL>(mem.words, j) != W_NONE));
