@@ -25,6 +25,7 @@ enum KeptRow : uint32_t {
 // tasks of its first out-edge's consumer (the bound of a run of releases), number of parts | HDR_* flags.
 constexpr uint32_t HDR_SPLIT01 = 1u << 16;   // dim 0 or 1 is split
 constexpr uint32_t HDR_SPLIT23 = 1u << 17;   // dim 2 or 3 is split
+constexpr uint32_t HDR_RELEASES = 1u << 18;  // the op's tasks have something to release when they have finished
 
 // Static records, small enough to stay close (the full records are 176 bytes per op and 128 per edge).
 struct EdgeLite { uint32_t word, in_pos, row, unused; };    // consumer | EL_* flags, position among the consumer's in-edges, first kept row

@@ -13,7 +13,8 @@ namespace ffsim {
 // register, a lane per op with an event:
 //   Q_OP16 / Q_OP   graphs of at most 16 / 64 ops: lane = op;
 //   Q_SLOT          any graph: lane = slot, a second register holds the slot's op; when all 64 slots are taken, the op
-//                   with the latest event moves to a spill list in memory and comes back when its turn does.
+//                   with the latest first event moves to a spill list in memory and comes back when its turn does.
+// There are two keys per op, of its first task to dequeue and of its first one to release (see run_loop for why they are kept apart).
 // A key is the event's word (2 * time + kind) relative to 2 * E, in 32 bits.  E, the epoch, follows the simulated time
 // in steps of about a second (advance_epoch); KEY_FAR stands for an event at a distance that does not fit (its word in
 // memory has it in full), KEY_NONE for no event.
@@ -23,9 +24,12 @@ constexpr uint32_t KEY_REFRESH = 0x80000000u;    // a smallest key from here on:
 constexpr uint32_t NO_OP = 0xffffffffu;
 constexpr u64 RESULT_RETRY = 2;                  // a link row is booked beyond 32 bits: simulate again with 64-bit rows
 constexpr uint32_t RUN_SPAN = 0x40000000u;       // events of one step lie at most this far apart
+constexpr uint32_t FAR_AWAY = 0xfffffffeu;       // a distance between events of one kind that 32 bits do not hold
+constexpr uint32_t RUN_EDGES = 8;                // ops with more out-edges release at one time only
 
 struct Queue {
-    uint32_t key, op;           // per lane
+    uint32_t kd, kr, op;        // per lane: keys of the first task to be dequeued and of the first to release, the op they are of
+    uint32_t ex;                // per lane: 2 * exeTime of that op (at most RUN_SPAN): none of the tasks still to be dequeued releases before kd + ex
     uint32_t n_spill;           // uniform
     u64 spill_min;              // smallest word on the spill list (absolute; W_NONE if it is empty)
 };
@@ -64,19 +68,35 @@ __device__ __forceinline__ uint32_t part_min_of(uint32_t v, u64 mask) {
     return part_min_u32<ROWL>(lanes_of(mask) ? v : KEY_NONE);
 }
 
-// smallest pending event of an op, from its words in memory (W_NONE: none)
+// smallest pending event of an op, from its words in memory (W_NONE: none); of one kind (1: dequeue, 0: release) if that is asked for
 template <int ROWL>
-__device__ __forceinline__ u64 op_min_word(const u64* words, uint32_t op) {
-    const u64 w = load_word<ROWL>(words, op);
+__device__ __forceinline__ u64 op_min_word(const u64* words, uint32_t op, int kind = -1) {
+    u64 w = load_word<ROWL>(words, op);
+    if (kind >= 0 && (int)(w & 1) != kind) w = W_NONE;
     const u64 m = wave_min_u64(w);
     return m >> 63 ? W_NONE : m;
 }
+// the bound that an op's exeTime sets, as a difference of keys
+__device__ __forceinline__ uint32_t exe_span(uint32_t exe) { return exe >= RUN_SPAN / 2 ? RUN_SPAN : 2 * exe; }
 __device__ __forceinline__ uint32_t rel_key(u64 word, u64 E) {
     const u64 d = word - 2 * E;
     return d >= KEY_FAR ? KEY_FAR : (uint32_t)d;
 }
+__device__ __forceinline__ uint32_t rel_key_or_none(u64 word, u64 E) { return word >> 63 ? KEY_NONE : rel_key(word, E); }
 
-__device__ __forceinline__ void queue_clear(Queue& q) { q.key = KEY_NONE; q.op = NO_OP; q.n_spill = 0; q.spill_min = W_NONE; }
+template <int Q>
+__device__ __forceinline__ void queue_clear(const LoopMem& mem, Queue& q, uint32_t n_ops) {
+    q.kd = KEY_NONE; q.kr = KEY_NONE; q.op = NO_OP; q.n_spill = 0; q.spill_min = W_NONE;
+    q.ex = Q != Q_SLOT && (uint32_t)lane_id() < n_ops ? exe_span(mem.hdr[lane_id()].x) : 0u;
+}
+// the key of an op's event at distance d behind the popped one (FAR_AWAY, or KEY_NONE: none)
+__device__ __forceinline__ uint32_t next_key(uint32_t kmin, uint32_t d) {
+    uint32_t k = __builtin_elementwise_add_sat(kmin, d);
+    k = k < KEY_FAR ? k : KEY_FAR;
+    return k > d ? k : d;
+}
+// first event of a slot, of either kind
+__device__ __forceinline__ uint32_t slot_key(const Queue& q) { return q.kd < q.kr ? q.kd : q.kr; }
 
 __device__ __forceinline__ void spill_push(const LoopMem& mem, Queue& q, uint32_t op, u64 word) {
     if (lane_id() == 0) { mem.spill_key[q.n_spill] = word; mem.spill_op[q.n_spill] = op; }
@@ -98,33 +118,38 @@ __device__ __forceinline__ void spill_remove(const LoopMem& mem, Queue& q, uint3
     spill_scan(mem, q);
 }
 
-// All slots are taken and op j, which has none, gets an event: the latest of the 65 events goes to the spill list.
+// All slots are taken and op j, which has none, gets an event: the op with the latest of the 65 first events goes to the spill list.
 template <int ROWL>
-__device__ __forceinline__ void queue_spill(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
+__device__ __forceinline__ void queue_spill(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t kd, uint32_t kr, uint32_t ex) {
     Queue& q = st.q;
-    const uint32_t kmax = ~wave_min_u32(~q.key);
+    const uint32_t key = kd < kr ? kd : kr, sk = slot_key(q);
+    const uint32_t kmax = ~wave_min_u32(~sk);
     // (a far event has its true word in memory; so has any other: the word is read back rather than rebuilt)
     if (key >= kmax) {
         spill_push(mem, q, j, key >= KEY_FAR ? op_min_word<ROWL>(mem.words, j) : 2 * st.E + key);
         return;
     }
-    const uint32_t slot = __builtin_ctzll(ballot(q.key == kmax));
+    const uint32_t slot = __builtin_ctzll(ballot(sk == kmax));
     const uint32_t old = readlane_u32(q.op, slot);
     spill_push(mem, q, old, kmax >= KEY_FAR ? op_min_word<ROWL>(mem.words, old) : 2 * st.E + kmax);
-    if ((uint32_t)lane_id() == slot) { q.key = key; q.op = j; }
+    if ((uint32_t)lane_id() == slot) { q.kd = kd; q.kr = kr; q.op = j; q.ex = ex; }
 }
 
-// gives op j the event `key` if it is earlier than what it has (it may end up on the spill list: only with n_spill > 0).  LEAN: see run_loop
-template <int Q, int ROWL, bool LEAN = false>
-__device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t key) {
+// gives op j the events kd (a task to dequeue) and kr (one to release), KEY_NONE for none, where they are earlier than what it has (it may end
+// up on the spill list: only with n_spill > 0).
+template <int Q, int ROWL>
+__device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, uint32_t j, uint32_t kd, uint32_t kr, uint32_t ex) {
     Queue& q = st.q;
     if (Q != Q_SLOT) {
-        const uint32_t k = (uint32_t)lane_id() == j ? key : KEY_NONE;
-        q.key = k < q.key ? k : q.key;
+        const bool me = (uint32_t)lane_id() == j;
+        const uint32_t d = me ? kd : KEY_NONE, r = me ? kr : KEY_NONE;
+        q.kd = d < q.kd ? d : q.kd;
+        q.kr = r < q.kr ? r : q.kr;
         return;
     }
     // on the spill list already?
     auto spilled = [&]() __attribute__((always_inline)) {
+        const uint32_t key = kd < kr ? kd : kr;
         for (uint32_t b = 0; b < q.n_spill; b += WAVE) {
             const uint32_t t = b + lane_id();
             const u64 hit = ballot(t < q.n_spill && mem.spill_op[t < q.n_spill ? t : 0] == j);
@@ -141,27 +166,22 @@ __device__ __forceinline__ void queue_insert(const LoopMem& mem, LoopState& st, 
     };
     // its slot, else the first free one
     u64 at = ballot(q.op == j);
-    if (LEAN) {
-        const u64 open = ballot(q.op == NO_OP);
-        if (__builtin_expect(at == 0 && (q.n_spill != 0 || open == 0), 0)) {
-            if (spilled()) return;
-            if (!open) { queue_spill<ROWL>(mem, st, j, key); return; }
-        }
-        at = at ? at : open & (0 - open);
-    } else if (!at) {
-        if (q.n_spill && spilled()) return;
-        at = ballot(q.op == NO_OP);
-        if (!at) { queue_spill<ROWL>(mem, st, j, key); return; }
-        at &= 0 - at;
+    const u64 open = ballot(q.op == NO_OP);
+    if (__builtin_expect(at == 0 && (q.n_spill != 0 || open == 0), 0)) {
+        if (spilled()) return;
+        if (!open) { queue_spill<ROWL>(mem, st, j, kd, kr, ex); return; }
     }
+    at = at ? at : open & (0 - open);
     const bool me = lanes_of(at);
-    const uint32_t k = me ? key : KEY_NONE;
-    q.key = k < q.key ? k : q.key;
+    const uint32_t d = me ? kd : KEY_NONE, r = me ? kr : KEY_NONE;
+    q.kd = d < q.kd ? d : q.kd;
+    q.kr = r < q.kr ? r : q.kr;
     q.op = me ? j : q.op;
+    q.ex = me ? ex : q.ex;
 }
 
-// The smallest event on the spill list is not later than the smallest one in the slots: it changes places with the
-// latest event there (or takes a free slot).
+// The smallest event on the spill list is not later than the smallest one in the slots: its op changes places with the
+// one with the latest first event there (or takes a free slot).
 template <int ROWL>
 __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st) {
     Queue& q = st.q;
@@ -177,7 +197,8 @@ __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st)
     const uint32_t mop = wave_min_u32(best == m ? bop : NO_OP);
     const uint32_t t = readlane_u32(bt, __builtin_ctzll(ballot(best == m && bop == mop)));
     spill_remove(mem, q, t);
-    const uint32_t key = rel_key(m, st.E);
+    const uint32_t kd = rel_key_or_none(op_min_word<ROWL>(mem.words, mop, 1), st.E), kr = rel_key_or_none(op_min_word<ROWL>(mem.words, mop, 0), st.E);
+    const uint32_t ex = exe_span(mem.hdr[mop].x);
     u64 at = ballot(q.op == NO_OP);
     uint32_t slot;
     if (at) {
@@ -185,12 +206,13 @@ __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st)
     } else {
         // the latest slot makes room (never a loop: the entry just taken off is not later than any slot that would
         // bring it back; among equal keys the highest op leaves)
-        const uint32_t kmax = ~wave_min_u32(~q.key);
-        const uint32_t omax = ~wave_min_u32(q.key == kmax ? ~q.op : NO_OP);
-        slot = __builtin_ctzll(ballot(q.key == kmax && q.op == omax));
+        const uint32_t sk = slot_key(q);
+        const uint32_t kmax = ~wave_min_u32(~sk);
+        const uint32_t omax = ~wave_min_u32(sk == kmax ? ~q.op : NO_OP);
+        slot = __builtin_ctzll(ballot(sk == kmax && q.op == omax));
         spill_push(mem, q, omax, kmax >= KEY_FAR ? op_min_word<ROWL>(mem.words, omax) : 2 * st.E + kmax);
     }
-    if ((uint32_t)lane_id() == slot) { q.key = key; q.op = mop; }
+    if ((uint32_t)lane_id() == slot) { q.kd = kd; q.kr = kr; q.op = mop; q.ex = ex; }
 }
 
 // Moves the epoch to the next pending event.  Returns false if there is none.
@@ -199,22 +221,23 @@ __device__ __forceinline__ void queue_unspill(const LoopMem& mem, LoopState& st)
 template <int Q, int ROWL, bool L64>
 __device__ __forceinline__ bool advance_epoch(const LoopMem& mem, LoopState& st, uint32_t n_links) {
     Queue& q = st.q;
-    u64 word = q.key >= KEY_FAR ? W_NONE : 2 * st.E + q.key;      // this lane's event in full
-    u64 far = ballot(q.key == KEY_FAR);
+    u64 wd = q.kd >= KEY_FAR ? W_NONE : 2 * st.E + q.kd, wr = q.kr >= KEY_FAR ? W_NONE : 2 * st.E + q.kr;      // this lane's events in full
+    u64 far = ballot(q.kd == KEY_FAR || q.kr == KEY_FAR);
     while (far) {
         const int l = __builtin_ctzll(far);
         far &= far - 1;
         const uint32_t op = Q == Q_SLOT ? readlane_u32(q.op, l) : (uint32_t)l;
-        const u64 w = op_min_word<ROWL>(mem.words, op);
-        if (lane_id() == l) word = w;
+        const u64 d = op_min_word<ROWL>(mem.words, op, 1), r = op_min_word<ROWL>(mem.words, op, 0);
+        if (lane_id() == l) { wd = d; wr = r; }
     }
-    u64 next = wave_min_u64(word);
+    u64 next = wave_min_u64(wd < wr ? wd : wr);
     if (Q == Q_SLOT) next = q.spill_min < next ? q.spill_min : next;
     if (next >> 63) return false;
     const u64 E = (next >> 1) > st.E ? next >> 1 : st.E;
     const u64 delta = E - st.E;
     st.E = E;
-    q.key = word >> 63 ? KEY_NONE : rel_key(word, E);
+    q.kd = rel_key_or_none(wd, E);
+    q.kr = rel_key_or_none(wr, E);
     if (!L64) {
         const uint32_t d32 = delta >> 32 ? 0xffffffffu : (uint32_t)delta;
         for (uint32_t r = lane_id(); r < n_links; r += WAVE) mem.lrow[r] = __builtin_elementwise_sub_sat(mem.lrow[r], d32);
@@ -281,7 +304,7 @@ __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem&
         beyond = beyond || r >= 0xffffffffull;
         mem.lrow[t - n_dev] = (uint32_t)r;
     }
-    queue_clear(st.q);
+    queue_clear<Q>(mem, st.q, n_ops);
     const u64* src = rec.snap_words + at * (size_t)n_ops * ROWL;
     // eight rows of 64 words in flight; a row of ROWL = 16 holds the words of four ops.  Q_SLOT: ops with an event are listed
     // first (where the queue's spill list will be) and get their slots afterwards.
@@ -299,14 +322,14 @@ __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem&
             if (ballot(!(v[u] >> 63))) {
                 for (uint32_t g = 0; g < PER; g++) {
                     const u64 mine = lane / ROWL == g ? v[u] : W_NONE;
-                    const u64 mn = wave_min_u64(mine);
-                    if (mn >> 63) continue;
+                    if (!ballot(!(mine >> 63))) continue;
                     const uint32_t op = (b + u * WAVE) / ROWL + g;
                     if (Q == Q_SLOT) {
-                        if (lane == 0) { mem.spill_key[n_listed] = mn; mem.spill_op[n_listed] = op; }
+                        if (lane == 0) mem.spill_op[n_listed] = op;
                         n_listed++;
                     } else {
-                        queue_insert<Q, ROWL>(mem, st, op, rel_key(mn, E));
+                        queue_insert<Q, ROWL>(mem, st, op, rel_key_or_none(wave_min_u64(mine & 1 ? mine : W_NONE), E),
+                                              rel_key_or_none(wave_min_u64(mine & 1 ? W_NONE : mine), E), 0u);
                     }
                 }
             }
@@ -316,7 +339,11 @@ __device__ __forceinline__ bool load_loop_snapshot(const SimX& m, const LoopMem&
     if (Q == Q_SLOT) {
         n_listed = first_u32(n_listed);
         // (an insertion puts at most one entry back on the list, over one already read)
-        for (uint32_t t = 0; t < n_listed; t++) queue_insert<Q, ROWL>(mem, st, first_u32(mem.spill_op[t]), rel_key(first_u64(mem.spill_key[t]), E));
+        for (uint32_t t = 0; t < n_listed; t++) {
+            const uint32_t op = first_u32(mem.spill_op[t]);
+            queue_insert<Q, ROWL>(mem, st, op, rel_key_or_none(op_min_word<ROWL>(mem.words, op, 1), E), rel_key_or_none(op_min_word<ROWL>(mem.words, op, 0), E),
+                                  exe_span(first_u32(mem.hdr[op].x)));
+        }
     }
     return !ballot(beyond);
 }
@@ -332,7 +359,7 @@ __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState
     for (uint32_t r = lane; r < m.S.n_rows - m.S.n_dev; r += WAVE) {
         if (L64) mem.lrow64[r] = 0; else mem.lrow[r] = 0;
     }
-    queue_clear(st.q);
+    queue_clear<Q>(mem, st.q, n_ops);
     st.E = 0;
     if constexpr (ROWL == 16 && Q != Q_SLOT && !SimX::kTrain) {
         if (fill) {
@@ -355,7 +382,7 @@ __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState
                 if (live) mem.words[(size_t)j * 16 + k] = w;
                 const u64 now_m = ballot(w == 1ull);
                 const uint32_t mine = own - base;              // op `lane` is the mine-th of these four
-                if (mine < 4 && ((uint32_t)(now_m >> (16 * mine)) & 0xffffu)) st.q.key = 1u;
+                if (mine < 4 && ((uint32_t)(now_m >> (16 * mine)) & 0xffffu)) st.q.kd = 1u;
                 cnt.n_compute += __popcll(ballot(task));
             }
             wave_sync();
@@ -400,7 +427,7 @@ __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState
             // pending < PENDING_LIMIT is guaranteed by ff_sim_create (at most 511 in-edges per op)
             const u64 w = lane >= cj.parts ? W_NONE : (pending == 0 ? 1ull : (W_WAIT | ((u64)pending << 48)));
             if (ROWL == WAVE || lane < (uint32_t)ROWL) mem.words[(size_t)j * ROWL + lane] = w;
-            if (ballot(w == 1ull)) queue_insert<Q, ROWL>(mem, st, j, 1u);
+            if (ballot(w == 1ull)) queue_insert<Q, ROWL>(mem, st, j, 1u, KEY_NONE, Q == Q_SLOT ? exe_span(first_u32(mem.hdr[j].x)) : 0u);
             cnt.n_compute += cj.parts;
         }
     }
@@ -410,12 +437,23 @@ __device__ __forceinline__ void init_loop(SimX& m, const LoopMem& mem, LoopState
 // Section 4: every configuration valid?  Fills the kept op records.
 template <int Q, class SimX>
 __device__ __forceinline__ StrategyClass validate_loop(const SimX& m, const LoopMem& mem) {
-    const StrategyClass cls = validate_with(m, [&](uint32_t i, const OpCfg& c, uint32_t exe) __attribute__((always_inline)) { mem.hdr[i] = kept_header(c, exe); });
-    if (Q == Q_SLOT && cls != STRATEGY_INVALID) {
+    const StrategyClass cls = validate_with(m, [&](uint32_t i, const OpCfg& c, uint32_t exe) __attribute__((always_inline)) {
+        uint4 h = kept_header(c, exe);
+        const OpLite& o = mem.op_lite[i];
+        if (o.out_end > o.out_begin || (SimX::kExt && m.S.sync && o.param_bytes != 0)) h.w |= HDR_RELEASES;
+        mem.hdr[i] = h;
+    });
+    if (cls != STRATEGY_INVALID) {
         wave_sync();
         for (uint32_t i = lane_id(); i < m.S.n_ops; i += WAVE) {
             const OpLite o = mem.op_lite[i];
-            if (o.out_end > o.out_begin) mem.hdr[i].z = mem.hdr[o.first.word & EL_DST].x;
+            uint32_t least = 0xffffffffu;
+            if (o.out_end > o.out_begin) {
+                least = mem.hdr[o.first.word & EL_DST].x;
+                if (o.out_end - o.out_begin > RUN_EDGES) least = 0;
+                else for (uint32_t e = o.out_begin + 1; e < o.out_end; e++) { const uint32_t x = mem.hdr[mem.edge_lite[e].word & EL_DST].x; least = x < least ? x : least; }
+            }
+            mem.hdr[i].z = least;
         }
     }
     wave_sync();
@@ -486,13 +524,22 @@ __device__ __forceinline__ uint32_t pair_product(u16x2 v) {
 }
 // Nothing is moved across: loads asked for above are all on their way before the first of them is waited for below.
 __device__ __forceinline__ void in_flight() { __builtin_amdgcn_sched_barrier(0); }
-// a distance in 32 bits, all ones where it does not fit (LEAN: the high half is looked at by itself; a comparison of all 64 bits wants its bound in
-// two scalar registers, and the loop has none to spare)
-template <bool LEAN>
+// FAR_AWAY where the high half h of a distance between events of one kind is not 0, else its low half (the high half is looked at by itself: a comparison of
+// all 64 bits wants its bound in two scalar registers, and the loop has none to spare)
 __device__ __forceinline__ uint32_t near_u32(u64 d) {
     uint32_t hi = (uint32_t)(d >> 32);
-    if (LEAN) asm("" : "+v"(hi));
-    return hi ? KEY_NONE : (uint32_t)d;
+    asm("" : "+v"(hi));
+    const uint32_t lo = (uint32_t)d < FAR_AWAY ? (uint32_t)d : FAR_AWAY;
+    return hi ? FAR_AWAY : lo;
+}
+// Distance of an event from the popped word K: KEY_NONE for events of the other kind (at odd distances), ones that lie before it and words that
+// are no events; FAR_AWAY where it does not fit 32 bits.  (A waiting task's word may come out as FAR_AWAY where K is beyond 2^48.  Such a key
+// delays nothing: it is looked into when the epoch gets there.)
+__device__ __forceinline__ uint32_t event_distance(u64 word, u64 K) {
+    const u64 d = word - K;
+    const int32_t x = (int32_t)(((uint32_t)d << 31) | (uint32_t)(d >> 32));      // 0: of the same kind, and fits; positive: of the same kind, does not fit
+    const uint32_t far = (uint32_t)(x >> 31) | FAR_AWAY;
+    return x == 0 ? (uint32_t)d : far;
 }
 // n + 1 on the lanes of a mask
 __device__ __forceinline__ uint32_t count_lanes(uint32_t n, u64 mask) {
@@ -534,7 +581,7 @@ __device__ __forceinline__ u16x2 meet(uint32_t lo_a, uint32_t hi_a, uint32_t lo_
 }
 
 // what a release has of an edge in registers: the consumer's words, the kept rows of both sides
-struct EdgeLoad { u64 w; uint32_t f, clo, chi, plo, phi, clo2, chi2, plo2, phi2, sortw; };
+struct EdgeLoad { u64 w; uint32_t exe, f, clo, chi, plo, phi, clo2, chi2, plo2, phi2, sortw; };
 
 // ---- pace ----------------------------------------------------------------------------------
 //
@@ -573,28 +620,33 @@ struct Pace {
 // 32 bits, the queue in a register: a pass over the consumer parts took 95 instructions in run_events, it takes 51 to 58
 // here), the former also for fewer crossings from the vector to the scalar unit and fewer taken branches: on a lone wavefront any
 // instruction takes 4.6 to 6.4 cycles, dependent or not, but a scalar instruction that reads a mask or a lane's value
-// just found waits 20, a taken branch 25.  Per launch, against run_events: 4096 x Inception-v3-shaped 9.28 -> 7.01 ms, 4096 x
-// ResNet-101-shaped 20.2 -> 13.9, 1024 x NMT-shaped 98.6 -> 67.9, 1024 x AlexNet-shaped 0.227 -> 0.183; general
-// strategies (777 x ResNet-101-shaped on 5 x 3 devices) 30.9 -> 22.1; training iterations (1024 x Inception-v3-shaped)
-// 24.3 -> 16.4.
-// LEAN (kernels without the refinements): what keeps the compiler from waiting for one load before it asks for the next (in_flight; left to itself it does
-// now and then, which costs a trip to memory per step), the first edge of a release asked for as soon as it is known that there is one,
-// and a few forms that need fewer scalar registers; together 2 to 3 % of a batch: 4096 x Inception-v3-shaped 7.17 -> 6.98 ms, 4096 x ResNet-101-shaped 13.88 -> 13.46, 1024 x
-// NMT-shaped 68.5 -> 67.2, 1024 x AlexNet-shaped 0.196 -> 0.191 (with the set-up of four edges at a time 0.188).  With the refinements the same costs 1 to 2 % (their loops have fewer registers
-// left), so they keep the plain forms.
+// just found waits 20, a taken branch 25.  So what is rare is looked for once per step, in one comparison; errors and bookings beyond 32 bits are
+// noticed behind the loop (or every 32 steps); loads are kept in flight together (in_flight: left to itself the compiler now and then waits for one before it asks
+// for the next, a trip to memory per step), the first edge of a release is asked for as soon as it is known that there is one.
+//
+// Order.  A dequeue touches its device row, a release the link rows of its node and the words of consumers.  So the only orders that matter are those of the
+// dequeues on a device, of the releases on a node, and that everything that may make a task READY has been released before one that is READY later is
+// dequeued, and the other way round.  Hence two queues: releases go on until the horizon, before which no task that is still to be dequeued can end (the first
+// READY time of every op and its exeTime: q.kd + q.ex), then dequeues until the next release.  Within a step an op's events of one kind go together up
+// to the other ops' first one (run_mask), whatever lies between them of the other kind; ops with several edges, or parameters, release of every node the
+// parts that come first.  Against one queue in the order of time, with runs of ops with one edge: steps of the Inception-v3-shaped graph 1980 -> 1752,
+// ResNet-101 4024 -> 3246, NMT 39148 -> 32856, AlexNet 157 -> 134.
+// Both together (with the parts of a step sorted only where two on a node are out of order), per launch: 4096 x Inception-v3-shaped 6.02 -> 5.24 ms, 4096 x ResNet-101-shaped
+// 11.4 -> 9.85, 1024 x NMT-shaped 67.5 -> 56.3, 1024 x AlexNet-shaped 0.179 -> 0.163, training iterations (1024 x Inception-v3-shaped) 16.4 -> 12.3, general strategies
+// (777 x ResNet-101-shaped on 5 x 3 devices) 21.9 -> 18.2, with parameter traffic (4096 x Inception-v3-shaped) 11.3 -> 7.4.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
 template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX, class PaceX = NoPace>
 __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec, PaceX pace = PaceX()) {
     static_assert(!(REG && L64), "64-bit link rows go with the general form");
-    constexpr bool RUNS = Q == Q_SLOT;       // runs of events (see run_events): on graphs of more than 64 ops
-    constexpr bool LEAN = !SimX::kExt;
+    constexpr bool EDGED = !SimX::kExt;      // without parameter traffic only ops with an edge have anything to release
     typedef typename std::conditional<L64, u64, uint32_t>::type T;      // times of transfers: absolute, or relative to the epoch
     const uint32_t lane = lane_id();
     PROF_DECL
     const SimDev& S = m.S;
     u64* words = mem.words;
-    u64 overflow_m = 0;                      // lanes that reached TIME_LIMIT
-    u64 retry_m = 0;                         // lanes whose link row is booked beyond 32 bits
+    uint32_t latest_hi = 0;                  // per lane: high half of the latest time (see TIME_LIMIT)
+    uint32_t latest_link = 0;                // per lane: latest time of a transfer relative to the epoch (all ones: a link row is booked beyond 32 bits)
+    auto beyond_32 = [&]() { return !L64 && ballot(latest_link == 0xffffffffu) != 0; };
     const uint32_t G = m.gpn();
     const uint32_t n_links = S.n_rows - S.n_dev;
     // chosen per lane between the two of a pair: in vector registers, so that a select needs one scalar operand only
@@ -608,8 +660,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     q.n_spill = first_u32(q.n_spill);
     q.spill_min = first_u64(q.spill_min);
     if (RECORD) { rec.step = first_u64(rec.step); rec.next = first_u32(rec.next); rec.n_snaps = first_u32(rec.n_snaps); rec.check_below = first_u32(rec.check_below); }
-    const uint32_t max_steps = 2 * S.n_ops * WAVE + 8;
-    uint32_t stop = PaceX::kOn ? 0 : max_steps, last = 0;
+    // Steps to the next look at the pace, and steps left behind that (every step deals with an event: a run that needs more has gone wrong).
+    uint32_t max_steps = 2 * S.n_ops * WAVE + 8, last = 0;
+    int32_t left = 0;
     uint32_t snap_key = KEY_NONE;            // RECORD: key of the next snapshot boundary
     auto set_snap_key = [&]() {
         if (RECORD) {
@@ -619,137 +672,119 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     };
     set_snap_key();
     auto keys_min = [&](uint32_t key) __attribute__((always_inline)) { return Q == Q_OP16 ? row0_min_u32(key) : wave_min_u32(key); };
-    uint32_t kmin = keys_min(q.key);
-    for (uint32_t step = 0;; step++) {
-        if (__builtin_expect(step >= stop, 0)) {
-            if (step >= max_steps) break;
-            pace.at(first_u32(last));
-            stop = step + PACE_STEPS < max_steps ? step + PACE_STEPS : max_steps;
-        }
-        // ---- pop.  kmin: smallest key of the slots
-        if (__builtin_expect(kmin >= KEY_REFRESH, 0)) {
-            if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
-            set_snap_key();
-            kmin = keys_min(q.key);
-        }
-        if (Q == Q_SLOT && q.n_spill) {
-            for (uint32_t guard = 0; q.n_spill && guard < S.n_ops + WAVE; guard++) {
-                const u64 top = 2 * st.E + kmin;
-                if (q.spill_min > top) break;
-                if (q.spill_min == top) {
-                    // equal keys: only needed if a spilled op comes first; bring in all of them
-                    const uint32_t lo_op = wave_min_u32(q.key == kmin ? q.op : NO_OP);
-                    uint32_t sop = NO_OP;
-                    for (uint32_t t = lane; t < q.n_spill; t += WAVE)
-                        if (mem.spill_key[t] == top && mem.spill_op[t] < sop) sop = mem.spill_op[t];
-                    if (wave_min_u32(sop) > lo_op) break;
-                }
-                queue_unspill<ROWL>(mem, st);
-                kmin = wave_min_u32(q.key);
+    // The smallest keys of both kinds, and the first one at which something not known yet may have to be released (at most KEY_REFRESH; 0: to be found).
+    uint32_t m_deq = keys_min(q.kd), m_rel = keys_min(q.kr), horizon = 0;
+    uint32_t spill_key = KEY_NONE;           // of the smallest word on the spill list
+    for (;;) {
+        // ---- pop
+        uint32_t kmin = m_deq < m_rel ? m_deq : m_rel;       // smallest key of the slots
+        left--;
+        if (__builtin_expect((int32_t)(kmin | (uint32_t)left | (Q == Q_SLOT ? 0u - q.n_spill : 0u)) < 0, 0)) {
+            if (left < 0) {
+                if (max_steps == 0) break;
+                if (beyond_32()) break;
+                if (PaceX::kOn) pace.at(first_u32(last));
+                left = (int32_t)(PACE_STEPS < max_steps ? PACE_STEPS : max_steps);
+                max_steps -= (uint32_t)left;
             }
-            if (LEAN) vector_loads_done();
+            if (kmin >= KEY_REFRESH) {
+                if (!advance_epoch<Q, ROWL, L64>(mem, st, n_links)) break;
+                set_snap_key();
+                m_deq = keys_min(q.kd);
+                m_rel = keys_min(q.kr);
+                kmin = m_deq < m_rel ? m_deq : m_rel;
+                horizon = 0;
+            }
+            if (Q == Q_SLOT && q.n_spill) {
+                for (uint32_t guard = 0; q.n_spill && guard < S.n_ops + WAVE; guard++) {
+                    const u64 top = 2 * st.E + kmin;
+                    if (q.spill_min > top) break;
+                    if (q.spill_min == top) {
+                        // equal keys: only needed if a spilled op comes first; bring in all of them
+                        const uint32_t lo_op = wave_min_u32(slot_key(q) == kmin ? q.op : NO_OP);
+                        uint32_t sop = NO_OP;
+                        for (uint32_t t = lane; t < q.n_spill; t += WAVE)
+                            if (mem.spill_key[t] == top && mem.spill_op[t] < sop) sop = mem.spill_op[t];
+                        if (wave_min_u32(sop) > lo_op) break;
+                    }
+                    queue_unspill<ROWL>(mem, st);
+                    m_deq = wave_min_u32(q.kd); m_rel = wave_min_u32(q.kr);
+                    kmin = m_deq < m_rel ? m_deq : m_rel;
+                }
+                horizon = 0;                     // (ops on the list are not looked at: everything in the order of time)
+                spill_key = q.n_spill ? rel_key(q.spill_min, st.E) : KEY_NONE;
+                vector_loads_done();
+            }
         }
         if (RECORD) {
             // the state before the first event at or after a multiple of `step` is a snapshot
             while (kmin >= snap_key) {
-                if (save_loop_snapshot<ROWL, L64>(m, mem, st, rec, st.E + (kmin >> 1))) return RUN_CONVERGED;
+                if (save_loop_snapshot<ROWL, L64>(m, mem, st, rec, st.E + (kmin >> 1))) return beyond_32() ? RESULT_RETRY : RUN_CONVERGED;
                 set_snap_key();
             }
         }
-        u64 at = ballot(q.key == kmin);
-        uint32_t i;
-        if (Q != Q_SLOT) {
-            i = __builtin_ctzll(at);         // lowest op among equal keys
-            at &= 0 - at;
-        } else {
-            if (at & (at - 1)) {
-                i = wave_min_u32(lanes_of(at) ? q.op : NO_OP);
-                at &= ballot(q.op == i);
+        // What is released next?  The first event if it is a release, else whatever comes before the horizon (and the next snapshot).
+        const uint32_t ahead = RECORD && snap_key < horizon ? snap_key : horizon;
+        const bool rel = m_rel < (m_deq > ahead ? m_deq : ahead);
+        // the first op with that event (its slot: at), the smallest key of the others
+        u64 at;
+        uint32_t i, other_key;
+        auto pop = [&](uint32_t key) __attribute__((always_inline)) {
+            at = ballot(key == kmin);
+            if (Q != Q_SLOT) {
+                i = __builtin_ctzll(at);         // lowest op among equal keys
+                at = ballot(lane == i);
             } else {
-                i = readlane_u32(q.op, __builtin_ctzll(at));
+                if (at & (at - 1)) {
+                    i = wave_min_u32(lanes_of(at) ? q.op : NO_OP);
+                    at &= ballot(q.op == i);
+                } else {
+                    i = readlane_u32(q.op, __builtin_ctzll(at));
+                }
             }
-        }
-        if (PaceX::kOn) last = i;
-        const u64 K = 2 * st.E + kmin;       // the popped word
-        PROF_MARK(1)
-        // Everything that depends only on i is requested together, the static record through the vector unit as well (a
-        // scalar load of it would be sunk below the wait for the words and be waited for once more), and the smallest key
-        // of the other ops is found while that is on its way.  It and the keys that come up in this step make the next kmin.
-        u64 k0 = load_word<ROWL>(words, i);
-        const uint4 h = mem.hdr[i];
-        const uint4* lite_at = (const uint4*)mem.op_lite + 2 * (size_t)vector_copy(i);
-        const uint4 lite0 = lite_at[0], lite1 = lite_at[1];
-        if (LEAN) in_flight();
-        const uint32_t other_key = keys_min(lanes_of(at) ? KEY_NONE : q.key);
-        if (LEAN) in_flight();
-        uint32_t next_kmin = other_key;
-        const uint32_t exe = first_u32(h.x), offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
-        OpCfg ci;
-        ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
-        OpLite lite;
-        lite.out_begin = first_u32(lite0.x); lite.out_end = first_u32(lite0.y); lite.param_bytes = first_u32(lite0.z);
-        lite.first.word = first_u32(lite1.x); lite.first.in_pos = SimX::kOvr ? first_u32(lite1.y) : 0u; lite.first.row = first_u32(lite1.z);
-        const uint32_t out_begin = lite.out_begin, out_end = lite.out_end;
-        // What a release needs of an edge: the consumer's words and the kept rows of both sides.
-        auto load_edge = [&](const EdgeLite& lit, uint32_t ei) __attribute__((always_inline)) {
-            const uint32_t j = lit.word & EL_DST;
-            const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
-            if (SimX::kOvr && mem.priv) {
-                // a trial mutation's own edges have rows of their own
-                if (i == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (ei - out_begin)) * (KEPT_ROWS * ROWL);
-                else if (j == m.ov_op) row = mem.priv + (size_t)lit.in_pos * (KEPT_ROWS * ROWL);
-            }
-            const uint32_t* p = row + (ROWL < WAVE ? (lane & (ROWL - 1)) : lane);
-            EdgeLoad v;
-            v.w = load_word<ROWL>(words, j);
-            v.f = p[KR_F * ROWL]; v.clo = p[KR_CLO * ROWL]; v.chi = p[KR_CHI * ROWL]; v.plo = p[KR_PLO * ROWL]; v.phi = p[KR_PHI * ROWL];
-            v.clo2 = 0; v.chi2 = 0; v.plo2 = 0; v.phi2 = 0; v.sortw = 0;
-            if (lit.word & EL_FOUR) { v.clo2 = p[KR_CLO2 * ROWL]; v.chi2 = p[KR_CHI2 * ROWL]; v.plo2 = p[KR_PLO2 * ROWL]; v.phi2 = p[KR_PHI2 * ROWL]; }
-            if (!REG) v.sortw = p[KR_SORT * ROWL];
-            if (LEAN) in_flight();
-            return v;
+            if (PaceX::kOn) last = i;
+            cnt.n_events++;
         };
-        // (from memory the first edge's are asked for now, and are there when it has been found out which parts are released)
-        constexpr bool EARLY = LEAN && Q == Q_SLOT;
-        EdgeLite lit = lite.first;
-        EdgeLoad ed;
-        const uint32_t dev_p = m.template device_of<REG>(i, ci);
-        PROF_MARK(1)
-        PROF_VMWAIT(2)
-        // distance of every event of the op from the popped one (words that are no events: all ones, an odd value)
-        uint32_t d = near_u32<LEAN>(k0 - K);
-        const u64 mask_same = ballot(d == 0);
-        if (!mask_same) { cnt.exit_code = 2; return RESULT_INTERNAL; }
-        if (EARLY && !(kmin & 1) && out_end > out_begin) ed = load_edge(lit, out_begin);
-        cnt.n_events++;
-        u64 mask = mask_same;
-        // events at several times (asked anew where it matters: kept, the answer would be a lane mask)
-        auto mixed = [&]() __attribute__((always_inline)) { return RUNS && (LEAN ? opaque64(mask & ~mask_same) != 0 : mask != mask_same); };
-        if (RUNS && ((kmin & 1) ? REG : (out_end - out_begin == 1 && !(SimX::kExt && S.sync)))) {
-            const u64 kind_m = ballot((d & 1u) == 0u);
-            if (kind_m != mask_same) {
-                uint32_t bound = other_key >= KEY_FAR ? KEY_NONE : other_key - kmin;
-                if (Q == Q_SLOT && q.n_spill) {
-                    const u64 s = q.spill_min - K;
-                    if (s < bound) bound = (uint32_t)s;
+        // A run: the events of the op up to the first event of another op of that kind, the first one of the other kind that may matter, the first one the
+        // run itself may bring about, and the next snapshot.
+        auto run_mask = [&](uint32_t d, uint32_t until, uint32_t first_new) __attribute__((always_inline)) {
+            uint32_t b = other_key < until ? other_key : until;
+            b = spill_key < b ? spill_key : b;
+            if (RECORD) b = snap_key < b ? snap_key : b;
+            b -= kmin;
+            first_new = exe_span(first_new);
+            b = b < first_new ? b : first_new;
+            return ballot(d < (b > 1u ? b : 1u));
+        };
+        if (!rel) {
+            // ---- dequeue READY tasks: start = max(readyTime, device free), end = start + exeTime
+            pop(q.kd);
+            const u64 K = 2 * st.E + kmin;       // the popped word
+            PROF_MARK(1)
+            // What depends only on i is requested together, and the smallest key of the other ops is found while that is on its way.
+            u64 k0 = load_word<ROWL>(words, i);
+            const uint4 h = mem.hdr[i];
+            in_flight();
+            other_key = keys_min(lanes_of(at) ? KEY_NONE : q.kd);
+            in_flight();
+            const uint32_t exe = first_u32(h.x), offs = first_u32(h.y), hflags = first_u32(h.w);
+            OpCfg ci;
+            ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
+            const uint32_t dev_p = m.template device_of<REG>(i, ci);
+            PROF_MARK(1)
+            PROF_VMWAIT(2)
+            const uint32_t d = event_distance(k0, K);
+            u64 mask = run_mask(d, m_rel, exe);
+            const bool may_share = !REG && ((SimX::kExt && m.devmap != nullptr) || !(ci.stride == 1 && ci.parts <= S.n_dev));
+            if (may_share) {
+                // of the parts on one device only the first
+                for (u64 t = mask & ballot(d != 0); t; t &= t - 1) {
+                    const int p = __builtin_ctzll(t);
+                    const uint32_t dp = readlane_u32(d, p), vp = readlane_u32(dev_p, p);
+                    if (ballot(dev_p == vp) & ballot(d < dp)) mask &= ~(1ull << p);
                 }
-                const u64 odd_m = ~kind_m & ballot(d != KEY_NONE);
-                if (odd_m) {
-                    const uint32_t odd = part_min_u32<ROWL>(lanes_of(odd_m) ? d : KEY_NONE);
-                    bound = odd < bound ? odd : bound;
-                }
-                const uint32_t e = (kmin & 1) ? exe : next_exe;
-                const uint32_t first_new = e >= RUN_SPAN / 2 ? RUN_SPAN : 2 * e;
-                bound = first_new < bound ? first_new : bound;
-                if (RECORD && snap_key < KEY_FAR) { const uint32_t s = snap_key - kmin; bound = s < bound ? s : bound; }
-                mask = mask_same | (kind_m & ballot(d < bound));
             }
-        }
-        const bool in_mask = lanes_of(mask);
-        uint32_t d_new = d;
-
-        if (kmin & 1) {
-            // dequeue READY tasks: start = max(readyTime, device free), end = start + exeTime
+            const bool in_mask = lanes_of(mask);
             u64 end;
             if (REG) {
                 const u64 f = mem.crow[dev_p];               // (in range for every lane)
@@ -758,28 +793,121 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 if (in_mask) mem.crow[dev_p] = end;
                 wave_sync();
             } else {
-                const bool may_share = (SimX::kExt && m.devmap != nullptr) || !(ci.stride == 1 && ci.parts <= S.n_dev);
-                end = fifo_commit(in_mask, dev_p, exe, K >> 1, may_share, m.L);
+                end = fifo_commit(in_mask, dev_p, exe, k0 >> 1, may_share, m.L);
             }
-            overflow_m |= mask & ballot(end >= TIME_LIMIT);
-            const bool releases = out_end > out_begin || (SimX::kExt && S.sync && lite.param_bytes != 0);
             const u64 w = end << 1;
-            if (releases) {
-                d_new = in_mask ? near_u32<LEAN>(w - K) : d;
-            } else {
-                d_new = in_mask ? KEY_NONE : d;
+            const uint32_t dw = near_u32(w - K);
+            const uint32_t none = (hflags & HDR_RELEASES) ? 0u : KEY_NONE;
+            if (in_mask) {
+                k0 = w | ((u64)none << 32 | none);           // (nothing to release: W_NONE)
+                words[(size_t)i * ROWL + lane] = k0;
+                latest_hi = (uint32_t)(end >> 32) > latest_hi ? (uint32_t)(end >> 32) : latest_hi;
+                if (RECORD && rec.end_try) rec.end_try[(size_t)i * ROWL + lane] = rec.tag | end;
             }
-            if (in_mask) k0 = releases ? w : W_NONE;
-            if (RECORD) { if (in_mask && rec.end_try) rec.end_try[(size_t)i * ROWL + lane] = rec.tag | end; }
             PROF_MARK(3)
+            // ---- the op's next events
+            const uint32_t nd = part_min_u32<ROWL>(in_mask ? KEY_NONE : d), nr = part_min_u32<ROWL>(in_mask ? dw | none : KEY_NONE);
+            const uint32_t nk = next_key(kmin, nd), new_rel = next_key(kmin, nr);
+            const bool me = lanes_of(at);
+            q.kd = me ? nk : q.kd;
+            const uint32_t r = me ? new_rel : KEY_NONE;
+            q.kr = r < q.kr ? r : q.kr;
+            if (Q == Q_SLOT) q.op = me && (q.kd & q.kr) == KEY_NONE ? NO_OP : q.op;
+            m_deq = nk < other_key ? nk : other_key;
+            m_rel = new_rel < m_rel ? new_rel : m_rel;
+            horizon = 0;
         } else {
+            // ---- release the successors of finished tasks
+            kmin = m_rel;
+            pop(q.kr);
+            const u64 K = 2 * st.E + kmin;
+            PROF_MARK(1)
+            // (the static record through the vector unit as well: a scalar load of it would be sunk below the wait for the words and be waited for once more)
+            u64 k0 = load_word<ROWL>(words, i);
+            const uint4 h = mem.hdr[i];
+            const uint4* lite_at = (const uint4*)mem.op_lite + 2 * (size_t)vector_copy(i);
+            const uint4 lite0 = lite_at[0], lite1 = lite_at[1];
+            in_flight();
+            other_key = keys_min(lanes_of(at) ? KEY_NONE : q.kr);
+            const uint32_t x = keys_min(__builtin_elementwise_add_sat(q.kd, q.ex));
+            horizon = (x < KEY_REFRESH ? x : KEY_REFRESH) - 1;
+            in_flight();
+            const uint32_t offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
+            OpCfg ci;
+            ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
+            OpLite lite;
+            lite.out_begin = first_u32(lite0.x); lite.out_end = first_u32(lite0.y); lite.param_bytes = first_u32(lite0.z);
+            lite.first.word = first_u32(lite1.x); lite.first.in_pos = SimX::kOvr ? first_u32(lite1.y) : 0u; lite.first.row = first_u32(lite1.z);
+            const uint32_t out_begin = lite.out_begin, out_end = lite.out_end;
+            // What a release needs of an edge: the consumer's words and the kept rows of both sides.
+            auto load_edge = [&](const EdgeLite& lit, uint32_t ei) __attribute__((always_inline)) {
+                const uint32_t j = lit.word & EL_DST;
+                const uint32_t* row = mem.rows + (size_t)lit.row * ROWL;
+                if (SimX::kOvr && mem.priv) {
+                    // a trial mutation's own edges have rows of their own
+                    if (i == m.ov_op) row = mem.priv + (size_t)(m.ov_in + (ei - out_begin)) * (KEPT_ROWS * ROWL);
+                    else if (j == m.ov_op) row = mem.priv + (size_t)lit.in_pos * (KEPT_ROWS * ROWL);
+                }
+                const uint32_t* p = row + (ROWL < WAVE ? (lane & (ROWL - 1)) : lane);
+                EdgeLoad v;
+                v.w = load_word<ROWL>(words, j);
+                v.exe = mem.hdr[j].x;
+                v.f = p[KR_F * ROWL]; v.clo = p[KR_CLO * ROWL]; v.chi = p[KR_CHI * ROWL]; v.plo = p[KR_PLO * ROWL]; v.phi = p[KR_PHI * ROWL];
+                v.clo2 = 0; v.chi2 = 0; v.plo2 = 0; v.phi2 = 0; v.sortw = 0;
+                if (lit.word & EL_FOUR) { v.clo2 = p[KR_CLO2 * ROWL]; v.chi2 = p[KR_CHI2 * ROWL]; v.plo2 = p[KR_PLO2 * ROWL]; v.phi2 = p[KR_PHI2 * ROWL]; }
+                if (!REG) v.sortw = p[KR_SORT * ROWL];
+                in_flight();
+                return v;
+            };
+            // (from memory the first edge's are asked for now, and are there when it has been found out which parts are released)
+            constexpr bool EARLY = Q == Q_SLOT;
+            EdgeLite lit = lite.first;
+            EdgeLoad ed;
+            const uint32_t dev_p = m.template device_of<REG>(i, ci);
+            PROF_MARK(1)
+            PROF_VMWAIT(2)
+            const uint32_t d = event_distance(k0, K);
+            if (EARLY && (EDGED || out_end > out_begin)) ed = load_edge(lit, out_begin);
+            u64 mask = run_mask(d, horizon, next_exe);
             const uint32_t node_p = m.node_of(dev_p);
-            const uint32_t now = kmin >> 1;                  // relative to the epoch
-            // The parts go in order: by part, or in a run by (time, part).  For a run what the passes read of the parts is
-            // first brought into that order (lane t then stands for the t-th part).
+            // Transfers from one node (whose link rows are its own) go in the order of (time, edge, part), those from different nodes in any.  The edges
+            // are gone through one after the other, each part by part, and parameters behind them: of the parts on a node only the first may go where there
+            // is more than one edge to go through, and with one edge the parts are sorted where one on the same node before it is later.
+            uint32_t sort = 0;
+            {
+                const u64 later = mask & ballot(d != 0);
+                if (later) {
+                    if (out_end - out_begin > 1 || (SimX::kExt && S.sync && lite.param_bytes)) {
+                        for (u64 t = later; t; t &= t - 1) {
+                            const int p = __builtin_ctzll(t);
+                            const uint32_t dp = readlane_u32(d, p), np = readlane_u32(node_p, p);
+                            if (ballot(node_p == np) & ballot(d < dp)) mask &= ~(1ull << p);
+                        }
+                    } else if (!REG) {
+                        sort = 1;
+                    } else {
+                        // (the parts of a node are consecutive lanes; on a machine that the op goes all the way round they may come up once more at the end)
+                        const uint32_t local = m.local_of(dev_p, node_p), mine = lanes_of(mask) ? d : KEY_NONE;
+                        uint32_t before = lanes_of(mask) ? d : 0u, latest = 0;
+                        for (uint32_t t = 1; t < G; t++) {
+                            before = wave_shr1_u32(before);
+                            before = local >= t ? before : 0u;
+                            latest = before > latest ? before : latest;
+                        }
+                        if (ballot(latest > mine)) sort = 1;
+                        if (ci.parts + G > S.n_dev) {
+                            const uint32_t node0 = readlane_u32(node_p, 0);
+                            const u64 same = mask & ballot(node_p == node0), again = same & ballot(dev_p < ci.off);
+                            if (again && same != again) sort = 1;
+                        }
+                    }
+                }
+            }
+            const bool in_mask = lanes_of(mask);
+            // sorted: by (time, part); lane t then stands for the t-th part in what the passes read of the parts
             uint32_t order = lane;
             u64 parts_m = mask;
-            if (mixed()) {
+            if (sort) {
                 uint32_t rank = 0;
                 u64 t = mask;
                 while (t) {
@@ -794,7 +922,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 parts_m = __popcll(mask) == 64 ? ~0ull : (1ull << __popcll(mask)) - 1;
             }
             uint32_t now_v = (kmin + d) >> 1, dev_v = dev_p;
-            if (mixed()) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
+            if (sort) { now_v = gather_u32(now_v, order); dev_v = gather_u32(dev_p, order); }
             // REG: what a pass needs of its producer part, ready to be read out of the part's lane
             const uint32_t node_v = m.node_of(dev_v);
             const uint32_t near_at_v = lds_addr(mem.lrow) + 4 * (dev_v * G), far_at_v = lds_addr(mem.lrow) + 4 * (S.n_nodes * G * G + node_v * S.n_nodes);
@@ -812,14 +940,12 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 lit.in_pos = SimX::kOvr ? readlane_u32(lits.y, l) : 0u;
                 lit.row = readlane_u32(lits.z, l);
             };
-            // (LEAN: without parameter traffic only ops with an edge have anything to release, so there is a first one)
-            for (uint32_t ei = out_begin; LEAN || ei < out_end; ei++) {
-                if (!LEAN && ei != out_begin) next_edge(ei);
+            for (uint32_t ei = out_begin; EDGED || ei < out_end; ei++) {
                 if (!EARLY) ed = load_edge(lit, ei);
                 const uint32_t el = lit.word;
                 const uint32_t j = el & EL_DST;
                 const u64 w = ed.w;
-                const uint32_t f = ed.f, sortw = ed.sortw;
+                const uint32_t f = ed.f, sortw = ed.sortw, ed_exe = ed.exe;
                 uint32_t clo = ed.clo, chi = ed.chi, plo = ed.plo, phi = ed.phi, clo2 = ed.clo2, chi2 = ed.chi2, plo2 = ed.plo2, phi2 = ed.phi2;
                 if (ROWL < WAVE) {
                     // (no part there: an empty range)
@@ -855,7 +981,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 PROF_MARK(4)
                 PROF_VMWAIT(5)
 
-                if (mixed()) {
+                if (sort) {
                     plo = gather_u32(plo, order); phi = gather_u32(phi, order);
                     if (el & EL_FOUR) { plo2 = gather_u32(plo2, order); phi2 = gather_u32(phi2, order); }
                 }
@@ -1011,32 +1137,38 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 if (touched_m) {
                     const uint32_t left = pending - hits;
                     const u64 abs = L64 ? (u64)ready : st.E + ready;
-                    if (!L64) retry_m |= touched_m & ballot(ready == 0xffffffffu);
-                    overflow_m |= touched_m & ballot(abs >= TIME_LIMIT);
-                    const u64 ready_m = touched_m & ballot(left == 0);
-                    if (touched) words[(size_t)j * ROWL + lane] = left == 0 ? (abs << 1) | 1u : (W_WAIT | ((u64)left << 48) | (abs & (TIME_LIMIT - 1)));
+                    const u64 zero_m = ballot(left == 0), ready_m = touched_m & zero_m;
+                    const uint32_t abs_lo = (uint32_t)abs, abs_hi = (uint32_t)(abs >> 32);
+                    const uint32_t w_lo = lanes_of(zero_m) ? (abs_lo << 1) | 1u : abs_lo;
+                    const uint32_t w_hi = lanes_of(zero_m) ? __builtin_amdgcn_alignbit(abs_hi, abs_lo, 31) : (left << 16) | 0x80000000u | (abs_hi & 0xffffu);
+                    if (lanes_of(touched_m)) {
+                        words[(size_t)j * ROWL + lane] = (u64)w_hi << 32 | w_lo;
+                        latest_hi = abs_hi > latest_hi ? abs_hi : latest_hi;
+                        if (!L64) latest_link = (uint32_t)ready > latest_link ? (uint32_t)ready : latest_link;
+                    }
                     if (ready_m) {
                         uint32_t rel = (uint32_t)ready;
                         if constexpr (L64) { const u64 r = ready - st.E; rel = r >= KEY_FAR ? KEY_FAR : (uint32_t)r; }
                         const uint32_t first = part_min_of<ROWL>(rel, ready_m);
                         const uint32_t key = first >= KEY_REFRESH - 1 ? KEY_FAR : 2 * first + 1;
-                        queue_insert<Q, ROWL, LEAN>(mem, st, j, key);
-                        next_kmin = key < next_kmin ? key : next_kmin;
+                        const uint32_t ex = exe_span(ed_exe);
+                        queue_insert<Q, ROWL>(mem, st, j, key, KEY_NONE, ex);
+                        m_deq = key < m_deq ? key : m_deq;
+                        const uint32_t x = first_u32(__builtin_elementwise_add_sat(key, ex) - 1);
+                        horizon = x < horizon ? x : horizon;
                     }
                 }
                 PROF_MARK(7)
-                if (LEAN) {
-                    if (ei + 1 >= out_end) break;
-                    next_edge(ei + 1);
-                    if (EARLY) ed = load_edge(lit, ei + 1);
-                }
+                if (ei + 1 >= out_end) break;
+                next_edge(ei + 1);
+                if (EARLY) ed = load_edge(lit, ei + 1);
             }
             // (chains: code that inputs without parameters do not run is laid out behind the rest -- 64 chains x 16 changes with unequal links on the
             // AlexNet-shaped graph 3.42 -> 3.32 ms, and 0.5 % less with parameters; in batches it costs 1 % with parameters and gives nothing)
             if (SimX::kExt && (RECORD ? __builtin_expect(S.sync, 0) : S.sync)) {
                 // parameter synchronisation (see run_events): a replica that has finished sends its gradient of the shard
                 // to the owner's device, queued on its link row after the op's transfers to consumers
-                const uint32_t pbytes = lite.param_bytes;
+                const uint32_t pbytes = lite.param_bytes, now = (kmin + d) >> 1;      // (parts that share a link row are released at one time)
                 if (pbytes) {
                     const OpCfg cfull = m.cfg(i);
                     const uint32_t pdims = m.T.ops[i].param_dims;
@@ -1074,11 +1206,11 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                         const u64 act_m = ballot(act);
                         if constexpr (L64) {
                             const u64 end = fifo_commit(act, act ? row_i : 0u, ns, st.E + now, true, WaveLds{mem.lrow64, nullptr, nullptr, mem.tag});
-                            overflow_m |= act_m & ballot(end >= TIME_LIMIT);
+                            if (act) latest_hi = (uint32_t)(end >> 32) > latest_hi ? (uint32_t)(end >> 32) : latest_hi;
                         } else {
                             const uint32_t end = fifo_links(act, act ? row_i : 0u, ns, now, true, mem);
-                            retry_m |= act_m & ballot(end == 0xffffffffu);
-                            overflow_m |= act_m & ballot(st.E + end >= TIME_LIMIT);
+                            const uint32_t hi = (uint32_t)((st.E + end) >> 32);
+                            if (act) { latest_link = end > latest_link ? end : latest_link; latest_hi = hi > latest_hi ? hi : latest_hi; }
                         }
                         if (STATS) {
                             cnt.n_comm += __popcll(act_m);
@@ -1087,26 +1219,25 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                     }
                 }
             }
-            d_new = in_mask ? KEY_NONE : d;
-            if (in_mask) k0 = W_NONE;
-        }
-        if (in_mask) words[(size_t)i * ROWL + lane] = k0;
-        // ---- the op's next event
-        const uint32_t nd = part_min_u32<ROWL>(d_new);
-        uint32_t nk = __builtin_elementwise_add_sat(kmin, nd);
-        if (nk >= KEY_FAR) nk = ballot((int32_t)(uint32_t)(k0 >> 32) >= 0) ? KEY_FAR : KEY_NONE;
-        {
+            if (in_mask) {
+                k0 = W_NONE;
+                words[(size_t)i * ROWL + lane] = k0;
+            }
+            // ---- the op's next event
+            const uint32_t nd = part_min_u32<ROWL>(in_mask ? KEY_NONE : d);
+            const uint32_t nk = next_key(kmin, nd);
             const bool me = lanes_of(at);
-            q.key = me ? nk : q.key;
-            if (Q == Q_SLOT && nk == KEY_NONE) q.op = me ? NO_OP : q.op;
+            q.kr = me ? nk : q.kr;
+            if (Q == Q_SLOT) q.op = me && (q.kd & q.kr) == KEY_NONE ? NO_OP : q.op;
+            m_rel = nk < other_key ? nk : other_key;
         }
-        kmin = nk < next_kmin ? nk : next_kmin;
-        if (Q == Q_SLOT && q.n_spill) kmin = wave_min_u32(q.key);        // (what came up may have gone to the spill list)
-        if (retry_m) return RESULT_RETRY;
+        if (Q == Q_SLOT && q.n_spill) { m_deq = wave_min_u32(q.kd); m_rel = wave_min_u32(q.kr); }        // (what came up may have gone to the spill list)
         PROF_MARK(7)
     }
     PROF_STORE(cnt)
-    return overflow_m ? RESULT_OVERFLOW : 0;
+    if (beyond_32()) return RESULT_RETRY;
+    if (left < 0 && max_steps == 0) { cnt.exit_code = 2; return RESULT_INTERNAL; }
+    return ballot(latest_hi >= (uint32_t)(TIME_LIMIT >> 32)) ? RESULT_OVERFLOW : 0;
 }
 
 }  // namespace ffsim
