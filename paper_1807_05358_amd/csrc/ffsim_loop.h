@@ -671,6 +671,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         }
     };
     set_snap_key();
+    auto keys_min2 = [&](uint32_t& a, uint32_t& b) __attribute__((always_inline)) { if (Q == Q_OP16) row0_min2_u32(a, b); else wave_min2_u32(a, b); };
     auto keys_min = [&](uint32_t key) __attribute__((always_inline)) { return Q == Q_OP16 ? row0_min_u32(key) : wave_min_u32(key); };
     // The smallest keys of both kinds, and the first one at which something not known yet may have to be released (at most KEY_REFRESH; 0: to be found).
     uint32_t m_deq = keys_min(q.kd), m_rel = keys_min(q.kr), horizon = 0;
@@ -806,7 +807,8 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             }
             PROF_MARK(3)
             // ---- the op's next events
-            const uint32_t nd = part_min_u32<ROWL>(in_mask ? KEY_NONE : d), nr = part_min_u32<ROWL>(in_mask ? dw | none : KEY_NONE);
+            uint32_t nd = in_mask ? KEY_NONE : d, nr = in_mask ? dw | none : KEY_NONE;
+            if (ROWL == 16) row0_min2_u32(nd, nr); else wave_min2_u32(nd, nr);
             const uint32_t nk = next_key(kmin, nd), new_rel = next_key(kmin, nr);
             const bool me = lanes_of(at);
             q.kd = me ? nk : q.kd;
@@ -823,18 +825,23 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             const u64 K = 2 * st.E + kmin;
             PROF_MARK(1)
             // (the static record through the vector unit as well: a scalar load of it would be sunk below the wait for the words and be waited for once more)
-            u64 k0 = load_word<ROWL>(words, i);
-            const uint4 h = mem.hdr[i];
+            // (and ahead of the words: it is the same for all candidates and close by, the words are this candidate's and often are not.  Loads come back
+            // in the order they were asked for in, so the first edge is asked for while the words are on their way:
+            // with the minima in pairs 1024 x AlexNet-shaped 163.4 -> 157.9 us, 1024 x NMT-shaped 56.3 -> 55.7 ms, 4096 proposals 57.7 -> 55.7.)
+            // With parameter traffic an op may have no edge to ask for, and the branch around it costs more than that gives: words first there.
             const uint4* lite_at = (const uint4*)mem.op_lite + 2 * (size_t)vector_copy(i);
-            const uint4 lite0 = lite_at[0], lite1 = lite_at[1];
+            u64 k0;
+            uint4 h, lite0, lite1;
+            if (!EDGED) { k0 = load_word<ROWL>(words, i); h = mem.hdr[i]; }
+            lite0 = lite_at[0]; lite1 = lite_at[1];
             in_flight();
-            other_key = keys_min(lanes_of(at) ? KEY_NONE : q.kr);
-            const uint32_t x = keys_min(__builtin_elementwise_add_sat(q.kd, q.ex));
+            if (EDGED) { k0 = load_word<ROWL>(words, i); h = mem.hdr[i]; }
+            in_flight();
+            uint32_t x = __builtin_elementwise_add_sat(q.kd, q.ex);
+            other_key = lanes_of(at) ? KEY_NONE : q.kr;
+            keys_min2(other_key, x);
             horizon = (x < KEY_REFRESH ? x : KEY_REFRESH) - 1;
             in_flight();
-            const uint32_t offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
-            OpCfg ci;
-            ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
             OpLite lite;
             lite.out_begin = first_u32(lite0.x); lite.out_end = first_u32(lite0.y); lite.param_bytes = first_u32(lite0.z);
             lite.first.word = first_u32(lite1.x); lite.first.in_pos = SimX::kOvr ? first_u32(lite1.y) : 0u; lite.first.row = first_u32(lite1.z);
@@ -863,11 +870,15 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             constexpr bool EARLY = Q == Q_SLOT;
             EdgeLite lit = lite.first;
             EdgeLoad ed;
+            if (EARLY && EDGED) ed = load_edge(lit, out_begin);
+            const uint32_t offs = first_u32(h.y), next_exe = first_u32(h.z), hflags = first_u32(h.w);
+            OpCfg ci;
+            ci.off = offs & 0xffffu; ci.stride = offs >> 16; ci.parts = hflags & 0xffffu;
             const uint32_t dev_p = m.template device_of<REG>(i, ci);
             PROF_MARK(1)
             PROF_VMWAIT(2)
             const uint32_t d = event_distance(k0, K);
-            if (EARLY && (EDGED || out_end > out_begin)) ed = load_edge(lit, out_begin);
+            if (EARLY && !EDGED && out_end > out_begin) ed = load_edge(lit, out_begin);
             u64 mask = run_mask(d, horizon, next_exe);
             const uint32_t node_p = m.node_of(dev_p);
             // Transfers from one node (whose link rows are its own) go in the order of (time, edge, part), those from different nodes in any.  The edges
@@ -1139,8 +1150,11 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                     const u64 abs = L64 ? (u64)ready : st.E + ready;
                     const u64 zero_m = ballot(left == 0), ready_m = touched_m & zero_m;
                     const uint32_t abs_lo = (uint32_t)abs, abs_hi = (uint32_t)(abs >> 32);
+                    // (both words, then a select: the compiler would put either side into a branch of its own)
+                    uint32_t waits_hi = (left << 16) | 0x80000000u | (abs_hi & 0xffffu), ready_hi = __builtin_amdgcn_alignbit(abs_hi, abs_lo, 31);
+                    asm("" : "+v"(waits_hi), "+v"(ready_hi));
                     const uint32_t w_lo = lanes_of(zero_m) ? (abs_lo << 1) | 1u : abs_lo;
-                    const uint32_t w_hi = lanes_of(zero_m) ? __builtin_amdgcn_alignbit(abs_hi, abs_lo, 31) : (left << 16) | 0x80000000u | (abs_hi & 0xffffu);
+                    const uint32_t w_hi = lanes_of(zero_m) ? ready_hi : waits_hi;
                     if (lanes_of(touched_m)) {
                         words[(size_t)j * ROWL + lane] = (u64)w_hi << 32 | w_lo;
                         latest_hi = abs_hi > latest_hi ? abs_hi : latest_hi;
