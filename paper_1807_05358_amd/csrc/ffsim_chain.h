@@ -34,7 +34,7 @@ struct ChainMeta {
     u64 idle_steps;     // search steps since the chain's best time last improved
     u64 n_converged;    // committed steps whose run stopped early because it re-joined the accepted timeline
     uint32_t loc;       // bit k: which of its two places holds snapshot k of the accepted timeline
-    uint32_t tag;       // tag of the last recorded run (1..0xffff; 0 marks entries never written)
+    uint32_t tag;       // tag of the last recorded run (1..0x7fff, with 0x8000 if it was simulated again, see simulate_loop; 0 marks entries never written)
     // searches that look ahead (ffsim_ahead.h)
     uint32_t moved;     // the strategy has changed since its timeline was recorded
     uint32_t n_tried, n_taken;   // proposals lately decided, and taken
@@ -530,7 +530,7 @@ __device__ __forceinline__ void chain_steps(Engine& en, SimX& m, const SimDev& S
                 const bool record = phase == 2 && !(k == 0 && seg.spare && s + 1 == s_end);
                 const u64 before = cnt.n_events;
                 if (record) {
-                    meta.tag = meta.tag >= 0xffffu ? 0u : meta.tag;
+                    meta.tag = meta.tag >= 0x7fffu ? 0u : meta.tag;
                     if (meta.tag == 0) {
                         // tags start over: forget what earlier runs wrote
                         for (uint32_t t = lane; t < n_words; t += WAVE) cm.end_try[t] = 0;

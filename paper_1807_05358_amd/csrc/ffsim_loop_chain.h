@@ -50,7 +50,8 @@ __device__ __forceinline__ void refresh_rows_for_op(const SimX& m, const LoopMem
 
 // One simulation, from time 0 (k = 0; fill: no edge has kept rows yet) or from snapshot k with op mo changed from
 // configuration ocfg.  Result as for run_loop, never RESULT_RETRY: a run that books a link more than 2^32 ns ahead is
-// started again with 64-bit link rows (what it recorded is written again, the same).
+// started again with 64-bit link rows, under a tag of its own: the first run may have gone on for some steps with times that did not fit,
+// and what it recorded must not be taken for the second one's, which may re-join the accepted timeline without writing the same entries.
 template <bool RECORD, int Q, int ROWL, class SimX>
 __device__ __forceinline__ u64 simulate_loop(SimX& m, const LoopMem& mem, StrategyClass cls, Counters& cnt, Recorder& rec, bool fill, uint32_t k,
                                              uint32_t mo, uint2 ocfg, uint32_t pend_new, u64& mk) {
@@ -76,6 +77,7 @@ __device__ __forceinline__ u64 simulate_loop(SimX& m, const LoopMem& mem, Strate
     }
     if (rc == RESULT_RETRY) {
         rec = rec0;
+        rec.tag |= 1ull << 63;
         cnt = cnt0;
         if (k == 0) {
             init_loop<Q, ROWL, true>(m, mem, st, cnt, false);
