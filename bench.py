@@ -25,19 +25,23 @@ HEADLINE = 4
 # the chip's vector issue peak: 256 CUs x 4 SIMDs x 2.4 GHz / 4 cycles per 64-lane instruction
 VALU_PEAK_G_PER_S = 256 * 4 * 2.4e9 / 4 / 1e9
 # rocprofv3 counter readings per launch (HBM traffic from FETCH_SIZE / WRITE_SIZE, instruction
-# counts from SQ_INSTS_*), one line per workload with the kernel instantiation they were read for
+# counts from SQ_INSTS_*), one line per workload with the kernel instantiation they were read for and
+# the digest of the sources it was built from
 COUNTER_FILE = os.path.join(ROOT, "profiles", "k_loop_batch_pmc_counters.txt")
 
 
 def profiled_counters():
     """{config id: {"kernel": name, "B": .., "traffic_bytes": .., "insts_valu": ..}} from the
-    tracked summary of the counter runs; {} if there is none."""
-    out = {}
+    tracked summary of the counter runs, as far as they were taken with the kernels as they are."""
+    from paper_1807_05358_amd import build
+    out, digest = {}, build.kernel_digest()
     try:
         for line in open(COUNTER_FILE):
             if not line.startswith("counters "):
                 continue
             f = dict(kv.split("=", 1) for kv in line.split()[1:] if "=" in kv)
+            if f.get("sources") != digest:
+                continue
             name = line.split('kernel="', 1)[1].split('"', 1)[0]
             out[int(f["config"])] = {"kernel": name, "B": int(f["B"]), "traffic_bytes": float(f["traffic_bytes"]),
                                      "insts_valu": float(f["insts_valu"])}

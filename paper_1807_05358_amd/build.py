@@ -2,7 +2,9 @@
 csrc/ are compiled side by side (the kernels are many template instantiations), then linked."""
 from __future__ import annotations
 
+import hashlib
 import os
+import re
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -25,6 +27,20 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                # keep the compiler from forming packed-fp32 instructions
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-Wno-unused-value"]
+
+
+def kernel_digest() -> str:
+    """of the kernels as they are compiled: their sources without comments and line breaks, and the compiler's flags.
+    Counter readings of a kernel name the digest of the sources they were taken with."""
+    h = hashlib.sha256(" ".join(HIPCC_FLAGS).encode())
+    for f in sorted(KERNEL_UNITS + HEADERS):
+        with open(os.path.join(CSRC, f)) as src:
+            h.update(without_comments(src.read()).encode())
+    return h.hexdigest()[:16]
+
+
+def without_comments(src: str) -> str:
+    return " ".join(re.sub(r"//[^\n]*|/\*.*?\*/", " ", src, flags=re.S).split())
 
 
 def build_library(force: bool = True, sections: bool = False) -> str:
