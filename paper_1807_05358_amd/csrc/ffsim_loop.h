@@ -25,6 +25,7 @@ constexpr uint32_t NO_OP = 0xffffffffu;
 constexpr u64 RESULT_RETRY = 2;                  // a link row is booked beyond 32 bits: simulate again with 64-bit rows
 constexpr uint32_t RUN_SPAN = 0x40000000u;       // events of one step lie at most this far apart
 constexpr uint32_t FAR_AWAY = 0xfffffffeu;       // a distance between events of one kind that 32 bits do not hold
+constexpr int32_t LOST = INT32_MIN;              // steps left (see run_loop) once the queue is found to have lost an event
 constexpr uint32_t RUN_EDGES = 8;                // ops with more out-edges release at one time only
 
 struct Queue {
@@ -551,7 +552,6 @@ __device__ __forceinline__ uint32_t count_lanes(uint32_t n, u64 mask) {
 __device__ __forceinline__ void vector_loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 // a uniform value the compiler is not to recompute (or to move into a branch of its own)
 __device__ __forceinline__ uint32_t opaque(uint32_t uniform) { asm("" : "+s"(uniform)); return uniform; }
-__device__ __forceinline__ u64 opaque64(u64 uniform) { asm("" : "+s"(uniform)); return uniform; }
 // LDS addresses as numbers
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 __device__ __forceinline__ uint32_t lds_addr(uint32_t* p) { return (uint32_t)(uintptr_t)(lds_u32*)p; }
@@ -682,7 +682,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
         left--;
         if (__builtin_expect((int32_t)(kmin | (uint32_t)left | (Q == Q_SLOT ? 0u - q.n_spill : 0u)) < 0, 0)) {
             if (left < 0) {
-                if (max_steps == 0) break;
+                if (max_steps == 0 || left != -1) break;
                 if (beyond_32()) break;
                 if (PaceX::kOn) pace.at(first_u32(last));
                 left = (int32_t)(PACE_STEPS < max_steps ? PACE_STEPS : max_steps);
@@ -716,6 +716,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 spill_key = q.n_spill ? rel_key(q.spill_min, st.E) : KEY_NONE;
                 vector_loads_done();
             }
+            if (kmin >= KEY_REFRESH) { left = LOST; break; }     // an event before the epoch
         }
         if (RECORD) {
             // the state before the first event at or after a multiple of `step` is a snapshot
@@ -746,6 +747,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             if (PaceX::kOn) last = i;
             cnt.n_events++;
         };
+        // An op whose words do not have the event that the queue has of it: noticed at the next pop.  (The step itself finds no part and changes no task
+        // of the op; what a release does to its consumers goes no further than that pop either.  A branch here would wait for the mask, a select does not.)
+        auto found = [&](u64 mask) __attribute__((always_inline)) { left = mask ? left : LOST + 1; };
         // A run: the events of the op up to the first event of another op of that kind, the first one of the other kind that may matter, the first one the
         // run itself may bring about, and the next snapshot.
         auto run_mask = [&](uint32_t d, uint32_t until, uint32_t first_new) __attribute__((always_inline)) {
@@ -776,6 +780,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             PROF_VMWAIT(2)
             const uint32_t d = event_distance(k0, K);
             u64 mask = run_mask(d, m_rel, exe);
+            found(mask);
             const bool may_share = !REG && ((SimX::kExt && m.devmap != nullptr) || !(ci.stride == 1 && ci.parts <= S.n_dev));
             if (may_share) {
                 // of the parts on one device only the first
@@ -880,6 +885,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             const uint32_t d = event_distance(k0, K);
             if (EARLY && !EDGED && out_end > out_begin) ed = load_edge(lit, out_begin);
             u64 mask = run_mask(d, horizon, next_exe);
+            found(mask);
             const uint32_t node_p = m.node_of(dev_p);
             // Transfers from one node (whose link rows are its own) go in the order of (time, edge, part), those from different nodes in any.  The edges
             // are gone through one after the other, each part by part, and parameters behind them: of the parts on a node only the first may go where there
@@ -1250,8 +1256,9 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
     }
     PROF_STORE(cnt)
     if (beyond_32()) return RESULT_RETRY;
-    if (left < 0 && max_steps == 0) { cnt.exit_code = 2; return RESULT_INTERNAL; }
-    return ballot(latest_hi >= (uint32_t)(TIME_LIMIT >> 32)) ? RESULT_OVERFLOW : 0;
+    if (ballot(latest_hi >= (uint32_t)(TIME_LIMIT >> 32))) return RESULT_OVERFLOW;
+    if (left < -1 || (left < 0 && max_steps == 0)) { cnt.exit_code = 2; return RESULT_INTERNAL; }
+    return 0;
 }
 
 }  // namespace ffsim
