@@ -748,7 +748,8 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             cnt.n_events++;
         };
         // An op whose words do not have the event that the queue has of it: noticed at the next pop.  (The step itself finds no part and changes no task
-        // of the op; what a release does to its consumers goes no further than that pop either.  A branch here would wait for the mask, a select does not.)
+        // of the op; what a release does to its consumers goes no further than that pop either.  Asked behind the step's work, by a select: where the mask is
+        // found, it costs 1024 x NMT-shaped 0.5 % and 1024 training iterations 0.9 % more, as a branch there training iterations 2 % and NMT-shaped 1 % less.)
         auto found = [&](u64 mask) __attribute__((always_inline)) { left = mask ? left : LOST + 1; };
         // A run: the events of the op up to the first event of another op of that kind, the first one of the other kind that may matter, the first one the
         // run itself may bring about, and the next snapshot.
@@ -780,7 +781,6 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             PROF_VMWAIT(2)
             const uint32_t d = event_distance(k0, K);
             u64 mask = run_mask(d, m_rel, exe);
-            found(mask);
             const bool may_share = !REG && ((SimX::kExt && m.devmap != nullptr) || !(ci.stride == 1 && ci.parts <= S.n_dev));
             if (may_share) {
                 // of the parts on one device only the first
@@ -811,6 +811,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 if (RECORD && rec.end_try) rec.end_try[(size_t)i * ROWL + lane] = rec.tag | end;
             }
             PROF_MARK(3)
+            found(mask);
             // ---- the op's next events
             uint32_t nd = in_mask ? KEY_NONE : d, nr = in_mask ? dw | none : KEY_NONE;
             if (ROWL == 16) row0_min2_u32(nd, nr); else wave_min2_u32(nd, nr);
@@ -885,7 +886,6 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
             const uint32_t d = event_distance(k0, K);
             if (EARLY && !EDGED && out_end > out_begin) ed = load_edge(lit, out_begin);
             u64 mask = run_mask(d, horizon, next_exe);
-            found(mask);
             const uint32_t node_p = m.node_of(dev_p);
             // Transfers from one node (whose link rows are its own) go in the order of (time, edge, part), those from different nodes in any.  The edges
             // are gone through one after the other, each part by part, and parameters behind them: of the parts on a node only the first may go where there
@@ -1243,6 +1243,7 @@ __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& 
                 k0 = W_NONE;
                 words[(size_t)i * ROWL + lane] = k0;
             }
+            found(mask);
             // ---- the op's next event
             const uint32_t nd = part_min_u32<ROWL>(in_mask ? KEY_NONE : d);
             const uint32_t nk = next_key(kmin, nd);
