@@ -21,8 +21,9 @@ enum KeptRow : uint32_t {
     KEPT_ROWS      // rows of any other edge
 };
 
-// Kept record of an op (16 bytes, the same for all lanes): exeTime of its tasks, device offset | stride << 16, exeTime of the
-// tasks of its first out-edge's consumer (the bound of a run of releases), number of parts | HDR_* flags.
+// Kept record of an op (16 bytes, the same for all lanes): exeTime of its tasks, device offset | stride << 16, the least exeTime
+// among the consumers of its out-edges (the bound of a run of releases; all ones: no out-edge, 0: too many to look at), number of
+// parts | HDR_* flags.
 constexpr uint32_t HDR_SPLIT01 = 1u << 16;   // dim 0 or 1 is split
 constexpr uint32_t HDR_SPLIT23 = 1u << 17;   // dim 2 or 3 is split
 constexpr uint32_t HDR_RELEASES = 1u << 18;  // the op's tasks have something to release when they have finished

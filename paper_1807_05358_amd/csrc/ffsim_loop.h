@@ -26,7 +26,9 @@ constexpr u64 RESULT_RETRY = 2;                  // a link row is booked beyond 
 constexpr uint32_t RUN_SPAN = 0x40000000u;       // events of one step lie at most this far apart
 constexpr uint32_t FAR_AWAY = 0xfffffffeu;       // a distance between events of one kind that 32 bits do not hold
 constexpr int32_t LOST = INT32_MIN;              // steps left (see run_loop) once the queue is found to have lost an event
-constexpr uint32_t RUN_EDGES = 8;                // ops with more out-edges release at one time only
+// Ops with more out-edges release at one time only: the set-up looks at the exeTimes behind all of them, and few have more.  Against 8, one edge takes
+// 1.17 times as long on 1024 training iterations (Inception-v3-shaped; its batch of 4096 1.08), two 1.04 (1.06), four 1.01 (1.00), 16 and 64 the same within 2 %.
+constexpr uint32_t RUN_EDGES = 8;
 
 struct Queue {
     uint32_t kd, kr, op;        // per lane: keys of the first task to be dequeued and of the first to release, the op they are of
@@ -590,9 +592,13 @@ struct EdgeLoad { u64 w; uint32_t exe, f, clo, chi, plo, phi, clo2, chi2, plo2, 
 // falls by one where half, three quarters and nine tenths of its ops are behind it (of all candidates it will simulate), and the others catch up.
 // They do so slowly, with no more than the difference between their share and a lone wavefront's pace (those ahead still get every slot that is
 // left), so the bounds come early: with the first at 0.7 or 0.8 half of the gain is lost; a quarter, a half and three quarters give 2 % less;
-// priorities that change hands by the clock give nothing (the shares are even enough, the lengths are not).  4096 x Inception-v3-shaped 6.99 -> 6.27 ms,
-// x ResNet-101-shaped 13.4 -> 11.4, 8192 x AlexNet-shaped 0.47 -> 0.41, 1024 searches x 32 steps (nodes four to a SIMD) 97.9 -> 90.9; with one
-// wavefront per SIMD nothing changes.  How far a wavefront is is looked at every 32 steps, where the loop's own bound is: a count of events costs such lone
+// priorities that change hands by the clock give nothing (the shares are even enough, the lengths are not).  One box, before the queues were
+// split: 4096 x Inception-v3-shaped 6.82 -> 6.05 ms, x ResNet-101-shaped 13.4 -> 11.3, 8192 x AlexNet-shaped 0.45 -> 0.40; after that, with and without: 5.94 -> 5.34,
+// 11.5 -> 9.85, 0.42 -> 0.37, 1024 searches x 32 steps (nodes four to a SIMD) 87.0 -> 80.5.  With one wavefront per SIMD nobody is waited for, and the code placed
+// around it moves times by 2 to 3 % either way (1024 x AlexNet-shaped 160 -> 155 us, x NMT-shaped 55.9 -> 57.1 ms).  Kernels of another stream run at priority 0, below
+// all but the last tenth: beside 4096 x Inception-v3-shaped a vector-bound one (the sine of 64 Mi values) takes 285 -> 450 us, a copy of 256 MiB 137 -> 142, a
+// product of 2048^3 55 -> 38, and the batch itself is done in 5.9 instead of 8.0 ms; beside one wavefront per SIMD they take what they took (131 and 131 us, 112 and
+// 112), so such launches have no rule of their own.  How far a wavefront is is looked at every 32 steps, where the loop's own bound is: a count of events costs such lone
 // wavefronts 1 to 4 %.  (Trials are dealt out by length already and gain nothing.)
 constexpr uint32_t PACE_STEPS = 32;      // queue steps between two looks at how far a wavefront is
 struct NoPace {
@@ -629,11 +635,13 @@ struct Pace {
 // dequeued, and the other way round.  Hence two queues: releases go on until the horizon, before which no task that is still to be dequeued can end (the first
 // READY time of every op and its exeTime: q.kd + q.ex), then dequeues until the next release.  Within a step an op's events of one kind go together up
 // to the other ops' first one (run_mask), whatever lies between them of the other kind; ops with several edges, or parameters, release of every node the
-// parts that come first.  Against one queue in the order of time, with runs of ops with one edge: steps of the Inception-v3-shaped graph 1980 -> 1752,
-// ResNet-101 4024 -> 3246, NMT 39148 -> 32856, AlexNet 157 -> 134.
-// Both together (with the parts of a step sorted only where two on a node are out of order), per launch: 4096 x Inception-v3-shaped 6.02 -> 5.24 ms, 4096 x ResNet-101-shaped
-// 11.4 -> 9.85, 1024 x NMT-shaped 67.5 -> 56.3, 1024 x AlexNet-shaped 0.179 -> 0.163, training iterations (1024 x Inception-v3-shaped) 16.4 -> 12.3, general strategies
-// (777 x ResNet-101-shaped on 5 x 3 devices) 21.9 -> 18.2, with parameter traffic (4096 x Inception-v3-shaped) 11.3 -> 7.4.
+// parts that come first.  Against one queue in the order of time, with runs of ops with one edge: steps of the Inception-v3-shaped graph 1980 -> 1732,
+// ResNet-101 4024 -> 3195, NMT 39148 -> 33224, AlexNet 158 -> 132.
+// Both together (with the parts of a step sorted only where two on a node are out of order), per launch, one box: 4096 x Inception-v3-shaped 6.05 -> 5.33 ms, 4096 x
+// ResNet-101-shaped 11.3 -> 9.88, 1024 x NMT-shaped 66.7 -> 57.0, 1024 x AlexNet-shaped 0.175 -> 0.162, training iterations (1024 x Inception-v3-shaped) 16.3 -> 11.9,
+// general strategies (777 x ResNet-101-shaped on 5 x 3 devices) 21.7 -> 17.4, with parameter traffic (4096 x Inception-v3-shaped) 10.3 -> 7.3.
+// A step has more to find out now, so calls in which few events go together lose: general strategies and explicit devices of the AlexNet-shaped graph on 4 to 8
+// devices 0.96 to 0.99x, chains of a few changes with parameter traffic on graphs of 6 and 12 ops 0.96 to 0.99x.
 // L64: link rows are absolute 64-bit times (mem.lrow64); the form for what RESULT_RETRY leaves over, REG = false only.
 template <bool RECORD, bool REG, bool STATS, int Q, int ROWL, bool L64 = false, class SimX, class PaceX = NoPace>
 __device__ __forceinline__ u64 run_loop(SimX& m, const LoopMem& mem, LoopState& st, Counters& cnt, Recorder& rec, PaceX pace = PaceX()) {
